@@ -12,7 +12,7 @@
 // Workspace of dmoe_forward_static: one array per GPU, held from the moment the library's code
 // object is loaded on that GPU until the process ends.  In host code this name is only a handle
 // for hipGetSymbolAddress (static_scratch_of_current_device below); it is never passed to a kernel.
-constexpr size_t kStaticScratchBytes = (size_t)32 << 20;
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace dmoe {
@@ -159,13 +159,15 @@ int check_launch(const char* what) {
 
 // ---- workspace layouts -----------------------------------------------------------------------------
 struct SelectWs {
-    size_t group_off, mask, total;
+    size_t group_off, sub_cnt, mask, total;
 };
 SelectWs select_ws(int T, int E, bool need_mask) {
     SelectWs w{};
     size_t o = 0;
     w.group_off = o;
     o += align_up(sizeof(int32_t) * (size_t)(div_up(T, kGroup) + 1) * E);
+    w.sub_cnt = o;  // raw counts per group where the list fill does the scan
+    o += align_up(sizeof(int32_t) * (size_t)std::min(div_up(T, kGroup), kFoldRows) * E);
     w.mask = o;
     if (need_mask) o += align_up(sizeof(uint64_t) * (size_t)T * div_up(E, 64));
     w.total = o;
@@ -205,12 +207,13 @@ LayerWs layer_ws(const dmoe_layer& L, int T) {
         w.hs8 = o;  o += align_up(h_fragments(L, T) * 16);
     }
     // small-token path: which tokens keep each expert, and the per-expert-group partial outputs
+    // (or the shares of a divided down-projection)
     w.colmask = o;
     w.partial = o;
     if (L.dtype == DMOE_BF16) {  // also above kSmallTokens: the workspace never shrinks as T grows
         o += align_up(sizeof(uint64_t) * (size_t)E);
         w.partial = o;
-        o += align_up(sizeof(float) * (size_t)kSmallMaxGroups * 16 * L.d_model);
+        o += align_up(sizeof(float) * std::max((size_t)kSmallMaxGroups * 16 * L.d_model, down_partial_floats(L, T)));
     }
     // hidden rows of the router: 16 for the small-token kernels, all T for a router that runs as
     // two launches
@@ -265,15 +268,22 @@ SmallMod small_mod(const dmoe_layer& L, char* ws, const LayerWs& w, float* score
     return M;
 }
 
-// Experts from mask bits whose group counts are already in group_off (both in the workspace).
+// Where the gate leaves the per-group counts of the list-based bf16 path: as raw rows in sub_cnt
+// when a group has several of them or the list fill adds them up itself, else in group_off, which
+// the scan kernel turns into prefix sums in place.
+bool counts_in_sub(const dmoe_layer& L, int T, int split) {
+    return L.dtype == DMOE_BF16 && !use_small_path(L, T) && (split > 1 || fold_scan(T, L.n_experts, 1));
+}
+
+// Experts from mask bits whose group counts are already in the workspace (counts_in_sub).
 // gate_mod: the small-token path takes the gate into its up-projection (the scores, the mask and
 // the counts are then outputs of that kernel, described by gate_mod).
 int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const LayerWs& w,
                 const uint64_t* mask, int32_t* offsets_out, int32_t* lists_out, void* y,
                 hipStream_t s, int split = 1, const SmallMod* gate_mod = nullptr) {
-    // split > 1: the counts are in sub_cnt, split rows per group (bf16 prefill path only)
+    // split: rows per group of the counts, where they are in sub_cnt (counts_in_sub)
     int32_t* group_off = reinterpret_cast<int32_t*>(ws + w.group_off);
-    const int32_t* sub_cnt = split > 1 ? reinterpret_cast<const int32_t*>(ws + w.sub_cnt) : nullptr;
+    const int32_t* sub_cnt = counts_in_sub(L, T, split) ? reinterpret_cast<const int32_t*>(ws + w.sub_cnt) : nullptr;
     int32_t* counts = reinterpret_cast<int32_t*>(ws + w.counts);
     int32_t* offsets = offsets_out ? offsets_out : reinterpret_cast<int32_t*>(ws + w.offsets);
     // the kernels read the work-item-aligned copy in the workspace; the caller's is compact
@@ -310,6 +320,7 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
                              up_rows_bf16(L), lists_out, alist, up_window_groups(L, T), witem,
                              wfirst, s, sub_cnt, split);
         void* H = ws + w.H;
+        float* partial = reinterpret_cast<float*>(ws + w.partial);
         // 8-bit hidden activations on the 8-bit matrix cores: the rows as codes + scale bytes
         const bool down8 = hidden_fp8(L) && down_x8_shape(L) && down_x8_addressable(L, T);
         uint8_t* H8 = down8 ? reinterpret_cast<uint8_t*>(ws + w.H8) : nullptr;
@@ -324,16 +335,19 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
             launch_up_bf16(L, x, T, witem, wfirst, alist, H, s);
         if (down8) {
             if (!up_writes_codes) launch_h_rows_to_e4m3(L, item_start, H, H8, hs8, s);
-            launch_down_x8(L, T, item_start, group_off, mask, H8, hs8, y, s);
+            launch_down_x8(L, T, item_start, group_off, mask, H8, hs8, y, partial, s);
             return check_launch("expert kernels");
         }
         if (hidden_fp8(L)) launch_h_rows_quantize(L, item_start, H, s);  // the bf16 kernels read hq
-        const long long max_sparse = down_max_pairs_sparse(L, T);
-        // both are launched and the pair count on the device decides, unless the limit already does
+        // Both are launched and the pair count on the device decides, unless the limit already does.
+        // (A walk that is divided over the chip is the faster one at any density; -1: also with no
+        // pairs at all.)
+        long long max_sparse = down_max_pairs_sparse(L, T);
+        if (max_sparse == 0 || (max_sparse != 0x7fffffffffffffffLL && down_parts(L, T) > 1)) max_sparse = -1;
         if (max_sparse > 0)
             launch_down_rmw_bf16(L, T, item_start, group_off, alist, offsets, H, y, max_sparse, s);
         if (max_sparse != 0x7fffffffffffffffLL)
-            launch_down_bf16(L, T, item_start, group_off, mask, offsets, H, y, max_sparse, s);
+            launch_down_bf16(L, T, item_start, group_off, mask, offsets, H, y, partial, max_sparse, s);
     }
     return check_launch("expert kernels");
 }
@@ -466,15 +480,17 @@ int select_impl(const float* scores, int32_t n_tokens, int32_t n_experts, Gate g
     char* ws = static_cast<char*>(workspace);
     hipStream_t s = (hipStream_t)stream;
     int32_t* group_off = reinterpret_cast<int32_t*>(ws + w.group_off);
+    int32_t* sub_cnt = n_tokens > 0 && fold_scan(n_tokens, n_experts, 1) ? reinterpret_cast<int32_t*>(ws + w.sub_cnt) : nullptr;
+    int32_t* cnt = sub_cnt ? sub_cnt : group_off;
     uint64_t* mask = mask_bits ? mask_bits : reinterpret_cast<uint64_t*>(ws + w.mask);
     if (n_tokens > 0) {
         if (gate.top_k < 0)
-            launch_mask_from_scores(scores, n_tokens, n_experts, gate.tau, mask, k_per_token, group_off, nullptr, s);
+            launch_mask_from_scores(scores, n_tokens, n_experts, gate.tau, mask, k_per_token, cnt, nullptr, s);
         else
-            launch_mask_topk(scores, n_tokens, n_experts, gate.top_k, mask, k_per_token, group_off, nullptr, s);
+            launch_mask_topk(scores, n_tokens, n_experts, gate.top_k, mask, k_per_token, cnt, nullptr, s);
     }
     launch_scan_and_fill(mask, n_tokens, n_experts, group_off, counts, offsets, nullptr, 64,
-                         n_tokens > 0 ? token_lists : nullptr, nullptr, 1, nullptr, nullptr, s);
+                         n_tokens > 0 ? token_lists : nullptr, nullptr, 1, nullptr, nullptr, s, sub_cnt);
     return check_launch("select");
 }
 
@@ -512,7 +528,8 @@ int32_t dmoe_expert_ffn(const dmoe_layer* layer, const void* x, int32_t n_tokens
     uint64_t* mask = reinterpret_cast<uint64_t*>(ws + w.mask);
     uint64_t* colmask = use_small_path(*layer, n_tokens) ? reinterpret_cast<uint64_t*>(ws + w.colmask) : nullptr;
     launch_mask_from_lists(offsets, token_lists, n_tokens, layer->n_experts, mask,
-                           reinterpret_cast<int32_t*>(ws + w.group_off), colmask, s);
+                           reinterpret_cast<int32_t*>(ws + (counts_in_sub(*layer, n_tokens, 1) ? w.sub_cnt : w.group_off)),
+                           colmask, s);
     return run_experts(*layer, x, n_tokens, ws, w, mask, nullptr, nullptr, y, s);
 }
 
@@ -537,8 +554,10 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
     hipStream_t s = (hipStream_t)stream;
     float* scores = scores_out ? scores_out : reinterpret_cast<float*>(ws + w.scores);
     uint64_t* mask = mask_out ? mask_out : reinterpret_cast<uint64_t*>(ws + w.mask);
-    int32_t* group_off = reinterpret_cast<int32_t*>(ws + w.group_off);
     uint64_t* colmask = use_small_path(*layer, n_tokens) ? reinterpret_cast<uint64_t*>(ws + w.colmask) : nullptr;
+    auto counts_of = [&](int parts) {  // where the gate's counts go
+        return reinterpret_cast<int32_t*>(ws + (counts_in_sub(*layer, n_tokens, parts) ? w.sub_cnt : w.group_off));
+    };
     // the MFMA router takes any number of experts; with the gate fused in, up to 512
     const bool fused_router = layer->dtype == DMOE_BF16 && router_fused_scores_supported(*layer);
     const bool fused_gate = fused_router && router_fused_supported(*layer);
@@ -547,10 +566,9 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
         // router, dynamic-k gate and group counts in one kernel (with few token groups: several
         // workgroups per group, each with its own row of counts)
         if (!colmask) split = router_fused_split(*layer, n_tokens);
-        int32_t* cnt = split > 1 ? reinterpret_cast<int32_t*>(ws + w.sub_cnt) : group_off;
         // (the gate works on the scores in registers: they go to memory only for a caller who
         // asked for them)
-        launch_router_fused(*layer, x, n_tokens, split, scores_out, tau, mask, nullptr, cnt, colmask, s);
+        launch_router_fused(*layer, x, n_tokens, split, scores_out, tau, mask, nullptr, counts_of(split), colmask, s);
     } else if (fused_router && colmask && gate.top_k < 0 &&
                layer->n_experts <= kSmallFusedSelectMaxE) {
         SmallGroup G{};
@@ -580,10 +598,10 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
             launch_router_bf16(*layer, x, n_tokens, scores, s);
         if (gate.top_k < 0)
             launch_mask_from_scores(scores, n_tokens, layer->n_experts, tau, mask, nullptr,
-                                    group_off, colmask, s);
+                                    counts_of(1), colmask, s);
         else
             launch_mask_topk(scores, n_tokens, layer->n_experts, gate.top_k, mask, nullptr,
-                             group_off, colmask, s);
+                             counts_of(1), colmask, s);
     }
     return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s, split);
 }

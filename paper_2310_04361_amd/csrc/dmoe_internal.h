@@ -194,7 +194,10 @@ void launch_mask_topk(const float* scores, int T, int E, int k, uint64_t* mask,
 void launch_mask_from_lists(const int32_t* offsets, const int32_t* lists, int T, int E,
                             uint64_t* mask, int32_t* group_off, uint64_t* colmask, hipStream_t s);
 // sub_cnt (nullable): the counts come as `split` rows per group (ceil(T * split / 64) rows) that
-// are added up into group_off on the way.
+// are added up into group_off on the way; with few such rows (fold_scan) the list fill does that
+// itself and there is no scan launch, so the counts of small batches should come this way.
+constexpr int kFoldRows = 32;
+bool fold_scan(int T, int E, int split);
 void launch_scan_and_fill(const uint64_t* mask, int T, int E, int32_t* group_off, int32_t* counts,
                           int32_t* offsets, int32_t* item_start, int rows_per_item,
                           int32_t* token_lists, int32_t* aligned_lists, int window_groups,
@@ -299,11 +302,39 @@ void launch_pack_down_bf16(const dmoe_layer& L, void* w2g, hipStream_t s);
 // more: the one that sums over experts inside the matrix cores (down_bf16.hip).
 void launch_down_bf16(const dmoe_layer& L, int T, const int32_t* item_start,
                       const int32_t* group_off, const uint64_t* mask, const int32_t* offsets,
-                      const void* H, void* y, long long max_pairs_sparse, hipStream_t s);
+                      const void* H, void* y, float* partial, long long max_pairs_sparse,
+                      hipStream_t s);
 void launch_down_rmw_bf16(const dmoe_layer& L, int T, const int32_t* item_start,
                           const int32_t* group_off, const int32_t* alist, const int32_t* offsets,
                           const void* H, void* y, long long max_pairs_sparse, hipStream_t s);
 long long down_max_pairs_sparse(const dmoe_layer& L, int T);
+
+// Batches too small to fill the chip: the walk over the experts is split over this many workgroups
+// per tile of outputs, whose fp32 shares (down_partial_floats of workspace) are added at the end.
+int down_parts(const dmoe_layer& L, int T);
+size_t down_partial_floats(const dmoe_layer& L, int T);
+void launch_down_finish(const dmoe_layer& L, int T, const float* partial, void* y, int parts, hipStream_t s);
+// Loop trips of one part: even, so that a part never starts at the last trip of a batch of experts.
+__host__ __device__ inline int down_part_trips(int trips, int parts) {
+    return parts <= 1 ? trips : ((trips + parts - 1) / parts + 1) / 2 * 2;
+}
+// Which 128-token chunk, column slice and part a workgroup of the matrix-core down kernels works
+// on (workgroups are dealt round-robin to the 8 XCDs).  Undivided walks: the column slices of one
+// chunk share its H rows, so they sit on one XCD and next to each other in launch order.  Divided
+// walks: with few chunks the weights are the traffic, so the chunks that read the same slice of the
+// same experts share an XCD.
+struct DownTile {
+    int chunk, slice, part;
+};
+__host__ __device__ inline DownTile down_tile(int block, int NS, int NC, int parts) {
+    const int xcd = block & 7, k = block >> 3;
+    if (parts <= 1) return DownTile{(k / NS) * 8 + xcd, k % NS, 0};
+    const int combo = (k / NC) * 8 + xcd;
+    return DownTile{k % NC, combo % NS, combo / NS};
+}
+inline int down_grid(int NC, int NS, int parts) {
+    return parts <= 1 ? round_up(NC, 8) * NS : 8 * NC * div_up(NS * parts, 8);
+}
 
 // ---- 8-bit hidden activations (down_x8.hip) -------------------------------------------------------
 // Row-wise quantisation of the H rows that the up-projection wrote (see DMOE_W_FP8_E4M3_A8 in
@@ -317,7 +348,7 @@ void launch_h_rows_to_e4m3(const dmoe_layer& L, const int32_t* item_start, const
 void launch_h_rows_quantize(const dmoe_layer& L, const int32_t* item_start, void* H, hipStream_t s);
 void launch_down_x8(const dmoe_layer& L, int T, const int32_t* item_start, const int32_t* group_off,
                     const uint64_t* mask, const uint8_t* H8, const uint8_t* hs8, void* y,
-                    hipStream_t s);
+                    float* partial, hipStream_t s);
 
 // ---- 8-bit expert inputs (ffn_x8.hip) -------------------------------------------------------------
 // Row-wise quantisation of x (see DMOE_W_FP8_E4M3_X8 in dmoe.h): x8[T][d] E4M3 codes, xscale[T]

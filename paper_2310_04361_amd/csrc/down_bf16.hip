@@ -129,7 +129,7 @@ __global__ __launch_bounds__(256, WPS) void down_bf16_kernel(
     const uint32_t* __restrict__ mask32, const int32_t* __restrict__ offsets,
     const __bf16* __restrict__ H, __bf16* __restrict__ y, int T, int d, int E, int NG, int W32,
     int rows_per_item, int row_shift, uint32_t w_bytes, uint32_t h_bytes,
-    long long max_pairs_sparse) {
+    long long max_pairs_sparse, int parts, float* __restrict__ partial) {
     static_assert((kDnTrip * KSP) % R == 0 && 32 % (kDnTrip * G) == 0, "loop trip");
     static_assert(UPE == 1 || (UPE == 2 && G == 1), "two units per expert: one unit per stage");
     if (offsets[E] <= max_pairs_sparse) return;  // sparse enough for the pair-proportional kernel
@@ -143,15 +143,19 @@ __global__ __launch_bounds__(256, WPS) void down_bf16_kernel(
     // round-robin to the 8 XCDs) and next to each other in launch order.
     constexpr int kDnCols = CT * kDnColStep;
     const int NS = d / kDnCols;
-    const int k_in_xcd = blockIdx.x >> 3;
-    const int chunk = (k_in_xcd / NS) * 8 + (blockIdx.x & 7), slice = k_in_xcd % NS;
+    const DownTile tile = down_tile(blockIdx.x, NS, (T + kDnTokens - 1) / kDnTokens, parts);
+    const int chunk = tile.chunk, slice = tile.slice;
     const int t_base = chunk * kDnTokens;
-    if (t_base >= T) return;  // the grid is rounded up to whole groups of 8 chunks
+    if (t_base >= T || tile.part >= parts) return;  // the grid is rounded up to whole groups of 8
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, c = lane & 31;
     const int col_w = slice * kDnCols + wave * (32 * CT);
-    const int n_trips = (E * UPE + kDnTrip * G - 1) / (kDnTrip * G);
+    // this workgroup's share of the walk over the experts (all of it unless parts > 1)
+    const int all_trips = (E * UPE + kDnTrip * G - 1) / (kDnTrip * G);
+    const int part_trips = down_part_trips(all_trips, parts);
+    const int trip0 = tile.part * part_trips, n_trips = min(all_trips, trip0 + part_trips);
+    const int e_first = trip0 * kExpertsPerTrip;  // its first expert
 
     // ---- tile-building role: select group bg of the chunk (lane = token), lane half bh
     const int bg = wave & 1, bh = wave >> 1;
@@ -228,7 +232,8 @@ __global__ __launch_bounds__(256, WPS) void down_bf16_kernel(
     for (int ct = 0; ct < CT; ++ct)
         a_voff[ct] = (uint32_t)(((col_w / 32 + ct) * KSP * 64 + lane) * 16);
     const uint32_t w_stage_bytes = (uint32_t)(d / 32) * KSP * 1024;
-    uint32_t a_stage = 0;  // byte offset of the stage the next weight request belongs to
+    // byte offset of the stage the next weight request belongs to
+    uint32_t a_stage = (uint32_t)(trip0 * kDnTrip) * w_stage_bytes;
     // requests the weights of the next phase in order, column tile by column tile; ks = its
     // k-step (compile-time)
     auto load_block = [&](int ks, int ct, bf16x8 (&a)[CT]) {
@@ -249,24 +254,25 @@ __global__ __launch_bounds__(256, WPS) void down_bf16_kernel(
     // computed for the worse of the two ways into the loop).
     {
         int is0, go0;
-        load_batch(0, mw, is0, go0);
-        load_batch(1, mw_next, is_next, go_next);
+        load_batch(e_first >> 5, mw, is0, go0);
+        load_batch((e_first >> 5) + 1, mw_next, is_next, go_next);
         rowv = is0 * rows_per_item + go0;
-        mw = tok_ok ? mw : 0u;
+        mw = tok_ok ? mw >> (e_first & 31) : 0u;
     }
+    const int sh_first = e_first & 31;
     // (two units per expert: stage i is unit i & 1 of expert i / 2 of the trip, and the offsets
     // of an expert are computed once, before its first unit)
 #pragma unroll
     for (int i = 0; i < kDnTrip; ++i) {
         if (UPE == 1) {
 #pragma unroll
-            for (int eo = 0; eo < G; ++eo) build_prepare(i * G + eo, eo);
+            for (int eo = 0; eo < G; ++eo) build_prepare(sh_first + i * G + eo, eo);
         } else if ((i & 1) == 0) {
-            build_prepare(i / 2, 0);
+            build_prepare(sh_first + i / 2, 0);
         }
         build_fetch(breg[i], UPE == 1 ? 0 : (i & 1));
     }
-    sh_base = kExpertsPerTrip & 31;
+    sh_base = (sh_first + kExpertsPerTrip) & 31;
 #pragma unroll
     for (int q = 0; q < R - 1; ++q) load_phase(q % KSP, aw[q]);
     // every accumulator starts at the output bias: lane (h, c) holds columns 16h .. 16h + 15 of
@@ -276,7 +282,7 @@ __global__ __launch_bounds__(256, WPS) void down_bf16_kernel(
         bf16x8 bias[CT][2];
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) bias[ct][0] = bias[ct][1] = zero8();
-        if (b_down) {
+        if (b_down && tile.part == 0) {
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
                 bias[ct][0] = load8(b_down + col_w + 32 * ct + 16 * h);
@@ -310,7 +316,10 @@ __global__ __launch_bounds__(256, WPS) void down_bf16_kernel(
     // pinned by scheduling barriers (left alone the scheduler groups them and the matrix pipe
     // idles meanwhile).  Four buffers keep a wavefront that runs ahead from overwriting tiles
     // that a slower one still reads.  A trip past the last stage multiplies zero tiles.
-    int trip = 0, trip_end = min(kTripsPerBatch - 1, n_trips), batch = 1;
+    // (a part starts at an even trip, so its first run, up to the last trip of its first batch,
+    // holds at least one)
+    int batch = (e_first >> 5) + 1;
+    int trip = trip0, trip_end = min(batch * kTripsPerBatch - 1, n_trips);
     for (;;) {
         do {
 #pragma unroll
@@ -371,6 +380,22 @@ __global__ __launch_bounds__(256, WPS) void down_bf16_kernel(
     }
 
     // lane (h, c) of tile (j, ct): columns col_w + 32ct + 16h .. +15 of token t_base + 32j + c
+    if (parts > 1) {  // this part's share of the sum, in fp32
+#pragma unroll
+        for (int j = 0; j < kDnTiles; ++j) {
+            const int t = t_base + 32 * j + c;
+            if (t < T) {
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    float* dst = partial + ((size_t)tile.part * T + t) * d + col_w + 32 * ct + 16 * h;
+#pragma unroll
+                    for (int i = 0; i < 16; i += 4)
+                        *reinterpret_cast<f32x4*>(dst + i) = f32x4{acc[j][ct][i], acc[j][ct][i + 1], acc[j][ct][i + 2], acc[j][ct][i + 3]};
+                }
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int j = 0; j < kDnTiles; ++j) {
         const int t = t_base + 32 * j + c;
@@ -391,6 +416,27 @@ __global__ __launch_bounds__(256, WPS) void down_bf16_kernel(
     }
 }
 
+// y = bf16(sum of the parts' shares, in order).  A thread owns eight consecutive columns of a token.
+__global__ __launch_bounds__(256) void down_finish_kernel(const float* __restrict__ partial,
+                                                          __bf16* __restrict__ y, size_t n8, int parts) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n8) return;
+    f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = s0;
+    const float* p = partial + i * 8;
+#pragma unroll 8
+    for (int k = 0; k < parts; ++k) {
+        s0 += *reinterpret_cast<const f32x4*>(p + (size_t)k * n8 * 8);
+        s1 += *reinterpret_cast<const f32x4*>(p + (size_t)k * n8 * 8 + 4);
+    }
+    bf16x8 o;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        o[r] = (__bf16)s0[r];
+        o[4 + r] = (__bf16)s1[r];
+    }
+    *reinterpret_cast<bf16x8*>(y + i * 8) = o;
+}
+
 // Bytes of the packed down weights and of the H rows the kernel may address: both are reached
 // through 32-bit buffer offsets.
 size_t down_w_bytes(const dmoe_layer& L) {
@@ -404,7 +450,8 @@ size_t down_h_bytes(const dmoe_layer& L, int T) {
 template <int KSP, int G, int R, int WPS, int CT, int UPE = 1>
 void launch_down_t(const dmoe_layer& L, const PackedLayout& P, int T, const int32_t* item_start,
                    const int32_t* group_off, const uint64_t* mask, const int32_t* offsets,
-                   const void* H, void* y, long long max_pairs_sparse, hipStream_t s) {
+                   const void* H, void* y, long long max_pairs_sparse, int parts, float* partial,
+                   hipStream_t s) {
     const int NG = div_up(T, kGroup), NC = div_up(T, kDnTokens), NS = L.d_model / (CT * kDnColStep);
     constexpr size_t lds = (size_t)kDnTrip * kDnTiles * KSP * 1024;
     static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
@@ -416,11 +463,11 @@ void launch_down_t(const dmoe_layer& L, const PackedLayout& P, int T, const int3
     const int row_bytes = 2 * m_pad_of(L.expert_size);
     int row_shift = 0;
     while ((1 << row_shift) < row_bytes) ++row_shift;
-    launch_kernel(down_bf16_kernel<KSP, G, R, WPS, CT, UPE>, round_up(NC, 8) * NS, 256, lds, s, 
+    launch_kernel(down_bf16_kernel<KSP, G, R, WPS, CT, UPE>, down_grid(NC, NS, parts), 256, lds, s,
         (const __bf16*)(pk + P.w2g), (const __bf16*)L.b_down, item_start, group_off,
         reinterpret_cast<const uint32_t*>(mask), offsets, (const __bf16*)H, (__bf16*)y, T,
         L.d_model, L.n_experts, NG, 2 * div_up(L.n_experts, 64), up_rows_bf16(L), row_shift,
-        (uint32_t)down_w_bytes(L), (uint32_t)down_h_bytes(L, T), max_pairs_sparse);
+        (uint32_t)down_w_bytes(L), (uint32_t)down_h_bytes(L, T), max_pairs_sparse, parts, partial);
 }
 
 }  // namespace
@@ -449,7 +496,7 @@ void launch_pack_down_bf16(const dmoe_layer& L, void* w2g, hipStream_t s) {
 
 void launch_down_bf16(const dmoe_layer& L, int T, const int32_t* item_start,
                       const int32_t* group_off, const uint64_t* mask, const int32_t* offsets,
-                      const void* H, void* y, long long max_pairs_sparse, hipStream_t s) {
+                      const void* H, void* y, float* partial, long long max_pairs_sparse, hipStream_t s) {
     LaunchTimer tm(kSlotDown, s);
     const PackedLayout P = packed_layout(L);
     const DownPacking dp = down_packing(L.expert_size);
@@ -462,11 +509,12 @@ void launch_down_bf16(const dmoe_layer& L, int T, const int32_t* item_start,
     const bool can3 = L.d_model % (3 * kDnColStep) == 0;
     const int wg3 = can3 ? NC * (L.d_model / (3 * kDnColStep)) : 0;
     const bool wide = can3 && wg3 <= 256 && wg2 > 256;
+    const int parts = down_parts(L, T);
     // at most one workgroup per CU: a wavefront may use the whole register file of its SIMD, which
     // buys a deeper ring of weight sets
-    const bool one_per_cu = wg2 <= 256;
+    const bool one_per_cu = wg2 * parts <= 256;
 #define DMOE_DOWN(KSP_, G_, R_, WPS_, CT_) \
-    launch_down_t<KSP_, G_, R_, WPS_, CT_>(L, P, T, item_start, group_off, mask, offsets, H, y, max_pairs_sparse, s)
+    launch_down_t<KSP_, G_, R_, WPS_, CT_>(L, P, T, item_start, group_off, mask, offsets, H, y, max_pairs_sparse, parts, partial, s)
     // Weight sets in flight per shape: wide / one narrow workgroup per CU / two per CU (R divides
     // 4 KSP).  With 8 k-steps per stage the four LDS buffers (128 KiB) leave room for one
     // workgroup per CU only.
@@ -482,9 +530,9 @@ void launch_down_bf16(const dmoe_layer& L, int T, const int32_t* item_start,
         else DMOE_DOWN(KSP_, G_, R1_, 1, 2);      \
     } while (0)
     if (dp.UPE == 2) {  // experts of exactly 128 neurons as two units of 64
-        if (wide) launch_down_t<4, 1, 8, 1, 3, 2>(L, P, T, item_start, group_off, mask, offsets, H, y, max_pairs_sparse, s);
-        else if (one_per_cu) launch_down_t<4, 1, 16, 1, 2, 2>(L, P, T, item_start, group_off, mask, offsets, H, y, max_pairs_sparse, s);
-        else launch_down_t<4, 1, 4, 2, 2, 2>(L, P, T, item_start, group_off, mask, offsets, H, y, max_pairs_sparse, s);
+        if (wide) launch_down_t<4, 1, 8, 1, 3, 2>(L, P, T, item_start, group_off, mask, offsets, H, y, max_pairs_sparse, parts, partial, s);
+        else if (one_per_cu) launch_down_t<4, 1, 16, 1, 2, 2>(L, P, T, item_start, group_off, mask, offsets, H, y, max_pairs_sparse, parts, partial, s);
+        else launch_down_t<4, 1, 4, 2, 2, 2>(L, P, T, item_start, group_off, mask, offsets, H, y, max_pairs_sparse, parts, partial, s);
     }
     else if (dp.KSP == 2 && dp.G == 4) DMOE_DOWN_BY_GRID(2, 4, 8, 8, 4);
     else if (dp.KSP == 2 && dp.G == 2) DMOE_DOWN_BY_GRID(2, 2, 8, 8, 4);
@@ -496,6 +544,46 @@ void launch_down_bf16(const dmoe_layer& L, int T, const int32_t* item_start,
 #undef DMOE_DOWN_ONE_PER_CU
 #undef DMOE_DOWN_BY_GRID
 #undef DMOE_DOWN
+    if (parts > 1) launch_down_finish(L, T, partial, y, parts, s);
+}
+
+void launch_down_finish(const dmoe_layer& L, int T, const float* partial, void* y, int parts, hipStream_t s) {
+    const size_t n8 = (size_t)T * L.d_model / 8;
+    launch_kernel(down_finish_kernel, (int)((n8 + 255) / 256), 256, 0, s, partial, (__bf16*)y, n8, parts);
+}
+
+// A workgroup walks all the experts for its 128 tokens x 256 columns, which takes as long for one
+// chunk of tokens as for a chip full of them (256 x 64 gated experts: 165 to 180 us from 17 tokens
+// to 4096).  With few chunks the walk is split over `parts` workgroups, at most as many as fill the
+// CUs once; each leaves its share of the sum in fp32 and one more kernel adds the shares up in
+// order.  The number of parts is the one with the smallest estimate of walk / parts + that kernel,
+// in us: 0.16 per k-step of the walk (32 to 180 us for the benchmark shapes), 4.5 for the launch,
+// and 8 bytes written and read per value at 4 TB/s.
+int down_parts(const dmoe_layer& L, int T) {
+    const int wgs = div_up(T, kDnTokens) * (L.d_model / (2 * kDnColStep));
+    const DownPacking dp = down_packing(L.expert_size);
+    const int trips = div_up(L.n_experts * dp.UPE, kDnTrip * dp.G);
+    const double walk = 0.16 * trips * kDnTrip * dp.KSP, share = 2e-6 * T * (double)L.d_model;
+    int best = 1;
+    double best_us = walk;
+    for (int p = 2; p <= std::min(256 / std::max(wgs, 1), div_up(trips, 2)); ++p) {
+        const int n = div_up(trips, down_part_trips(trips, p));  // without the parts that would be empty
+        const double us = walk * down_part_trips(trips, p) / trips + 4.5 + share * n;
+        if (us < best_us) {
+            best_us = us;
+            best = n;
+        }
+    }
+    return best;
+}
+
+// ... and the fp32 values they need, for any batch of up to T tokens: parts * T * d, which never
+// exceeds one tile per CU.
+size_t down_partial_floats(const dmoe_layer& L, int T) {
+    if (L.dtype != DMOE_BF16) return 0;
+    const size_t cap = (size_t)256 * kDnTokens * 2 * kDnColStep;
+    const int most = std::max(1, 256 / std::max(1, L.d_model / (2 * kDnColStep)));
+    return std::min(cap, (size_t)most * T * L.d_model);
 }
 
 }  // namespace dmoe

@@ -154,6 +154,9 @@ constexpr int kD8Image = kD8Tiles * 64 * 32;   // the four B tiles of one expert
 constexpr int kD8Buf = kD8Image + kD8Tokens;   // + one scale byte per token
 constexpr int kD8Lds = 2 * kD8Buf;
 
+// Batches of 32 experts per part of a divided walk (down_parts).
+__host__ __device__ inline int d8_part_batches(int E, int parts) { return ((E + 31) / 32 + parts - 1) / parts; }
+
 // UPE = units of 64 neurons per expert (H rows of 64 * UPE bytes).
 template <int UPE>
 __global__ __launch_bounds__(256) void down_x8_kernel(
@@ -162,14 +165,19 @@ __global__ __launch_bounds__(256) void down_x8_kernel(
     const int32_t* __restrict__ group_off, const uint32_t* __restrict__ mask32,
     const uint8_t* __restrict__ H8, const uint8_t* __restrict__ hs8, __bf16* __restrict__ y, int T,
     int d, int E, int NG, int W32, int rows_per_item, uint32_t w_bytes, uint32_t h_bytes,
-    uint32_t hs_bytes) {
+    uint32_t hs_bytes, int parts, float* __restrict__ partial) {
     extern __shared__ __attribute__((aligned(16))) char img[];  // [2][kD8Buf]
     constexpr int kCols = kD8CT * 128;
     const int NS = d / kCols;
-    const int k_in_xcd = blockIdx.x >> 3;
-    const int chunk = (k_in_xcd / NS) * 8 + (blockIdx.x & 7), slice = k_in_xcd % NS;
+    const DownTile tile = down_tile(blockIdx.x, NS, (T + kD8Tokens - 1) / kD8Tokens, parts);
+    const int chunk = tile.chunk, slice = tile.slice;
     const int t_base = chunk * kD8Tokens;
-    if (t_base >= T) return;
+    if (t_base >= T || tile.part >= parts) return;
+    // this workgroup's share of the walk: whole batches of 32 experts
+    constexpr int kQuadsPerBatch = 8 * UPE;  // 32 experts
+    const int all_quads = (E * UPE + 3) >> 2;
+    const int part_quads = parts <= 1 ? all_quads : d8_part_batches(E, parts) * kQuadsPerBatch;
+    const int quad0 = tile.part * part_quads, n_quads = min(all_quads, quad0 + part_quads);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, c = lane & 31;
@@ -198,13 +206,13 @@ __global__ __launch_bounds__(256) void down_x8_kernel(
         is_next = item_start[ec];
         go_next = grow[ec];
     };
-    load_batch(0);
+    load_batch(quad0 / kQuadsPerBatch);
     // fetch state of the next unit in order; the fetches run FOUR units ahead of the MFMAs, so a
     // batch of 32 experts starts between two quads of the loop below, which keeps the quad's
     // body free of branches (with a branch inside, the compiler moved all MFMAs of a quad behind
     // its memory operations)
-    int fe = 0;  // next unit to fetch
-    int fbatch = 0;
+    int fe = 4 * quad0;  // next unit to fetch
+    int fbatch = quad0 / kQuadsPerBatch;
     auto next_batch = [&]() {
         mw = (tok_ok && fbatch < n_batches) ? mw_next : 0u;
         rowv = is_next * rows_per_item + go_next;
@@ -248,7 +256,7 @@ __global__ __launch_bounds__(256) void down_x8_kernel(
 #pragma unroll
     for (int ct = 0; ct < kD8CT; ++ct) a_voff[ct] = (uint32_t)(((col_w / 32 + ct) * 64 + lane) * 32);
     const uint32_t w_expert_bytes = (uint32_t)(d / 32) * 2048;
-    int we = 0;  // next unit whose weights are requested
+    int we = 4 * quad0;  // next unit whose weights are requested
     auto load_w = [&](i32x8 (&a)[kD8CT], int& sa) {
 #pragma unroll
         for (int ct = 0; ct < kD8CT; ++ct) {
@@ -267,7 +275,7 @@ __global__ __launch_bounds__(256) void down_x8_kernel(
         bf16x8 bias[kD8CT][2];
 #pragma unroll
         for (int ct = 0; ct < kD8CT; ++ct) bias[ct][0] = bias[ct][1] = zero8();
-        if (b_down) {
+        if (b_down && tile.part == 0) {
 #pragma unroll
             for (int ct = 0; ct < kD8CT; ++ct) {
                 bias[ct][0] = load8(b_down + col_w + 32 * ct + 16 * h);
@@ -309,9 +317,7 @@ __global__ __launch_bounds__(256) void down_x8_kernel(
     int sb[2][kD8Tiles];
 #pragma unroll
     for (int j = 0; j < kD8Tiles; ++j) read_b(0, j, bb[0][j], sb[0][j]);
-    const int n_quads = (n_units + 3) >> 2;
-    constexpr int kQuadsPerBatch = 8 * UPE;  // 32 experts
-    for (int qd = 0; qd < n_quads; ++qd) {
+    for (int qd = quad0; qd < n_quads; ++qd) {
         // the last quad of a batch fetches the first four units of the next batch
         if ((qd & (kQuadsPerBatch - 1)) == kQuadsPerBatch - 1) next_batch();
 #pragma unroll
@@ -353,7 +359,15 @@ __global__ __launch_bounds__(256) void down_x8_kernel(
 #pragma unroll
     for (int j = 0; j < kD8Tiles; ++j) {
         const int t = t_base + 32 * j + c;
-        if (t < T) {
+        if (t < T && parts > 1) {  // this part's share of the sum, in fp32
+#pragma unroll
+            for (int ct = 0; ct < kD8CT; ++ct) {
+                float* dst = partial + ((size_t)tile.part * T + t) * d + col_w + 32 * ct + 16 * h;
+#pragma unroll
+                for (int i = 0; i < 16; i += 4)
+                    *reinterpret_cast<f32x4*>(dst + i) = f32x4{acc[j][ct][i], acc[j][ct][i + 1], acc[j][ct][i + 2], acc[j][ct][i + 3]};
+            }
+        } else if (t < T) {
 #pragma unroll
             for (int ct = 0; ct < kD8CT; ++ct) {
                 bf16x8 o0, o1;
@@ -415,7 +429,7 @@ void launch_h_rows_quantize(const dmoe_layer& L, const int32_t* item_start, void
 
 void launch_down_x8(const dmoe_layer& L, int T, const int32_t* item_start, const int32_t* group_off,
                     const uint64_t* mask, const uint8_t* H8, const uint8_t* hs8, void* y,
-                    hipStream_t s) {
+                    float* partial, hipStream_t s) {
     LaunchTimer tm(kSlotDown, s);
     const PackedLayout P = packed_layout(L);
     const char* pk = static_cast<const char*>(L.packed);
@@ -425,11 +439,15 @@ void launch_down_x8(const dmoe_layer& L, int T, const int32_t* item_start, const
     const size_t w_bytes = (size_t)E * upe * (d / 32) * 2048;
     const int NG = div_up(T, kGroup), NC = div_up(T, kD8Tokens), NS = d / (kD8CT * 128);
     auto* kernel = upe == 1 ? down_x8_kernel<1> : down_x8_kernel<2>;
-    launch_kernel(kernel, round_up(NC, 8) * NS, 256, kD8Lds, s, (const uint8_t*)(pk + P.w2x8),
+    // (at most as many parts as the workspace was sized for, each of whole batches of 32 experts)
+    int parts = down_parts(L, T);
+    if (parts > 1) parts = div_up(div_up(E, 32), d8_part_batches(E, parts));
+    launch_kernel(kernel, down_grid(NC, NS, parts), 256, kD8Lds, s, (const uint8_t*)(pk + P.w2x8),
                   (const uint8_t*)(pk + P.wsc8), (const __bf16*)L.b_down, item_start, group_off,
                   reinterpret_cast<const uint32_t*>(mask), H8, hs8, (__bf16*)y, T, d, E, NG,
                   2 * div_up(E, 64), up_rows_bf16(L), (uint32_t)w_bytes,
-                  (uint32_t)(rows * 64 * upe), (uint32_t)rows);
+                  (uint32_t)(rows * 64 * upe), (uint32_t)rows, parts, partial);
+    if (parts > 1) launch_down_finish(L, T, partial, y, parts, s);
 }
 
 }  // namespace dmoe
