@@ -175,7 +175,7 @@ SelectWs select_ws(int T, int E, bool need_mask) {
 }
 
 struct LayerWs {
-    size_t scores, mask, group_off, sub_cnt, counts, offsets, item_start, witem, wfirst, lists, H, H8, hs8, colmask, partial, hid, x8, xscale, xhat, total;
+    size_t scores, mask, group_off, sub_cnt, counts, offsets, item_start, witem, wfirst, worder, lists, H, H8, hs8, colmask, partial, hid, x8, xscale, xhat, total;
 };
 LayerWs layer_ws(const dmoe_layer& L, int T) {
     LayerWs w{};
@@ -196,6 +196,9 @@ LayerWs layer_ws(const dmoe_layer& L, int T) {
     const int n_windows = L.dtype == DMOE_BF16 ? div_up(div_up(T, kGroup), up_window_groups(L, T)) : 0;
     w.witem = o;      o += align_up(sizeof(int32_t) * (size_t)n_windows * (E + 1));
     w.wfirst = o;     o += align_up(sizeof(int32_t) * (size_t)n_windows * E);
+    // order of the wide up-projection's work items: (expert, item) each
+    w.worder = o;
+    if (L.dtype == DMOE_BF16 && up_rows_bf16(L) == 256) o += align_up(8 * ((size_t)T * E / 256 + E));
     // token lists aligned to work items: one entry per row of H
     w.lists = o;      o += align_up(sizeof(int32_t) * h_fragments(L, T) * 16);
     w.H = o;
@@ -318,7 +321,8 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
         int32_t* wfirst = reinterpret_cast<int32_t*>(ws + w.wfirst);
         launch_scan_and_fill(mask, T, L.n_experts, group_off, counts, offsets, item_start,
                              up_rows_bf16(L), lists_out, alist, up_window_groups(L, T), witem,
-                             wfirst, s, sub_cnt, split);
+                             wfirst, s, sub_cnt, split, up_rows_bf16(L) == 256 ? ws + w.worder : nullptr,
+                             up_items_by_experts(L));
         void* H = ws + w.H;
         float* partial = reinterpret_cast<float*>(ws + w.partial);
         // 8-bit hidden activations on the 8-bit matrix cores: the rows as codes + scale bytes
@@ -329,10 +333,10 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
         // up-projection a kernel of its own quantises the bf16 rows)
         const bool up_writes_codes = down8 && up_x8_supported(L);
         if (up_x8_supported(L))
-            launch_up_x8(L, x8, xscale, T, witem, wfirst, alist, H, up_writes_codes ? H8 : nullptr,
+            launch_up_x8(L, x8, xscale, T, witem, ws + w.worder, alist, H, up_writes_codes ? H8 : nullptr,
                          up_writes_codes ? hs8 : nullptr, s);
         else
-            launch_up_bf16(L, x, T, witem, wfirst, alist, H, s);
+            launch_up_bf16(L, x, T, witem, wfirst, ws + w.worder, alist, H, s);
         if (down8) {
             if (!up_writes_codes) launch_h_rows_to_e4m3(L, item_start, H, H8, hs8, s);
             launch_down_x8(L, T, item_start, group_off, mask, H8, hs8, y, partial, s);

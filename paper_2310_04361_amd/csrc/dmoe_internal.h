@@ -202,7 +202,13 @@ void launch_scan_and_fill(const uint64_t* mask, int T, int E, int32_t* group_off
                           int32_t* offsets, int32_t* item_start, int rows_per_item,
                           int32_t* token_lists, int32_t* aligned_lists, int window_groups,
                           int32_t* witem, int32_t* wfirst, hipStream_t s,
-                          const int32_t* sub_cnt = nullptr, int split = 1);
+                          const int32_t* sub_cnt = nullptr, int split = 1, void* worder = nullptr,
+                          bool by_experts = false);
+// First of the N work items of the wide up-projection (in the order of worder) that XCD k takes.
+__host__ __device__ inline int xcd_first(int N, int k) { return (int)((long long)N * k / 8); }
+// Whether an XCD takes a share of the experts (and all the tokens) rather than a stretch of tokens
+// (and all the experts): see the order of the work items in select.hip.
+bool up_items_by_experts(const dmoe_layer& L);
 // The up-projection walks its work items window by window (window = window_groups consecutive
 // 64-token groups, window w on XCD w % 8) so that the x rows an XCD gathers stay in its L2:
 // witem[NW][E+1], wfirst[NW][E] are built with the lists (nullable: no tables).  A single window
@@ -291,7 +297,7 @@ void launch_pack_bf16(const dmoe_layer& L, void* packed, hipStream_t s);
 // H holds one row of m_pad hidden activations per list row (layout: see ffn_bf16.hip).
 // alist is the work-item-aligned token list (see select.hip); its index is the row index of H.
 void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* witem,
-                    const int32_t* wfirst, const int32_t* alist, void* H, hipStream_t s);
+                    const int32_t* wfirst, const void* worder, const int32_t* alist, void* H, hipStream_t s);
 // Down-projection and merge (down_bf16.hip): mask is the token-major selection bitmask that the
 // lists were built from; group_off[g][e] = rows of expert e that belong to tokens before group g.
 bool down_bf16_supported(const dmoe_layer& L);
@@ -360,7 +366,7 @@ void launch_pack_x8(const dmoe_layer& L, void* packed, hipStream_t s);
 // H8 / hs8 non-null: the rows go out quantised for the 8-bit
 // down-projection instead of as bf16 rows in H.
 void launch_up_x8(const dmoe_layer& L, const uint8_t* x8, const float* xscale, int T,
-                  const int32_t* witem, const int32_t* wfirst, const int32_t* alist, void* H,
+                  const int32_t* witem, const void* worder, const int32_t* alist, void* H,
                   uint8_t* H8, uint8_t* hs8, hipStream_t s);
 
 bool experts_bf16_supported(const dmoe_layer& L);

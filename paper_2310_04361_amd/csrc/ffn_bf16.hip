@@ -515,15 +515,25 @@ __global__ __launch_bounds__(256) void up_tiny_kernel(
 // across the end of an item, so that the first blocks of the next item arrive during the
 // activation epilogue of the current one instead of after it (an item is only 12 to 32 blocks
 // long, and a round trip beyond L2 takes as long as two or three blocks).
+//
+// What bounds it is the vector memory path: a CU keeps a fixed number of lines in flight, so a KB that
+// L2 answers costs about 17 cycles and one from beyond L2 about 88 (fits this kernel at three
+// different traffic figures).  Hence the order of the items (select.hip): 4096 tokens x 256 gated
+// experts of 64, d = 2048, 37 % density: 1.84 -> 0.74 GB from beyond L2, 272 -> 220 us; 24 x 128
+// experts at 50432 tokens: 195 -> 170 us.  The 32x32x16 MFMA takes half the instructions of the
+// 16x16x32 one (2048 tokens: 131 -> 123 us).  Built and slower: x rows by LDS-DMA and the weights
+// straight to registers, with a 2 x 2 split over the wavefronts (236 us: LDS instructions down to
+// a sixth, but more bytes and more drift between the workgroups, 0.96 GB).
 template <int MT, bool GATED, int TT>
 __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf,
     const __bf16* __restrict__ wgatef, const __bf16* __restrict__ b_up,
-    const int32_t* __restrict__ witem, const int32_t* __restrict__ wfirst,
+    const int32_t* __restrict__ witem, const int2* __restrict__ worder,
     const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act) {
     constexpr int BR = GATED ? 2 : 1;
     constexpr int KS = MT / 2;
     constexpr int NT = BR * MT;         // neuron tiles per K step
+    constexpr int NJ = NT / 2, TJ = TT / 2;  // tiles of the 32x32x16 MFMA: neurons, list rows
     constexpr int WR = TT * 16;         // rows per wavefront
     constexpr int UR = 4 * WR;          // rows per work item
     constexpr int NL = TT * 2;          // x load instructions per K block
@@ -532,24 +542,21 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     static_assert(NWF % 4 == 0 && MT % 2 == 0, "weight fragments are copied four at a time");
     extern __shared__ char smem[];
     char* wbuf = smem;                                   // [2][NWF][1024]
-    const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, h = lane >> 5, c32 = lane & 31, w = threadIdx.x >> 6;
     char* xs = smem + 2 * NWF * 1024 + w * (WR * kUpRowBytes);   // [WR][kUpRowBytes], private
     float* sbias = reinterpret_cast<float*>(smem + 2 * NWF * 1024 + 4 * (WR * kUpRowBytes));  // [2][MT * 16]
     const int NK32 = d / 32, NKB = d / 64;   // NKB >= 2
     const int ld_row = lane >> 3, ld_piece = lane & 7;
-    const int total = witem[E];
-    int j = blockIdx.x;
+    // this XCD's share of the items (workgroups are dealt round-robin to the 8 XCDs; the grid is a
+    // multiple of 8), in the order laid out by the list fill
+    const int xcd = blockIdx.x & 7, step = gridDim.x >> 3;
+    const int total = xcd_first(witem[E], xcd + 1);
+    int j = xcd_first(witem[E], xcd) + (blockIdx.x >> 3);
     if (j >= total) return;
-
-    // item j: its expert is the last e with witem[e] <= j (uniform binary search)
     auto locate = [&](int jj, int& e, int& item) {
-        int lo = 0, hi = E;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (witem[mid] <= jj) lo = mid; else hi = mid;
-        }
-        e = lo;
-        item = wfirst[lo] + (jj - witem[lo]);
+        const int2 v = worder[jj];
+        e = v.x;
+        item = v.y;
     };
     // tokens of the x rows this lane fetches; padding rows (-1) read token 0 and produce H rows
     // that nobody merges
@@ -608,38 +615,51 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     for (;;) {
         // the item after this one (the last item names itself: its first blocks are read again
         // and never used)
-        const int jn = j + (int)gridDim.x;
+        const int jn = j + step;
         const bool more = jn < total;
         int en = e, itemn = item;
         if (more) locate(jn, en, itemn);
 
-        f32x4 acc[NT][TT];
+        f32x16 acc[NJ][TJ];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+        for (int nj = 0; nj < NJ; ++nj)
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt) acc[nt][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int tj = 0; tj < TJ; ++tj)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[nj][tj][r] = 0.f;
         auto multiply = [&]() {
             if (active) {
-                const char* wsrc_l = wbuf + buf * NWF * 1024 + lane * 16;
-                const char* xsrc = xs + c * kUpRowBytes + q * 16;
+                // operands of k-step s (16 wide): neuron tile nj from the fragments of its two
+                // 16-row tiles, token tile tj from the staged rows; the next neuron tile's (and the
+                // next k-step's) operands are read while the current tile's MFMAs run
+                const char* wsrc_l = wbuf + buf * NWF * 1024 + (c32 >> 4) * 2048 + (h * 16 + (c32 & 15)) * 16;
+                const char* xsrc = xs + c32 * kUpRowBytes + h * 16;
+                auto read_a = [&](int s, int nj) {
+                    return *reinterpret_cast<const bf16x8*>(wsrc_l + nj * 4096 + (s >> 1) * 1024 + (s & 1) * 512);
+                };
+                auto read_b = [&](int s, int tj) {
+                    return *reinterpret_cast<const bf16x8*>(xsrc + tj * 32 * kUpRowBytes + s * 32);
+                };
+                bf16x8 b[2][TJ], a_next = read_a(0, 0);
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    bf16x8 b[TT];
+                for (int tj = 0; tj < TJ; ++tj) b[0][tj] = read_b(0, tj);
+                __builtin_amdgcn_sched_group_barrier(0x100, TJ + 1, 0);  // the reads so far
 #pragma unroll
-                    for (int tt = 0; tt < TT; ++tt)
-                        b[tt] = *reinterpret_cast<const bf16x8*>(xsrc + tt * 16 * kUpRowBytes + ks * 64);
-                    // the weight tile of the next four MFMAs is read while the current four run
-                    bf16x8 a_next = *reinterpret_cast<const bf16x8*>(wsrc_l + ks * 1024);
-                    __builtin_amdgcn_sched_group_barrier(0x100, TT + 1, 0);  // the reads so far
+                for (int s = 0; s < 4; ++s) {
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
+                    for (int nj = 0; nj < NJ; ++nj) {
                         const bf16x8 a = a_next;
-                        if (nt + 1 < NT)
-                            a_next = *reinterpret_cast<const bf16x8*>(wsrc_l + ((nt + 1) * 2 + ks) * 1024);
+                        const int n1 = nj + 1 < NJ ? nj + 1 : 0, s1 = nj + 1 < NJ ? s : s + 1;
+                        if (s1 < 4) a_next = read_a(s1, n1);
+                        if (nj == 0 && s + 1 < 4) {
 #pragma unroll
-                        for (int tt = 0; tt < TT; ++tt) acc[nt][tt] = mfma16(a, b[tt], acc[nt][tt]);
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read ...
-                        __builtin_amdgcn_sched_group_barrier(0x008, TT, 0); // ... then the MFMAs
+                            for (int tj = 0; tj < TJ; ++tj) b[(s + 1) & 1][tj] = read_b(s + 1, tj);
+                        }
+#pragma unroll
+                        for (int tj = 0; tj < TJ; ++tj) acc[nj][tj] = mfma32(a, b[s & 1][tj], acc[nj][tj]);
+                        if (nj == 0) __builtin_amdgcn_sched_group_barrier(0x100, 1 + TJ, 0);  // LDS reads ...
+                        else __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x008, TJ, 0);  // ... then the MFMAs
                     }
                 }
             }
@@ -673,28 +693,32 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
         if (active) with_activation(act, [&](auto act_c) {
             constexpr int ACT = decltype(act_c)::value;
             const float* sb = sbias + par * MT * 16;
+            // lane (h, c) of tile (nj, tj): list row 32 tj + c; registers 0..3 and 8..11 are the eight
+            // neurons of piece 4 nj + h of the H row, 4..7 and 12..15 those of piece 4 nj + 2 + h
+            // (neuron_of_slot over a pair of 16-row tiles)
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt) {
-                __bf16* dst = Hf + ((size_t)item * UR + w * WR + 16 * tt + c) * (KS * 32) + 8 * q;
+            for (int tj = 0; tj < TJ; ++tj) {
+                __bf16* dst = Hf + ((size_t)item * UR + w * WR + 32 * tj + c32) * (KS * 32);
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    bf16x8 hv;
+                for (int nj = 0; nj < KS; ++nj) {
 #pragma unroll
                     for (int half = 0; half < 2; ++half) {
-                        const int mt = 2 * ks + half;
+                        const int n0 = 8 * (4 * nj + 2 * half + h);
+                        bf16x8 hv;
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
+                        for (int r = 0; r < 8; ++r) {
+                            const int i = 4 * half + (r & 3) + 8 * (r >> 2);
                             float v;
-                            if (GATED) v = activate_fast(ACT, acc[MT + mt][tt][r]) * acc[mt][tt][r];
-                            else v = activate_fast(ACT, acc[mt][tt][r] + sb[neuron_of_slot(mt, 4 * q + r)]);
-                            if (neuron_of_slot(mt, 4 * q + r) >= m) v = 0.0f;
-                            hv[half * 4 + r] = (__bf16)v;
+                            if (GATED) v = activate_fast(ACT, acc[NJ / 2 + nj][tj][i]) * acc[nj][tj][i];
+                            else v = activate_fast(ACT, acc[nj][tj][i] + sb[n0 + r]);
+                            if (n0 + r >= m) v = 0.0f;
+                            hv[r] = (__bf16)v;
                         }
+                        *reinterpret_cast<bf16x8*>(dst + n0) = hv;
+                        // eight values at a time: interleaving more of them costs registers the
+                        // requests in flight are using
+                        __builtin_amdgcn_sched_barrier(0);
                     }
-                    *reinterpret_cast<bf16x8*>(dst + ks * 32) = hv;
-                    // eight values at a time: interleaving more of them costs registers the
-                    // requests in flight are using
-                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
         });
@@ -730,7 +754,7 @@ void launch_up_t(const dmoe_layer& L, const void* x, const PackedLayout& P, cons
 
 template <int MT, bool GATED, int TT>
 void launch_up_wide_t(const dmoe_layer& L, const void* x, const PackedLayout& P,
-                      const int32_t* witem, const int32_t* wfirst, const int32_t* alist,
+                      const int32_t* witem, const void* worder, const int32_t* alist,
                       void* H, int grid, hipStream_t s) {
     constexpr int NWF = 2 * (GATED ? 2 : 1) * MT;
     const size_t lds = 2 * NWF * 1024 + 4 * (size_t)TT * 16 * kUpRowBytes + 2 * MT * 16 * sizeof(float);
@@ -742,7 +766,7 @@ void launch_up_wide_t(const dmoe_layer& L, const void* x, const PackedLayout& P,
     const char* pk = static_cast<const char*>(L.packed);
     launch_kernel(up_wide_bf16_kernel<MT, GATED, TT>, grid, 256, lds, s, 
         (const __bf16*)x, (const __bf16*)(pk + P.wupf), (const __bf16*)(pk + P.wgatef),
-        (const __bf16*)L.b_up, witem, wfirst, alist, (__bf16*)H, L.d_model, L.n_experts,
+        (const __bf16*)L.b_up, witem, (const int2*)worder, alist, (__bf16*)H, L.d_model, L.n_experts,
         L.expert_size, L.act);
 }
 
@@ -801,6 +825,14 @@ void launch_pack_bf16(const dmoe_layer& L, void* packed, hipStream_t s) {
     }
 }
 
+// Where the weights of all experts fit an L2 or so, every XCD may as well read all of them and keep
+// to its own tokens; else the weights are what must not be read by every XCD.
+bool up_items_by_experts(const dmoe_layer& L) {
+    const size_t bytes = (size_t)L.n_experts * (L.gated ? 2 : 1) * m_pad_of(L.expert_size) * L.d_model *
+                         (up_x8_supported(L) ? 1 : 2);
+    return bytes > ((size_t)8 << 20);
+}
+
 // Groups of 64 tokens per up-projection window: the x rows of a window (about 3 MB) should stay
 // in the 4 MB L2 of the XCD that works on it, and the number of windows is a multiple of 8 so
 // that every XCD gets the same number.
@@ -816,7 +848,8 @@ int up_window_groups(const dmoe_layer& L, int T) {
 }
 
 void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* witem,
-                    const int32_t* wfirst, const int32_t* alist, void* H, hipStream_t s) {
+                    const int32_t* wfirst, const void* worder, const int32_t* alist, void* H,
+                    hipStream_t s) {
     LaunchTimer tm(kSlotUp, s);
     const PackedLayout P = packed_layout(L);
     const int NW = div_up(div_up(T, kGroup), up_window_groups(L, T));
@@ -828,8 +861,8 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
     if (up_rows_bf16(L) == 256) {  // wide experts: weights shared through LDS
         const int wgrid = round_up(
             (int)std::min<long long>((long long)T * L.n_experts / 256 + L.n_experts, 512), 8);
-        if (L.gated) launch_up_wide_t<4, true, 4>(L, x, P, witem, wfirst, alist, H, wgrid, s);
-        else launch_up_wide_t<8, false, 4>(L, x, P, witem, wfirst, alist, H, wgrid, s);
+        if (L.gated) launch_up_wide_t<4, true, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
+        else launch_up_wide_t<8, false, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
         return;
     }
     if (up_tiny_supported(L)) {

@@ -153,7 +153,7 @@ __global__ __launch_bounds__(256, 2) void up_wide_x8_kernel(
     const uint8_t* __restrict__ x8, const float* __restrict__ xscale,
     const uint8_t* __restrict__ wupx, const uint8_t* __restrict__ wgatex,
     const float* __restrict__ w_scales, const __bf16* __restrict__ b_up,
-    const int32_t* __restrict__ witem, const int32_t* __restrict__ wfirst,
+    const int32_t* __restrict__ witem, const int2* __restrict__ worder,
     const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, uint8_t* __restrict__ H8,
     uint8_t* __restrict__ hs8, int d, int E, int m, int act) {
     constexpr int BR = GATED ? 2 : 1;
@@ -171,19 +171,16 @@ __global__ __launch_bounds__(256, 2) void up_wide_x8_kernel(
     float* sbias = reinterpret_cast<float*>(smem + 2 * NT * 2048 + 4 * (WR * kX8RowBytes));  // [2][MT * 16]
     const int NKB = d / 128;   // >= 2
     const int ld_row = lane >> 3, ld_piece = lane & 7;
-    const int total = witem[E];
-    int j = blockIdx.x;
+    // this XCD's share of the items (workgroups are dealt round-robin to the 8 XCDs; the grid is a
+    // multiple of 8), in the order laid out by the list fill
+    const int xcd = blockIdx.x & 7, step = gridDim.x >> 3;
+    const int total = xcd_first(witem[E], xcd + 1);
+    int j = xcd_first(witem[E], xcd) + (blockIdx.x >> 3);
     if (j >= total) return;
-
-    // item j: its expert is the last e with witem[e] <= j (uniform binary search)
     auto locate = [&](int jj, int& e, int& item) {
-        int lo = 0, hi = E;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (witem[mid] <= jj) lo = mid; else hi = mid;
-        }
-        e = lo;
-        item = wfirst[lo] + (jj - witem[lo]);
+        const int2 v = worder[jj];
+        e = v.x;
+        item = v.y;
     };
     // tokens of the x rows this lane fetches; padding rows (-1) read token 0 and produce H rows
     // that nobody merges
@@ -246,7 +243,7 @@ __global__ __launch_bounds__(256, 2) void up_wide_x8_kernel(
     for (;;) {
         // the item after this one (the last item names itself: its first blocks are read again
         // and never used)
-        const int jn = j + (int)gridDim.x;
+        const int jn = j + step;
         const bool more = jn < total;
         int en = e, itemn = item;
         if (more) locate(jn, en, itemn);
@@ -388,7 +385,7 @@ __global__ __launch_bounds__(256, 2) void up_wide_x8_kernel(
 
 template <int MT, bool GATED, int TT, bool H8OUT>
 void launch_up_x8_t(const dmoe_layer& L, const PackedLayout& P, const uint8_t* x8,
-                    const float* xscale, const int32_t* witem, const int32_t* wfirst,
+                    const float* xscale, const int32_t* witem, const void* worder,
                     const int32_t* alist, void* H, uint8_t* H8, uint8_t* hs8, int grid,
                     hipStream_t s) {
     constexpr int NT = (GATED ? 2 : 1) * MT;
@@ -401,7 +398,7 @@ void launch_up_x8_t(const dmoe_layer& L, const PackedLayout& P, const uint8_t* x
     const char* pk = static_cast<const char*>(L.packed);
     launch_kernel(up_wide_x8_kernel<MT, GATED, TT, H8OUT>, grid, 256, lds, s, x8, xscale,
                   (const uint8_t*)(pk + P.wupx8), (const uint8_t*)(pk + P.wgatex8),
-                  (const float*)(pk + P.scales), (const __bf16*)L.b_up, witem, wfirst, alist,
+                  (const float*)(pk + P.scales), (const __bf16*)L.b_up, witem, (const int2*)worder, alist,
                   (__bf16*)H, H8, hs8, L.d_model, L.n_experts, L.expert_size, L.act);
 }
 
@@ -426,16 +423,16 @@ void launch_pack_x8(const dmoe_layer& L, void* packed, hipStream_t s) {
 }
 
 void launch_up_x8(const dmoe_layer& L, const uint8_t* x8, const float* xscale, int T,
-                  const int32_t* witem, const int32_t* wfirst, const int32_t* alist, void* H,
+                  const int32_t* witem, const void* worder, const int32_t* alist, void* H,
                   uint8_t* H8, uint8_t* hs8, hipStream_t s) {
     LaunchTimer tm(kSlotUp, s);
     const PackedLayout P = packed_layout(L);
     const int grid = round_up(
         (int)std::min<long long>((long long)T * L.n_experts / 256 + L.n_experts, 512), 8);
-    if (L.gated && H8) launch_up_x8_t<4, true, 4, true>(L, P, x8, xscale, witem, wfirst, alist, H, H8, hs8, grid, s);
-    else if (L.gated) launch_up_x8_t<4, true, 4, false>(L, P, x8, xscale, witem, wfirst, alist, H, nullptr, nullptr, grid, s);
-    else if (H8) launch_up_x8_t<8, false, 4, true>(L, P, x8, xscale, witem, wfirst, alist, H, H8, hs8, grid, s);
-    else launch_up_x8_t<8, false, 4, false>(L, P, x8, xscale, witem, wfirst, alist, H, nullptr, nullptr, grid, s);
+    if (L.gated && H8) launch_up_x8_t<4, true, 4, true>(L, P, x8, xscale, witem, worder, alist, H, H8, hs8, grid, s);
+    else if (L.gated) launch_up_x8_t<4, true, 4, false>(L, P, x8, xscale, witem, worder, alist, H, nullptr, nullptr, grid, s);
+    else if (H8) launch_up_x8_t<8, false, 4, true>(L, P, x8, xscale, witem, worder, alist, H, H8, hs8, grid, s);
+    else launch_up_x8_t<8, false, 4, false>(L, P, x8, xscale, witem, worder, alist, H, nullptr, nullptr, grid, s);
 }
 
 }  // namespace dmoe

@@ -274,7 +274,8 @@ __global__ __launch_bounds__(256) void fill_lists_kernel(
     const int32_t* __restrict__ sub, int split, int sub_rows,
     int row_shift, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
     int32_t* __restrict__ item_start, int32_t* __restrict__ lists, int32_t* __restrict__ alist,
-    int GW, int NW, int32_t* __restrict__ witem, int32_t* __restrict__ wfirst) {
+    int GW, int NW, int32_t* __restrict__ witem, int32_t* __restrict__ wfirst,
+    int2* __restrict__ worder, int by_experts) {
     extern __shared__ int32_t sm[];
     int32_t* s_off = sm;                 // [E + 1]
     int32_t* s_item = sm + (E + 1);      // [E + 1]
@@ -424,6 +425,54 @@ __global__ __launch_bounds__(256) void fill_lists_kernel(
         }
     }
 
+    // Order of the wide up-projection's work items.  XCD k takes the items k N / 8 .. of the order
+    // below; the workgroups of an XCD walk them side by side, so what those in flight share comes
+    // out of its L2.  Items are ordered by where their tokens lie (item i of an expert's n covers
+    // about the tokens i T / n .. (i + 1) T / n), so that the experts working on one stretch of
+    // tokens gather the same x rows: over all items (every XCD works on its own stretch with all
+    // the experts), or, by_experts, over the items of the XCD's own share of the experts (each
+    // XCD goes over all the tokens, but no two read the same weights).
+    if (worder) {
+        const int N = s_item[E];
+        auto expert_of = [&](int n) {  // the last e with s_item[e] <= n
+            int lo = 0, hi = E;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (s_item[mid] <= n) lo = mid; else hi = mid;
+            }
+            return lo;
+        };
+        // one wavefront per item, its lanes over the experts that share the item's range
+        const int waves = gridDim.x * gridDim.y * 4;
+        for (int n = (blockIdx.y * gridDim.x + blockIdx.x) * 4 + wave; n < N; n += waves) {
+            int lo = 0, hi = N;
+            if (by_experts) {
+                int k = 0;
+                while (k < 7 && n >= xcd_first(N, k + 1)) ++k;
+                lo = xcd_first(N, k);
+                hi = xcd_first(N, k + 1);
+            }
+            // (the three searches are one walk of three lanes)
+            const int found = expert_of(lane == 0 ? n : (lane == 1 ? lo : hi - 1));
+            const int e = __shfl(found, 0, kWave), e0 = __shfl(found, 1, kWave), e1 = __shfl(found, 2, kWave);
+            const double ne = (double)(s_item[e + 1] - s_item[e]), key = (double)(2 * (n - s_item[e]) + 1);
+            const double inv = 0.5 / ne;
+            int rank = 0;
+            for (int o = e0 + lane; o <= e1; o += kWave) {  // items of expert o in [lo, hi) that come before
+                const int no = s_item[o + 1] - s_item[o];
+                const int c0 = max(0, lo - s_item[o]), c1 = min(no, hi - s_item[o]);
+                // (2 i' + 1) / no < (2 i + 1) / ne, at equality the lower expert first
+                // (floor of an integer over 2 ne; the half added keeps the quotient off the integers,
+                // which makes the rounding of the multiplication harmless)
+                const double num = key * (double)no + ne - 1.0 + (o < e ? 1.0 : 0.0);
+                rank += max(0, min(c1, (int)((num + 0.5) * inv)) - c0);
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) rank += __shfl_xor(rank, off, kWave);
+            if (lane == 0) worder[lo + rank] = make_int2(e, n);
+        }
+    }
+
     // one workgroup per group of 64 tokens (lane = token); wavefront w takes the experts
     // 64*word + 16w .. +15 of every mask word
     if (g >= NG || (!lists && !alist)) return;
@@ -540,7 +589,7 @@ void launch_scan_and_fill(const uint64_t* mask, int T, int E, int32_t* group_off
                           int32_t* offsets, int32_t* item_start, int rows_per_item,
                           int32_t* token_lists, int32_t* aligned_lists, int window_groups,
                           int32_t* witem, int32_t* wfirst, hipStream_t s, const int32_t* sub_cnt,
-                          int split) {
+                          int split, void* worder, bool by_experts) {
     const int W = div_up(E, 64), NG = div_up(T, kGroup);
     const int NW = witem ? div_up(NG, window_groups) : 0;
     const bool fold = sub_cnt && NG > 0 && fold_scan(T, E, split);
@@ -570,7 +619,7 @@ void launch_scan_and_fill(const uint64_t* mask, int T, int E, int32_t* group_off
     while ((1 << row_shift) < rows_per_item) ++row_shift;
     launch_kernel(fold ? fill_lists_kernel<true> : fill_lists_kernel<false>, dim3(std::max(1, NG), ny), 256, lds, s,
         mask, T, E, W, group_off, sub_cnt, split, div_up(T, kGroup / split), row_shift, counts, offsets,
-        item_start, token_lists, aligned_lists, window_groups, NW, witem, wfirst);
+        item_start, token_lists, aligned_lists, window_groups, NW, witem, wfirst, (int2*)worder, by_experts ? 1 : 0);
 }
 
 }  // namespace dmoe
