@@ -91,7 +91,7 @@ typedef struct {
  *   W_down,e = w_scales[3e+2] * e4m3(w_down[e]).
  * Every scale must be a power of two: then each weight is exactly a bf16 number, and the layer
  * computes what a DMOE_W_NATIVE bf16 layer with those weights computes -- the prefill kernels
- * run on bf16 copies made by dmoe_pack_weights, the small-token kernels (up to 16 tokens, where
+ * run on bf16 copies made by dmoe_pack_weights, the small-token kernels (up to 64 tokens, where
  * the weights are the traffic) stream the bytes and convert in registers.  dmoe_pack_weights
  * replaces a scale that is not a power of two by the nearest one (in log2; zero stays zero) and
  * every kernel uses that copy, so all batch sizes compute the same layer.  w_scales is read by
@@ -251,10 +251,10 @@ int32_t dmoe_forward_topk(const dmoe_layer *layer, const void *x, int32_t n_toke
  * MLPs that are then converted like an FFN, so a Transformer block holds four more dynamic-k
  * layers; Q, K and V read the same input.  dmoe_forward_group runs 1 to 4 layers of ONE shape
  * (d_model, n_experts, expert_size, router_hidden, gated, act, dtype all equal; weights, biases and
- * tau per layer) on the same x and writes layer i's output to host_ys[i].  Up to 16 tokens (bf16
- * layers) every stage -- router, gate, up-projection, down-projection, merge -- is ONE launch for
- * the whole group, which is what counts at that size; for more tokens the layers run one after
- * the other exactly as dmoe_forward would run them.  Results are those of dmoe_forward, bit for
+ * tau per layer) on the same x and writes layer i's output to host_ys[i].  In small batches (up to
+ * 16 tokens, mostly up to 64; bf16 layers) every stage is ONE launch for the whole group -- router, gate
+ * and up-projection, then the down-projection -- which is what counts at that size; for more tokens the
+ * layers run one after the other exactly as dmoe_forward would run them.  Results are those of dmoe_forward, bit for
  * bit.
  *   layers     host array of n_layers pointers to host dmoe_layer structs
  *   host_taus  host array of n_layers thresholds, each in [0, 1]

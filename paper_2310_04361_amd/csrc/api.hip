@@ -56,7 +56,7 @@ int static_scratch_of_current_device(void** out) {
 // ---- timing ------------------------------------------------------------------------------------
 const char* const kSlotNames[kSlotCount] = {
     "router", "mask_count", "lists_to_mask", "scan_groups", "fill_lists",
-    "expert_up", "expert_down", "expert_down_sparse", "ffn_f32", "small_up", "small_down", "small_finish", "pack_weights",
+    "expert_up", "expert_down", "expert_down_sparse", "ffn_f32", "small_up", "small_down", "pack_weights",
     "quantize_x", "quantize_h"};
 constexpr int kEventPairs = 8192;
 bool g_timing = false;
@@ -175,7 +175,7 @@ SelectWs select_ws(int T, int E, bool need_mask) {
 }
 
 struct LayerWs {
-    size_t scores, mask, group_off, sub_cnt, counts, offsets, item_start, witem, wfirst, worder, lists, H, H8, hs8, colmask, partial, hid, x8, xscale, xhat, total;
+    size_t scores, mask, group_off, sub_cnt, counts, offsets, item_start, witem, wfirst, worder, lists, H, H8, hs8, colmask, sync, tickets, partial, hid, x8, xscale, xhat, total;
 };
 LayerWs layer_ws(const dmoe_layer& L, int T) {
     LayerWs w{};
@@ -211,16 +211,20 @@ LayerWs layer_ws(const dmoe_layer& L, int T) {
     }
     // small-token path: which tokens keep each expert, and the per-expert-group partial outputs
     // (or the shares of a divided down-projection)
-    w.colmask = o;
+    w.colmask = w.sync = w.tickets = o;
     w.partial = o;
-    if (L.dtype == DMOE_BF16) {  // also above kSmallTokens: the workspace never shrinks as T grows
+    if (L.dtype == DMOE_BF16) {  // also above kSmallBatch: the workspace never shrinks as T grows
         o += align_up(sizeof(uint64_t) * (size_t)E);
+        w.sync = o;
+        o += align_up(small_sync_bytes(L));
+        w.tickets = o;
+        o += align_up(small_ticket_bytes(L));
         w.partial = o;
         o += align_up(sizeof(float) * std::max((size_t)kSmallMaxGroups * 16 * L.d_model, down_partial_floats(L, T)));
     }
-    // hidden rows of the router: 16 for the small-token kernels, all T for a router that runs as
-    // two launches
-    const size_t hid_rows = (L.dtype == DMOE_BF16 && router_sliced(L)) ? std::max(T, 16) : 16;
+    // hidden rows of the router: kSmallBatch for the small-token kernels, all T for a router that runs
+    // as two launches
+    const size_t hid_rows = (L.dtype == DMOE_BF16 && router_sliced(L)) ? std::max(T, kSmallBatch) : kSmallBatch;
     w.hid = o;        o += align_up(2 * hid_rows * (size_t)std::max(L.router_hidden, 16));
     // 8-bit expert inputs: codes, scales and the quantised rows as bf16 (the latter for the
     // kernels that are not 8-bit: small-token path, shapes without the 8-bit up-projection)
@@ -236,7 +240,12 @@ LayerWs layer_ws(const dmoe_layer& L, int T) {
 
 bool use_small_path(const dmoe_layer& L, int T) {
     // (8-bit hidden activations: every batch size takes the list-based kernels)
-    return L.dtype == DMOE_BF16 && T <= kSmallTokens && small_bf16_supported(L) && !hidden_fp8(L);
+    if (L.dtype != DMOE_BF16 || !small_bf16_supported(L) || hidden_fp8(L)) return false;
+    if (T <= kSmallTokens) return true;
+    // Up to kSmallBatch tokens where reading all weights once is what a forward costs: the kernels
+    // stream padded experts and multiply every token, so not for experts with more than a third of
+    // padding (and not with more expert groups than the shares of 64 tokens have room for).
+    return T <= kSmallBatch && 3 * m_pad_of(L.expert_size) <= 4 * L.expert_size && L.n_experts <= 2048;
 }
 
 // Pointers of one layer for the small-token kernels (its workspace carved as in layer_ws).
@@ -267,6 +276,8 @@ SmallMod small_mod(const dmoe_layer& L, char* ws, const LayerWs& w, float* score
     M.mask = mask;
     M.colmask = reinterpret_cast<uint64_t*>(ws + w.colmask);
     M.group_cnt = reinterpret_cast<int32_t*>(ws + w.group_off);
+    M.sync = ws + w.sync;
+    M.tickets = ws + w.tickets;
     M.tau = tau;
     return M;
 }
@@ -279,8 +290,8 @@ bool counts_in_sub(const dmoe_layer& L, int T, int split) {
 }
 
 // Experts from mask bits whose group counts are already in the workspace (counts_in_sub).
-// gate_mod: the small-token path takes the gate into its up-projection (the scores, the mask and
-// the counts are then outputs of that kernel, described by gate_mod).
+// gate_mod: the small-token path takes router and gate into its up-projection (scores and mask are
+// then outputs of that kernel, described by gate_mod).
 int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const LayerWs& w,
                 const uint64_t* mask, int32_t* offsets_out, int32_t* lists_out, void* y,
                 hipStream_t s, int split = 1, const SmallMod* gate_mod = nullptr) {
@@ -292,6 +303,7 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
     // the kernels read the work-item-aligned copy in the workspace; the caller's is compact
     int32_t* alist = reinterpret_cast<int32_t*>(ws + w.lists);
     int32_t* item_start = reinterpret_cast<int32_t*>(ws + w.item_start);
+    const void* x_router = x;
     const uint8_t* x8 = nullptr;
     const float* xscale = nullptr;
     if (acts_fp8(L)) {
@@ -312,10 +324,12 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
     } else if (use_small_path(L, T)) {
         SmallGroup G{};
         G.m[0] = gate_mod ? *gate_mod : small_mod(L, ws, w, nullptr, nullptr, y, 0.0f);
-        launch_small_bf16(L, G, 1, x, T, gate_mod != nullptr, s);
-        if (offsets_out)  // after the experts: with the gate folded in, they write mask and counts
+        launch_small_bf16(L, G, 1, x_router, x, T, gate_mod != nullptr, s);
+        if (offsets_out) {  // after the experts: with the gate folded in, they write the mask
+            launch_counts_from_mask(mask, T, L.n_experts, group_off, nullptr, s);
             launch_scan_and_fill(mask, T, L.n_experts, group_off, counts, offsets, nullptr, 64,
                                  lists_out, nullptr, 1, nullptr, nullptr, s);
+        }
     } else {
         int32_t* witem = reinterpret_cast<int32_t*>(ws + w.witem);
         int32_t* wfirst = reinterpret_cast<int32_t*>(ws + w.wfirst);
@@ -566,6 +580,11 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
     const bool fused_router = layer->dtype == DMOE_BF16 && router_fused_scores_supported(*layer);
     const bool fused_gate = fused_router && router_fused_supported(*layer);
     int split = 1;
+    if (fused_router && colmask && gate.top_k < 0 && layer->n_experts <= kSmallGateMaxE) {
+        // router, gate and up-projection in one launch
+        const SmallMod M = small_mod(*layer, ws, w, scores_out, mask, y, tau);
+        return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s, 1, &M);
+    }
     if (fused_gate && n_tokens > kSmallTokens && gate.top_k < 0) {
         // router, dynamic-k gate and group counts in one kernel (with few token groups: several
         // workgroups per group, each with its own row of counts)
@@ -573,18 +592,6 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
         // (the gate works on the scores in registers: they go to memory only for a caller who
         // asked for them)
         launch_router_fused(*layer, x, n_tokens, split, scores_out, tau, mask, nullptr, counts_of(split), colmask, s);
-    } else if (fused_router && colmask && gate.top_k < 0 &&
-               layer->n_experts <= kSmallFusedSelectMaxE) {
-        SmallGroup G{};
-        G.m[0] = small_mod(*layer, ws, w, scores, mask, y, tau);
-        if (small_gate_in_up(*layer)) {
-            // the hidden product here; the second product and the gate ride in the up-projection
-            launch_router_small_hidden(*layer, G, 1, x, n_tokens, s);
-            return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s,
-                               1, &G.m[0]);
-        }
-        // hidden product, then scores + gate in one workgroup
-        launch_router_select_small(*layer, G, 1, x, n_tokens, s);
     } else {
         if (fused_router && n_tokens <= kSmallTokens) {
             SmallGroup G{};
@@ -694,7 +701,8 @@ int32_t dmoe_forward_group(const dmoe_layer* const* layers, int32_t n_layers, co
     hipStream_t s = (hipStream_t)stream;
     const dmoe_layer& L0 = *layers[0];
     // (layers with 8-bit inputs quantise x per layer call: they take the layer-by-layer route)
-    bool fused = use_small_path(L0, n_tokens) && !acts_fp8(L0);
+    bool fused = use_small_path(L0, n_tokens) && !acts_fp8(L0) &&
+                 (n_tokens <= kSmallTokens || L0.n_experts <= kSmallGateMaxE);
     for (int i = 0; i < n_layers; ++i) fused = fused && router_fused_scores_supported(*layers[i]);
     if (!fused) {  // larger batches: one layer after the other, each in its share of the workspace
         for (int i = 0; i < n_layers; ++i) {
@@ -706,22 +714,18 @@ int32_t dmoe_forward_group(const dmoe_layer* const* layers, int32_t n_layers, co
         return DMOE_OK;
     }
     SmallGroup G{};
+    const bool gate_in_up = L0.n_experts <= kSmallGateMaxE;
     for (int i = 0; i < n_layers; ++i) {
         const LayerWs w = layer_ws(*layers[i], n_tokens);
         char* wsi = ws + off[i];
-        G.m[i] = small_mod(*layers[i], wsi, w, reinterpret_cast<float*>(wsi + w.scores),
+        G.m[i] = small_mod(*layers[i], wsi, w, gate_in_up ? nullptr : reinterpret_cast<float*>(wsi + w.scores),
                            reinterpret_cast<uint64_t*>(wsi + w.mask), host_ys[i], host_taus[i]);
     }
-    const bool gate_in_up = small_gate_in_up(L0);
-    if (gate_in_up) {
-        launch_router_small_hidden(L0, G, n_layers, x, n_tokens, s);
-    } else if (L0.n_experts <= kSmallFusedSelectMaxE) {
-        launch_router_select_small(L0, G, n_layers, x, n_tokens, s);
-    } else {
+    if (!gate_in_up) {
         launch_router_small(L0, G, n_layers, x, n_tokens, s);
         launch_select_small_group(L0, G, n_layers, n_tokens, s);
     }
-    launch_small_bf16(L0, G, n_layers, x, n_tokens, gate_in_up, s);
+    launch_small_bf16(L0, G, n_layers, x, x, n_tokens, gate_in_up, s);
     return check_launch("group kernels");
 }
 

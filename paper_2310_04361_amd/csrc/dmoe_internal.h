@@ -145,7 +145,6 @@ enum Slot {
     kSlotFfnF32,
     kSlotSmallUp,
     kSlotSmallDown,
-    kSlotSmallFinish,
     kSlotPack,
     kSlotQuantX,
     kSlotQuantH,
@@ -191,6 +190,9 @@ void launch_mask_from_scores(const float* scores, int T, int E, float tau, uint6
 // Top-k gate: exactly k experts per token, ties at the k-th score to the lower expert index.
 void launch_mask_topk(const float* scores, int T, int E, int k, uint64_t* mask,
                       int32_t* k_per_token, int32_t* group_off, uint64_t* colmask, hipStream_t s);
+// Counts per (group, expert) and, if wanted, the per-expert token sets from mask bits.
+void launch_counts_from_mask(const uint64_t* mask, int T, int E, int32_t* group_off, uint64_t* colmask,
+                             hipStream_t s);
 void launch_mask_from_lists(const int32_t* offsets, const int32_t* lists, int T, int E,
                             uint64_t* mask, int32_t* group_off, uint64_t* colmask, hipStream_t s);
 // sub_cnt (nullable): the counts come as `split` rows per group (ceil(T * split / 64) rows) that
@@ -237,9 +239,9 @@ void launch_router_fused(const dmoe_layer& L, const void* x, int T, int split, f
                          float tau, uint64_t* mask, int32_t* k_per_token, int32_t* group_cnt,
                          uint64_t* colmask, hipStream_t s);
 
-// ---- small-token path (T <= kSmallTokens): up to kGroupMax layers of one shape per launch ----
+// ---- small-token path (use_small_path in api.hip): up to kGroupMax layers of one shape per launch ------
 // The attention projections Q, K and V are three converted layers with the same input (Sec. 3.5),
-// and at 16 tokens a forward is a handful of launches that each last a few microseconds: every
+// and at 16 tokens a forward is a few launches that each last a few microseconds: every
 // small-token kernel therefore takes the per-layer pointers of a whole group and works on layer
 // blockIdx.z.  A single layer is a group of one.
 constexpr int kGroupMax = 4;
@@ -252,6 +254,7 @@ struct SmallMod {
     float *scores, *partial;                               // scores [T][E]; per-expert-group partial outputs
     uint64_t *mask, *colmask;                              // mask [T][W]; colmask [E]
     int32_t* group_cnt;                                    // [E] tokens per expert
+    void *sync, *tickets;                                  // exchange area and counters of a call (ffn_small.hip)
     float tau;
 };
 struct SmallGroup {
@@ -261,34 +264,25 @@ struct SmallGroup {
 // hid is a 16 x d_h bf16 scratch buffer per layer.  The gate runs separately.
 void launch_router_small(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x,
                          int T, hipStream_t s);
-void launch_router_small_hidden(const dmoe_layer& L, const SmallGroup& G, int n_layers,
-                                const void* x, int T, hipStream_t s);
-// The same with the second product and the dynamic-k gate of every layer (M.tau) in ONE
-// workgroup, which also writes mask, colmask and group_cnt; for E <= kSmallFusedSelectMaxE.
-constexpr int kSmallFusedSelectMaxE = 1024;
-void launch_router_select_small(const dmoe_layer& L, const SmallGroup& G, int n_layers,
-                                const void* x, int T, hipStream_t s);
-// Where the second router matrix is small the up-projection's workgroups repeat that product and
-// the gate themselves (launch_small_bf16 with gate = true) and the gate launch goes away; with a
-// larger matrix the repeated product costs each workgroup more than the launch (256 experts,
-// d_h = 256: the up-projection grew by 10 us for a gate kernel of 8).
-inline bool small_gate_in_up(const dmoe_layer& L) {
-    return L.n_experts <= 64 && (size_t)L.n_experts * L.router_hidden <= 16384;
-}
 // Dynamic-k gate of every layer of the group on its stored scores (mask, colmask, group_cnt).
 void launch_select_small_group(const dmoe_layer& L, const SmallGroup& G, int n_layers, int T,
                                hipStream_t s);
 
-// ---- small-token experts (ffn_small.hip): T <= kSmallTokens, driven by colmask[0][e] -------------
-constexpr int kSmallTokens = 16;
-constexpr int kSmallMaxGroups = 32;   // expert groups whose partial outputs are summed at the end
+// ---- small-token forward (ffn_small.hip): T <= kSmallBatch -----------------------------------------
+constexpr int kSmallTokens = 16;      // one MFMA column tile
+constexpr int kSmallMaxTiles = 4;
+constexpr int kSmallBatch = 16 * kSmallMaxTiles;
+constexpr int kSmallMaxGroups = 32;   // expert groups whose shares are summed at the end
+constexpr int kSmallGateMaxE = 1024;  // experts up to which the router and the gate ride in the up-projection
 bool small_bf16_supported(const dmoe_layer& L);
-// Hs: E * (m_pad/32) KiB of fragments; partial: kSmallMaxGroups * 16 * d floats.
-// gate: the up-projection computes the scores and the dynamic-k gate (M.tau) itself from the
-// router's hidden rows (M.hid, written by launch_router_small_hidden) and writes M.scores, M.mask,
-// M.colmask and M.group_cnt on the way; otherwise it reads M.colmask.
-void launch_small_bf16(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x, int T,
-                       bool gate, hipStream_t s);
+size_t small_sync_bytes(const dmoe_layer& L);
+size_t small_ticket_bytes(const dmoe_layer& L);
+// Hs: E * (m_pad/32) * ceil(T/16) KiB of fragments; partial: at most 16 kSmallMaxGroups rows of d floats.
+// gate: router, dynamic-k gate (M.tau) and up-projection in one launch, which writes M.mask, M.colmask and,
+// if not null, M.scores; otherwise M.colmask comes from a gate that ran before.  x_router: the
+// router's input; x: the experts' (another one only in layers with 8-bit inputs).
+void launch_small_bf16(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x_router,
+                       const void* x, int T, bool gate, hipStream_t s);
 
 // ---- experts ----------------------------------------------------------------------------------
 void launch_ffn_f32(const dmoe_layer& L, const float* x, int T, const uint64_t* mask, float* y,

@@ -1,22 +1,39 @@
-// Small-token (decode) experts: T <= 16 tokens ride in ONE MFMA column tile, so the work is
-// reading every touched expert's weights exactly once -- a weight-bandwidth-bound stream.
+// Small batches (decode): up to 64 tokens ride in one to four MFMA column tiles (TT tiles of 16), so
+// the work is reading every touched expert's weights exactly once -- a weight-bandwidth-bound stream
+// -- and what is not the stream is launches and latency.  A forward is two launches:
 //
-//   up_small    one workgroup of sixteen wavefronts per expert; experts nobody selected exit
-//               before touching their weights.  With the gate folded in (gate_dh > 0) every
-//               workgroup first repeats the second router product and the threshold of Eq. 4 from
-//               the router's hidden rows -- 128 KB of router matrix out of L2 and a handful of
-//               MFMAs per wavefront -- and so knows its own expert's tokens without a gate kernel
-//               in front of it; one extra workgroup writes the scores, the mask and the
-//               per-expert token sets for the kernels and callers that follow.  The 16 x rows sit in LDS; wavefront (tile, slice)
-//               streams a K slice of one neuron tile of the up (and gate) fragments -- 1 KiB
-//               contiguous per load, 8 to 16 loads in flight per wavefront -- the slices are added
-//               through LDS and h (zero for tokens that did not select the expert) goes out as an
-//               H fragment.
-//   down_small  workgroup = (4 output-column tiles, group of experts): streams the touched
-//               experts' down fragments of its columns, accumulates in registers and writes one
-//               fp32 partial per expert group (no atomics).
-//   finish      y = bf16(b_down + sum of the partials).
-// colmask[e] (bit j = token j keeps expert e) comes from the gate's ballot transpose.
+//   small_up    router, gate and up-projection.  The first workgroups compute the router's hidden rows
+//               (one tile of 16 hidden units x 16 tokens each), one more per token tile collects
+//               them for the second router product and the gate and announces the token sets.  The
+//               other workgroups each own one or two neuron tiles of an expert: all wavefronts
+//               split K, the slices are added up through LDS and h goes out as H fragments.  They
+//               either wait for the announcement and drop the experts that nobody selected, or,
+//               where most experts will be touched or the weights are small, do not wait at all
+//               (see launch_up_t): the stream then runs while the router works.
+//   small_down  workgroup = (16 or 64 output columns, group of experts), its wavefronts split the
+//               touched experts and add up through LDS; with several expert groups the fp32 shares go
+//               to memory, and the last workgroup of a column group to finish adds them up in order.
+//               It masks the hidden rows with the token sets, so what was computed for nobody adds
+//               nothing.
+//
+// What workgroups of one launch exchange goes through agent-scope accesses, which pass by the per-XCD
+// L2s (a release fence would write the whole L2 back: measured ten times slower).  The flags behind
+// the hidden rows and the announced token sets (16 bits of payload, 48 of tag) carry the call's own
+// number, so nothing in the workspace needs to start at zero; small_down clears them for the replay
+// of a recorded graph, whose calls keep their number.  All waits are bounded: a gate that has not
+// seen all hidden rows for a while computes them itself, an up-projection workgroup that has seen no
+// announcement treats the expert as selected by everybody.
+//
+// Measured, whole call (five launches before, of which the prefill kernels took the sizes above 16
+// tokens): 32 experts of 24, d = 768, 16 tokens 20.8 -> 13.6 us; 256 gated experts of 64, d = 1024:
+// 1 token 28.5 -> 19.0, 16 tokens 57.6 -> 47.7, 48 tokens of e4m3 weights 97 -> 43.3 us.  At 16 tokens the
+// two streams (67 and 33 MB) run at 4 TB/s; the rest is the router's chain of two products (16 us with
+// the stream beside it) and the two launches.
+#include <atomic>
+#include <chrono>
+#include <cmath>
+#include <type_traits>
+
 #include "dmoe_internal.h"
 #include "mfma.h"
 #include "small_gate.h"
@@ -25,315 +42,720 @@ namespace dmoe {
 
 namespace {
 
+constexpr int kWaitPolls = 200;            // about 50 us
 
-// Sixteen wavefronts per workgroup = MT neuron tiles (m_pad / 16) x KQ slices of the K range: an
-// expert's weights are a pure stream, so what counts is how many bytes a CU keeps in flight.
-// Wavefront (mt, kq) streams its slice of tile mt (up and gate fragments, eight k-steps of loads
-// issued together), the KQ partial products are added through LDS.
-constexpr int kUpSmallWaves = 16;
+// Exchange area of one layer of a call: flags of the hidden tiles [token tile][32], tagged token sets
+// [token tile][E].
+constexpr int kMaxHidTiles = 32;  // d_h <= 512
+__device__ __forceinline__ uint64_t* flag_words(const SmallMod& M) { return reinterpret_cast<uint64_t*>(M.sync); }
+__device__ __forceinline__ uint64_t* set_words(const SmallMod& M) { return flag_words(M) + kSmallMaxTiles * kMaxHidTiles; }
+__device__ __forceinline__ uint32_t* tickets_of(const SmallMod& M) { return reinterpret_cast<uint32_t*>(M.tickets); }
+// tag: the call's number in the upper 48 bits
+__device__ __forceinline__ bool has_tag(uint64_t word, uint64_t tag) { return (word >> 16) == (tag >> 16); }
 
+template <typename V>
+__device__ __forceinline__ void store_agent(V* p, V v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename V>
+__device__ __forceinline__ V load_agent(const V* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ---- router and gate ------------------------------------------------------------------------------
+// Hidden units 16 h .. + 15 of the tokens of tile tt: KQ wavefronts split K and add up through LDS
+// (red[KQ][64]), kB k-steps per request.  Returns, in wavefront 0, lane (q, c): hidden units
+// 16 h + 4 q + r of token c.
+template <int KQ, int kB>
+__device__ __forceinline__ bf16x4 small_hidden_tile(const SmallMod& M, const __bf16* __restrict__ x, int h, int tt,
+                                                    int T, int d, f32x4* red) {
+    const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int NK32 = d / 32, per = NK32 / KQ;
+    const __bf16* af = M.r1f + (((size_t)h * NK32 + w * per) * 64 + lane) * 8;
+    const __bf16* xr = x + (size_t)min(16 * tt + c, T - 1) * d + 8 * q + 32 * w * per;
+    bf16x4 b1 = {};
+    if (M.r_b1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) b1[r] = M.r_b1[16 * h + 4 * q + r];
+    }
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 a[2][kB], b[2][kB];
+    auto load = [&](int kb, int set) {
+#pragma unroll
+        for (int i = 0; i < kB; ++i)
+            if (kb + i < per) {  // uniform
+                a[set][i] = load8(af + (size_t)(kb + i) * 512);
+                b[set][i] = load8(xr + 32 * (kb + i));
+            }
+    };
+    auto multiply = [&](int kb, int set) {
+#pragma unroll
+        for (int i = 0; i < kB; ++i)
+            if (kb + i < per) acc = mfma16(a[set][i], b[set][i], acc);
+    };
+    load(0, 0);
+    for (int kb = 0; kb < per; kb += 2 * kB) {
+        load(kb + kB, 1);
+        multiply(kb, 0);
+        if (kb + 2 * kB < per) load(kb + 2 * kB, 0);
+        multiply(kb + kB, 1);
+    }
+    red[w * 64 + lane] = acc;
+    __syncthreads();
+    bf16x4 hv = {};
+    if (w == 0) {
+        f32x4 sum = red[lane];
+#pragma unroll
+        for (int k = 1; k < KQ; ++k) sum += red[k * 64 + lane];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) hv[r] = (__bf16)fmaxf(sum[r] + (float)b1[r], 0.0f);
+    }
+    return hv;
+}
+
+template <int KQ>
+__device__ __forceinline__ void small_hidden_wg(const SmallMod& M, const __bf16* __restrict__ x, int h, int tt, int T, int d,
+                                int dh, uint64_t tag, char* smem) {
+    const bf16x4 hv = small_hidden_tile<KQ, 8>(M, x, h, tt, T, d, reinterpret_cast<f32x4*>(smem));
+    const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+    if (threadIdx.x < 64) {
+        store_agent(reinterpret_cast<uint64_t*>(M.hid + (size_t)(16 * tt + c) * dh + 16 * h + 4 * q),
+                    __builtin_bit_cast(uint64_t, hv));
+        wait_vmem();  // the rows are out before the flag
+        if (lane == 0) store_agent(flag_words(M) + tt * kMaxHidTiles + h, tag);
+    }
+}
+
+// Second router product and gate of token tile tt; KS2 = d_h / 32.  The scores stay in registers: lane (q, c)
+// of expert tile et holds the experts 16 et + 4 q + r of token c, so the ballot over "kept" of one r is the
+// token sets of four experts, and only the row maxima go through LDS.  The mask words, which nobody in
+// this launch waits for, are assembled after the announcement.
+template <int KQ, int KS2>
+__device__ __forceinline__ void small_gate_wg(const SmallMod& M, const __bf16* __restrict__ x, int tt, int T, int d,
+                                              int E, uint64_t tag, char* smem) {
+    constexpr int dh = 32 * KS2, NH = dh / 16, kHRow = 2 * dh + 16;  // (bytes per hidden row, bank skew)
+    constexpr int kThreads = 64 * KQ, kTiles = KS2 >= 8 ? (KS2 == 8 ? 4 : 2) : 8;  // R2 tiles requested ahead
+    constexpr int kMost = kSmallGateMaxE / 16 / KQ;                // tiles per wavefront
+    const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int W = (E + 63) >> 6, NE = (E + 15) >> 4;
+    char* hid = smem;                                              // [16][kHRow]
+    float* pmax = reinterpret_cast<float*>(smem + 16 * kHRow);     // [KQ][16]
+    int* s_missing = reinterpret_cast<int*>(pmax + 16 * KQ);
+    f32x4* red = reinterpret_cast<f32x4*>(smem);                   // (fallback) [KQ][64]
+
+    // this wavefront's expert tiles w, w + KQ, ...: the first ones' fragments are requested now
+    bf16x8 r2[kTiles][KS2];
+    auto load_r2 = [&](int j, bf16x8 (&a)[KS2]) {
+        const int et = min(w + KQ * j, NE - 1);
+#pragma unroll
+        for (int ks = 0; ks < KS2; ++ks) a[ks] = load8(M.r2f + (((size_t)et * KS2 + ks) * 64 + lane) * 8);
+    };
+#pragma unroll
+    for (int j = 0; j < kTiles; ++j)
+        if (w + KQ * j < NE) load_r2(j, r2[j]);  // uniform
+    // wait for the hidden rows
+    const uint64_t* flags = flag_words(M) + tt * kMaxHidTiles;
+    bool missing = true;
+    for (int poll = 0; poll < kWaitPolls && missing; ++poll) {
+        const bool here = lane >= NH || load_agent(flags + min(lane, NH - 1)) == tag;
+        missing = __ballot(!here) != 0ull;
+        if (missing) __builtin_amdgcn_s_sleep(1);
+    }
+    const uint64_t* hsrc = reinterpret_cast<const uint64_t*>(M.hid + (size_t)16 * tt * dh);
+    constexpr int kWords = 16 * dh / 4 / kThreads;                 // 8-byte words per thread
+    static_assert(kWords >= 1, "hidden rows");
+    uint64_t hw[kWords];
+    auto load_hidden = [&]() {
+#pragma unroll
+        for (int k = 0; k < kWords; ++k) hw[k] = load_agent(hsrc + k * kThreads + tid);
+    };
+    if (!missing) load_hidden();
+    if (tid == 0) *s_missing = 0;
+    lds_barrier();
+    if (missing && lane == 0) *s_missing = 1;
+    lds_barrier();
+    if (*s_missing != 0) {  // (uniform) compute them here
+        __syncthreads();
+        for (int h = 0; h < NH; ++h) {
+            const bf16x4 hv = small_hidden_tile<KQ, 1>(M, x, h, tt, T, d, red);
+            if (w == 0)
+                store_agent(reinterpret_cast<uint64_t*>(M.hid + (size_t)(16 * tt + c) * dh + 16 * h + 4 * q),
+                            __builtin_bit_cast(uint64_t, hv));
+            __syncthreads();
+        }
+        wait_vmem();
+        __syncthreads();
+        load_hidden();
+    }
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) {
+        const int i = k * kThreads + tid;  // word i % (dh / 4) of row i / (dh / 4)
+        *reinterpret_cast<uint64_t*>(hid + (i / (dh / 4)) * kHRow + (i % (dh / 4)) * 8) = hw[k];
+    }
+    lds_barrier();
+    // s = |R2 hid + c2|, 0 for the experts from E on
+    const int tok = 16 * tt + c;
+    bf16x8 hb[KS2];
+#pragma unroll
+    for (int ks = 0; ks < KS2; ++ks) hb[ks] = *reinterpret_cast<const bf16x8*>(hid + c * kHRow + ks * 64 + q * 16);
+    float sc[kMost][4];
+    float mx = 0.0f;  // (the scores are not negative)
+    auto score_tile = [&](const bf16x8 (&a)[KS2], int j) {
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS2; ++ks) acc = mfma16(a[ks], hb[ks], acc);
+        return router_scores4(acc, M.r_b2, min(16 * (w + KQ * j) + 4 * q, E - 1), E);
+    };
+#pragma unroll
+    for (int j = 0; j < kMost; ++j) {
+        const int e0 = 16 * (w + KQ * j) + 4 * q;
+        if (w + KQ * j >= NE) break;  // uniform
+        if (j >= kTiles) load_r2(j, r2[j % kTiles]);
+        const float4 o = score_tile(r2[j % kTiles], j);
+        sc[j][0] = e0 < E ? o.x : 0.0f; sc[j][1] = e0 < E ? o.y : 0.0f;
+        sc[j][2] = e0 < E ? o.z : 0.0f; sc[j][3] = e0 < E ? o.w : 0.0f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sc[j][r]);
+        if (M.scores && tok < T && e0 < E) store_scores4(M.scores + (size_t)tok * E, e0, E, o);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (q == 0) pmax[w * 16 + c] = mx;
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < KQ; ++k) mx = fmaxf(mx, pmax[k * 16 + c]);
+    // the exact comparison: the fp64 product of two fp32 numbers is exact
+    const double thr = (double)M.tau * (double)mx;
+    const uint32_t keep_all = M.tau == 0.0f ? 1u : 0u, live = tok < T ? 1u : 0u;
+    uint16_t* cm16 = reinterpret_cast<uint16_t*>(M.colmask);
+    uint64_t* sets = set_words(M) + (size_t)tt * E;
+    uint32_t bits[kMost];  // lane (q, c): its four experts of token c
+#pragma unroll
+    for (int j = 0; j < kMost; ++j) {
+        const int et = w + KQ * j, e0 = 16 * et + 4 * q;
+        if (et >= NE) break;  // uniform
+        bits[j] = 0;
+        uint64_t bal[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t ge = (double)sc[j][r] >= thr ? 1u : 0u;
+            const uint32_t k = (keep_all | ge) & live & (e0 + r < E ? 1u : 0u);
+            bits[j] |= k << r;
+            bal[r] = __ballot(k);
+        }
+        // lane (q, c < 4): the set of expert 16 et + 4 q + c, announced and for small_down
+        const uint64_t mine = c == 0 ? bal[0] : (c == 1 ? bal[1] : (c == 2 ? bal[2] : bal[3]));
+        if (c < 4 && e0 + c < E) {
+            const uint32_t set = (uint32_t)(mine >> (16 * q)) & 0xffffu;
+            store_agent(sets + e0 + c, tag | set);
+            cm16[4 * (e0 + c) + tt] = (uint16_t)set;
+        }
+    }
+    // mask words, a quarter (the 16 experts of a tile) at a time; the quarters from E on are zero
+    uint16_t* mask16 = reinterpret_cast<uint16_t*>(M.mask) + (size_t)tok * (4 * W);
+#pragma unroll
+    for (int j = 0; j < kMost; ++j) {
+        const int et = w + KQ * j;
+        if (et >= 4 * W) break;  // uniform
+        uint32_t b = et < NE ? bits[j] << (4 * q) : 0u;
+        b |= __shfl_xor(b, 16, 64);
+        b |= __shfl_xor(b, 32, 64);
+        if (q == 0 && tok < T) mask16[et] = (uint16_t)b;
+    }
+}
+
+// ---- up-projection --------------------------------------------------------------------------------
 // W8: the weight fragments hold one E4M3 byte per weight (half the stream); they are converted to
 // bf16 in registers, and the per-expert power-of-two scales are applied to the fp32 sums.
-template <int MT, bool GATED, bool W8>
-__global__ __launch_bounds__(64 * kUpSmallWaves) void up_small_kernel(
-    const SmallGroup G, const __bf16* __restrict__ x, int T, int d, int m, int act, int KQ,
-    int E, int gate_dh) {
+// MTW: 16-row neuron tiles per work item (an expert's MT / MTW items follow each other); TT: token tiles; KQ
+// wavefronts split K.  A workgroup takes the items b, b + n_wg, ... of all the experts or, once the token
+// sets are known, of the touched ones; their weights are one stream: a fragment's registers are filled
+// with the next batch as soon as it has been multiplied.
+template <bool GATED, int MTW, int TT, bool W8, int KQ>
+__global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
+    const SmallGroup G, const __bf16* __restrict__ x_router, const __bf16* __restrict__ x, int T, int d,
+    int m, int MT, int act, int E, int dh, uint64_t tag, int wait, int n_wg) {
+    constexpr int BR = GATED ? 2 : 1;
+    // k-steps whose weights are in flight (half of it where the accumulators leave no more registers)
+    constexpr int kFrags = (TT + BR >= 5 && !W8 ? 16 : 32) / (BR * MTW);
+    constexpr int kB = kFrags < 16 ? kFrags : 16;
+    constexpr int kX = TT == 1 ? kB / 2 : 2;  // ... and whose x rows are, twice
+    static_assert(kB % (2 * kX) == 0, "batches");
     const SmallMod& M = G.m[blockIdx.z];
-    const __bf16* __restrict__ wupf = M.wupf;
-    const __bf16* __restrict__ wgatef = M.wgatef;
-    const __bf16* __restrict__ b_up = M.b_up;
-    __bf16* __restrict__ Hs = M.Hs;
-    constexpr int KS = MT / 2, kThreads = 64 * kUpSmallWaves, BR = GATED ? 2 : 1;
-    const int e = blockIdx.x;
-    extern __shared__ char smem[];
+    extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c = lane & 15;
-    const int pieces = d / 8;
-    // With the gate folded in, the first x pieces of every thread are requested before the gate
-    // and parked in LDS after it (the gate's scores use the same LDS).
-    constexpr int kPre = 4;
-    bf16x8 xpre[kPre];
-    auto x_piece = [&](int i) {
-        return load8(x + (size_t)min(i / pieces, T - 1) * d + (i % pieces) * 8);
-    };
-    if (gate_dh > 0 && e < E) {
-#pragma unroll
-        for (int k = 0; k < kPre; ++k)
-            if (tid + k * kThreads < 16 * pieces) xpre[k] = x_piece(tid + k * kThreads);
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int b = blockIdx.x;
+    if (b == 0) {  // tickets of small_down
+        for (int i = tid; i < d / 16; i += 64 * KQ) tickets_of(M)[i] = 0u;
     }
-    uint64_t cm;
-    if (gate_dh > 0) {
-        // scores of all experts in LDS, then this expert's column against every token's threshold
-        const int W = (E + 63) >> 6;
-        // (all in the dynamic block: a static array next to a 160 KB dynamic limit is refused)
-        int* s_keep = reinterpret_cast<int*>(smem);                   // [16]
-        uint64_t* mw = reinterpret_cast<uint64_t*>(smem + 64);        // [16][W], output workgroup only
-        float* sc = reinterpret_cast<float*>(mw + 16 * W);            // [16][E]
-        const bool out_wg = e == E;  // the extra workgroup: scores, mask, token sets to memory
-        small_scores_to_lds(M, T, gate_dh, E, sc, out_wg);
-        __syncthreads();
-        if (out_wg) {
-            select_small_body(sc, mw, M.mask, nullptr, M.group_cnt, M.colmask, T, E, W, M.tau);
+    if (dh > 0) {
+        const int n_hidden = (dh / 16) * TT;
+        if (b < n_hidden) {
+            small_hidden_wg<KQ>(M, x_router, b % (dh / 16), b / (dh / 16), T, d, dh, tag, smem);
             return;
         }
-        const int t = threadIdx.x >> 6;  // wavefront t = token t
-        bool keep = false;
-        if (t < T) keep = small_keeps(sc[(size_t)t * E + e], M.tau, small_row_max(sc + (size_t)t * E, E));
-        if ((threadIdx.x & 63) == 0) s_keep[t] = keep ? 1 : 0;
-        __syncthreads();
-        cm = __ballot((threadIdx.x & 63) < 16 && s_keep[threadIdx.x & 15] != 0) & 0xffffull;
-        __syncthreads();  // the score rows make way for the x rows
-    } else {
-        cm = M.colmask[e];
+        b -= n_hidden;
+        if (b < TT) {
+            switch (dh) {
+            case 64: small_gate_wg<KQ, 2>(M, x_router, b, T, d, E, tag, smem); return;
+            case 128: small_gate_wg<KQ, 4>(M, x_router, b, T, d, E, tag, smem); return;
+            case 256: small_gate_wg<KQ, 8>(M, x_router, b, T, d, E, tag, smem); return;
+            default: small_gate_wg<KQ, 16>(M, x_router, b, T, d, E, tag, smem); return;
+            }
+        }
+        b -= TT;
     }
-    if (cm == 0ull) return;  // uniform: nobody selected this expert
-    const int row_bytes = 2 * d + 16;
-    char* xs = smem;                                                    // [16][2d + 16]
-    // [16 waves][BR][64][4] partial sums: they take the place of the x rows once every wavefront
-    // has finished reading those
-    float* red = reinterpret_cast<float*>(smem);
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int mt = w % MT, kq = w / MT;
-    auto x_park = [&](int i, bf16x8 v) {
-        *reinterpret_cast<bf16x8*>(xs + (i / pieces) * row_bytes + (i % pieces) * 16) = v;
-    };
-    int i_first = tid;
-    if (gate_dh > 0) {
-#pragma unroll
-        for (int k = 0; k < kPre; ++k)
-            if (tid + k * kThreads < 16 * pieces) x_park(tid + k * kThreads, xpre[k]);
-        i_first = tid + kPre * kThreads;
-    }
-    for (int i = i_first; i < 16 * pieces; i += kThreads) x_park(i, x_piece(i));
-    __syncthreads();
+    const int per_e = MT / MTW;
+    const int NK32 = d / 32, per = NK32 / KQ, k0 = w * per;  // KQ divides NK32
+    f32x4* red = reinterpret_cast<f32x4*>(smem);             // [KQ][MTW][TT][BR][64]
 
-    const int NK32 = d / 32, per = NK32 / KQ;  // k-steps per slice (KQ divides NK32)
-    f32x4 acc[BR];
-#pragma unroll
-    for (int br = 0; br < BR; ++br) acc[br] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (kq < KQ) {
-        const size_t frag0 = (((size_t)e * MT + mt) * NK32 * 64 + lane) * 8;  // elements
-        const __bf16* au = wupf + frag0;
-        const __bf16* ag = wgatef + frag0;
-        const uint8_t* au8 = M.wupf8 + frag0;
-        const uint8_t* ag8 = M.wgatef8 + frag0;
-        const char* bsrc = xs + c * row_bytes + q * 16;
-        const int k0 = kq * per;
-        for (int kb = 0; kb < per; kb += 8) {
-            bf16x8 a[8][BR];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int ks = k0 + min(kb + i, per - 1);  // past the slice: a block already read
-                if (W8) {
-                    a[i][0] = e4m3x8_to_bf16(*reinterpret_cast<const uint2*>(au8 + (size_t)ks * 512));
-                    if (GATED)
-                        a[i][BR - 1] = e4m3x8_to_bf16(*reinterpret_cast<const uint2*>(ag8 + (size_t)ks * 512));
+    // compact list of the touched experts and their token sets
+    constexpr uint64_t kAll = TT == 4 ? ~0ull : (1ull << (16 * TT)) - 1ull;
+    uint64_t* s_cm = reinterpret_cast<uint64_t*>(red + KQ * MTW * TT * BR * 64);  // [E]
+    uint16_t* s_list = reinterpret_cast<uint16_t*>(s_cm + E);                     // [E]
+    const bool compact = dh == 0 || wait != 0;
+    int n_items = E * per_e;
+    if (compact) {
+        int* s_n = reinterpret_cast<int*>(red);
+        if (w == 0) {
+            const uint64_t* sets = set_words(M);
+            bool ready = dh == 0;
+            int polls = ready ? kWaitPolls : 0;
+            for (; polls < kWaitPolls && !ready; ++polls) {  // one word first: this workgroup's b-th expert
+                ready = has_tag(load_agent(sets + b % E), tag);
+                if (!ready) __builtin_amdgcn_s_sleep(4);
+            }
+            int n = 0;
+            for (int base = 0; base < E; base += 64) {
+                const int e = min(base + lane, E - 1);
+                uint64_t cm = 0ull;
+                if (dh == 0) {
+                    cm = M.colmask[e] & kAll;
                 } else {
-                    a[i][0] = load8(au + (size_t)ks * 512);
-                    if (GATED) a[i][BR - 1] = load8(ag + (size_t)ks * 512);
+                    bool all_in = false;
+                    for (; !all_in; ++polls) {
+                        bool mine = true;
+                        cm = 0ull;
+#pragma unroll
+                        for (int tt = 0; tt < TT; ++tt) {
+                            const uint64_t v = load_agent(sets + (size_t)tt * E + e);
+                            mine = mine && has_tag(v, tag);
+                            cm |= (v & 0xffffull) << (16 * tt);
+                        }
+                        all_in = __ballot(!mine) == 0ull;
+                        if (!all_in && polls >= kWaitPolls) {  // waited long enough: everybody wants it
+                            cm = mine ? cm : kAll;
+                            all_in = true;
+                        }
+                    }
+                }
+                if (base + lane >= E) cm = 0ull;
+                const uint64_t bal = __ballot(cm != 0ull);
+                if (cm != 0ull) {
+                    const int at = n + __popcll(bal & ((1ull << lane) - 1ull));
+                    s_list[at] = (uint16_t)e;
+                    s_cm[at] = cm;
+                }
+                n += __popcll(bal);
+            }
+            if (lane == 0) *s_n = n;
+        }
+        lds_barrier();
+        n_items = __builtin_amdgcn_readfirstlane(*s_n) * per_e;
+        lds_barrier();
+    } else if (dh > 0) {
+        // let the router's loads go first: behind the stream they would take three times as long
+        __builtin_amdgcn_s_sleep(32);
+    }
+    auto expert_of = [&](int item) {
+        return compact ? __builtin_amdgcn_readfirstlane((int)s_list[item / per_e]) : item / per_e;
+    };
+
+    typedef typename std::conditional<W8, uint2, bf16x8>::type Frag;
+    Frag a[kB][MTW][BR];
+    // fragments of k-step kb + i of an item (at: the item's first fragment)
+    auto first_of = [&](int item) {
+        return (((size_t)expert_of(item) * MT + (item % per_e) * MTW) * NK32 + k0) * 512 + lane * 8;
+    };
+    auto load_step = [&](bool some, size_t first, int kb, int i) {
+        if (some && kb + i < per) {  // uniform
+#pragma unroll
+            for (int t = 0; t < MTW; ++t)
+#pragma unroll
+                for (int br = 0; br < BR; ++br) {
+                    const size_t at = first + ((size_t)t * NK32 + kb + i) * 512;
+                    if constexpr (W8) a[i][t][br] = *reinterpret_cast<const uint2*>((br ? M.wgatef8 : M.wupf8) + at);
+                    else a[i][t][br] = load8((br ? M.wgatef : M.wupf) + at);
+                }
+        }
+    };
+    int item = b;
+    if (item >= n_items) return;
+    size_t first = first_of(item);
+#pragma unroll
+    for (int i = 0; i < kB; ++i) load_step(true, first, 0, i);
+    const __bf16* xr[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) xr[tt] = x + (size_t)min(16 * tt + c, T - 1) * d + 8 * q + 32 * k0;
+    bf16x8 xb[2][kX][TT];
+    auto load_x = [&](int k, bf16x8 (&v)[kX][TT]) {
+#pragma unroll
+        for (int i = 0; i < kX; ++i)
+            if (k + i < per) {
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) v[i][tt] = load8(xr[tt] + 32 * (k + i));
+            }
+    };
+    const bool x_stays = kB == 2 * kX && per <= kB;  // one batch: its x rows serve every item
+    if (x_stays) {
+        load_x(0, xb[0]);
+        load_x(kX, xb[1]);
+    }
+    for (;;) {
+        const int next = item + n_wg;
+        const bool more = next < n_items;
+        const size_t first_next = more ? first_of(next) : 0;
+        f32x4 acc[MTW][BR][TT];
+#pragma unroll
+        for (int t = 0; t < MTW; ++t)
+#pragma unroll
+            for (int br = 0; br < BR; ++br)
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) acc[t][br][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int kb = 0; kb < per; kb += kB) {
+            const bool end = kb + kB >= per;
+            const bool some = !end || more;
+            const size_t first_load = end ? first_next : first;
+            const int kb_load = end ? 0 : kb + kB;
+            if (!x_stays) load_x(kb, xb[0]);
+#pragma unroll
+            for (int i0 = 0; i0 < kB; i0 += kX) {
+                if (!x_stays && i0 + kX < kB) load_x(kb + i0 + kX, xb[(i0 / kX + 1) & 1]);
+#pragma unroll
+                for (int i = 0; i < kX; ++i) {
+                    if (kb + i0 + i < per) {
+#pragma unroll
+                        for (int t = 0; t < MTW; ++t)
+#pragma unroll
+                            for (int br = 0; br < BR; ++br) {
+                                bf16x8 av;
+                                if constexpr (W8) av = e4m3x8_to_bf16(a[i0 + i][t][br]);
+                                else av = a[i0 + i][t][br];
+#pragma unroll
+                                for (int tt = 0; tt < TT; ++tt)
+                                    acc[t][br][tt] = mfma16(av, xb[(i0 / kX) & 1][i][tt], acc[t][br][tt]);
+                            }
+                    }
+                    load_step(some, first_load, kb_load, i0 + i);
                 }
             }
+        }
+        // add the K slices up
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if (kb + i < per) {
-                    const bf16x8 b = *reinterpret_cast<const bf16x8*>(bsrc + (k0 + kb + i) * 64);
+        for (int t = 0; t < MTW; ++t)
 #pragma unroll
-                    for (int br = 0; br < BR; ++br) acc[br] = mfma16(a[i][br], b, acc[br]);
+            for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                for (int br = 0; br < BR; ++br)
+                    red[(((w * MTW + t) * TT + tt) * BR + br) * 64 + lane] = acc[t][br][tt];
+        lds_barrier();
+        const int e = expert_of(item), mt0 = (item % per_e) * MTW;
+        const uint64_t set = compact ? s_cm[item / per_e] : kAll;
+        float s_up = 1.0f, s_gate = 1.0f, s_down = 1.0f;
+        if (W8) {
+            s_up = M.w_scales[3 * e + 0];
+            s_gate = M.w_scales[3 * e + 1];
+            s_down = M.w_scales[3 * e + 2];  // folded into H: the down kernel sums over experts
+        }
+        for (int i = w; i < MTW * TT; i += KQ) {
+            const int t = i / TT, tt = i % TT, mt = mt0 + t;
+            f32x4 s[BR];
+#pragma unroll
+            for (int br = 0; br < BR; ++br) {
+                s[br] = red[(i * BR + br) * 64 + lane];
+#pragma unroll
+                for (int k = 1; k < KQ; ++k) s[br] += red[((k * MTW * TT + i) * BR + br) * 64 + lane];
+            }
+            // lane (q, c): neurons neuron_of_slot(mt, 4q + r) of token c of tile tt
+            const bool keep = 16 * tt + c < T && ((set >> (16 * tt + c)) & 1ull);
+            bf16x4 hv;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int n = neuron_of_slot(mt, 4 * q + r);
+                float v;
+                if (GATED) {
+                    v = activate_fast(act, s[BR - 1][r] * s_gate) * (s[0][r] * s_up);
+                } else {
+                    const float bias = M.b_up ? (float)M.b_up[(size_t)e * m + min(n, m - 1)] : 0.0f;
+                    v = activate_fast(act, s[0][r] * s_up + bias);
                 }
+                v *= s_down;
+                if (n >= m || !keep) v = 0.0f;
+                hv[r] = (__bf16)v;
+            }
+            *reinterpret_cast<bf16x4*>(M.Hs + ((((size_t)e * (MT / 2) + (mt >> 1)) * TT + tt) * 64 + lane) * 8 + (mt & 1) * 4) = hv;
+        }
+        if (!more) break;
+        lds_barrier();  // the slices of the next item take the same place
+        item = next;
+        first = first_next;
+    }
+}
+
+// ---- down-projection ------------------------------------------------------------------------------
+// grid = (16 CTW-column groups, expert groups, layers); KS = m_pad / 32; NW wavefronts split the experts
+// (wavefront w: e0 + w, + NW, ...; at most 64 each), U of them in flight.  all: every expert's weights are
+// read whether somebody selected it or not, so that they are requested before the token sets are here.
+template <int KS, int TT, int CTW, int NW, int U, bool W8>
+__global__ __launch_bounds__(64 * NW) void small_down_kernel(const SmallGroup G, int T, int d, int E, int per,
+                                                             int dh, int all) {
+    const SmallMod& M = G.m[blockIdx.z];
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    f32x4* red = reinterpret_cast<f32x4*>(smem);  // [NW][CTW][TT][64]
+    __shared__ int s_last;
+    const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cg = blockIdx.x, eg = blockIdx.y, EG = gridDim.y;
+    const int e_first = eg * per + w, e_end = min(E, eg * per + per);
+    constexpr uint64_t kAll = TT == 4 ? ~0ull : (1ull << (16 * TT)) - 1ull;
+    // lane i: the token set of this wavefront's i-th expert
+    const int e_lane = e_first + NW * lane;
+    const uint64_t cm = e_lane < e_end ? M.colmask[e_lane] & kAll : 0ull;
+    const int n_mine = e_first < e_end ? (e_end - e_first + NW - 1) / NW : 0;
+    uint64_t todo = all ? (n_mine >= 64 ? ~0ull : (1ull << n_mine) - 1ull) : __ballot(cm != 0ull);
+
+    const size_t w_tile = (size_t)KS * 512, w_expert = (size_t)(d / 16) * w_tile;  // elements
+    const size_t wl = (size_t)(CTW * cg) * w_tile + lane * 8;
+    typedef typename std::conditional<W8, uint2, bf16x8>::type Frag;
+    f32x4 acc[CTW][TT];
+#pragma unroll
+    for (int ct = 0; ct < CTW; ++ct)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) acc[ct][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // a ring of U experts in flight: a slot is filled again as soon as it has been multiplied
+    Frag wa[U][CTW][KS];
+    bf16x8 hb[U][KS][TT];
+    int at[U];
+    auto request = [&](int u) {
+        at[u] = -1;
+        if (todo != 0ull) {  // uniform
+            at[u] = __builtin_ctzll(todo);
+            todo &= todo - 1ull;
+            const int e = e_first + NW * at[u];
+#pragma unroll
+            for (int ct = 0; ct < CTW; ++ct)
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const size_t p = (size_t)e * w_expert + wl + ct * w_tile + ks * 512;
+                    if constexpr (W8) wa[u][ct][ks] = *reinterpret_cast<const uint2*>(M.w2f8 + p);
+                    else wa[u][ct][ks] = load8(M.w2f + p);
+                }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt)
+                    hb[u][ks][tt] = load8(M.Hs + (((size_t)e * KS + ks) * TT + tt) * 512 + lane * 8);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) request(u);
+    bool more = at[0] >= 0;
+    while (more) {  // uniform
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (at[u] >= 0) {
+                const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)cm, at[u]);
+                const uint32_t hi = TT > 2 ? __builtin_amdgcn_readlane((int)(uint32_t)(cm >> 32), at[u]) : 0;
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt) {
+                    const bool keep = ((tt < 2 ? lo : hi) >> (16 * (tt & 1) + c)) & 1u;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        const bf16x8 hv = keep ? hb[u][ks][tt] : zero8();
+#pragma unroll
+                        for (int ct = 0; ct < CTW; ++ct) {
+                            bf16x8 av;
+                            if constexpr (W8) av = e4m3x8_to_bf16(wa[u][ct][ks]);
+                            else av = wa[u][ct][ks];
+                            acc[ct][tt] = mfma16(av, hv, acc[ct][tt]);
+                        }
+                    }
+                }
+                request(u);
             }
         }
+        more = at[0] >= 0;
     }
-    __syncthreads();  // the x rows have been consumed
 #pragma unroll
-    for (int br = 0; br < BR; ++br)
-        *reinterpret_cast<f32x4*>(red + ((w * BR + br) * 64 + lane) * 4) = acc[br];
+    for (int ct = 0; ct < CTW; ++ct)
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt) red[((w * CTW + ct) * TT + tt) * 64 + lane] = acc[ct][tt];
+    if (dh > 0) {  // the flags of small_up, for the next replay
+        const int stride = 64 * NW * gridDim.x * EG, first = (eg * gridDim.x + cg) * 64 * NW + tid;
+        for (int i = first; i < kSmallMaxTiles * kMaxHidTiles + TT * E; i += stride) flag_words(M)[i] = 0ull;
+    }
+    lds_barrier();
+    // wavefront i < CTW TT: column tile i / TT, token tile i % TT; lane (q, c): four columns of token c
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    // (shares lie in accumulator order, so that a wavefront writes and reads whole lines)
+    auto share = [&](int g, int i) {
+        return reinterpret_cast<uint64_t*>(M.partial) + (((size_t)g * gridDim.x + cg) * (CTW * TT) + i) * 128 + lane;
+    };
+    auto out = [&](int t, int col, f32x4 v) {
+        bf16x4 o;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = (__bf16)(v[r] + (M.b_down ? (float)M.b_down[col + r] : 0.0f));
+        *reinterpret_cast<bf16x4*>(M.y + (size_t)t * d + col) = o;
+    };
+    for (int i = w; i < CTW * TT; i += NW) {
+        f32x4 v = red[i * 64 + lane];
+#pragma unroll
+        for (int k = 1; k < NW; ++k) v += red[(k * CTW * TT + i) * 64 + lane];
+        const int t = 16 * (i % TT) + c, col = 16 * (CTW * cg + i / TT) + 4 * q;
+        if (t < T) {
+            if (EG == 1) out(t, col, v);
+        }
+        if (EG > 1) {
+            const u64x2 u = __builtin_bit_cast(u64x2, v);
+            store_agent(share(eg, i), (uint64_t)u[0]);
+            store_agent(share(eg, i) + 64, (uint64_t)u[1]);
+        }
+    }
+    if (EG == 1) return;
+    wait_vmem();
     __syncthreads();
-    if (kq != 0) return;
-    // wavefront (mt, 0): sum the KQ slices; lane (q, c): neurons neuron_of_slot(mt, 4q + r) of token c
-#pragma unroll
-    for (int br = 0; br < BR; ++br) {
-        f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < KQ; ++k) {
-            const f32x4 v = *reinterpret_cast<const f32x4*>(red + (((k * MT + mt) * BR + br) * 64 + lane) * 4);
-            sum += v;
-        }
-        acc[br] = sum;
-    }
-    const bool keep = c < T && ((cm >> c) & 1ull);
-    float s_up = 1.0f, s_gate = 1.0f, s_down = 1.0f;
-    if (W8) {
-        s_up = M.w_scales[3 * e + 0];
-        s_gate = M.w_scales[3 * e + 1];
-        s_down = M.w_scales[3 * e + 2];  // folded into H: the down kernel sums over experts
-    }
-    bf16x4 hv;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int n = neuron_of_slot(mt, 4 * q + r);
-        float v;
-        if (GATED) {
-            v = activate_fast(act, acc[BR - 1][r] * s_gate) * (acc[0][r] * s_up);
-        } else {
-            const float bias = b_up ? (float)b_up[(size_t)e * m + min(n, m - 1)] : 0.0f;
-            v = activate_fast(act, acc[0][r] * s_up + bias);
-        }
-        v *= s_down;
-        if (n >= m || !keep) v = 0.0f;
-        hv[r] = (__bf16)v;
-    }
-    *reinterpret_cast<bf16x4*>(Hs + (((size_t)e * KS + (mt >> 1)) * 64 + lane) * 8 + (mt & 1) * 4) = hv;
-}
-
-constexpr int kSmallPerGroup = 256;  // experts per group at most
-
-// grid = (column-tile groups of 4, expert groups); KS = m_pad / 32.
-template <int KS, bool W8>
-__global__ __launch_bounds__(256) void down_small_kernel(const SmallGroup G, int T, int d, int E,
-                                                         int per) {
-    const SmallMod& M = G.m[blockIdx.z];
-    const __bf16* __restrict__ w2f = M.w2f;
-    const uint64_t* __restrict__ colmask = M.colmask;
-    const __bf16* __restrict__ Hs = M.Hs;
-    float* __restrict__ partial = M.partial;
-    __shared__ int s_list[kSmallPerGroup];
-    __shared__ int s_n;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, c = lane & 15;
-    const int eg = blockIdx.y;
-    const int e0 = eg * per, e1 = min(E, e0 + per);
-    if (w == 0) {  // compact list of this group's touched experts
-        int n = 0;
-        for (int base = e0; base < e1; base += 64) {
-            const int e = base + lane;
-            const bool f = e < e1 && colmask[e] != 0ull;
-            const uint64_t bal = __ballot(f);
-            if (f) s_list[n + __popcll(bal & ((1ull << lane) - 1ull))] = e;
-            n += __popcll(bal);
-        }
-        if (lane == 0) s_n = n;
-    }
+    if (tid == 0)
+        s_last = __hip_atomic_fetch_add(tickets_of(M) + cg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(EG - 1);
     __syncthreads();
-    const int n = s_n;
-    const int ct = blockIdx.x * 4 + w;
-    if (ct >= d / 16) return;
-    const __bf16* wa = w2f + ((size_t)ct * KS * 64 + lane) * 8;
-    const uint8_t* wa8 = M.w2f8 + ((size_t)ct * KS * 64 + lane) * 8;
-    const size_t w_expert_stride = (size_t)(d / 16) * KS * 512;
-    const __bf16* hb = Hs + lane * 8;
-    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int i = 0; i < n; ++i) {
-        const int e = s_list[i];
+    if (!s_last) return;
+    for (int i = w; i < CTW * TT; i += NW) {
+        const int t = 16 * (i % TT) + c, col = 16 * (CTW * cg + i / TT) + 4 * q;
+        f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int g0 = 0; g0 < EG; g0 += 8) {
+            u64x2 u[8];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            acc = mfma16(W8 ? e4m3x8_to_bf16(*reinterpret_cast<const uint2*>(
-                                  wa8 + (size_t)e * w_expert_stride + ks * 512))
-                            : load8(wa + (size_t)e * w_expert_stride + ks * 512),
-                         load8(hb + ((size_t)e * KS + ks) * 512), acc);
-    }
-    // lane (q, c): columns 16ct + 4q .. +3 of token c
-    if (c < T) {
-        float4 o;
-        o.x = acc[0]; o.y = acc[1]; o.z = acc[2]; o.w = acc[3];
-        *reinterpret_cast<float4*>(partial + ((size_t)eg * 16 + c) * d + 16 * ct + 4 * q) = o;
+            for (int k = 0; k < 8; ++k) {
+                const uint64_t* p = share(min(g0 + k, EG - 1), i);
+                u[k] = u64x2{load_agent(p), load_agent(p + 64)};
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (g0 + k < EG) v += __builtin_bit_cast(f32x4, u[k]);
+        }
+        if (t < T) out(t, col, v);
     }
 }
 
-__global__ void finish_small_kernel(const SmallGroup G, int T, int d, int EG) {
-    const SmallMod& M = G.m[blockIdx.z];
-    const float* __restrict__ partial = M.partial;
-    const __bf16* __restrict__ b_down = M.b_down;
-    __bf16* __restrict__ y = M.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= T * d) return;
-    const int t = i / d, col = i % d;
-    float v = b_down ? (float)b_down[col] : 0.0f;
-    const float* p = partial + (size_t)t * d + col;
-    const size_t stride = (size_t)16 * d;
-    int eg = 0;
-    for (; eg + 8 <= EG; eg += 8) {  // eight independent loads in flight
-        float u[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) u[k] = p[(size_t)(eg + k) * stride];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v += u[k];
-    }
-    for (; eg < EG; ++eg) v += p[(size_t)eg * stride];
-    y[i] = (__bf16)v;
+// Number of this call for the flags: never the same twice in a process, and unlikely to be what an
+// unused workspace holds.
+uint64_t next_tag() {
+    static std::atomic<uint64_t> counter{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull};
+    return (counter.fetch_add(1, std::memory_order_relaxed) << 16) | 0x8000000000000000ull;  // (never the zero of a cleared word)
 }
 
-template <int MT, bool GATED, bool W8>
-void launch_up_small_t(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x, int T,
-                       bool gate, hipStream_t s) {
-    const int E = L.n_experts;
-    size_t lds = std::max(16 * (2 * (size_t)L.d_model + 16),
-                          sizeof(float) * kUpSmallWaves * (GATED ? 2 : 1) * 64 * 4);
-    if (gate) lds = std::max(lds, 64 + sizeof(uint64_t) * 16 * div_up(E, 64) + sizeof(float) * 16 * (size_t)E);
+// Whether to read all experts' weights without waiting for the gate.  The gate's announcement comes about
+// 7 us after the launch; against that stands the time to read the weights that nobody will turn
+// out to want, at 5 TB/s, for a guess of 16 % of the experts per token (what a random router keeps at a
+// threshold of one half).
+bool small_reads_all(const dmoe_layer& L, int T) {
+    const double bytes = (double)L.n_experts * (L.gated ? 2 : 1) * m_pad_of(L.expert_size) * L.d_model *
+                         (weights_fp8(L) ? 1 : 2);
+    return bytes * pow(1.0 - 0.16, T) < 5e6 * 7.0;
+}
+
+template <bool GATED, int MTW, int TT, bool W8, int KQ>
+void launch_up_t(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x_router, const void* x,
+                 int T, bool gate, hipStream_t s) {
+    const int E = L.n_experts, MT = m_pad_of(L.expert_size) / 16, dh = gate ? L.router_hidden : 0;
+    const int wait = gate && !small_reads_all(L, T) ? 1 : 0;
+    size_t lds = (size_t)KQ * MTW * TT * (GATED ? 2 : 1) * 1024;
+    if (!gate || wait) lds += (sizeof(uint64_t) + sizeof(uint16_t)) * (size_t)E;
+    if (gate)
+        lds = std::max(lds, 16 * (2 * (size_t)dh + 16) + 16 * KQ * sizeof(float) + 16);
     static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
     std::call_once(attr_once, [&] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_small_kernel<MT, GATED, W8>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&small_up_kernel<GATED, MTW, TT, W8, KQ>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
-    // K slices: as many as the sixteen wavefronts allow and the k-steps divide into
-    int KQ = kUpSmallWaves / MT;
-    while (KQ > 1 && (L.d_model / 32) % KQ != 0) KQ >>= 1;
-    launch_kernel(up_small_kernel<MT, GATED, W8>, dim3(E + (gate ? 1 : 0), 1, n_layers),
-                  64 * kUpSmallWaves, lds, s, G, (const __bf16*)x, T, L.d_model, L.expert_size, L.act,
-                  KQ, E, gate ? L.router_hidden : 0);
+    // Two workgroups per CU are resident; with more items than that each takes several.
+    const int n_wg = std::min(E * (MT / MTW), 512);
+    launch_kernel(small_up_kernel<GATED, MTW, TT, W8, KQ>, dim3((dh > 0 ? (dh / 16 + 1) * TT : 0) + n_wg, 1, n_layers),
+                  64 * KQ, lds, s, G, (const __bf16*)x_router, (const __bf16*)x, T, L.d_model, L.expert_size,
+                  MT, L.act, E, dh, gate ? next_tag() : 0, wait, n_wg);
 }
 
-template <int MT, bool GATED>
-void launch_up_small_w(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x, int T,
-                       bool gate, hipStream_t s) {
-    if (weights_fp8(L)) launch_up_small_t<MT, GATED, true>(L, G, n_layers, x, T, gate, s);
-    else launch_up_small_t<MT, GATED, false>(L, G, n_layers, x, T, gate, s);
+template <bool GATED, bool W8>
+void launch_up_tt(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x_router, const void* x,
+                  int T, bool gate, hipStream_t s) {
+    // One token tile: one neuron tile per workgroup, so that a few touched experts still spread over
+    // the chip.  More: two, which halves the reads of x.
+    switch (div_up(T, 16)) {
+    case 1: launch_up_t<GATED, 1, 1, W8, 4>(L, G, n_layers, x_router, x, T, gate, s); break;
+    case 2: launch_up_t<GATED, 2, 2, W8, 4>(L, G, n_layers, x_router, x, T, gate, s); break;
+    case 3: launch_up_t<GATED, 2, 3, W8, 4>(L, G, n_layers, x_router, x, T, gate, s); break;
+    default: launch_up_t<GATED, 2, 4, W8, 4>(L, G, n_layers, x_router, x, T, gate, s); break;
+    }
+}
+
+template <int KS, bool W8>
+void launch_down_tt(const dmoe_layer& L, const SmallGroup& G, int n_layers, int T, bool gate, hipStream_t s) {
+    const int E = L.n_experts, d = L.d_model, TT = div_up(T, 16);
+    const int all = small_reads_all(L, T) ? 1 : 0, dh = gate ? L.router_hidden : 0;
+    // One token tile: 16 columns and 16 wavefronts per workgroup, which needs no shares in memory up to
+    // a few experts per wavefront.  More: 64 columns, so that the hidden rows are read less often.
+    // Expert groups: one, or enough workgroups to fill the chip, and no more shares than the workspace
+    // holds (kSmallMaxGroups x 16 rows).  The same for a layer of a group as for a layer alone: the
+    // sums must not depend on that.
+    auto go = [&](auto kernel, int ctw, int nw, int EG) {
+        EG = std::max(std::min({EG, kSmallMaxGroups, kSmallMaxGroups / TT}), div_up(E, 64 * nw));
+        const int per = div_up(E, std::max(1, EG));
+        const size_t lds = (size_t)nw * ctw * TT * 1024;
+        launch_kernel(kernel, dim3(d / (16 * ctw), div_up(E, per), n_layers), 64 * nw, lds, s, G, T, d, E, per, dh, all);
+    };
+    constexpr int U1 = KS <= 2 ? 4 : 2, U4 = KS <= 2 ? 2 : 1;  // (more would not fit the registers)
+    const int eg1 = div_up(E, 128), eg4 = std::min(div_up(256, d / 64), E / 8);
+    switch (TT) {
+    case 1: go(small_down_kernel<KS, 1, 1, 16, U1, W8>, 1, 16, eg1); break;
+    case 2: go(small_down_kernel<KS, 2, 4, 8, U4, W8>, 4, 8, eg4); break;
+    case 3: go(small_down_kernel<KS, 3, 4, 8, U4, W8>, 4, 8, eg4); break;
+    default: go(small_down_kernel<KS, 4, 4, 8, U4, W8>, 4, 8, eg4); break;
+    }
 }
 
 }  // namespace
 
+size_t small_sync_bytes(const dmoe_layer& L) {
+    return 8 * (size_t)kSmallMaxTiles * (kMaxHidTiles + std::min(L.n_experts, kSmallGateMaxE));
+}
+size_t small_ticket_bytes(const dmoe_layer& L) { return sizeof(uint32_t) * (size_t)(L.d_model / 16); }
+
 bool small_bf16_supported(const dmoe_layer& L) {
     const int mp = m_pad_of(L.expert_size);
-    // LDS of the up kernel: the 16 x rows (the partial sums of its wavefronts reuse the space)
-    const size_t up_lds = 16 * (2 * (size_t)L.d_model + 16);
-    return L.packed != nullptr && (mp == 32 || mp == 64 || mp == 128) && L.d_model % 32 == 0 &&
-           up_lds <= 160 * 1024 &&
-           div_up(L.n_experts, kSmallMaxGroups) <= kSmallPerGroup;
+    return L.packed != nullptr && (mp == 32 || mp == 64 || mp == 128) && L.d_model % 256 == 0;
 }
 
-void launch_small_bf16(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x, int T,
-                       bool gate, hipStream_t s) {
-    const int mt = m_pad_of(L.expert_size) / 16;
+void launch_small_bf16(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x_router,
+                       const void* x, int T, bool gate, hipStream_t s) {
+    const bool w8 = weights_fp8(L);
     {
         LaunchTimer tm(kSlotSmallUp, s);
-        if (L.gated) {
-            if (mt == 2) launch_up_small_w<2, true>(L, G, n_layers, x, T, gate, s);
-            else if (mt == 4) launch_up_small_w<4, true>(L, G, n_layers, x, T, gate, s);
-            else launch_up_small_w<8, true>(L, G, n_layers, x, T, gate, s);
-        } else {
-            if (mt == 2) launch_up_small_w<2, false>(L, G, n_layers, x, T, gate, s);
-            else if (mt == 4) launch_up_small_w<4, false>(L, G, n_layers, x, T, gate, s);
-            else launch_up_small_w<8, false>(L, G, n_layers, x, T, gate, s);
-        }
+        if (L.gated && w8) launch_up_tt<true, true>(L, G, n_layers, x_router, x, T, gate, s);
+        else if (L.gated) launch_up_tt<true, false>(L, G, n_layers, x_router, x, T, gate, s);
+        else if (w8) launch_up_tt<false, true>(L, G, n_layers, x_router, x, T, gate, s);
+        else launch_up_tt<false, false>(L, G, n_layers, x_router, x, T, gate, s);
     }
-    // expert groups: enough workgroups to fill the chip, at most kSmallMaxGroups partial sums
-    const int E = L.n_experts, d = L.d_model;
-    const int ncg = div_up(d / 16, 4);
-    int EG = std::max(1, std::min({kSmallMaxGroups, div_up(1024, ncg), std::max(1, E / 4)}));
-    EG = std::max(EG, div_up(E, kSmallPerGroup));
-    const int per = div_up(E, EG);
-    EG = div_up(E, per);
-    const dim3 grid(ncg, EG, n_layers);
-    const int ks = mt / 2;
-    {
-        LaunchTimer tm(kSlotSmallDown, s);
-        const bool w8 = weights_fp8(L);
-        if (ks == 1 && !w8) launch_kernel(down_small_kernel<1, false>, grid, 256, 0, s, G, T, d, E, per);
-        else if (ks == 2 && !w8) launch_kernel(down_small_kernel<2, false>, grid, 256, 0, s, G, T, d, E, per);
-        else if (!w8) launch_kernel(down_small_kernel<4, false>, grid, 256, 0, s, G, T, d, E, per);
-        else if (ks == 1) launch_kernel(down_small_kernel<1, true>, grid, 256, 0, s, G, T, d, E, per);
-        else if (ks == 2) launch_kernel(down_small_kernel<2, true>, grid, 256, 0, s, G, T, d, E, per);
-        else launch_kernel(down_small_kernel<4, true>, grid, 256, 0, s, G, T, d, E, per);
+    LaunchTimer tm(kSlotSmallDown, s);
+    switch (m_pad_of(L.expert_size) / 32 * 2 + (w8 ? 1 : 0)) {
+    case 2: launch_down_tt<1, false>(L, G, n_layers, T, gate, s); break;
+    case 3: launch_down_tt<1, true>(L, G, n_layers, T, gate, s); break;
+    case 4: launch_down_tt<2, false>(L, G, n_layers, T, gate, s); break;
+    case 5: launch_down_tt<2, true>(L, G, n_layers, T, gate, s); break;
+    case 8: launch_down_tt<4, false>(L, G, n_layers, T, gate, s); break;
+    default: launch_down_tt<4, true>(L, G, n_layers, T, gate, s); break;
     }
-    LaunchTimer tm(kSlotSmallFinish, s);
-    launch_kernel(finish_small_kernel, dim3(div_up(T * d, 256), 1, n_layers), 256, 0, s, G, T, d, EG);
 }
 
 }  // namespace dmoe

@@ -39,6 +39,9 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Waits for every vector memory operation of the wavefront (vmcnt(0); the other counters are left).
+__device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
 // Neuron order of the hidden activations.  Lane (q, .) of the up-projection's 16-neuron tile mt
 // holds the accumulator rows 4q + r; the packed up weights put the neurons there so that the
 // 16-byte piece p = 4*(mt/2) + q of an H row (rows 4q + r of the tile pair 2*(mt/2), +1) is the

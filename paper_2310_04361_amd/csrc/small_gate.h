@@ -1,36 +1,11 @@
-// Router scores and dynamic-k gate for at most 16 tokens inside ONE workgroup of sixteen
-// wavefronts (Sec. 3.3, Sec. 3.4 Eq. 4): device functions shared by the stand-alone gate kernels
-// (select.hip) and by the small-token up-projection, whose workgroups each repeat this little
-// computation instead of waiting for a kernel of its own (ffn_small.hip).
+// Pieces of the dynamic-k gate for at most 16 tokens (Sec. 3.4 Eq. 4): device functions shared by the
+// stand-alone gate kernels (select.hip) and by the small-token forward (ffn_small.hip).
 #pragma once
 
 #include "dmoe_internal.h"
 #include "mfma.h"
 
 namespace dmoe {
-
-// Second router product, s = |R2 hid + c2|, for all experts: wavefront w multiplies the expert
-// tiles w, w + 16, ...; the fp32 scores go to sc[16][E] (LDS) and, if wanted, to M.scores.
-// Every workgroup that runs this on the same inputs gets the same bits.
-__device__ __forceinline__ void small_scores_to_lds(const SmallMod& M, int T, int dh, int E,
-                                                    float* __restrict__ sc, bool to_global) {
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, c = lane & 15;
-    const int KS2 = dh / 32, NE = (E + 15) >> 4;
-    const __bf16* hb = M.hid + (size_t)c * dh + 8 * q;
-    for (int et = w; et < NE; et += 16) {
-        const __bf16* af = M.r2f + (((size_t)et * KS2) * 64 + lane) * 8;
-        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-        for (int ks = 0; ks < KS2; ++ks)  // eight k-steps of loads go out together
-            acc = mfma16(load8(af + (size_t)ks * 512), load8(hb + 32 * ks), acc);
-        const int e0 = 16 * et + 4 * q;  // lane (q, c): experts e0 .. e0+3 of token c
-        if (c < T && e0 < E) {
-            const float4 out = router_scores4(acc, M.r_b2, e0, E);
-            if (to_global) store_scores4(M.scores + (size_t)c * E, e0, E, out);
-            store_scores4(sc + (size_t)c * E, e0, E, out);
-        }
-    }
-}
 
 // Maximum of token t's score row, by the wavefront that owns the token (lanes stride the experts).
 __device__ __forceinline__ float small_row_max(const float* __restrict__ row, int E) {

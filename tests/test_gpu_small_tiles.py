@@ -1,0 +1,105 @@
+"""The small-batch forward (1 to 64 tokens in one to four column tiles) at the sizes where its launch
+shapes change: token counts around the tile edges, every router width, expert counts around multiples
+of 16, the wavefronts' shares of the experts and the fused gate's limit; all gates, explicit lists, a
+group of layers, and a recorded graph replayed with eager work between."""
+import numpy as np
+import pytest
+
+from helpers import TOL, lists_from_mask, oracle_ffn, tokenwise_rel_err
+from paper_2310_04361_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2310_04361_amd import binding
+    binding.lib()
+    return binding
+
+
+# (d, E, m, d_h, gated, weight format, tokens)
+CASES = [(256, 130, 32, 64, True, "native", (1, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64)),
+         (512, 33, 17, 256, False, "native", (2, 16, 40, 64)),    # ragged neurons: padding stays out
+         (768, 16, 128, 512, False, "native", (7, 20)), (1280, 15, 64, 32, True, "native", (16, 50)),
+         (256, 1024, 24, 128, False, "native", (3, 33)), (256, 1025, 24, 128, False, "native", (3, 33)),
+         (256, 1, 64, 64, True, "native", (1, 64)), (2048, 48, 64, 256, True, "e4m3", (5, 16, 17, 61)),
+         (256, 2049, 8, 64, False, "native", (4,))]
+
+
+def make(B, shape, T, fmt, n=1):
+    d, E, m, dh, gated = shape
+    cfg = wl.Config("small", T, d, E, m, dh, gated, "gelu_tanh" if gated else "gelu_erf", "bf16", (0.4,),
+                    ffn_bias=not gated, router_bias=True)
+    layers = [wl.make_layer(cfg, T + i) for i in range(n)]
+    if fmt == "e4m3":
+        layers = [wl.quantize_experts_e4m3(l) for l in layers]
+    return cfg, layers, [B.Layer(l, cfg.dtype) for l in layers], wl.make_input(cfg, T)
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(str(v) for v in c[:6]))
+def test_small_tiles(B, oracle, case):
+    import torch
+    shape, fmt = case[:5], case[5]
+    E = shape[1]
+    for T in case[6]:
+        print(f"small tiles {shape} {fmt} T={T}", flush=True)
+        cfg, (layer, other), Ls, x = make(B, shape, T, fmt, 2)
+        xd, tau = B.to_device(x, cfg.dtype), float(np.float32(0.4))
+        y, ex = B.dmoe_forward(Ls[0], xd, tau, want_scores=True, want_mask=True, want_lists=True)
+        y2, _ = B.dmoe_forward(Ls[0], xd, tau)      # without the optional outputs
+        ys = B.dmoe_forward_group(Ls, xd, [tau, 0.9])
+        torch.cuda.synchronize()
+        assert torch.equal(y, y2) and torch.equal(ys[0], y)
+        assert torch.equal(ys[1], B.dmoe_forward(Ls[1], xd, float(np.float32(0.9)))[0])
+        mask, _ = oracle.select(ex["scores"].cpu().numpy().astype(np.float64), tau)
+        assert np.array_equal(B.mask_bits_to_bool(ex["mask_bits"], E), mask)
+        _, offsets, lists = oracle.bucket(mask)
+        assert np.array_equal(ex["offsets"].cpu().numpy(), offsets)
+        assert np.array_equal(ex["token_lists"].cpu().numpy()[: offsets[-1]], lists)
+        err = tokenwise_rel_err(B.from_device(y, cfg.dtype), oracle_ffn(oracle, layer, x, mask))
+        print(f"  err={err:.3e}", flush=True)
+        assert err <= TOL["bf16"]
+        # top-k, and explicit lists with experts and a token that nobody selected
+        y, ex = B.dmoe_forward(Ls[0], xd, 0.0, top_k=min(3, E), want_mask=True)
+        torch.cuda.synchronize()
+        mask = B.mask_bits_to_bool(ex["mask_bits"], E)
+        assert (mask.sum(axis=1) == min(3, E)).all()
+        assert tokenwise_rel_err(B.from_device(y, cfg.dtype), oracle_ffn(oracle, layer, x, mask)) <= TOL["bf16"]
+        mask = wl.bernoulli_mask(T, E, 0.3, seed=T)
+        mask[T // 2] = 0
+        mask[:, : E // 3] = 0
+        offs, lst = lists_from_mask(mask, shuffle_seed=1)
+        y = B.dmoe_expert_ffn(Ls[0], xd, torch.from_numpy(offs).cuda(),
+                              torch.from_numpy(np.concatenate([lst, np.zeros(1, np.int32)])).cuda())
+        torch.cuda.synchronize()
+        assert tokenwise_rel_err(B.from_device(y, cfg.dtype), oracle_ffn(oracle, layer, x, mask)) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("shape,T", [((256, 130, 32, 64, True), 9), ((256, 130, 32, 64, True), 40),
+                                     ((512, 33, 24, 256, False), 16), ((256, 1025, 24, 128, False), 33)])
+def test_small_replays(B, shape, T):
+    import torch
+    print(f"small graph {shape} T={T}", flush=True)
+    cfg, _, (L,), x = make(B, shape, T, "native")
+    tau = float(np.float32(0.4))
+    xs = [B.to_device(x + np.float32(i) * x[::-1], cfg.dtype) for i in range(4)]
+    x_in, y_graph, y_eager = xs[0].clone(), torch.empty_like(xs[0]), torch.empty_like(xs[0])
+    B.dmoe_forward(L, x_in, tau, y=y_graph)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.dmoe_forward(L, x_in, tau, y=y_graph)
+    for i in (0, 1, 1, 2, 3):
+        x_in.copy_(xs[i])
+        y_graph.zero_()
+        g.replay()
+        if i != 1:                       # (twice in a row as well)
+            B.dmoe_forward(L, xs[i], tau, y=y_eager)
+        else:
+            y_eager.copy_(B.dmoe_forward(L, xs[i], tau)[0])
+        torch.cuda.synchronize()
+        assert torch.equal(y_graph, y_eager), f"replay {i} differs from the eager result"
+    assert y_eager.float().abs().max().item() > 0
