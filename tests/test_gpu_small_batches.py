@@ -25,7 +25,7 @@ WIDE_GATED = (512, 130, 64, 128, True, "native")
 NARROW = (768, 100, 24, 128, False, "native")
 TINY = (256, 700, 6, 64, False, "native")
 CASES = [(shape, T) for shape in (WIDE_GATED, NARROW) for T in (17, 33, 64, 65, 129, 500, 513, 1100)] + \
-        [(TINY, T) for T in (64, 200, 1030)] + \
+        [(NARROW, 2364)] + [(TINY, T) for T in (64, 200, 1030)] + \
         [((512, 260, 64, 64, True, "a8"), T) for T in (17, 65, 520)] + \
         [((256, 40, 128, 64, False, "a8"), 100), ((512, 130, 64, 128, True, "e4m3"), 48)]
 
