@@ -213,8 +213,9 @@ __host__ __device__ inline int xcd_first(int N, int k) { return (int)((long long
 bool up_items_by_experts(const dmoe_layer& L);
 // The up-projection walks its work items window by window (window = window_groups consecutive
 // 64-token groups, window w on XCD w % 8) so that the x rows an XCD gathers stay in its L2:
-// witem[NW][E+1], wfirst[NW][E] are built with the lists (nullable: no tables).  A single window
-// (wide experts, whose weight stream would flush the rows anyway) is shared by all XCDs.
+// witem[NW][E+1], wfirst[NW][E] are built with the lists (nullable: no tables).  Of fewer
+// than 8 windows each is shared by several XCDs; wide experts (whose weight stream would flush the
+// rows anyway) have a single one.
 int up_window_groups(const dmoe_layer& L, int T);
 constexpr int kMaxExperts = 4096;  // the list fill keeps 2 ints per expert in LDS
 

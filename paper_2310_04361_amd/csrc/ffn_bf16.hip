@@ -131,6 +131,15 @@ __global__ void pack_up_tiny_kernel(const void* __restrict__ w_up, const void* _
 // branch.  K advances in blocks of 64: the wavefront loads the next block of its x rows
 // (lane = (row % 8, 16-byte piece of the 128-byte row segment)) and of the weight fragments
 // while the MFMAs run on the current block out of LDS / registers.
+//
+// Which of an XCD's n_waves wavefronts this one is: neighbouring items (one expert's, as a rule) go to
+// one workgroup, whose wavefronts then find its weights in their L1, unless there are too few items
+// for that: then every CU gets one before any gets two.
+__device__ __forceinline__ int wave_of(int n_items, int wave_in_block, int n_waves) {
+    const int wg = (int)(blockIdx.x >> 3);
+    return n_items > n_waves ? wg * 4 + wave_in_block : wave_in_block * (n_waves >> 2) + wg;
+}
+
 template <int MT, bool GATED, int TT, int NBUF>
 __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf,
@@ -152,21 +161,20 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
     const int ld_row = lane >> 3, ld_piece = lane & 7;
 
     // Work items are walked window by window: the wavefronts of XCD k (workgroups are dealt
-    // round-robin to the 8 XCDs) take the windows k, k+8, ... so that the x rows they gather --
-    // each row is used by every expert its token selected -- stay in that XCD's L2; gathered out
-    // of the last-level cache the same rows come in at about a third of the rate.
-    // A single window is shared by all workgroups.
-    const bool windowed = NW > 1;
-    const int wg = windowed ? (int)(blockIdx.x >> 3) : (int)blockIdx.x;
-    const int n_wg = windowed ? (int)(gridDim.x >> 3) : (int)gridDim.x;
-    const int wave = wg * (blockDim.x >> 6) + wave_in_block;
-    const int n_waves = n_wg * (blockDim.x >> 6);
-    for (int wdx = windowed ? (int)(blockIdx.x & 7) : 0; wdx < NW; wdx += 8) {
+    // round-robin to the 8 XCDs; the grid is a multiple of 8) take the windows k, k+8, ... so that the
+    // x rows they gather -- each row is used by every expert its token selected -- stay in that XCD's
+    // L2; gathered out of the last-level cache the same rows come in at about a third of the rate.
+    // Of fewer than eight windows each belongs to several XCDs, which share its items: neighbouring
+    // experts on one XCD.
+    const int xcd = blockIdx.x & 7, shares = NW < 8 ? 8 / NW : 1, share = xcd % shares;
+    for (int wdx = xcd / shares; wdx < NW; wdx += 8) {
     __syncthreads();  // the previous window's table is no longer read
     for (int i = threadIdx.x; i <= 2 * E; i += blockDim.x)
         s_wit[i] = i <= E ? witem[(size_t)wdx * (E + 1) + i] : wfirst[(size_t)wdx * E + (i - E - 1)];
     __syncthreads();
-    const int total = s_wit[E];
+    const long long all = s_wit[E];
+    const int first = (int)(all * share / shares), total = (int)(all * (share + 1) / shares);
+    const int n_waves = (int)(gridDim.x >> 3) * 4, wave = wave_of(total - first, wave_in_block, n_waves);
     // item jj: its expert is the last e with s_wit[e] <= jj
     auto locate = [&](int jj, int& e, int& item) {
         int lo = 0, hi = E;
@@ -177,7 +185,7 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
         e = lo;
         item = s_wf[lo] + (jj - s_wit[lo]);
     };
-    int j = wave;
+    int j = first + wave;
     if (j < total) {
         int e, item;
         locate(j, e, item);
@@ -368,18 +376,17 @@ __global__ __launch_bounds__(256) void up_tiny_kernel(
     const int NK32 = d / 32, NKB = d / 64;
     const int ld_row = lane >> 3, ld_piece = lane & 7;
 
-    const bool windowed = NW > 1;
-    const int wg = windowed ? (int)(blockIdx.x >> 3) : (int)blockIdx.x;
-    const int n_wg = windowed ? (int)(gridDim.x >> 3) : (int)gridDim.x;
-    const int wave = wg * (blockDim.x >> 6) + wave_in_block;
-    const int n_waves = n_wg * (blockDim.x >> 6);
-    for (int wdx = windowed ? (int)(blockIdx.x & 7) : 0; wdx < NW; wdx += 8) {
+    // (who works on what: see up_bf16_kernel)
+    const int xcd = blockIdx.x & 7, shares = NW < 8 ? 8 / NW : 1, share = xcd % shares;
+    for (int wdx = xcd / shares; wdx < NW; wdx += 8) {
     __syncthreads();  // the previous window's table is no longer read
     for (int i = threadIdx.x; i < 2 * E; i += blockDim.x)
         s_wit[i] = i < E ? witem[(size_t)wdx * (E + 1) + i] : wfirst[(size_t)wdx * E + (i - E)];
-    const int total = witem[(size_t)wdx * (E + 1) + E];
+    const long long all = witem[(size_t)wdx * (E + 1) + E];
+    const int first = (int)(all * share / shares), total = (int)(all * (share + 1) / shares);
+    const int n_waves = (int)(gridDim.x >> 3) * 4, wave = wave_of(total - first, wave_in_block, n_waves);
     __syncthreads();
-    for (int j = wave; j < total; j += n_waves) {
+    for (int j = first + wave; j < total; j += n_waves) {
         int lo = 0, hi = E;  // last e with s_wit[e] <= j
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
@@ -834,14 +841,32 @@ bool up_items_by_experts(const dmoe_layer& L) {
 }
 
 // Groups of 64 tokens per up-projection window: the x rows of a window (about 3 MB) should stay
-// in the 4 MB L2 of the XCD that works on it, and the number of windows is a multiple of 8 so
-// that every XCD gets the same number.
+// in the 4 MB L2 of the XCD that works on it, and the number of windows is a multiple of 8, or
+// divides 8, so that every XCD gets the same share.
 int up_window_groups(const dmoe_layer& L, int T) {
     const int NG = div_up(T, kGroup);
     // wide experts: per window the XCD would stream every expert's weights (far more than its
     // L2) through the same cache, and the 256-row items span more than a window; measured slower
     if (up_rows_bf16(L) != 64) return std::max(1, NG);
     const double x_bytes = 2.0 * (double)NG * kGroup * L.d_model;
+    // Small batches: 1, 2, 4 or 8 windows, the XCDs of a window sharing the experts -- the number with
+    // which the least comes from beyond the L2s (the weights once per window, x once per share), while
+    // the x rows of a window are not much more than an L2 holds; a little more is taken where the
+    // weights are the larger part.  (Up-projection, us, with 1 / 2 / 4 / 8 windows: 2048 gated experts of
+    // 8, d = 2048, 1800 tokens 106 / 111 / 128 / 139, 4096 tokens 261 / 223 / 191 / 216; 512 experts of
+    // 6, d = 768, 5000 tokens 36 / 34 / 34 / 40, 16384 tokens 172 / 136 / 104 / 95; 128 experts of 24,
+    // 16384 tokens 76 / 62 / 50 / 47.)
+    const double rows = up_tiny_supported(L) ? 16 : (L.gated ? 2 : 1) * m_pad_of(L.expert_size);
+    const double w_bytes = 2.0 * L.n_experts * rows * L.d_model, most = w_bytes > x_bytes ? 8.0e6 : 6.0e6;
+    if (x_bytes <= 8 * most) {
+        int best = 8;
+        for (int a = 4; a >= 1; a /= 2)
+            if (x_bytes <= a * most && a * w_bytes + 8 / a * x_bytes < best * w_bytes + 8 / best * x_bytes) best = a;
+        // (whole groups per window: where that does not come out as a number of windows that divides the
+        // XCDs, one window)
+        const int groups = div_up(NG, best);
+        return 8 % div_up(NG, groups) == 0 ? groups : std::max(1, NG);
+    }
     const double window_bytes = 3.2 * 1048576.0;
     const int n_windows = 8 * std::max(1, (int)ceil(x_bytes / (8.0 * window_bytes)));
     return std::max(1, div_up(NG, n_windows));
@@ -853,10 +878,10 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
     LaunchTimer tm(kSlotUp, s);
     const PackedLayout P = packed_layout(L);
     const int NW = div_up(div_up(T, kGroup), up_window_groups(L, T));
-    // persistent wavefronts: enough to cover the worst case once, capped at two workgroups per
-    // CU; a multiple of 8 so that every XCD runs the same number
+    // persistent workgroups, capped at what a CU holds; with few items at most one wavefront each has
+    // one (wave_of); a multiple of 8 so that every XCD runs the same number
     const long long worst = (long long)T * L.n_experts / up_rows_bf16(L) + L.n_experts;
-    const int grid = round_up((int)std::min<long long>((worst + 3) / 4, 256 * 2), 8);
+    const int grid = round_up((int)std::min<long long>(worst, 256 * 2), 8);
     const int mt = m_pad_of(L.expert_size) / 16;
     if (up_rows_bf16(L) == 256) {  // wide experts: weights shared through LDS
         const int wgrid = round_up(
@@ -872,7 +897,7 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
         // as many workgroups per CU as LDS allows, at most the three that the registers allow
         // (squeezed into a fourth wavefront per SIMD's share of registers the kernel got slower)
         const int per_cu = std::max(1, std::min(3, (int)(160 * 1024 / lds)));
-        const int grid = round_up((int)std::min<long long>((worst + 3) / 4, 256 * per_cu), 8);
+        const int grid = round_up((int)std::min<long long>(worst, 256 * per_cu), 8);
         static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
         std::call_once(attr_once, [&] {
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_tiny_kernel<TT, true>),
@@ -897,7 +922,7 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
     } else {
         if (mt == 2) {
             // 32-neuron rows: one staging buffer, three workgroups per CU
-            const int grid3 = round_up((int)std::min<long long>((worst + 3) / 4, 256 * 3), 8);
+            const int grid3 = round_up((int)std::min<long long>(worst, 256 * 3), 8);
             launch_up_t<2, false, 4, 1>(L, x, P, witem, wfirst, NW, alist, H, grid3, s);
         }
         else if (mt == 4) launch_up_t<4, false, 4>(L, x, P, witem, wfirst, NW, alist, H, grid, s);

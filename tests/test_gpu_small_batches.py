@@ -1,6 +1,7 @@
 """Whole forwards at the token counts between a decode batch and a full prefill, where the launch
 shapes change: the walk of the down-projection divided into more or fewer parts, the scan over the
-token groups inside the list fill or in a kernel of its own, one to a few token groups.  Lists and
+token groups inside the list fill or in a kernel of its own, one to a few token groups, one to eight
+windows of the up-projection.  Lists and
 masks bit-exact, outputs against the oracle on every token."""
 import numpy as np
 import pytest
@@ -25,7 +26,9 @@ WIDE_GATED = (512, 130, 64, 128, True, "native")
 NARROW = (768, 100, 24, 128, False, "native")
 TINY = (256, 700, 6, 64, False, "native")
 CASES = [(shape, T) for shape in (WIDE_GATED, NARROW) for T in (17, 33, 64, 65, 129, 500, 513, 1100)] + \
-        [(NARROW, 2364)] + [(TINY, T) for T in (64, 200, 1030)] + \
+        [(NARROW, 2364)] + [((256, E, m, 64, g, "native"), 2950) for m, g in ((6, False), (8, True), (24, False))
+                            for E in (10, 40, 80)] + \
+        [(TINY, T) for T in (64, 200, 1030)] + \
         [((512, 260, 64, 64, True, "a8"), T) for T in (17, 65, 520)] + \
         [((256, 40, 128, 64, False, "a8"), 100), ((512, 130, 64, 128, True, "e4m3"), 48)]
 
