@@ -607,12 +607,12 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
             launch_router_f32(*layer, (const float*)x, n_tokens, scores, s);
         else
             launch_router_bf16(*layer, x, n_tokens, scores, s);
+        // (the fp32 kernel works from the mask: without lists for the caller nobody reads the counts)
+        int32_t* cnt = layer->dtype == DMOE_F32 && !offsets_out && n_tokens > 16 ? nullptr : counts_of(1);
         if (gate.top_k < 0)
-            launch_mask_from_scores(scores, n_tokens, layer->n_experts, tau, mask, nullptr,
-                                    counts_of(1), colmask, s);
+            launch_mask_from_scores(scores, n_tokens, layer->n_experts, tau, mask, nullptr, cnt, colmask, s);
         else
-            launch_mask_topk(scores, n_tokens, layer->n_experts, gate.top_k, mask, nullptr,
-                             counts_of(1), colmask, s);
+            launch_mask_topk(scores, n_tokens, layer->n_experts, gate.top_k, mask, nullptr, cnt, colmask, s);
     }
     return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s, split);
 }

@@ -183,6 +183,7 @@ inline void launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_
 // ---- select / bucket (select.hip) -----------------------------------------------------------
 // group_off is [(NG+1)][E] int32 with NG = ceil(T/64): after the scans, group_off[g][e] is the
 // number of tokens < 64*g that selected expert e, and row NG holds the per-expert totals.
+// (For more than 16 tokens group_off may be null, if colmask is: then nothing is counted.)
 // colmask (nullable) is [NG][E] u64: bit j of colmask[g][e] = token 64g + j keeps expert e.
 void launch_mask_from_scores(const float* scores, int T, int E, float tau, uint64_t* mask,
                              int32_t* k_per_token, int32_t* group_off, uint64_t* colmask,

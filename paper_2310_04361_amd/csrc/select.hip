@@ -512,6 +512,7 @@ void launch_mask_from_scores(const float* scores, int T, int E, float tau, uint6
     else if (W <= 16) launch_kernel(tau_mask_kernel<16>, grid, 256, 0, s, scores, mask, k_per_token, T, E, W, tau);
     else if (W <= 32) launch_kernel(tau_mask_kernel<32>, grid, 256, 0, s, scores, mask, k_per_token, T, E, W, tau);
     else launch_kernel(tau_mask_kernel<64>, grid, 256, 0, s, scores, mask, k_per_token, T, E, W, tau);
+    if (!group_off && !colmask) return;  // nobody reads the counts
     launch_kernel(count_from_mask_kernel, div_up(NG * W, 4), 256, 0, s, mask, group_off, colmask, T, E, W);
 }
 
@@ -554,6 +555,7 @@ void launch_mask_topk(const float* scores, int T, int E, int k, uint64_t* mask,
     else if (W <= 16) launch_kernel(topk_mask_kernel<16>, grid, 256, 0, s, scores, mask, k_per_token, T, E, W, k);
     else if (W <= 32) launch_kernel(topk_mask_kernel<32>, grid, 256, 0, s, scores, mask, k_per_token, T, E, W, k);
     else launch_kernel(topk_mask_kernel<64>, grid, 256, 0, s, scores, mask, k_per_token, T, E, W, k);
+    if (!group_off && !colmask) return;  // nobody reads the counts
     // counts per (group, expert) and, if wanted, the per-expert token sets
     launch_kernel(count_from_mask_kernel, div_up(NG * W, 4), 256, 0, s, mask, group_off, colmask, T, E, W);
 }

@@ -153,6 +153,9 @@ def test_wide_models(B, oracle, T, d, E, m, gated):
     (50, 96, 7, 5, 16, False, "relu", 0.5), (33, 256, 20, 33, 64, True, "gelu_tanh", 0.3),
     (200, 64, 130, 3, 32, False, "gelu_erf", 0.7), (17, 1000, 4, 200, 100, False, "relu", 0.0),
     (1, 40, 3, 9, 8, True, "gelu_tanh", 0.9),
+    # more selected neurons than LDS holds at a time, a row count that is no multiple of 4, 16 or 32;
+    # the most LDS that x, y and one expert's hidden values may take (2 d + m = 16384)
+    (20, 64, 130, 41, 32, True, "gelu_tanh", 0.0), (3, 8000, 3, 384, 32, False, "relu", 0.3),
 ])
 def test_fp32_layers_of_other_shapes(B, oracle, T, d, E, m, d_h, gated, act, tau):
     """The fp32 kernels (the exactness configuration) away from the 64-wide benchmark layer: both
