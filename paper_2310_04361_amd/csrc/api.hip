@@ -193,7 +193,10 @@ LayerWs layer_ws(const dmoe_layer& L, int T) {
     w.offsets = o;    o += align_up(sizeof(int32_t) * (size_t)(E + 1));
     w.item_start = o; o += align_up(sizeof(int32_t) * (size_t)(E + 2));
     // window tables of the up-projection
-    const int n_windows = L.dtype == DMOE_BF16 ? div_up(div_up(T, kGroup), up_window_groups(L, T)) : 0;
+    // (their number may fall as T grows, the workspace may not: room for the most that batches of up to T have)
+    const int NG = div_up(T, kGroup);
+    int n_windows = L.dtype == DMOE_BF16 ? div_up(NG, up_window_groups(L, T)) : 0;
+    if (L.dtype == DMOE_BF16 && up_rows_bf16(L) == 64) n_windows = std::max(n_windows, std::min(NG, 8));
     w.witem = o;      o += align_up(sizeof(int32_t) * (size_t)n_windows * (E + 1));
     w.wfirst = o;     o += align_up(sizeof(int32_t) * (size_t)n_windows * E);
     // order of the wide up-projection's work items: (expert, item) each

@@ -844,7 +844,7 @@ bool up_items_by_experts(const dmoe_layer& L) {
 // in the 4 MB L2 of the XCD that works on it, and the number of windows is a multiple of 8, or
 // divides 8, so that every XCD gets the same share.
 int up_window_groups(const dmoe_layer& L, int T) {
-    const int NG = div_up(T, kGroup);
+    const int NG = std::max(1, div_up(T, kGroup));
     // wide experts: per window the XCD would stream every expert's weights (far more than its
     // L2) through the same cache, and the 256-row items span more than a window; measured slower
     if (up_rows_bf16(L) != 64) return std::max(1, NG);
