@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
     int32_t* s_wf = s_wit + (E + 1);
     const int items_bytes = ((2 * E + 1) * 4 + 15) & ~15;
     const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
-    const int wave_in_block = threadIdx.x >> 6;
+    const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     char* xs = smem + items_bytes + wave_in_block * (NBUF * UR * kUpRowBytes);
     const int NK32 = d / 32, NKB = d / 64;
     const int ld_row = lane >> 3, ld_piece = lane & 7;
