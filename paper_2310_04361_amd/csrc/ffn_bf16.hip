@@ -126,12 +126,6 @@ __global__ void pack_up_tiny_kernel(const void* __restrict__ w_up, const void* _
 }
 
 // ---- up-projection ---------------------------------------------------------------------------------
-// One wavefront per work item = (expert, UR = 16*TT consecutive list rows); no workgroup-level
-// synchronisation after the work-item table has been staged.  MT = m_pad / 16 neuron tiles per
-// branch.  K advances in blocks of 64: the wavefront loads the next block of its x rows
-// (lane = (row % 8, 16-byte piece of the 128-byte row segment)) and of the weight fragments
-// while the MFMAs run on the current block out of LDS / registers.
-//
 // Which of an XCD's n_waves wavefronts this one is: neighbouring items (one expert's, as a rule) go to
 // one workgroup, whose wavefronts then find its weights in their L1, unless there are too few items
 // for that: then every CU gets one before any gets two.
@@ -140,6 +134,11 @@ __device__ __forceinline__ int wave_of(int n_items, int wave_in_block, int n_wav
     return n_items > n_waves ? wg * 4 + wave_in_block : wave_in_block * (n_waves >> 2) + wg;
 }
 
+// One wavefront per work item = (expert, UR = 16*TT consecutive list rows); no workgroup-level
+// synchronisation after the work-item table has been staged.  MT = m_pad / 16 neuron tiles per
+// branch.  K advances in blocks of 64: the wavefront loads the next block of its x rows
+// (lane = (row % 8, 16-byte piece of the 128-byte row segment)) and of the weight fragments
+// while the MFMAs run on the current block out of LDS / registers.
 template <int MT, bool GATED, int TT, int NBUF>
 __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf,
