@@ -270,6 +270,17 @@ int32_t dmoe_forward_group(const dmoe_layer *const *layers, int32_t n_layers, co
                            int32_t n_tokens, const float *host_taus, void *const *host_ys,
                            void *workspace, size_t workspace_bytes, void *stream);
 
+/* ---- waits of the small-batch kernels (test aid) --------------------------------------------- */
+
+/*
+ * The first launch of a small batch holds workgroups that wait, for a bounded time, for what others
+ * compute; one that has waited too long goes on without it (it computes what is missing, or
+ * more than is needed).  With every = n > 0 each n-th workgroup of the launches that the CALLING THREAD
+ * makes from now on does not wait at all but takes that way; 0, the default, is the normal course.
+ * Results are the same bit for bit.  DMOE_ERR_SHAPE for a negative number.
+ */
+int32_t dmoe_small_give_up(int32_t every);
+
 /* ---- per-kernel timing (measurement aid) ----------------------------------------------------- */
 
 /*

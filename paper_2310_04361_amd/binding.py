@@ -26,7 +26,7 @@ EXPORTS = (
     "dmoe_version", "dmoe_last_error", "dmoe_workspace_bytes", "dmoe_select_workspace_bytes",
     "dmoe_packed_bytes", "dmoe_pack_weights", "dmoe_router", "dmoe_select", "dmoe_expert_ffn",
     "dmoe_forward", "dmoe_forward_static", "dmoe_select_topk", "dmoe_forward_topk", "dmoe_group_workspace_bytes",
-    "dmoe_forward_group", "dmoe_timing_enable", "dmoe_timing_reset", "dmoe_timing_slots",
+    "dmoe_forward_group", "dmoe_small_give_up", "dmoe_timing_enable", "dmoe_timing_reset", "dmoe_timing_slots",
     "dmoe_timing_read",
 )
 
@@ -80,6 +80,7 @@ def lib() -> ctypes.CDLL:
         L.dmoe_forward_topk.argtypes = [LP, V, I, I, V, V, V, V, V, V, SZ, V]
         L.dmoe_group_workspace_bytes.argtypes = [P(LP), I, I, P(SZ)]
         L.dmoe_forward_group.argtypes = [P(LP), I, V, I, P(F), P(V), V, SZ, V]
+        L.dmoe_small_give_up.argtypes = [I]
         L.dmoe_timing_enable.argtypes = [I]
         L.dmoe_timing_read.argtypes = [I, P(ctypes.c_char_p), P(ctypes.c_int64), P(ctypes.c_double)]
         for name in EXPORTS:

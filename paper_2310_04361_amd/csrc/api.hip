@@ -732,6 +732,12 @@ int32_t dmoe_forward_group(const dmoe_layer* const* layers, int32_t n_layers, co
     return check_launch("group kernels");
 }
 
+int32_t dmoe_small_give_up(int32_t every) {
+    if (every < 0) return fail(DMOE_ERR_SHAPE, "every must not be negative");
+    small_give_up(every);
+    return DMOE_OK;
+}
+
 int32_t dmoe_timing_enable(int32_t on) {
     if (on && g_ev.empty()) {
         g_ev.resize(2 * kEventPairs);

@@ -285,6 +285,7 @@ size_t small_ticket_bytes(const dmoe_layer& L);
 // router's input; x: the experts' (another one only in layers with 8-bit inputs).
 void launch_small_bf16(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x_router,
                        const void* x, int T, bool gate, hipStream_t s);
+void small_give_up(int every);  // dmoe_small_give_up
 
 // ---- experts ----------------------------------------------------------------------------------
 void launch_ffn_f32(const dmoe_layer& L, const float* x, int T, const uint64_t* mask, float* y,

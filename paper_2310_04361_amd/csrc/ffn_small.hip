@@ -21,8 +21,9 @@
 // the hidden rows and the announced token sets (16 bits of payload, 48 of tag) carry the call's own
 // number, so nothing in the workspace needs to start at zero; small_down clears them for the replay
 // of a recorded graph, whose calls keep their number.  All waits are bounded: a gate that has not
-// seen all hidden rows for a while computes them itself, an up-projection workgroup that has seen no
-// announcement treats the expert as selected by everybody.
+// seen all hidden rows for a while computes them itself.  An up-projection workgroup that has not seen all
+// announcements for much longer does not know which work items the others leave to it (they are numbered
+// by the list of the touched experts), so it computes them all.
 //
 // Measured, whole call (five launches before, of which the prefill kernels took the sizes above 16
 // tokens): 32 experts of 24, d = 768, 16 tokens 20.8 -> 13.6 us; 256 gated experts of 64, d = 1024:
@@ -42,7 +43,14 @@ namespace dmoe {
 
 namespace {
 
-constexpr int kWaitPolls = 200;            // about 50 us
+// Polls of a workgroup that waits for the hidden rows (about 50 us: several times what they take), and for
+// the announcements (about 1 ms: several times what a gate takes that computes the hidden rows of 512
+// units itself).  give_up: see dmoe_small_give_up.
+constexpr int kHiddenPolls = 200, kSetPolls = 4000;
+__device__ __forceinline__ int wait_budget(int polls, int give_up) {
+    return give_up > 0 && blockIdx.x % give_up == 0 ? 0 : polls;
+}
+
 
 // Exchange area of one layer of a call: flags of the hidden tiles [token tile][32], tagged token sets
 // [token tile][E].
@@ -133,7 +141,7 @@ __device__ __forceinline__ void small_hidden_wg(const SmallMod& M, const __bf16*
 // this launch waits for, are assembled after the announcement.
 template <int KQ, int KS2>
 __device__ __forceinline__ void small_gate_wg(const SmallMod& M, const __bf16* __restrict__ x, int tt, int T, int d,
-                                              int E, uint64_t tag, char* smem) {
+                                              int E, uint64_t tag, int budget, char* smem) {
     constexpr int dh = 32 * KS2, NH = dh / 16, kHRow = 2 * dh + 16;  // (bytes per hidden row, bank skew)
     constexpr int kThreads = 64 * KQ, kTiles = KS2 >= 8 ? (KS2 == 8 ? 4 : 2) : 8;  // R2 tiles requested ahead
     constexpr int kMost = kSmallGateMaxE / 16 / KQ;                // tiles per wavefront
@@ -158,7 +166,7 @@ __device__ __forceinline__ void small_gate_wg(const SmallMod& M, const __bf16* _
     // wait for the hidden rows
     const uint64_t* flags = flag_words(M) + tt * kMaxHidTiles;
     bool missing = true;
-    for (int poll = 0; poll < kWaitPolls && missing; ++poll) {
+    for (int poll = 0; poll < budget && missing; ++poll) {
         const bool here = lane >= NH || load_agent(flags + min(lane, NH - 1)) == tag;
         missing = __ballot(!here) != 0ull;
         if (missing) __builtin_amdgcn_s_sleep(1);
@@ -276,7 +284,7 @@ __device__ __forceinline__ void small_gate_wg(const SmallMod& M, const __bf16* _
 template <bool GATED, int MTW, int TT, bool W8, int KQ>
 __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
     const SmallGroup G, const __bf16* __restrict__ x_router, const __bf16* __restrict__ x, int T, int d,
-    int m, int MT, int act, int E, int dh, uint64_t tag, int wait, int n_wg) {
+    int m, int MT, int act, int E, int dh, uint64_t tag, int wait, int n_wg, int give_up) {
     constexpr int BR = GATED ? 2 : 1;
     // k-steps whose weights are in flight (half of it where the accumulators leave no more registers)
     constexpr int kFrags = (TT + BR >= 5 && !W8 ? 16 : 32) / (BR * MTW);
@@ -299,11 +307,12 @@ __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
         }
         b -= n_hidden;
         if (b < TT) {
+            const int budget = wait_budget(kHiddenPolls, give_up);
             switch (dh) {
-            case 64: small_gate_wg<KQ, 2>(M, x_router, b, T, d, E, tag, smem); return;
-            case 128: small_gate_wg<KQ, 4>(M, x_router, b, T, d, E, tag, smem); return;
-            case 256: small_gate_wg<KQ, 8>(M, x_router, b, T, d, E, tag, smem); return;
-            default: small_gate_wg<KQ, 16>(M, x_router, b, T, d, E, tag, smem); return;
+            case 64: small_gate_wg<KQ, 2>(M, x_router, b, T, d, E, tag, budget, smem); return;
+            case 128: small_gate_wg<KQ, 4>(M, x_router, b, T, d, E, tag, budget, smem); return;
+            case 256: small_gate_wg<KQ, 8>(M, x_router, b, T, d, E, tag, budget, smem); return;
+            default: small_gate_wg<KQ, 16>(M, x_router, b, T, d, E, tag, budget, smem); return;
             }
         }
         b -= TT;
@@ -316,20 +325,21 @@ __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
     constexpr uint64_t kAll = TT == 4 ? ~0ull : (1ull << (16 * TT)) - 1ull;
     uint64_t* s_cm = reinterpret_cast<uint64_t*>(red + KQ * MTW * TT * BR * 64);  // [E]
     uint16_t* s_list = reinterpret_cast<uint16_t*>(s_cm + E);                     // [E]
-    const bool compact = dh == 0 || wait != 0;
-    int n_items = E * per_e;
+    bool compact = dh == 0 || wait != 0;
+    int n_items = E * per_e, stride = n_wg;
     if (compact) {
         int* s_n = reinterpret_cast<int*>(red);
         if (w == 0) {
             const uint64_t* sets = set_words(M);
+            const int budget = wait_budget(kSetPolls, give_up);
             bool ready = dh == 0;
-            int polls = ready ? kWaitPolls : 0;
-            for (; polls < kWaitPolls && !ready; ++polls) {  // one word first: this workgroup's b-th expert
+            int polls = 0;
+            for (; polls < budget && !ready; ++polls) {  // one word first: this workgroup's b-th expert
                 ready = has_tag(load_agent(sets + b % E), tag);
                 if (!ready) __builtin_amdgcn_s_sleep(4);
             }
-            int n = 0;
-            for (int base = 0; base < E; base += 64) {
+            int n = 0;  // -1: not all announced in time
+            for (int base = 0; base < E && n >= 0; base += 64) {
                 const int e = min(base + lane, E - 1);
                 uint64_t cm = 0ull;
                 if (dh == 0) {
@@ -346,10 +356,11 @@ __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
                             cm |= (v & 0xffffull) << (16 * tt);
                         }
                         all_in = __ballot(!mine) == 0ull;
-                        if (!all_in && polls >= kWaitPolls) {  // waited long enough: everybody wants it
-                            cm = mine ? cm : kAll;
-                            all_in = true;
-                        }
+                        if (!all_in && polls >= budget) break;
+                    }
+                    if (!all_in) {
+                        n = -1;
+                        break;
                     }
                 }
                 if (base + lane >= E) cm = 0ull;
@@ -364,8 +375,15 @@ __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
             if (lane == 0) *s_n = n;
         }
         lds_barrier();
-        n_items = __builtin_amdgcn_readfirstlane(*s_n) * per_e;
+        const int n = __builtin_amdgcn_readfirstlane(*s_n);
         lds_barrier();
+        if (n >= 0) {
+            n_items = n * per_e;
+        } else {  // all items, whatever the others do
+            compact = false;
+            b = 0;
+            stride = 1;
+        }
     } else if (dh > 0) {
         // let the router's loads go first: behind the stream they would take three times as long
         __builtin_amdgcn_s_sleep(32);
@@ -415,7 +433,7 @@ __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
         load_x(kX, xb[1]);
     }
     for (;;) {
-        const int next = item + n_wg;
+        const int next = item + stride;
         const bool more = next < n_items;
         const size_t first_next = more ? first_of(next) : 0;
         f32x4 acc[MTW][BR][TT];
@@ -656,6 +674,8 @@ uint64_t next_tag() {
     return (counter.fetch_add(1, std::memory_order_relaxed) << 16) | 0x8000000000000000ull;  // (never the zero of a cleared word)
 }
 
+thread_local int g_give_up = 0;
+
 // Whether to read all experts' weights without waiting for the gate.  The gate's announcement comes about
 // 7 us after the launch; against that stands the time to read the weights that nobody will turn
 // out to want, at 5 TB/s, for a guess of 16 % of the experts per token (what a random router keeps at a
@@ -684,7 +704,7 @@ void launch_up_t(const dmoe_layer& L, const SmallGroup& G, int n_layers, const v
     const int n_wg = std::min(E * (MT / MTW), 512);
     launch_kernel(small_up_kernel<GATED, MTW, TT, W8, KQ>, dim3((dh > 0 ? (dh / 16 + 1) * TT : 0) + n_wg, 1, n_layers),
                   64 * KQ, lds, s, G, (const __bf16*)x_router, (const __bf16*)x, T, L.d_model, L.expert_size,
-                  MT, L.act, E, dh, gate ? next_tag() : 0, wait, n_wg);
+                  MT, L.act, E, dh, gate ? next_tag() : 0, wait, n_wg, g_give_up);
 }
 
 template <bool GATED, bool W8>
@@ -726,6 +746,8 @@ void launch_down_tt(const dmoe_layer& L, const SmallGroup& G, int n_layers, int 
 }
 
 }  // namespace
+
+void small_give_up(int every) { g_give_up = every; }
 
 size_t small_sync_bytes(const dmoe_layer& L) {
     return 8 * (size_t)kSmallMaxTiles * (kMaxHidTiles + std::min(L.n_experts, kSmallGateMaxE));

@@ -183,6 +183,7 @@ def test_entry_points_reject_bad_arguments_before_launch(lib):
                                  1 << 30, None) == B.DMOE_ERR_NULL
     assert lib.dmoe_pack_weights(ref(_layer(dtype=B.DMOE_BF16, d_model=256, router_hidden=48)), 0x10000,
                                  1 << 30, None) == B.DMOE_ERR_UNSUPPORTED
+    assert lib.dmoe_small_give_up(-1) == B.DMOE_ERR_SHAPE and lib.dmoe_small_give_up(0) == B.DMOE_OK
     # timing slots are readable without enabling
     assert lib.dmoe_timing_slots() >= 8
     assert lib.dmoe_timing_read(999, None, None, None) == B.DMOE_ERR_SHAPE

@@ -23,7 +23,8 @@ def B():
 # (d, E, m, d_h, gated, weight format, tokens)
 CASES = [(256, 130, 32, 64, True, "native", (1, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64)),
          (512, 33, 17, 256, False, "native", (2, 16, 40, 64)),    # ragged neurons: padding stays out
-         (768, 16, 128, 512, False, "native", (7, 20)), (1280, 15, 64, 32, True, "native", (16, 50)),
+         (768, 16, 128, 512, False, "native", (7, 20)), (256, 1024, 24, 512, False, "native", (3, 33)),
+         (1280, 15, 64, 32, True, "native", (16, 50)),
          (256, 1024, 24, 128, False, "native", (3, 33)), (256, 1025, 24, 128, False, "native", (3, 33)),
          (256, 1, 64, 64, True, "native", (1, 64)), (2048, 48, 64, 256, True, "e4m3", (5, 16, 17, 61)),
          (256, 2049, 8, 64, False, "native", (4,))]
