@@ -13,8 +13,8 @@
 //   small_down  workgroup = (16 or 64 output columns, group of experts), its wavefronts split the
 //               touched experts and add up through LDS; with several expert groups the fp32 shares go
 //               to memory, and the last workgroup of a column group to finish adds them up in order.
-//               It masks the hidden rows with the token sets, so what was computed for nobody adds
-//               nothing.
+//               It masks the hidden rows with the token sets and skips the experts that nobody selected,
+//               so what was computed for nobody adds nothing.
 //
 // What workgroups of one launch exchange goes through agent-scope accesses, which pass by the per-XCD
 // L2s (a release fence would write the whole L2 back: measured ten times slower).  The flags behind
@@ -526,7 +526,8 @@ __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
 // ---- down-projection ------------------------------------------------------------------------------
 // grid = (16 CTW-column groups, expert groups, layers); KS = m_pad / 32; NW wavefronts split the experts
 // (wavefront w: e0 + w, + NW, ...; at most 64 each), U of them in flight.  all: every expert's weights are
-// read whether somebody selected it or not, so that they are requested before the token sets are here.
+// read whether somebody selected it or not, so that they are requested before the token sets are here
+// (and dropped where the set turns out empty: the weights and what lies in Hs may be anything).
 template <int KS, int TT, int CTW, int NW, int U, bool W8>
 __global__ __launch_bounds__(64 * NW) void small_down_kernel(const SmallGroup G, int T, int d, int E, int per,
                                                              int dh, int all) {
@@ -587,18 +588,20 @@ __global__ __launch_bounds__(64 * NW) void small_down_kernel(const SmallGroup G,
             if (at[u] >= 0) {
                 const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)cm, at[u]);
                 const uint32_t hi = TT > 2 ? __builtin_amdgcn_readlane((int)(uint32_t)(cm >> 32), at[u]) : 0;
+                if ((lo | hi) != 0u) {  // uniform: the weights of an expert for nobody are not multiplied, whatever they are
 #pragma unroll
-                for (int tt = 0; tt < TT; ++tt) {
-                    const bool keep = ((tt < 2 ? lo : hi) >> (16 * (tt & 1) + c)) & 1u;
+                    for (int tt = 0; tt < TT; ++tt) {
+                        const bool keep = ((tt < 2 ? lo : hi) >> (16 * (tt & 1) + c)) & 1u;
 #pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) {
-                        const bf16x8 hv = keep ? hb[u][ks][tt] : zero8();
+                        for (int ks = 0; ks < KS; ++ks) {
+                            const bf16x8 hv = keep ? hb[u][ks][tt] : zero8();
 #pragma unroll
-                        for (int ct = 0; ct < CTW; ++ct) {
-                            bf16x8 av;
-                            if constexpr (W8) av = e4m3x8_to_bf16(wa[u][ct][ks]);
-                            else av = wa[u][ct][ks];
-                            acc[ct][tt] = mfma16(av, hv, acc[ct][tt]);
+                            for (int ct = 0; ct < CTW; ++ct) {
+                                bf16x8 av;
+                                if constexpr (W8) av = e4m3x8_to_bf16(wa[u][ct][ks]);
+                                else av = wa[u][ct][ks];
+                                acc[ct][tt] = mfma16(av, hv, acc[ct][tt]);
+                            }
                         }
                     }
                 }

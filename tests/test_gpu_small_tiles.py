@@ -104,3 +104,32 @@ def test_small_replays(B, shape, T):
         torch.cuda.synchronize()
         assert torch.equal(y_graph, y_eager), f"replay {i} differs from the eager result"
     assert y_eager.float().abs().max().item() > 0
+
+
+@pytest.mark.parametrize("shape,T,tau", [((256, 130, 32, 64, True), 1, 0.6), ((256, 130, 32, 64, True), 16, 0.97),
+                                         ((512, 128, 24, 128, False), 5, 0.9), ((512, 128, 24, 128, False), 40, 0.97),
+                                         ((256, 300, 128, 64, False), 17, 0.95)])
+def test_small_unselected_experts(B, shape, T, tau):
+    """Experts that nobody selected may hold anything: no result depends on it."""
+    import torch
+    print(f"small unselected {shape} T={T}", flush=True)
+    cfg, _, (L,), x = make(B, shape, T, "native")
+    xd, tau, E = B.to_device(x, cfg.dtype), float(np.float32(tau)), shape[1]
+
+    def calls(offsets, lists):
+        L.workspace(T).fill_(255)          # ... nor on what lies where their hidden rows would be
+        yield B.dmoe_forward(L, xd, tau)[0]
+        L.workspace(T).fill_(255)
+        yield B.dmoe_expert_ffn(L, xd, offsets, lists)
+
+    _, ex = B.dmoe_forward(L, xd, tau, want_mask=True, want_lists=True)
+    idle = torch.from_numpy(np.flatnonzero(B.mask_bits_to_bool(ex["mask_bits"], E).sum(axis=0) == 0)).cuda()
+    assert 0 < len(idle) < E
+    want = [y.clone() for y in calls(ex["offsets"], ex["token_lists"])]
+    for k in ("w_up", "w_gate", "w_down", "b_up"):
+        if L.t[k] is not None:
+            L.t[k][idle[::2]], L.t[k][idle[1::2]] = float("nan"), float("inf")
+    B.check(B.lib().dmoe_pack_weights(L.ref(), L.packed.data_ptr(), L.packed.numel(), torch.cuda.current_stream().cuda_stream))
+    for y, y0 in zip(calls(ex["offsets"], ex["token_lists"]), want):
+        torch.cuda.synchronize()
+        assert torch.isfinite(y0).all() and torch.equal(y, y0)
