@@ -13,8 +13,8 @@
 //   small_down  workgroup = (16 or 64 output columns, group of experts), its wavefronts split the
 //               touched experts and add up through LDS; with several expert groups the fp32 shares go
 //               to memory, and the last workgroup of a column group to finish adds them up in order.
-//               It masks the hidden rows with the token sets and skips the experts that nobody selected,
-//               so what was computed for nobody adds nothing.
+//               It masks the hidden rows with the token sets and reads only the touched experts, so what
+//               was computed for nobody adds nothing.
 //
 // What workgroups of one launch exchange goes through agent-scope accesses, which pass by the per-XCD
 // L2s (a release fence would write the whole L2 back: measured ten times slower).  The flags behind
@@ -321,65 +321,87 @@ __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
     const int NK32 = d / 32, per = NK32 / KQ, k0 = w * per;  // KQ divides NK32
     f32x4* red = reinterpret_cast<f32x4*>(smem);             // [KQ][MTW][TT][BR][64]
 
-    // compact list of the touched experts and their token sets
+    // compact list of the touched experts and their token sets: each wavefront scans kScan words a lane at a time
+    constexpr int kScan = 4;
     constexpr uint64_t kAll = TT == 4 ? ~0ull : (1ull << (16 * TT)) - 1ull;
     uint64_t* s_cm = reinterpret_cast<uint64_t*>(red + KQ * MTW * TT * BR * 64);  // [E]
     uint16_t* s_list = reinterpret_cast<uint16_t*>(s_cm + E);                     // [E]
-    bool compact = dh == 0 || wait != 0;
+    bool compact = dh == 0 || ((wait >> blockIdx.z) & 1) != 0;
     int n_items = E * per_e, stride = n_wg;
     if (compact) {
-        int* s_n = reinterpret_cast<int*>(red);
-        if (w == 0) {
-            const uint64_t* sets = set_words(M);
-            const int budget = wait_budget(kSetPolls, give_up);
-            bool ready = dh == 0;
-            int polls = 0;
-            for (; polls < budget && !ready; ++polls) {  // one word first: this workgroup's b-th expert
-                ready = has_tag(load_agent(sets + b % E), tag);
-                if (!ready) __builtin_amdgcn_s_sleep(4);
-            }
-            int n = 0;  // -1: not all announced in time
-            for (int base = 0; base < E && n >= 0; base += 64) {
-                const int e = min(base + lane, E - 1);
-                uint64_t cm = 0ull;
-                if (dh == 0) {
-                    cm = M.colmask[e] & kAll;
-                } else {
-                    bool all_in = false;
-                    for (; !all_in; ++polls) {
-                        bool mine = true;
-                        cm = 0ull;
+        int* s_n = reinterpret_cast<int*>(red);  // [KQ] experts found; -1: not all announced in time
+        const uint64_t* sets = set_words(M);
+        const int budget = wait_budget(kSetPolls, give_up);
+        int n_touched = 0, polls = 0;
+        for (int round = 0; round < E; round += 64 * kScan * KQ) {
+            const int base = round + 64 * kScan * w;
+            uint64_t cm[kScan];
+            int n = 0;
+            if (base < E) {
+                bool all_in = dh == 0;
+                for (; polls < budget && !all_in; ++polls) {  // one word first: of some expert, another one per workgroup
+                    all_in = __ballot(!has_tag(load_agent(sets + base + b % min(E - base, 64 * kScan)), tag)) == 0ull;
+                    if (!all_in) __builtin_amdgcn_s_sleep(4);
+                }
+                all_in = false;
+                for (; !all_in; ++polls) {
+                    bool mine = true;
 #pragma unroll
-                        for (int tt = 0; tt < TT; ++tt) {
-                            const uint64_t v = load_agent(sets + (size_t)tt * E + e);
-                            mine = mine && has_tag(v, tag);
-                            cm |= (v & 0xffffull) << (16 * tt);
+                    for (int k = 0; k < kScan; ++k) {
+                        const int e = min(base + 64 * k + lane, E - 1);
+                        cm[k] = 0ull;
+                        if (dh == 0) {
+                            cm[k] = M.colmask[e] & kAll;
+                        } else {
+#pragma unroll
+                            for (int tt = 0; tt < TT; ++tt) {
+                                const uint64_t v = load_agent(sets + (size_t)tt * E + e);
+                                mine = mine && has_tag(v, tag);
+                                cm[k] |= (v & 0xffffull) << (16 * tt);
+                            }
                         }
-                        all_in = __ballot(!mine) == 0ull;
-                        if (!all_in && polls >= budget) break;
+                        if (base + 64 * k + lane >= E) cm[k] = 0ull;
                     }
-                    if (!all_in) {
-                        n = -1;
-                        break;
-                    }
+                    all_in = __ballot(!mine) == 0ull;
+                    if (!all_in && polls >= budget) break;
                 }
-                if (base + lane >= E) cm = 0ull;
-                const uint64_t bal = __ballot(cm != 0ull);
-                if (cm != 0ull) {
-                    const int at = n + __popcll(bal & ((1ull << lane) - 1ull));
-                    s_list[at] = (uint16_t)e;
-                    s_cm[at] = cm;
-                }
-                n += __popcll(bal);
+#pragma unroll
+                for (int k = 0; k < kScan; ++k) n += __popcll(__ballot(cm[k] != 0ull));
+                if (!all_in) n = -1;
             }
-            if (lane == 0) *s_n = n;
+            if (lane == 0) s_n[w] = n;
+            lds_barrier();
+            int at = n_touched;
+            bool all_in = true;
+#pragma unroll
+            for (int k = 0; k < KQ; ++k) {
+                const int nk = __builtin_amdgcn_readfirstlane(s_n[k]);
+                all_in = all_in && nk >= 0;
+                at += k < w ? nk : 0;
+                n_touched += nk;
+            }
+            if (!all_in) {
+                n_touched = -1;
+                break;
+            }
+            if (n > 0) {
+#pragma unroll
+                for (int k = 0; k < kScan; ++k) {
+                    const uint64_t bal = __ballot(cm[k] != 0ull);
+                    if (cm[k] != 0ull) {
+                        const int i = at + __popcll(bal & ((1ull << lane) - 1ull));
+                        s_list[i] = (uint16_t)(base + 64 * k + lane);
+                        s_cm[i] = cm[k];
+                    }
+                    at += __popcll(bal);
+                }
+            }
+            lds_barrier();
         }
-        lds_barrier();
-        const int n = __builtin_amdgcn_readfirstlane(*s_n);
-        lds_barrier();
-        if (n >= 0) {
-            n_items = n * per_e;
+        if (n_touched >= 0) {
+            n_items = n_touched * per_e;
         } else {  // all items, whatever the others do
+            lds_barrier();
             compact = false;
             b = 0;
             stride = 1;
@@ -413,6 +435,10 @@ __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
     int item = b;
     if (item >= n_items) return;
     size_t first = first_of(item);
+    // Nothing is on its way any more, but the compiler, which sees the loads of the scan above in one of the
+    // paths to here, would wait for them (vmcnt(0)) before each of the following requests: one after the
+    // other instead of all at once, 2 us of the kernel's 26 at 32 tokens of 256 x 64.
+    wait_vmem();
 #pragma unroll
     for (int i = 0; i < kB; ++i) load_step(true, first, 0, i);
     const __bf16* xr[TT];
@@ -525,12 +551,12 @@ __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
 
 // ---- down-projection ------------------------------------------------------------------------------
 // grid = (16 CTW-column groups, expert groups, layers); KS = m_pad / 32; NW wavefronts split the experts
-// (wavefront w: e0 + w, + NW, ...; at most 64 each), U of them in flight.  all: every expert's weights are
-// read whether somebody selected it or not, so that they are requested before the token sets are here
-// (and dropped where the set turns out empty: the weights and what lies in Hs may be anything).
+// (wavefront w: e0 + w, + NW, ...; at most 64 each), U of the touched ones in flight.  (Requesting the weights
+// ahead of the token sets, of all experts, never gained more than 0.3 us, and lost from 2 MB on that
+// nobody wanted: 1 us at 5 MB, 5 to 9 at 30.)
 template <int KS, int TT, int CTW, int NW, int U, bool W8>
 __global__ __launch_bounds__(64 * NW) void small_down_kernel(const SmallGroup G, int T, int d, int E, int per,
-                                                             int dh, int all) {
+                                                             int dh) {
     const SmallMod& M = G.m[blockIdx.z];
     extern __shared__ __attribute__((aligned(16))) char smem[];
     f32x4* red = reinterpret_cast<f32x4*>(smem);  // [NW][CTW][TT][64]
@@ -543,8 +569,7 @@ __global__ __launch_bounds__(64 * NW) void small_down_kernel(const SmallGroup G,
     // lane i: the token set of this wavefront's i-th expert
     const int e_lane = e_first + NW * lane;
     const uint64_t cm = e_lane < e_end ? M.colmask[e_lane] & kAll : 0ull;
-    const int n_mine = e_first < e_end ? (e_end - e_first + NW - 1) / NW : 0;
-    uint64_t todo = all ? (n_mine >= 64 ? ~0ull : (1ull << n_mine) - 1ull) : __ballot(cm != 0ull);
+    uint64_t todo = __ballot(cm != 0ull);
 
     const size_t w_tile = (size_t)KS * 512, w_expert = (size_t)(d / 16) * w_tile;  // elements
     const size_t wl = (size_t)(CTW * cg) * w_tile + lane * 8;
@@ -588,20 +613,18 @@ __global__ __launch_bounds__(64 * NW) void small_down_kernel(const SmallGroup G,
             if (at[u] >= 0) {
                 const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)cm, at[u]);
                 const uint32_t hi = TT > 2 ? __builtin_amdgcn_readlane((int)(uint32_t)(cm >> 32), at[u]) : 0;
-                if ((lo | hi) != 0u) {  // uniform: the weights of an expert for nobody are not multiplied, whatever they are
 #pragma unroll
-                    for (int tt = 0; tt < TT; ++tt) {
-                        const bool keep = ((tt < 2 ? lo : hi) >> (16 * (tt & 1) + c)) & 1u;
+                for (int tt = 0; tt < TT; ++tt) {
+                    const bool keep = ((tt < 2 ? lo : hi) >> (16 * (tt & 1) + c)) & 1u;
 #pragma unroll
-                        for (int ks = 0; ks < KS; ++ks) {
-                            const bf16x8 hv = keep ? hb[u][ks][tt] : zero8();
+                    for (int ks = 0; ks < KS; ++ks) {
+                        const bf16x8 hv = keep ? hb[u][ks][tt] : zero8();
 #pragma unroll
-                            for (int ct = 0; ct < CTW; ++ct) {
-                                bf16x8 av;
-                                if constexpr (W8) av = e4m3x8_to_bf16(wa[u][ct][ks]);
-                                else av = wa[u][ct][ks];
-                                acc[ct][tt] = mfma16(av, hv, acc[ct][tt]);
-                            }
+                        for (int ct = 0; ct < CTW; ++ct) {
+                            bf16x8 av;
+                            if constexpr (W8) av = e4m3x8_to_bf16(wa[u][ct][ks]);
+                            else av = wa[u][ct][ks];
+                            acc[ct][tt] = mfma16(av, hv, acc[ct][tt]);
                         }
                     }
                 }
@@ -679,22 +702,33 @@ uint64_t next_tag() {
 
 thread_local int g_give_up = 0;
 
-// Whether to read all experts' weights without waiting for the gate.  The gate's announcement comes about
-// 7 us after the launch; against that stands the time to read the weights that nobody will turn
-// out to want, at 5 TB/s, for a guess of 16 % of the experts per token (what a random router keeps at a
-// threshold of one half).
-bool small_reads_all(const dmoe_layer& L, int T) {
+// Share of the experts that a token keeps at threshold tau, for the scores of a random router: the share
+// of a half-normal distribution above tau times the median of the largest of E.
+double expected_density(int E, double tau) {
+    double top = sqrt(2.0 * log(E + 1.0));
+    for (int i = 0; i < 2; ++i) top = sqrt(std::max(0.45, 2.0 * log(1.15 * E / top)));  // E erfc(top / sqrt 2) = ln 2
+    return std::max(erfc(tau * top * M_SQRT1_2), 1.0 / E);
+}
+
+// Whether an up-projection with the gate inside reads the weights of all experts without waiting for the
+// token sets: the sets are there about 7 us after the launch, and against that stands the time to read,
+// at 5 TB/s, what nobody of the T tokens turns out to want.  Measured with either course at 1 to 64
+// tokens and thresholds 0.3 to 0.9 (256 x 64, 1024 x 24, 128 x 24, 24 x 128; weights from HBM and from the last-level cache):
+// reading all is ahead by 3 to 16 us where nearly everything is wanted, by 1 to 6 at 30 MB unwanted, even at
+// 30 to 45, behind by 4 to 12 us at 50 to 65.
+bool small_reads_all(const dmoe_layer& L, int T, float tau) {
     const double bytes = (double)L.n_experts * (L.gated ? 2 : 1) * m_pad_of(L.expert_size) * L.d_model *
                          (weights_fp8(L) ? 1 : 2);
-    return bytes * pow(1.0 - 0.16, T) < 5e6 * 7.0;
+    return bytes * pow(1.0 - expected_density(L.n_experts, tau), T) < 5e6 * 7.0;
 }
 
 template <bool GATED, int MTW, int TT, bool W8, int KQ>
 void launch_up_t(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x_router, const void* x,
                  int T, bool gate, hipStream_t s) {
     const int E = L.n_experts, MT = m_pad_of(L.expert_size) / 16, dh = gate ? L.router_hidden : 0;
-    const int wait = gate && !small_reads_all(L, T) ? 1 : 0;
     size_t lds = (size_t)KQ * MTW * TT * (GATED ? 2 : 1) * 1024;
+    int wait = 0;  // bit i: layer i waits for its token sets
+    for (int i = 0; i < n_layers && gate; ++i) wait |= small_reads_all(L, T, G.m[i].tau) ? 0 : 1 << i;
     if (!gate || wait) lds += (sizeof(uint64_t) + sizeof(uint16_t)) * (size_t)E;
     if (gate)
         lds = std::max(lds, 16 * (2 * (size_t)dh + 16) + 16 * KQ * sizeof(float) + 16);
@@ -726,7 +760,7 @@ void launch_up_tt(const dmoe_layer& L, const SmallGroup& G, int n_layers, const 
 template <int KS, bool W8>
 void launch_down_tt(const dmoe_layer& L, const SmallGroup& G, int n_layers, int T, bool gate, hipStream_t s) {
     const int E = L.n_experts, d = L.d_model, TT = div_up(T, 16);
-    const int all = small_reads_all(L, T) ? 1 : 0, dh = gate ? L.router_hidden : 0;
+    const int dh = gate ? L.router_hidden : 0;
     // One token tile: 16 columns and 16 wavefronts per workgroup, which needs no shares in memory up to
     // a few experts per wavefront.  More: 64 columns, so that the hidden rows are read less often.
     // Expert groups: one, or enough workgroups to fill the chip, and no more shares than the workspace
@@ -736,7 +770,7 @@ void launch_down_tt(const dmoe_layer& L, const SmallGroup& G, int n_layers, int 
         EG = std::max(std::min({EG, kSmallMaxGroups, kSmallMaxGroups / TT}), div_up(E, 64 * nw));
         const int per = div_up(E, std::max(1, EG));
         const size_t lds = (size_t)nw * ctw * TT * 1024;
-        launch_kernel(kernel, dim3(d / (16 * ctw), div_up(E, per), n_layers), 64 * nw, lds, s, G, T, d, E, per, dh, all);
+        launch_kernel(kernel, dim3(d / (16 * ctw), div_up(E, per), n_layers), 64 * nw, lds, s, G, T, d, E, per, dh);
     };
     constexpr int U1 = KS <= 2 ? 4 : 2, U4 = KS <= 2 ? 2 : 1;  // (more would not fit the registers)
     const int eg1 = div_up(E, 128), eg4 = std::min(div_up(256, d / 64), E / 8);
