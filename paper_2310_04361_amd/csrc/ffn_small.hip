@@ -69,6 +69,16 @@ template <typename V>
 __device__ __forceinline__ V load_agent(const V* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// The two sides of an exchange.  Writer: its stores are out (vmcnt) before it announces them.  Reader: once
+// it has seen the announcement, and branched on it, its loads are issued, and an agent-scope load finds
+// no older value in a cache.  The fences forbid the compiler to move an access to the other side; at wavefront scope
+// they are no instruction (an agent-scope acquire would invalidate the L2 under the weight stream).
+__device__ __forceinline__ void stores_are_out() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    wait_vmem();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+__device__ __forceinline__ void announcement_seen() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront"); }
 
 // ---- router and gate ------------------------------------------------------------------------------
 // Hidden units 16 h .. + 15 of the tokens of tile tt: KQ wavefronts split K and add up through LDS
@@ -130,7 +140,7 @@ __device__ __forceinline__ void small_hidden_wg(const SmallMod& M, const __bf16*
     if (threadIdx.x < 64) {
         store_agent(reinterpret_cast<uint64_t*>(M.hid + (size_t)(16 * tt + c) * dh + 16 * h + 4 * q),
                     __builtin_bit_cast(uint64_t, hv));
-        wait_vmem();  // the rows are out before the flag
+        stores_are_out();
         if (lane == 0) store_agent(flag_words(M) + tt * kMaxHidTiles + h, tag);
     }
 }
@@ -179,6 +189,7 @@ __device__ __forceinline__ void small_gate_wg(const SmallMod& M, const __bf16* _
 #pragma unroll
         for (int k = 0; k < kWords; ++k) hw[k] = load_agent(hsrc + k * kThreads + tid);
     };
+    announcement_seen();
     if (!missing) load_hidden();
     if (tid == 0) *s_missing = 0;
     lds_barrier();
@@ -193,8 +204,9 @@ __device__ __forceinline__ void small_gate_wg(const SmallMod& M, const __bf16* _
                             __builtin_bit_cast(uint64_t, hv));
             __syncthreads();
         }
-        wait_vmem();
+        stores_are_out();
         __syncthreads();
+        announcement_seen();
         load_hidden();
     }
 #pragma unroll
@@ -669,12 +681,13 @@ __global__ __launch_bounds__(64 * NW) void small_down_kernel(const SmallGroup G,
         }
     }
     if (EG == 1) return;
-    wait_vmem();
+    stores_are_out();
     __syncthreads();
     if (tid == 0)
         s_last = __hip_atomic_fetch_add(tickets_of(M) + cg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(EG - 1);
     __syncthreads();
     if (!s_last) return;
+    announcement_seen();
     for (int i = w; i < CTW * TT; i += NW) {
         const int t = 16 * (i % TT) + c, col = 16 * (CTW * cg + i / TT) + 4 * q;
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};

@@ -1,6 +1,7 @@
 """The waits inside the small-batch forward: workgroups that give up on what others compute
 (dmoe_small_give_up) leave the same results, bit for bit, as those that see it, also where only some of
-them give up and on a workspace that holds NaN everywhere."""
+them give up and on a workspace that holds NaN everywhere; and calls on several streams, each with a
+workspace of its own, do not see each other's exchange."""
 import numpy as np
 import pytest
 
@@ -79,3 +80,27 @@ def test_give_up_in_a_group(B):
             assert all(torch.equal(a, b) for a, b in zip(ys, ys2))
     finally:
         B.check(B.lib().dmoe_small_give_up(0))
+
+
+@pytest.mark.parametrize("shape,T,tau", [((512, 130, 64, 256, True), 16, 0.5), ((768, 512, 24, 128, False), 1, 0.7),
+                                         ((768, 512, 24, 128, False), 40, 0.95)])
+def test_streams(B, shape, T, tau):
+    import torch
+    print(f"streams {shape} T={T} tau={tau}", flush=True)
+    cfg, _, Ls, x = make(B, shape, T, "native", 3)
+    rng, tau = np.random.default_rng(T), float(np.float32(tau))
+    xs = [B.to_device(x[rng.permutation(T)] * np.float32(2.0 ** (i % 3)), cfg.dtype) for i in range(12)]
+    want = [[B.dmoe_forward(L, xd, tau)[0] for xd in xs] for L in Ls]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in Ls]
+    got = [[torch.empty_like(xd) for xd in xs] for _ in Ls]
+    for L in Ls:
+        L.workspace(T)                      # (one per layer, so one per stream)
+    torch.cuda.synchronize()
+    for i, xd in enumerate(xs):
+        for L, s, ys in zip(Ls, streams, got):
+            with torch.cuda.stream(s):
+                B.dmoe_forward(L, xd, tau, y=ys[i])
+    torch.cuda.synchronize()
+    for ys, ws in zip(got, want):
+        assert all(torch.equal(a, b) for a, b in zip(ys, ws))
