@@ -154,7 +154,7 @@ constexpr int kD8Image = kD8Tiles * 64 * 32;   // the four B tiles of one expert
 constexpr int kD8Buf = kD8Image + kD8Tokens;   // + one scale byte per token
 constexpr int kD8Lds = 2 * kD8Buf;
 
-// Batches of 32 experts per part of a divided walk (down_parts).
+// Batches of 32 experts per part of a divided walk (d8_parts).
 __host__ __device__ inline int d8_part_batches(int E, int parts) { return ((E + 31) / 32 + parts - 1) / parts; }
 
 // UPE = units of 64 neurons per expert (H rows of 64 * UPE bytes).
@@ -394,6 +394,28 @@ void launch_pack_down_x8(const dmoe_layer& L, void* packed, hipStream_t s) {
                   L.n_experts, L.expert_size, L.d_model, m_pad_of(L.expert_size) / 64);
 }
 
+// Parts of the walk over the experts (see down_parts), each of whole batches of 32 experts.  Measured over 40
+// to 512 experts, d = 512 to 4096 and 17 to 5000 tokens: 0.29 us per unit of the longest part, 5.5 for the
+// second kernel and 1.5 per million values of the shares.  For one batch and a bit (40 experts) dividing never
+// pays (17 us against 22 to 26), for 64 x 64 at d = 768 up to about 1700 tokens (1000: 23.6 -> 22.2 us; 4000:
+// 24.3 -> 28.9), for 96 x 64 up to 3500, and 256 x 64 at d = 2048 and 2000 tokens takes two (79.7 -> 65.4 us).
+int d8_parts(const dmoe_layer& L, int T) {
+    const int E = L.n_experts, batches = div_up(E, 32);
+    const int wgs = div_up(T, kD8Tokens) * (L.d_model / (kD8CT * 128));
+    const double unit = 0.29 * (m_pad_of(L.expert_size) / 64), share = 1.5e-6 * T * (double)L.d_model;
+    int best = 1;
+    double best_us = unit * E;
+    for (int p = 2; p <= std::min(256 / std::max(wgs, 1), batches); ++p) {
+        const int per = d8_part_batches(E, p), n = div_up(batches, per);  // without the parts that would be empty
+        const double us = unit * std::min(E, 32 * per) + 5.5 + share * n;
+        if (us < best_us) {
+            best_us = us;
+            best = n;
+        }
+    }
+    return best;
+}
+
 // The kernel reaches the packed weights and H8 through 32-bit buffer offsets, and marks
 // unselected tokens with offsets from 2^31 up.
 bool down_x8_addressable(const dmoe_layer& L, int T) {
@@ -439,9 +461,7 @@ void launch_down_x8(const dmoe_layer& L, int T, const int32_t* item_start, const
     const size_t w_bytes = (size_t)E * upe * (d / 32) * 2048;
     const int NG = div_up(T, kGroup), NC = div_up(T, kD8Tokens), NS = d / (kD8CT * 128);
     auto* kernel = upe == 1 ? down_x8_kernel<1> : down_x8_kernel<2>;
-    // (at most as many parts as the workspace was sized for, each of whole batches of 32 experts)
-    int parts = down_parts(L, T);
-    if (parts > 1) parts = div_up(div_up(E, 32), d8_part_batches(E, parts));
+    const int parts = d8_parts(L, T);
     launch_kernel(kernel, down_grid(NC, NS, parts), 256, kD8Lds, s, (const uint8_t*)(pk + P.w2x8),
                   (const uint8_t*)(pk + P.wsc8), (const __bf16*)L.b_down, item_start, group_off,
                   reinterpret_cast<const uint32_t*>(mask), H8, hs8, (__bf16*)y, T, d, E, NG,

@@ -30,6 +30,7 @@ CASES = [(shape, T) for shape in (WIDE_GATED, NARROW) for T in (17, 33, 64, 65, 
                             for E in (10, 40, 80)] + \
         [(TINY, T) for T in (64, 200, 1030)] + \
         [((512, 260, 64, 64, True, "a8"), T) for T in (17, 65, 520)] + \
+        [((512, E, 64, 64, True, "a8"), 300) for E in (33, 97)] + \
         [((256, 40, 128, 64, False, "a8"), 100), ((512, 130, 64, 128, True, "e4m3"), 48)]
 
 
