@@ -217,7 +217,7 @@ int32_t dmoe_forward(const dmoe_layer *layer, const void *x, int32_t n_tokens, f
  * array that lives in the library's device image -- every GPU the library runs on holds its own
  * copy until the process ends -- so the call refuses (DMOE_ERR_WORKSPACE, nothing launched) any
  * layer / n_tokens whose dmoe_workspace_bytes() exceeds 64 MiB: e.g. the 256 x 64 gated layer of
- * the 16-token decode configuration needs 14 MiB, 128 experts of 24 fit up to about 3000 tokens.
+ * the 16-token decode configuration needs 13 MiB, 128 experts of 24 fit up to about 3500 tokens.
  * It calls no hipMalloc / hipFree or other allocating routine.  The first call on a GPU looks the
  * array's address up once (make that call outside a graph capture).  All calls on one GPU share
  * that GPU's array, which keeps the previous call's contents -- nothing in it needs to start at

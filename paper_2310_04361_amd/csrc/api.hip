@@ -174,6 +174,16 @@ SelectWs select_ws(int T, int E, bool need_mask) {
     return w;
 }
 
+bool use_small_path(const dmoe_layer& L, int T) {
+    // (8-bit hidden activations: every batch size takes the list-based kernels)
+    if (L.dtype != DMOE_BF16 || !small_bf16_supported(L) || hidden_fp8(L)) return false;
+    if (T <= kSmallTokens) return true;
+    // Up to kSmallBatch tokens where reading all weights once is what a forward costs: the kernels
+    // stream padded experts and multiply every token, so not for experts with more than a third of
+    // padding (and not with more expert groups than the shares of 64 tokens have room for).
+    return T <= kSmallBatch && 3 * m_pad_of(L.expert_size) <= 4 * L.expert_size && L.n_experts <= 2048;
+}
+
 struct LayerWs {
     size_t scores, mask, group_off, sub_cnt, counts, offsets, item_start, witem, wfirst, worder, lists, H, H8, hs8, colmask, sync, tickets, partial, hid, x8, xscale, xhat, total;
 };
@@ -223,7 +233,8 @@ LayerWs layer_ws(const dmoe_layer& L, int T) {
         w.tickets = o;
         o += align_up(small_ticket_bytes(L));
         w.partial = o;
-        o += align_up(sizeof(float) * std::max((size_t)kSmallMaxGroups * 16 * L.d_model, down_partial_floats(L, T)));
+        o += align_up(sizeof(float) * std::max((size_t)kSmallMaxGroups * 16 * L.d_model,
+                                               use_small_path(L, T) ? 0 : down_partial_floats(L, T)));
     }
     // hidden rows of the router: kSmallBatch for the small-token kernels, all T for a router that runs
     // as two launches
@@ -239,16 +250,6 @@ LayerWs layer_ws(const dmoe_layer& L, int T) {
     }
     w.total = o;
     return w;
-}
-
-bool use_small_path(const dmoe_layer& L, int T) {
-    // (8-bit hidden activations: every batch size takes the list-based kernels)
-    if (L.dtype != DMOE_BF16 || !small_bf16_supported(L) || hidden_fp8(L)) return false;
-    if (T <= kSmallTokens) return true;
-    // Up to kSmallBatch tokens where reading all weights once is what a forward costs: the kernels
-    // stream padded experts and multiply every token, so not for experts with more than a third of
-    // padding (and not with more expert groups than the shares of 64 tokens have room for).
-    return T <= kSmallBatch && 3 * m_pad_of(L.expert_size) <= 4 * L.expert_size && L.n_experts <= 2048;
 }
 
 // Pointers of one layer for the small-token kernels (its workspace carved as in layer_ws).

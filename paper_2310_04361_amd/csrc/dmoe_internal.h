@@ -314,7 +314,9 @@ long long down_max_pairs_sparse(const dmoe_layer& L, int T);
 
 // Batches too small to fill the chip: the walk over the experts is split over this many workgroups
 // per tile of outputs, whose fp32 shares (down_partial_floats of workspace) are added at the end.
+// down_parts_limit: as many as the chip and the workspace hold.
 int down_parts(const dmoe_layer& L, int T);
+int down_parts_limit(const dmoe_layer& L, int T);
 size_t down_partial_floats(const dmoe_layer& L, int T);
 void launch_down_finish(const dmoe_layer& L, int T, const float* partial, void* y, int parts, hipStream_t s);
 // Loop trips of one part: even, so that a part never starts at the last trip of a batch of experts.

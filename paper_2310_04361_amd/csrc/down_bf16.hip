@@ -559,14 +559,30 @@ void launch_down_finish(const dmoe_layer& L, int T, const float* partial, void* 
 // order.  The number of parts is the one with the smallest estimate of walk / parts + that kernel,
 // in us: 0.16 per k-step of the walk (32 to 180 us for the benchmark shapes), 4.5 for the launch,
 // and 8 bytes written and read per value at 4 TB/s.
-int down_parts(const dmoe_layer& L, int T) {
-    const int wgs = div_up(T, kDnTokens) * (L.d_model / (2 * kDnColStep));
+struct DownWalk {
+    int trips;
+    double us;
+};
+static DownWalk down_walk(const dmoe_layer& L) {
     const DownPacking dp = down_packing(L.expert_size);
     const int trips = div_up(L.n_experts * dp.UPE, kDnTrip * dp.G);
-    const double walk = 0.16 * trips * kDnTrip * dp.KSP, share = 2e-6 * T * (double)L.d_model;
+    return DownWalk{trips, 0.16 * trips * kDnTrip * dp.KSP};
+}
+constexpr double kShareUs = 2e-6;  // per value
+
+int down_parts_limit(const dmoe_layer& L, int T) {
+    const int wgs = div_up(T, kDnTokens) * (L.d_model / (2 * kDnColStep));
+    const size_t values = (size_t)std::max(T, 1) * L.d_model;
+    return (int)std::min<size_t>(256 / std::max(wgs, 1), down_partial_floats(L, T) / values);
+}
+
+int down_parts(const dmoe_layer& L, int T) {
+    const DownWalk dw = down_walk(L);
+    const int trips = dw.trips;
+    const double walk = dw.us, share = kShareUs * T * (double)L.d_model;
     int best = 1;
     double best_us = walk;
-    for (int p = 2; p <= std::min(256 / std::max(wgs, 1), div_up(trips, 2)); ++p) {
+    for (int p = 2; p <= std::min(down_parts_limit(L, T), div_up(trips, 2)); ++p) {
         const int n = div_up(trips, down_part_trips(trips, p));  // without the parts that would be empty
         const double us = walk * down_part_trips(trips, p) / trips + 4.5 + share * n;
         if (us < best_us) {
@@ -577,13 +593,20 @@ int down_parts(const dmoe_layer& L, int T) {
     return best;
 }
 
-// ... and the fp32 values they need, for any batch of up to T tokens: parts * T * d, which never
-// exceeds one tile per CU.
+// ... and the fp32 values they need, for any batch of up to T tokens (so that it never falls as T
+// grows): nothing where the walk cannot be divided, else parts * T * d for the largest batch that
+// still is.  The estimate is smallest near sqrt(walk / share) parts; it never took more than 1 + 1.41
+// times that over some 60000 shapes of 1 to 4096 experts, d = 256 to 8192 and 17 to 8700 tokens, and
+// 1 + 1.5 times are what the workspace holds (and the rule of the 8-bit walk keeps to, d8_parts).
 size_t down_partial_floats(const dmoe_layer& L, int T) {
     if (L.dtype != DMOE_BF16) return 0;
-    const size_t cap = (size_t)256 * kDnTokens * 2 * kDnColStep;
-    const int most = std::max(1, 256 / std::max(1, L.d_model / (2 * kDnColStep)));
-    return std::min(cap, (size_t)most * T * L.d_model);
+    const DownWalk dw = down_walk(L);
+    const int slices = std::max(1, L.d_model / (2 * kDnColStep));
+    const int most = std::min(256 / slices, div_up(dw.trips, 2));
+    if (most < 2) return 0;
+    const double values = (double)std::min(T, kDnTokens * (128 / slices)) * L.d_model;  // beyond: no two parts on 256 CUs
+    const size_t tiles = (size_t)256 * kDnTokens * 2 * kDnColStep;
+    return std::min({tiles, (size_t)(most * values), (size_t)(values + 1.5 * sqrt(dw.us * values / kShareUs))});
 }
 
 }  // namespace dmoe

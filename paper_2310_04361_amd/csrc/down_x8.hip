@@ -401,11 +401,10 @@ void launch_pack_down_x8(const dmoe_layer& L, void* packed, hipStream_t s) {
 // 24.3 -> 28.9), for 96 x 64 up to 3500, and 256 x 64 at d = 2048 and 2000 tokens takes two (79.7 -> 65.4 us).
 int d8_parts(const dmoe_layer& L, int T) {
     const int E = L.n_experts, batches = div_up(E, 32);
-    const int wgs = div_up(T, kD8Tokens) * (L.d_model / (kD8CT * 128));
     const double unit = 0.29 * (m_pad_of(L.expert_size) / 64), share = 1.5e-6 * T * (double)L.d_model;
     int best = 1;
     double best_us = unit * E;
-    for (int p = 2; p <= std::min(256 / std::max(wgs, 1), batches); ++p) {
+    for (int p = 2; p <= std::min(down_parts_limit(L, T), batches); ++p) {
         const int per = d8_part_batches(E, p), n = div_up(batches, per);  // without the parts that would be empty
         const double us = unit * std::min(E, 32 * per) + 5.5 + share * n;
         if (us < best_us) {

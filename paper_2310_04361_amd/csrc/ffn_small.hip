@@ -806,7 +806,7 @@ size_t small_ticket_bytes(const dmoe_layer& L) { return sizeof(uint32_t) * (size
 
 bool small_bf16_supported(const dmoe_layer& L) {
     const int mp = m_pad_of(L.expert_size);
-    return L.packed != nullptr && (mp == 32 || mp == 64 || mp == 128) && L.d_model % 256 == 0;
+    return (mp == 32 || mp == 64 || mp == 128) && L.d_model % 256 == 0;
 }
 
 void launch_small_bf16(const dmoe_layer& L, const SmallGroup& G, int n_layers, const void* x_router,

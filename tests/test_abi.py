@@ -167,7 +167,7 @@ def test_entry_points_reject_bad_arguments_before_launch(lib):
     assert sfw(L=_layer(r_w2=None)) == B.DMOE_ERR_NULL
     assert sfw(T=-1) == B.DMOE_ERR_SHAPE
     assert sfw(T=0) == B.DMOE_OK
-    assert sfw(T=2 ** 20) == B.DMOE_ERR_WORKSPACE                            # beyond the 32 MiB array
+    assert sfw(T=2 ** 20) == B.DMOE_ERR_WORKSPACE                            # beyond the 64 MiB array
     assert b"static" in lib.dmoe_last_error()
     # pack
     Lb = _layer(dtype=B.DMOE_BF16, d_model=256)
@@ -187,6 +187,31 @@ def test_entry_points_reject_bad_arguments_before_launch(lib):
     # timing slots are readable without enabling
     assert lib.dmoe_timing_slots() >= 8
     assert lib.dmoe_timing_read(999, None, None, None) == B.DMOE_ERR_SHAPE
+
+
+def test_bf16_workspace_follows_use(lib):
+    """The workspace never falls as the batch grows, does not depend on the packed pointer, and holds no more
+    shares of a divided down-projection than a batch can use: bounds in MB at 16, 48, 333 and 1000 tokens."""
+    n = ctypes.c_size_t(0)
+
+    def size(L, T):
+        assert lib.dmoe_workspace_bytes(ctypes.byref(L), T, ctypes.byref(n)) == B.DMOE_OK
+        return n.value
+
+    for (d, E, m, dh, gated, fmt), bounds in (((768, 128, 24, 128, 0, 0), (3, 4, 15, 40)),
+                                              ((768, 24, 128, 128, 0, 0), (4, 4, 12, 30)),
+                                              ((768, 32, 24, 128, 0, 0), (2, 3, 4, 10)),
+                                              ((256, 1, 64, 64, 1, 0), (1, 1, 1, 1)),
+                                              ((2048, 256, 64, 256, 1, 0), (14, 15, 55, 80)),
+                                              ((2048, 256, 64, 256, 1, 3), (20, 30, 70, 110)),
+                                              ((768, 512, 6, 128, 0, 0), (5, 7, 35, 75))):
+        kw = dict(d_model=d, n_experts=E, expert_size=m, router_hidden=dh, gated=gated, dtype=B.DMOE_BF16,
+                  weight_format=fmt, w_gate=0x1000 if gated else None, w_scales=0x1000 if fmt else None)
+        L, P = _layer(**kw), _layer(packed=0x10000, **kw)
+        sizes = [size(L, T) for T in range(1, 4200, 7)]
+        assert sizes == sorted(sizes)
+        for T, mb in zip((16, 48, 333, 1000), bounds):
+            assert size(L, T) == size(P, T) <= mb * 1e6, (d, E, m, T, size(L, T))
 
 
 def test_group_calls_reject_bad_arguments_before_launch(lib):

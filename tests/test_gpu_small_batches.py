@@ -65,3 +65,30 @@ def test_small_batches(B, oracle, shape, T):
         err = tokenwise_rel_err(got, oracle_ffn(oracle, layer, x, mask))
         print(f"  err={err:.3e}", flush=True)
         assert err <= TOL["bf16"]
+
+
+# (d, E, m, d_h, gated, weight format), tokens: where a divided walk takes the most shares for its size, and
+# the last batch that is divided
+@pytest.mark.parametrize("shape,T", [((256, 17, 128, 64, False, "native"), 4781), ((256, 2016, 16, 64, False, "native"), 40),
+                                     ((768, 97, 48, 64, False, "a8"), 2439), ((256, 700, 64, 64, True, "a8"), 128),
+                                     ((512, 130, 64, 128, True, "native"), 8192), ((512, 130, 64, 128, True, "native"), 65)])
+def test_nothing_behind_the_workspace(B, shape, T):
+    import torch
+    d, E, m, dh, gated, fmt = shape
+    print(f"workspace {shape} T={T}", flush=True)
+    cfg = wl.Config("small", T, d, E, m, dh, gated, "gelu_tanh" if gated else "gelu_erf", "bf16", (0.4,),
+                    ffn_bias=not gated, router_bias=True)
+    layer = wl.make_layer(cfg, T)
+    if fmt != "native":
+        layer = wl.quantize_experts_e4m3(layer)
+        layer["x8"] = layer["a8"] = True
+    L, tau = B.Layer(layer, cfg.dtype), float(np.float32(0.4))
+    xd = B.to_device(wl.make_input(cfg, T), cfg.dtype)
+    y = B.dmoe_forward(L, xd, tau)[0]
+    need = L.workspace(T).numel()
+    room = torch.full((need + (64 << 20),), 255, dtype=torch.uint8, device="cuda")
+    L._ws = room[:need]
+    y2 = B.dmoe_forward(L, xd, tau)[0]
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+    assert bool((room[need:] == 255).all())
