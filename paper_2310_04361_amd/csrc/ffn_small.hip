@@ -732,7 +732,8 @@ double expected_density(int E, double tau) {
 bool small_reads_all(const dmoe_layer& L, int T, float tau) {
     const double bytes = (double)L.n_experts * (L.gated ? 2 : 1) * m_pad_of(L.expert_size) * L.d_model *
                          (weights_fp8(L) ? 1 : 2);
-    return bytes * pow(1.0 - expected_density(L.n_experts, tau), T) < 5e6 * 7.0;
+    constexpr double kUnwanted = 5e6 * 7.0;
+    return bytes < kUnwanted || bytes * pow(1.0 - expected_density(L.n_experts, tau), T) < kUnwanted;
 }
 
 template <bool GATED, int MTW, int TT, bool W8, int KQ>
