@@ -469,7 +469,7 @@ int32_t dmoe_router(const dmoe_layer* layer, const void* x, int32_t n_tokens, fl
     if (layer->dtype == DMOE_F32) launch_router_f32(*layer, (const float*)x, n_tokens, scores, s);
     else if (router_fused_scores_supported(*layer))
         launch_router_fused(*layer, x, n_tokens, router_fused_split(*layer, n_tokens), scores, 0.0f,
-                            nullptr, nullptr, nullptr, nullptr, s);
+                            nullptr, nullptr, s);
     else launch_router_bf16(*layer, x, n_tokens, scores, s);
     return check_launch("router");
 }
@@ -591,11 +591,12 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
     }
     if (fused_gate && n_tokens > kSmallTokens && gate.top_k < 0) {
         // router, dynamic-k gate and group counts in one kernel (with few token groups: several
-        // workgroups per group, each with its own row of counts)
-        if (!colmask) split = router_fused_split(*layer, n_tokens);
+        // workgroups per group, each with its own row of counts); never a small batch, whose gate of up
+        // to 512 experts is the one above
+        split = router_fused_split(*layer, n_tokens);
         // (the gate works on the scores in registers: they go to memory only for a caller who
         // asked for them)
-        launch_router_fused(*layer, x, n_tokens, split, scores_out, tau, mask, nullptr, counts_of(split), colmask, s);
+        launch_router_fused(*layer, x, n_tokens, split, scores_out, tau, mask, counts_of(split), s);
     } else {
         if (fused_router && n_tokens <= kSmallTokens) {
             SmallGroup G{};
@@ -606,7 +607,7 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
             launch_router_sliced(*layer, x, n_tokens, ws + w.hid, scores, s);
         else if (fused_router)
             launch_router_fused(*layer, x, n_tokens, router_fused_split(*layer, n_tokens), scores,
-                                0.0f, nullptr, nullptr, nullptr, nullptr, s);
+                                0.0f, nullptr, nullptr, s);
         else if (layer->dtype == DMOE_F32)
             launch_router_f32(*layer, (const float*)x, n_tokens, scores, s);
         else

@@ -230,7 +230,7 @@ bool router_fused_scores_supported(const dmoe_layer& L);
 // split = 1, 2 or 4 workgroups per group of 64 tokens (router_fused_split: more where the groups
 // alone would leave most of the chip idle).  With the gate and split > 1, group_cnt is a table
 // of split rows per group -- row r holds the counts of the tokens 64 r / split .. -- that
-// launch_scan_and_fill adds up; colmask forces split = 1.
+// launch_scan_and_fill adds up.
 int router_fused_split(const dmoe_layer& L, int T);
 // Large routers (2 MB of matrices or more) without the gate: two launches with the matrices split
 // over the workgroups; hid is a [T][d_h] bf16 scratch buffer.
@@ -238,8 +238,7 @@ bool router_sliced(const dmoe_layer& L);
 void launch_router_sliced(const dmoe_layer& L, const void* x, int T, void* hid, float* scores,
                           hipStream_t s);
 void launch_router_fused(const dmoe_layer& L, const void* x, int T, int split, float* scores,
-                         float tau, uint64_t* mask, int32_t* k_per_token, int32_t* group_cnt,
-                         uint64_t* colmask, hipStream_t s);
+                         float tau, uint64_t* mask, int32_t* group_cnt, hipStream_t s);
 
 // ---- small-token path (use_small_path in api.hip): up to kGroupMax layers of one shape per launch ------
 // The attention projections Q, K and V are three converted layers with the same input (Sec. 3.5),

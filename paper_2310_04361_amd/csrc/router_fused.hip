@@ -41,8 +41,7 @@ __global__ __launch_bounds__(256) void router_fused_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ r1f, const __bf16* __restrict__ r_b1,
     const __bf16* __restrict__ r2f, const __bf16* __restrict__ r_b2, float* __restrict__ scores,
     int T, int d, int E, float tau, int do_select, uint64_t* __restrict__ mask,
-    int32_t* __restrict__ k_per_token, int32_t* __restrict__ group_cnt,
-    uint64_t* __restrict__ colmask, __bf16* __restrict__ hid_g, int dh_g, int tiles_y) {
+    int32_t* __restrict__ group_cnt, __bf16* __restrict__ hid_g, int dh_g, int tiles_y) {
     constexpr int dh = NH * 16, HT = NH / 4, TOK = 16 * TT;
     constexpr int NR = (TOK + 31) / 32;  // staging passes of 32 rows
     constexpr int kHRow = dh * 2 + 16;  // bytes per hidden row in LDS
@@ -313,7 +312,6 @@ __global__ __launch_bounds__(256) void router_fused_kernel(
     if (tid < 64) {
         const int t = t0 + tid;
         const bool mine = tid < TOK && t < T;  // lanes from TOK up: no token, an all-zero row
-        int kt = 0;
         for (int wi = 0; wi < W; ++wi) {
             uint64_t word = 0ull;
             if (tid < TOK)
@@ -321,9 +319,7 @@ __global__ __launch_bounds__(256) void router_fused_kernel(
                        pw[(2 * 64 + tid) * W + wi] | pw[(3 * 64 + tid) * W + wi];
             fin[tid * W + wi] = mine ? word : 0ull;
             if (mine) mask[(size_t)t * W + wi] = word;
-            kt += __popcll(word);
         }
-        if (mine && k_per_token) k_per_token[t] = kt;
     }
     lds_barrier();
     // ballot transpose: lane = token; wavefront w handles the experts 64wi + 16w .. +15 of every
@@ -338,16 +334,13 @@ __global__ __launch_bounds__(256) void router_fused_kernel(
             if (lane == b) col = bal;
         }
         const int e = 64 * wi + lane;
-        if ((lane >> 4) == w && e < E) {
-            group_cnt[(size_t)g * E + e] = __popcll(col);
-            if (colmask) colmask[(size_t)g * E + e] = col;
-        }
+        if ((lane >> 4) == w && e < E) group_cnt[(size_t)g * E + e] = __popcll(col);
     }
 }
 
 template <int NH, int ETW, int KBC, int TT>
 void launch_t3(const dmoe_layer& L, const void* x, int T, float* scores, float tau, uint64_t* mask,
-               int32_t* k_per_token, int32_t* group_cnt, uint64_t* colmask, hipStream_t s) {
+               int32_t* group_cnt, hipStream_t s) {
     const PackedLayout P = packed_layout(L);
     const int E = L.n_experts, W = div_up(E, 64);
     constexpr int TOK = 16 * TT;
@@ -362,24 +355,23 @@ void launch_t3(const dmoe_layer& L, const void* x, int T, float* scores, float t
     launch_kernel(router_fused_kernel<NH, ETW, KBC, TT>, div_up(T, TOK), 256, lds, s, 
         (const __bf16*)x, (const __bf16*)(pk + P.r1f), (const __bf16*)L.r_b1,
         (const __bf16*)(pk + P.r2f), (const __bf16*)L.r_b2, scores, T, L.d_model, E, tau,
-        mask != nullptr, mask, k_per_token, group_cnt, colmask, nullptr, 0, 0);
+        mask != nullptr, mask, group_cnt, nullptr, 0, 0);
 }
 
 template <int NH, int ETW>
 void launch_t2(const dmoe_layer& L, const void* x, int T, int split, float* scores, float tau,
-               uint64_t* mask, int32_t* k_per_token, int32_t* group_cnt, uint64_t* colmask,
-               hipStream_t s) {
+               uint64_t* mask, int32_t* group_cnt, hipStream_t s) {
     constexpr int kBig = NH <= 8 ? 12 : (NH == 16 ? 8 : 4);
     // parts of a group per workgroup: only where workgroups are few (one per CU, nothing hides
     // the latency of an x chunk), and the fewer rows leave LDS for chunks of 1024 columns
     if (split == 4)
-        launch_t3<NH, ETW, 16, 1>(L, x, T, scores, tau, mask, k_per_token, group_cnt, colmask, s);
+        launch_t3<NH, ETW, 16, 1>(L, x, T, scores, tau, mask, group_cnt, s);
     else if (split == 2)
-        launch_t3<NH, ETW, 16, 2>(L, x, T, scores, tau, mask, k_per_token, group_cnt, colmask, s);
+        launch_t3<NH, ETW, 16, 2>(L, x, T, scores, tau, mask, group_cnt, s);
     else if (kBig > 4 && div_up(T, 64) <= 512)
-        launch_t3<NH, ETW, kBig, 4>(L, x, T, scores, tau, mask, k_per_token, group_cnt, colmask, s);
+        launch_t3<NH, ETW, kBig, 4>(L, x, T, scores, tau, mask, group_cnt, s);
     else
-        launch_t3<NH, ETW, 4, 4>(L, x, T, scores, tau, mask, k_per_token, group_cnt, colmask, s);
+        launch_t3<NH, ETW, 4, 4>(L, x, T, scores, tau, mask, group_cnt, s);
 }
 
 // ---- T <= 16: the same two products spread over many workgroups --------------------------------
@@ -448,14 +440,13 @@ __global__ __launch_bounds__(256) void router_small_scores_kernel(const SmallGro
 
 template <int NH>
 void launch_t(const dmoe_layer& L, const void* x, int T, int split, float* scores, float tau,
-              uint64_t* mask, int32_t* k_per_token, int32_t* group_cnt, uint64_t* colmask,
-              hipStream_t s) {
+              uint64_t* mask, int32_t* group_cnt, hipStream_t s) {
     if (L.n_experts <= 128 || !mask)  // the router alone keeps no scores in registers
-        launch_t2<NH, 2>(L, x, T, split, scores, tau, mask, k_per_token, group_cnt, colmask, s);
+        launch_t2<NH, 2>(L, x, T, split, scores, tau, mask, group_cnt, s);
     else if (L.n_experts <= 256)
-        launch_t2<NH, 4>(L, x, T, split, scores, tau, mask, k_per_token, group_cnt, colmask, s);
+        launch_t2<NH, 4>(L, x, T, split, scores, tau, mask, group_cnt, s);
     else
-        launch_t2<NH, 8>(L, x, T, split, scores, tau, mask, k_per_token, group_cnt, colmask, s);
+        launch_t2<NH, 8>(L, x, T, split, scores, tau, mask, group_cnt, s);
 }
 
 }  // namespace
@@ -506,7 +497,7 @@ static void launch_scores_slices(const dmoe_layer& L, const PackedLayout& P, int
     const char* pk = static_cast<const char*>(L.packed);
     launch_kernel(router_fused_kernel<NH, 2, 4, 4, kScoresSlice>, dim3(NG, div_up(NE, tiles_y)), 256, lds, s, 
         nullptr, nullptr, nullptr, (const __bf16*)(pk + P.r2f), (const __bf16*)L.r_b2, scores, T,
-        L.d_model, L.n_experts, 0.0f, 0, nullptr, nullptr, nullptr, nullptr,
+        L.d_model, L.n_experts, 0.0f, 0, nullptr, nullptr,
         const_cast<__bf16*>(hid), L.router_hidden, tiles_y);
 }
 
@@ -527,7 +518,7 @@ void launch_router_sliced(const dmoe_layer& L, const void* x, int T, void* hid, 
         });
         launch_kernel(router_fused_kernel<NH, 2, KBC, 4, kHiddenSlice>, dim3(NG, dh / 128), 256, lds, s, 
             (const __bf16*)x, (const __bf16*)(pk + P.r1f), (const __bf16*)L.r_b1, nullptr, nullptr,
-            nullptr, T, L.d_model, L.n_experts, 0.0f, 0, nullptr, nullptr, nullptr, nullptr,
+            nullptr, T, L.d_model, L.n_experts, 0.0f, 0, nullptr, nullptr,
             (__bf16*)hid, dh, 0);
     }
     if (dh == 256) launch_scores_slices<16>(L, P, T, (const __bf16*)hid, scores, s);
@@ -543,15 +534,13 @@ int router_fused_split(const dmoe_layer&, int T) {
 }
 
 void launch_router_fused(const dmoe_layer& L, const void* x, int T, int split, float* scores,
-                         float tau, uint64_t* mask, int32_t* k_per_token, int32_t* group_cnt,
-                         uint64_t* colmask, hipStream_t s) {
+                         float tau, uint64_t* mask, int32_t* group_cnt, hipStream_t s) {
     LaunchTimer tm(kSlotRouter, s);
-    if (colmask) split = 1;  // the token sets of an expert are per whole group
     switch (L.router_hidden) {
-    case 64: launch_t<4>(L, x, T, split, scores, tau, mask, k_per_token, group_cnt, colmask, s); break;
-    case 128: launch_t<8>(L, x, T, split, scores, tau, mask, k_per_token, group_cnt, colmask, s); break;
-    case 256: launch_t<16>(L, x, T, split, scores, tau, mask, k_per_token, group_cnt, colmask, s); break;
-    case 512: launch_t<32>(L, x, T, split, scores, tau, mask, k_per_token, group_cnt, colmask, s); break;
+    case 64: launch_t<4>(L, x, T, split, scores, tau, mask, group_cnt, s); break;
+    case 128: launch_t<8>(L, x, T, split, scores, tau, mask, group_cnt, s); break;
+    case 256: launch_t<16>(L, x, T, split, scores, tau, mask, group_cnt, s); break;
+    case 512: launch_t<32>(L, x, T, split, scores, tau, mask, group_cnt, s); break;
     default: break;  // refused by router_fused_supported
     }
 }
