@@ -525,11 +525,12 @@ __global__ __launch_bounds__(256) void up_tiny_kernel(
 // What bounds it is the vector memory path: a CU keeps a fixed number of lines in flight, so a KB that
 // L2 answers costs about 17 cycles and one from beyond L2 about 88 (fits this kernel at three
 // different traffic figures).  Hence the order of the items (select.hip): 4096 tokens x 256 gated
-// experts of 64, d = 2048, 37 % density: 1.84 -> 0.74 GB from beyond L2, 272 -> 220 us; 24 x 128
-// experts at 50432 tokens: 195 -> 170 us.  The 32x32x16 MFMA takes half the instructions of the
-// 16x16x32 one (2048 tokens: 131 -> 123 us).  Built and slower: x rows by LDS-DMA and the weights
-// straight to registers, with a 2 x 2 split over the wavefronts (236 us: LDS instructions down to
-// a sixth, but more bytes and more drift between the workgroups, 0.96 GB).
+// experts of 64, d = 2048, 37 % density: 1.84 -> 0.82 GB from beyond L2 and, with the 32x32x16 MFMA (half
+// the instructions of the 16x16x32 one), 276 -> 240 us, both on one card in turn (224 to 253 over
+// cards and clocks); 24 x 128 experts, half of them per token, at 50432 tokens: 210 -> 204 us.  Built and
+// slower: x rows by LDS-DMA and the weights straight to registers, with a 2 x 2 split over the
+// wavefronts (236 us against 220 on the card of that day: LDS instructions down to a sixth, but more bytes and more
+// drift between the workgroups, 0.96 GB).
 template <int MT, bool GATED, int TT>
 __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf,

@@ -26,10 +26,11 @@
 // by the list of the touched experts), so it computes them all.
 //
 // Measured, whole call (five launches before, of which the prefill kernels took the sizes above 16
-// tokens): 32 experts of 24, d = 768, 16 tokens 20.8 -> 13.6 us; 256 gated experts of 64, d = 1024:
-// 1 token 28.5 -> 19.0, 16 tokens 57.6 -> 47.7, 48 tokens of e4m3 weights 97 -> 43.3 us.  At 16 tokens the
-// two streams (67 and 33 MB) run at 4 TB/s; the rest is the router's chain of two products (16 us with
-// the stream beside it) and the two launches.
+// tokens), weights in the last-level cache: three layers of 32 experts of 24, d = 768, 16 tokens 20.7 -> 13.6 us;
+// 256 gated experts of 64, d = 2048: 1 token 28.9 -> 19.5, 16 tokens 57.3 -> 45.3, 48 tokens of e4m3
+// weights 289 -> 43.3 us.  At 16 tokens, with weights from HBM, the two streams (134 MB of up and gate, 64 MB
+// of down weights) run at about 5 and 4.4 TB/s; the rest is the router's chain of two products (16 us with the
+// stream beside it) and the two launches.
 #include <atomic>
 #include <chrono>
 #include <cmath>
