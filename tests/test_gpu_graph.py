@@ -1,5 +1,5 @@
 """dmoe_forward under HIP graph capture: the library neither allocates nor synchronises and uses
-no memset nodes, so a caller may record the whole layer (six to seven kernel launches) once and
+no memset nodes, so a caller may record the whole layer (two to seven kernel launches) once and
 replay it.  Every replay is checked against the eager result on fresh inputs, with eager work
 and synchronisations between the replays."""
 import numpy as np
