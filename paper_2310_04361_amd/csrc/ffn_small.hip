@@ -566,7 +566,7 @@ __global__ __launch_bounds__(64 * KQ, 2) void small_up_kernel(
 // grid = (16 CTW-column groups, expert groups, layers); KS = m_pad / 32; NW wavefronts split the experts
 // (wavefront w: e0 + w, + NW, ...; at most 64 each), U of the touched ones in flight.  (Requesting the weights
 // ahead of the token sets, of all experts, never gained more than 0.3 us, and lost from 2 MB on that
-// nobody wanted: 1 us at 5 MB, 5 to 9 at 30.)
+// nobody wanted: 0.6 to 2 us at 5 MB, 6 to 14 at 30.)
 template <int KS, int TT, int CTW, int NW, int U, bool W8>
 __global__ __launch_bounds__(64 * NW) void small_down_kernel(const SmallGroup G, int T, int d, int E, int per,
                                                              int dh) {
@@ -727,9 +727,9 @@ double expected_density(int E, double tau) {
 // Whether an up-projection with the gate inside reads the weights of all experts without waiting for the
 // token sets: the sets are there about 7 us after the launch, and against that stands the time to read,
 // at 5 TB/s, what nobody of the T tokens turns out to want.  Measured with either course at 1 to 64
-// tokens and thresholds 0.3 to 0.9 (256 x 64, 1024 x 24, 128 x 24, 24 x 128; weights from HBM and from the last-level cache):
-// reading all is ahead by 3 to 16 us where nearly everything is wanted, by 1 to 6 at 30 MB unwanted, even at
-// 30 to 45, behind by 4 to 12 us at 50 to 65.
+// tokens and thresholds 0.3 to 0.9 (256 x 64, 1024 x 24, 128 x 24, 24 x 128; weights from HBM and from the
+// last-level cache): reading all is ahead by 2 to 16 us below 5 MB unwanted, between 7 ahead and 4 behind from 24
+// to 36 MB, behind by 2 to 9 us from 55 to 66 MB and by 10 to 16 above 110.
 bool small_reads_all(const dmoe_layer& L, int T, float tau) {
     const double bytes = (double)L.n_experts * (L.gated ? 2 : 1) * m_pad_of(L.expert_size) * L.d_model *
                          (weights_fp8(L) ? 1 : 2);
