@@ -44,9 +44,9 @@ namespace dmoe {
 
 namespace {
 
-// Polls of a workgroup that waits for the hidden rows (about 50 us: several times what they take), and for
-// the announcements (about 1 ms: several times what a gate takes that computes the hidden rows of 512
-// units itself).  give_up: see dmoe_small_give_up.
+// Polls of a workgroup that waits, each a round trip past the L2s of about half a microsecond: for the hidden
+// rows some 0.1 ms (they take a few us), and for the announcements some 2 ms, several times what a gate
+// takes that computes the hidden rows of 512 units itself.  give_up: see dmoe_small_give_up.
 constexpr int kHiddenPolls = 200, kSetPolls = 4000;
 __device__ __forceinline__ int wait_budget(int polls, int give_up) {
     return give_up > 0 && blockIdx.x % give_up == 0 ? 0 : polls;
