@@ -200,7 +200,8 @@ int32_t dmoe_expert_ffn(const dmoe_layer *layer, const void *x, int32_t n_tokens
  * The whole layer on one stream with no host synchronisation: router (Sec. 3.3), dynamic-k gate
  * (Sec. 3.4, Eq. 4), bucketing (the metadata of Appendix C) and the selected experts summed on
  * top of b_down (Sec. 3.2; gated experts Appendix G) -- what dmoe_router, dmoe_select and
- * dmoe_expert_ffn compute one after the other.  Optional outputs (each nullable):
+ * dmoe_expert_ffn compute one after the other: the scores it decides by are those of dmoe_router
+ * bit for bit, whatever the batch size.  Optional outputs (each nullable):
  * scores_out [T][E] fp32, mask_out [T][ceil(E/64)], offsets_out [E+1] and token_lists_out
  * (capacity T*E; both or neither).  An output that is not asked for may never be written at all
  * (the fused router and gate keep the scores in registers), so NULL is also the faster call.

@@ -256,7 +256,7 @@ bool router_sliced(const dmoe_layer& L);
 void launch_router_sliced(const dmoe_layer& L, const void* x, int T, void* hid, float* scores,
                           hipStream_t s);
 // Small and medium batches of a router whose first matrix takes 512 KB or more: the hidden rows (a [T][d_h] bf16 buffer) in one launch, the
-// scores and the gate in another; same outputs as launch_router_fused with the gate.
+// scores and the gate in another; the bits of launch_router_fused with the gate.
 bool router_two_launches(const dmoe_layer& L, int T);
 void launch_router_two(const dmoe_layer& L, const void* x, int T, int split, void* hid, float* scores, float tau,
                        uint64_t* mask, int32_t* group_cnt, hipStream_t s);

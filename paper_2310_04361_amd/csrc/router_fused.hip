@@ -14,6 +14,8 @@
 //            tokens of the group that keep it.
 // The scores that are written and the mask come from the same registers, so a caller that gates
 // the returned scores again gets the same mask bit for bit.
+#include <type_traits>
+
 #include "dmoe_internal.h"
 #include "mfma.h"
 
@@ -375,94 +377,127 @@ void launch_t2(const dmoe_layer& L, const void* x, int T, int split, float* scor
 }
 
 // ---- hidden rows of a large router, tile by tile ------------------------------------------------------
-// hid[T][d_h] = relu(x R1^T + c1) rounded to bf16.  Workgroup = 16 TT tokens x 16 UT hidden units; its four
-// wavefronts split K, so that they share nothing until their sums meet in LDS: each streams its own
-// fragments of R1 and its own columns of x (turned through LDS of its own), D blocks of 64 columns ahead.
-// What bounds it is how many bytes a CU gets: with one workgroup per 16 tokens for the whole router every CU
-// read all of R1.  Workgroup b runs on XCD b % 8: by_tokens, one XCD takes all the hidden units of a tile of tokens, so
-// that x leaves memory once, and R1, which is then the smaller, once per XCD; otherwise an XCD takes a few hidden
-// units of all the tokens.
-template <int TT, int UT, int D>
-__global__ __launch_bounds__(256) void router_hidden_kernel(const __bf16* __restrict__ x, const __bf16* __restrict__ r1f,
-                                                            const __bf16* __restrict__ r_b1, __bf16* __restrict__ hid_g,
-                                                            int T, int d, int dh, int by_tokens) {
-    constexpr int kRow = 144;                        // 64 columns of one x row + 16 bytes of bank skew
-    constexpr int kStage = 16 * TT * kRow;
-    constexpr int kRed = UT * TT * 1024;             // one wavefront's sums
-    constexpr int kLds = kStage > kRed ? kStage : kRed;
-    __shared__ __attribute__((aligned(16))) char smem[4 * kLds];
+// hid[T][d_h] = relu(x R1^T + c1) rounded to bf16.  What bounds it is how many bytes a CU gets: with one workgroup per 16
+// tokens for the whole router every CU read all of R1.  Every sum is ONE chain of MFMAs over the k-steps in
+// ascending order, as in router_fused_kernel: a hidden value has the same bits whichever of the forms runs, so
+// that dmoe_forward decides by the very scores that dmoe_router returns at every batch size.
+// Workgroup b runs on XCD b % 8: by_tokens, one XCD takes all the hidden units of a tile of tokens, so that x leaves
+// memory once, and R1, which is then the smaller, once per XCD; otherwise an XCD takes a few hidden units of all the
+// tokens.
+constexpr int kHidRow = 144;  // bytes per staged x row: 64 columns and 16 bytes of bank skew
+
+// 32 tokens x 16 UT hidden units; a wavefront owns NU tiles of units and 16 TTW tokens.  x goes through LDS, which all
+// wavefronts read, in chunks of 256 columns: while chunk k is multiplied, k + 1 is in LDS, k + 2 goes there and k + 3
+// and k + 4 are on their way; R1 fragments are requested four chunks ahead.  The last trip of four chunks requests nothing.
+template <int UT>
+__global__ __launch_bounds__(256, UT > 4 ? 1 : 2) void router_hidden_kernel(
+    const __bf16* __restrict__ x, const __bf16* __restrict__ r1f, const __bf16* __restrict__ r_b1,
+    __bf16* __restrict__ hid_g, int T, int d, int dh, int by_tokens) {
+    constexpr int NU = UT > 4 ? UT / 4 : 1, WU = UT / NU;  // WU: wavefronts side by side over the units
+    constexpr int TTW = WU / 2;
+    extern __shared__ __attribute__((aligned(16))) char smem[];  // [4 chunks][4 blocks][32][kHidRow]
     const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_u = dh / (16 * UT), i = by_tokens ? blockIdx.x >> 3 : blockIdx.x;
-    const int t0 = (by_tokens ? i / n_u * 8 + (blockIdx.x & 7) : i / n_u) * (16 * TT), u0 = i % n_u * UT;  // u0: a tile of 16
+    const int t0 = 32 * (by_tokens ? i / n_u * 8 + (blockIdx.x & 7) : i / n_u);
+    const int u = i % n_u * UT + w % WU * NU, tt0 = w / WU * TTW;  // this wavefront's first tiles
     if (t0 >= T) return;  // (by_tokens: the last eight)
-    const int NK32 = d / 32, n = d / 256, kb0 = w * n;  // this wavefront's blocks kb0 .. kb0 + n - 1
-    char* xs = smem + w * kLds;
-    const __bf16* xp[2 * TT];
+    const int NK32 = d / 32, NKB = d / 64;
+    const int ld_row = threadIdx.x >> 3, ld_piece = threadIdx.x & 7;
+    const __bf16* xp = x + (size_t)min(t0 + ld_row, T - 1) * d + 8 * ld_piece;
+    const __bf16* af = r1f + (size_t)u * NK32 * 512 + lane * 8;
+    char* const xdst = smem + ld_row * kHidRow + ld_piece * 16;
+    const char* const xsrc = smem + (16 * tt0 + c) * kHidRow + q * 16;
+    bf16x8 xr[2][4], a[16][NU][2], b[2][2][TTW];  // two chunks of x; R1 of four chunks; x operands of two blocks
+    // (past the end: the last block again, never used)
+    auto load_x = [&](int kb, bf16x8& r) { r = load8(xp + 64 * min(kb, NKB - 1)); };
+    auto park_x = [&](int slot, const bf16x8& r) { *reinterpret_cast<bf16x8*>(xdst + slot * 32 * kHidRow) = r; };
+    auto load_a = [&](int kb, bf16x8 (&r)[NU][2]) {
 #pragma unroll
-    for (int i = 0; i < 2 * TT; ++i)
-        xp[i] = x + (size_t)min(t0 + 8 * i + (lane >> 3), T - 1) * d + 8 * (lane & 7) + 64 * kb0;
-    const __bf16* af = r1f + ((size_t)u0 * NK32 + 2 * kb0) * 512 + lane * 8;
-    struct Block {
-        bf16x8 x[2 * TT], a[UT][2];
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int n = 0; n < NU; ++n) r[n][ks] = load8(af + ((size_t)n * NK32 + 2 * min(kb, NKB - 1) + ks) * 512);
     };
-    Block st[D];
-    auto load = [&](int b, Block& r) {
-        const int k = min(b, n - 1);  // past the end: the last block again, never used
+    auto read_b = [&](int slot, bf16x8 (&r)[2][TTW]) {
 #pragma unroll
-        for (int i = 0; i < 2 * TT; ++i) r.x[i] = load8(xp[i] + 64 * k);
+        for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int u = 0; u < UT; ++u)
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) r.a[u][ks] = load8(af + ((size_t)u * NK32 + 2 * k + ks) * 512);
+            for (int tt = 0; tt < TTW; ++tt)
+                r[ks][tt] = *reinterpret_cast<const bf16x8*>(xsrc + (slot * 32 + 16 * tt) * kHidRow + ks * 64);
     };
-    f32x4 acc[UT][TT];
+    f32x4 acc[NU][TTW];
 #pragma unroll
-    for (int u = 0; u < UT; ++u)
+    for (int n = 0; n < NU; ++n)
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) acc[u][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int tt = 0; tt < TTW; ++tt) acc[n][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int k = 0; k < D; ++k) load(k, st[k]);
-    for (int b0 = 0; b0 < n; b0 += D) {
+    for (int i = 0; i < 8; ++i) load_x(i, xr[i / 4][i % 4]);
 #pragma unroll
-        for (int k = 0; k < D; ++k) {
-            if (b0 + k < n) {  // uniform
-                Block& r = st[k];
+    for (int i = 0; i < 8; ++i) load_a(i, a[i]);
 #pragma unroll
-                for (int i = 0; i < 2 * TT; ++i)
-                    *reinterpret_cast<bf16x8*>(xs + (8 * i + (lane >> 3)) * kRow + (lane & 7) * 16) = r.x[i];
+    for (int i = 0; i < 8; ++i) {
+        park_x(i, xr[i / 4][i % 4]);
+        load_x(8 + i, xr[i / 4][i % 4]);
+        load_a(8 + i, a[8 + i]);
+    }
+    lds_barrier();
+    read_b(0, b[0]);
+    // chunk C of the trip that starts at block kb0
+    auto chunk = [&](auto c_c, auto more_c, int kb0) {
+        constexpr int C = decltype(c_c)::value;
+        constexpr bool kMore = decltype(more_c)::value;
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    bf16x8 b[TT];
+        for (int j = 0; j < 4; ++j) {
+            const int i = 4 * C + j;
+            __builtin_amdgcn_sched_barrier(0);
+            read_b((i + 1) & 15, b[(i + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int tt = 0; tt < TT; ++tt)
-                        b[tt] = *reinterpret_cast<const bf16x8*>(xs + (16 * tt + c) * kRow + ks * 64 + q * 16);
+            for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-                    for (int u = 0; u < UT; ++u)
+                for (int n = 0; n < NU; ++n)
 #pragma unroll
-                        for (int tt = 0; tt < TT; ++tt) acc[u][tt] = mfma16(r.a[u][ks], b[tt], acc[u][tt]);
-                }
-                if (b0 + k + D < n) load(b0 + k + D, r);
+                    for (int tt = 0; tt < TTW; ++tt) acc[n][tt] = mfma16(a[i][n][ks], b[i & 1][ks][tt], acc[n][tt]);
+            if (kMore || C < 2) park_x((i + 8) & 15, xr[C & 1][j]);
+            if (kMore) {
+                load_a(kb0 + i + 16, a[i]);
+                load_x(kb0 + i + 16, xr[C & 1][j]);
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        lds_barrier();
+    };
+    const std::integral_constant<int, 0> c0;
+    const std::integral_constant<int, 1> c1;
+    const std::integral_constant<int, 2> c2;
+    const std::integral_constant<int, 3> c3;
+    int kb0 = 0;
+    for (; kb0 + 16 < NKB; kb0 += 16) {
+        chunk(c0, std::true_type{}, kb0);
+        chunk(c1, std::true_type{}, kb0);
+        chunk(c2, std::true_type{}, kb0);
+        chunk(c3, std::true_type{}, kb0);
+    }
+    chunk(c0, std::false_type{}, kb0);
+    if (kb0 + 4 < NKB) {  // (uniform)
+        chunk(c1, std::false_type{}, kb0);
+        if (kb0 + 8 < NKB) {
+            chunk(c2, std::false_type{}, kb0);
+            if (kb0 + 12 < NKB) chunk(c3, std::false_type{}, kb0);
         }
     }
-    // the shares of K meet: tile i = (u, tt) of wavefront w at red[w][i]; wavefront w finishes the tiles w, w + 4, ...
-    __syncthreads();
-    f32x4* red = reinterpret_cast<f32x4*>(smem);
+    // lane (q, c) of tile (n, tt): units 16 (u + n) + 4 q .. + 3 of token 16 tt + c
 #pragma unroll
-    for (int u = 0; u < UT; ++u)
+    for (int n = 0; n < NU; ++n) {
+        const int hu = 16 * (u + n) + 4 * q;
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) red[(w * UT * TT + u * TT + tt) * 64 + lane] = acc[u][tt];
-    __syncthreads();
-    for (int i = w; i < UT * TT; i += 4) {
-        f32x4 v = red[i * 64 + lane];
+        for (int tt = 0; tt < TTW; ++tt) {
+            const int t = t0 + 16 * (tt0 + tt) + c;
+            bf16x4 hv;
 #pragma unroll
-        for (int k = 1; k < 4; ++k) v += red[(k * UT * TT + i) * 64 + lane];
-        const int hu = 16 * (u0 + i / TT) + 4 * q, t = t0 + 16 * (i % TT) + c;
-        bf16x4 hv;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) hv[r] = (__bf16)fmaxf(v[r] + (r_b1 ? (float)r_b1[hu + r] : 0.0f), 0.0f);
-        if (t < T) *reinterpret_cast<bf16x4*>(hid_g + (size_t)t * dh + hu) = hv;
+            for (int r = 0; r < 4; ++r) hv[r] = (__bf16)fmaxf(acc[n][tt][r] + (r_b1 ? (float)r_b1[hu + r] : 0.0f), 0.0f);
+            if (t < T) *reinterpret_cast<bf16x4*>(hid_g + (size_t)t * dh + hu) = hv;
+        }
     }
 }
 
@@ -594,11 +629,11 @@ static void launch_scores_slices(const dmoe_layer& L, const PackedLayout& P, int
 }
 
 // Hidden rows of small and medium batches.  Router in all, us, against one workgroup per 16 or 64 tokens and all
-// (or 128) hidden units: d = 2048, d_h = 256, 256 experts, 333 / 1000 / 2000 / 4096 / 6000 tokens 16.9 / 17.2 / 19.0 / 20.8 /
-// 35.5 before, 10.8 / 12.2 / 14.5 / 18.2 / 23.4 now; d_h = 512, 500 / 1000 / 2000 / 4096 tokens (27.0 before at 2000,
-// 33.0 at 4096) 14.0 / 16.1 / 19.4 / 26.9 now; d_h = 128, 4096 tokens 17.7 before, 13.1 now.
-// From 6144 tokens on (8192: 25.4 in one launch, 29.2 in two; d_h = 512 38.5 and 45.8) a workgroup of the one launch has
-// more than 16 tokens to use its share of R1 for.
+// (or 128) hidden units: d = 2048, d_h = 256, 256 experts, 333 / 1000 / 2000 / 4096 / 6000 tokens 16.4 / 16.3 / 18.0 / 20.7 /
+// 36.8 before, 11.4 / 12.2 / 14.0 / 19.4 / 27.6 now; d_h = 512, 500 / 1000 / 2000 / 4096 tokens 27.9 / 27.4 / 28.3 / 32.1 before,
+// 13.4 / 15.2 / 17.8 / 22.4 now; d_h = 128, 4096 tokens 13.6 before, 11.4 now.
+// From 6144 tokens on (6200: 25.0 in one launch, 32.3 in two; d_h = 512, 8192: 36.3 and 42.3) a workgroup of the one
+// launch has more than 16 tokens to use its share of R1 for.
 static bool router_tiles(const dmoe_layer&, int T) { return div_up(T, kGroup) < 96; }
 static void launch_router_hidden(const dmoe_layer& L, const void* x, int T, void* hid, hipStream_t s) {
     const PackedLayout P = packed_layout(L);
@@ -620,20 +655,30 @@ static void launch_router_hidden(const dmoe_layer& L, const void* x, int T, void
             (__bf16*)hid, dh, 0);
         return;
     }
-    // x is the larger of the two that the XCDs share (d_h = 256: 333 tokens 10.8 us either way, 1000 tokens 12.2 against
-    // 13.1; d_h = 512: 500 tokens 14.9 against 14.0, 2000 tokens 19.4 against 21.5)
+    // x is the larger of the two that the XCDs share (by_tokens 1 / 0, router in all: d_h = 256, 333 tokens 11.5 us either
+    // way, 1000 tokens 12.2 / 13.3; d_h = 128, 4096 tokens 11.4 / 15.3; d_h = 512, 333 tokens 14.2 / 13.1, 2000 tokens 17.9 / 18.2)
     const int by_tokens = T >= 2 * dh ? 1 : 0;
+    constexpr size_t kTileLds = 16 * 32 * kHidRow;
     auto go = [&](auto kernel, int tok, int units) {
         const int n = div_up(T, tok);
-        launch_kernel(kernel, (by_tokens ? round_up(n, 8) : n) * (dh / units), 256, 0, s, (const __bf16*)x, r1f,
+        launch_kernel(kernel, (by_tokens ? round_up(n, 8) : n) * (dh / units), 256, kTileLds, s, (const __bf16*)x, r1f,
                       (const __bf16*)L.r_b1, (__bf16*)hid, T, L.d_model, dh, by_tokens);
     };
-    // The larger tile reads less and needs workgroups enough to fill the chip.  Hidden rows alone, d_h = 256, 1000 /
-    // 1500 / 2000 tokens (128 / 188 / 252 tiles of 32 x 64) 6.3 / 8.9 / 9.5 us in tiles of 32 x 32, 7.6 / 7.4 / 8.2 in 32 x 64
-    // (10.6 / 11.0 / 10.4 in 64 x 64); 4096 tokens 14.7 / 11.4 / 12.1.
-    if (div_up(T, 32) * (dh / 64) >= 160) go(router_hidden_kernel<2, 4, 3>, 32, 64);
-    else if (div_up(T, 32) * (dh / 32) >= 128) go(router_hidden_kernel<2, 2, 4>, 32, 32);
-    else go(router_hidden_kernel<1, 1, 8>, 16, 16);
+    static std::once_flag tile_once;  // kernel attributes: once per process, thread-safe
+    std::call_once(tile_once, [] {
+        for (const void* f : {reinterpret_cast<const void*>(&router_hidden_kernel<8>),
+                              reinterpret_cast<const void*>(&router_hidden_kernel<4>),
+                              reinterpret_cast<const void*>(&router_hidden_kernel<2>)})
+            (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    });
+    // The larger tile reads less and needs workgroups enough to fill the chip.  Router in all, d_h = 256, in tiles of 32 x
+    // 32 / 64 / 128: 1000 tokens (n4 = 128) 12.0 / 14.1 / 17.2 us, 1250 (160) 14.5 / 13.3 / 16.6, 2000 (252) 16.4 / 14.0 / 17.5,
+    // 3000 (376) 20.0 / 18.8 / 18.0, 4096 (512: as many tiles of 128 as CUs) 24.9 / 19.8 / 18.4, 6000 (752) 36.3 / 27.6 /
+    // 30.9; d_h = 512, 500 tokens (128) 13.3 / 14.6 / 16.6, 1000 (256) 16.5 / 15.3 / 16.8, 2000 (504) 23.3 / 19.4 / 17.7.
+    const int n4 = div_up(T, 32) * (dh / 64);
+    if (n4 >= 320 && n4 <= 512) go(router_hidden_kernel<8>, 32, 128);
+    else if (n4 >= 160) go(router_hidden_kernel<4>, 32, 64);
+    else go(router_hidden_kernel<2>, 32, 32);
 }
 
 bool router_two_launches(const dmoe_layer& L, int T) {

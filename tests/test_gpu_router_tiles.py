@@ -39,3 +39,31 @@ def test_router_tiles(oracle, T, d, E, d_h, bias):
     assert np.array_equal(ex["offsets"].cpu().numpy(), offsets)
     assert np.array_equal(ex["token_lists"].cpu().numpy()[:offsets[-1]], lists)
     assert torch.equal(ex["mask_bits"], ex2["mask_bits"]) and torch.equal(y, y2)
+
+
+@pytest.mark.parametrize("T,d,E,d_h,top_k", [
+    # small batches, one launch, and every tile of the hidden rows on either side of its rule (2048 wide: 32 x 32 below 160 tiles
+    # of 32 x 64, 32 x 128 from 320 to 512 of them), the first batch in one launch again
+    (1, 2048, 256, 256, None), (16, 2048, 256, 256, None), (64, 2048, 256, 256, None), (65, 2048, 256, 256, None),
+    (333, 2048, 256, 256, None), (1248, 2048, 256, 256, None), (1249, 2048, 256, 256, None), (2528, 2048, 256, 256, None),
+    (2529, 2048, 256, 256, None), (4096, 2048, 256, 256, None), (4097, 2048, 256, 256, None), (6081, 2048, 256, 256, None),
+    # part of a trip of 16 K blocks: 8, 12, 20 and 36 of them
+    (300, 512, 120, 512, None), (1500, 768, 120, 512, None), (2600, 1280, 65, 256, None), (700, 2304, 64, 128, None),
+    # the top-k gate, and more experts than the fused gate takes
+    (333, 2048, 256, 512, 9), (2000, 2048, 256, 256, 9), (1023, 2048, 600, 512, None), (2049, 2048, 1100, 512, None),
+    (9, 512, 1100, 128, 5), (12, 256, 30, 64, 3), (40, 256, 1030, 32, None), (50, 768, 128, 128, None), (700, 768, 128, 128, None),
+])
+def test_forward_decides_by_the_scores_of_the_router(oracle, T, d, E, d_h, top_k):
+    """One order of the sums in all forms of the router: the same bits from dmoe_router and dmoe_forward."""
+    import torch
+    from paper_2310_04361_amd import binding as B
+    cfg = wl.Config("router_bits", T, d, E, 8, d_h, True, "gelu_tanh", "bf16", (0.5,), router_bias=True)
+    print(f"router bits T={T} d={d} E={E} d_h={d_h} top_k={top_k}", flush=True)
+    layer, x = wl.make_layer(cfg, 4), wl.make_input(cfg, 4)
+    L, xd, tau = B.Layer(layer, cfg.dtype), B.to_device(x, cfg.dtype), float(np.float32(0.5))
+    _, ex = B.dmoe_forward(L, xd, tau, want_scores=True, want_mask=True, top_k=top_k)
+    scores = B.dmoe_router(L, xd)
+    sel = B.dmoe_select(scores, tau, top_k=top_k)
+    torch.cuda.synchronize()
+    assert torch.equal(ex["scores"], scores)
+    assert torch.equal(ex["mask_bits"], sel["mask_bits"])
