@@ -311,12 +311,18 @@ void launch_layer_f32_any(const dmoe_layer& L, const float* x, int T, bool gate,
                           float* scores_out, float* y, hipStream_t s) {
     LaunchTimer tm(kSlotFfnF32, s);
     const size_t lds = layer_f32_lds(L, gate);
+    // (a launch holds fewer than 2^32 threads: beyond, the runtime takes their number modulo 2^32)
+    constexpr int kSlice = 1 << 21;  // tokens
     auto go = [&](auto kernel) {
-        launch_kernel(kernel, T, kLayerThreads, lds, s, x, (const float*)L.r_w1, (const float*)L.r_b1,
-                      (const float*)L.r_w2, (const float*)L.r_b2, (const float*)L.w_up,
-                      L.gated ? (const float*)L.w_gate : nullptr, (const float*)L.b_up, (const float*)L.w_down,
-                      (const float*)L.b_down, mask, scores_out, y, L.d_model, L.router_hidden, L.n_experts,
-                      L.expert_size, div_up(L.n_experts, 64), L.act, tau);
+        const int E = L.n_experts, W = div_up(E, 64);
+        for (int t0 = 0; t0 < T; t0 += std::min(kSlice, T - t0)) {
+            launch_kernel(kernel, std::min(kSlice, T - t0), kLayerThreads, lds, s, x + (size_t)t0 * L.d_model,
+                          (const float*)L.r_w1, (const float*)L.r_b1, (const float*)L.r_w2, (const float*)L.r_b2,
+                          (const float*)L.w_up, L.gated ? (const float*)L.w_gate : nullptr, (const float*)L.b_up,
+                          (const float*)L.w_down, (const float*)L.b_down, mask ? mask + (size_t)t0 * W : nullptr,
+                          scores_out ? scores_out + (size_t)t0 * E : nullptr, y + (size_t)t0 * L.d_model, L.d_model,
+                          L.router_hidden, E, L.expert_size, W, L.act, tau);
+        }
     };
     const int dc = div_up(L.d_model, 64);
 #define DMOE_F32(DC_) (gate ? go(layer_f32_kernel<DC_, true>) : go(layer_f32_kernel<DC_, false>))

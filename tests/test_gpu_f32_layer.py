@@ -43,3 +43,29 @@ def test_fp32_layer_edges(oracle, T, d, E, m, d_h, gated, tau):
     y2 = B.dmoe_expert_ffn(L, xd, torch.from_numpy(offsets).cuda(), torch.from_numpy(np.resize(lists, max(len(lists), 1))).cuda())
     ref = oracle_ffn(oracle, layer, x, (mask * keep).astype(mask.dtype))
     assert tokenwise_rel_err(B.from_device(y2, cfg.dtype), ref) <= TOL["f32"]
+
+
+def test_fp32_layer_of_more_tokens_than_one_launch_holds(oracle):
+    """A workgroup of 1024 threads per token: 2^22 tokens are 2^32 threads, more than a launch can have."""
+    import torch
+    from paper_2310_04361_amd import binding as B
+    T, d, E, m, d_h = (1 << 22) + 70, 4, 2, 1, 4
+    cfg = wl.Config("f32_many", 64, d, E, m, d_h, False, "relu", "f32", (0.5,), ffn_bias=True, router_bias=True)
+    layer = wl.make_layer(cfg, 3)
+    L = B.Layer(layer, cfg.dtype)
+    x = torch.randn((T, d), device="cuda", generator=torch.Generator(device="cuda").manual_seed(5))
+    bad = torch.full_like(x, float("nan"))
+    y, ex = B.dmoe_forward(L, x, 0.5, want_scores=True, want_mask=True, y=bad.clone())
+    y1, _ = B.dmoe_forward(L, x, 0.5, y=bad.clone())
+    yk, _ = B.dmoe_forward_topk(L, x, 1, y=bad.clone())
+    assert torch.equal(y, y1)
+    assert torch.equal(ex["scores"], B.dmoe_router(L, x))
+    for t0 in (0, 1 << 21, 1 << 22, T - 64):  # ends of launches
+        rows = slice(max(t0 - 32, 0), min(t0 + 64, T))
+        xs, scores = x[rows].cpu().numpy().astype(np.float64), ex["scores"][rows].cpu().numpy().astype(np.float64)
+        mask, _ = oracle.select(scores, 0.5)
+        assert np.array_equal(B.mask_bits_to_bool(ex["mask_bits"][rows], E), mask)
+        assert tokenwise_rel_err(B.from_device(y[rows], cfg.dtype), oracle_ffn(oracle, layer, xs, mask)) <= TOL["f32"]
+        top = oracle.select_topk(scores, 1)
+        assert tokenwise_rel_err(B.from_device(yk[rows], cfg.dtype), oracle_ffn(oracle, layer, xs, top)) <= TOL["f32"]
+    assert torch.isfinite(y).all() and torch.isfinite(yk).all()
