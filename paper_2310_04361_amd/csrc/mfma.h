@@ -153,7 +153,9 @@ __device__ __forceinline__ float activate_fast(int act, float v) {
         p = fmaf(p, t, -0.142248368f);
         p = fmaf(p, t, 0.127414796f);
         const float q = p * t * __builtin_amdgcn_exp2f(v * v * -0.721347520f);  // exp(-v^2 / 2)
-        return fmaf(-fminf(a, 1e30f), q, fmaxf(v, 0.0f));                       // (an infinite v: 1e30 * 0)
+        // -|v|, but of +inf a finite number, whose product with q = 0 is no NaN (of -inf it is one, as -inf * Phi(-inf) is)
+        const float neg = fmaxf(-a, fminf(v, -1e30f));
+        return fmaf(neg, q, fmaxf(v, 0.0f));
     }
     // -2 u / ln 2 = v (c0 + c1 v^2)
     const float e = __builtin_amdgcn_exp2f(v * fmaf(v * v, -0.102943240f, -2.302208198f));
