@@ -98,7 +98,7 @@ __global__ __launch_bounds__(64 * kDqWaves, 2) void down_quad_kernel(
     if (offsets[E] > max_pairs) return;  // dense enough for down_bf16_kernel
     if constexpr (PG > 4) {
         if (offsets[E] <= max_rmw) {  // so sparse that work in proportion to the pairs is less
-            down_rmw_body<PG == 16 ? 4 : 2>(w2f, b_down, item_start, group_off, alist, H, y, T, d, E, NG, rows_per_item, PG == 16 ? 128 : 64, img);
+            down_rmw_body<PG == 16 ? 4 : 2>(w2f, b_down, item_start, group_off, alist, H, y, T, d, E, NG, rows_per_item, img);
             return;
         }
     }

@@ -19,7 +19,12 @@
 // Operands of the next kDepth tiles are kept in flight while the current one is merged.
 // Weights: the 16x16x32 fragments w2f (also used by the small-token path); H rows as written by
 // the up kernel (16-byte piece 4ks + q of a row = neurons 8(4ks + q) .. +7 = the k values of lane
-// group q in k-step ks).
+// group q in k-step ks).  RN: neurons per H row (h_row_neurons).  Rows of one or two pieces have nothing for the
+// other lane groups: those read, at every tile, the zeros that the packed weights of the first expert are there.
+// (Rows of a size known only at run time and a zero chosen where the row is loaded, which waits for the load
+// and ends the ring, against this, 1 % density, d = 768: 20000 tokens x 2048 experts of 24 1075 / 962 us; 50432
+// tokens x 2048 experts of 8 2678 / 2368, x 1024 experts of 16 1341 / 1228.  All of those lanes at one address, or
+// zeros chosen where they are used, 2539 and 2560 for the experts of 8.)
 #pragma once
 
 #include "dmoe_internal.h"
@@ -35,14 +40,15 @@ constexpr int kDownStride = kDownCols + 4;     // LDS row stride in floats
 constexpr size_t kDownLds = sizeof(float) * kChunk * kDownStride +
                             sizeof(int2) * kDownBatch * kDownTilesPerExpert;
 
-template <int KS>
+template <int KS, int RN = 32 * KS>
 __device__ __forceinline__ void down_rmw_body(
     const __bf16* __restrict__ w2f, const __bf16* __restrict__ b_down,
     const int32_t* __restrict__ item_start, const int32_t* __restrict__ group_off,
     const int32_t* __restrict__ alist, const __bf16* __restrict__ Hf, __bf16* __restrict__ y, int T, int d, int E, int NG, int rows_per_item,
-    int row_neurons, char* smem) {
+    char* smem) {
     constexpr int kThreads = kDownWaves * 64;
     constexpr int kDepth = KS <= 2 ? 4 : 2;  // tiles of operands in flight per wavefront
+    static_assert(RN == 32 * KS || (KS == 1 && (RN == 8 || RN == 16)), "row");
     float* smem_f = reinterpret_cast<float*>(smem);  // kDownLds bytes
     float* Y = smem_f;  // [kChunk][kDownStride]
     int2* tiles = reinterpret_cast<int2*>(smem_f + kChunk * kDownStride);
@@ -56,6 +62,8 @@ __device__ __forceinline__ void down_rmw_body(
     const int t_base = chunk * kChunk, col0 = slice * kDownCols;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6, q = lane >> 4, c = lane & 15;
+    constexpr bool whole = RN == 32 * KS;
+    const bool real = whole || 8 * q < RN;  // this lane group has a piece of the row
     {   // every row of the tile starts as the output bias of this slice
         static_assert(kThreads % kDownCols == 0, "one column per thread");
         const int col = tid % kDownCols;
@@ -69,6 +77,8 @@ __device__ __forceinline__ void down_rmw_body(
     // weight fragments of this wavefront's two column tiles: + (e * d/16) fragments per expert
     const __bf16* wbase =
         w2f + ((size_t)(col0 / 16 + 2 * __builtin_amdgcn_readfirstlane(wave)) * KS * 64 + lane) * 8;
+    const __bf16* hbase = real ? Hf + 8 * q : wbase;
+    const uint32_t row_mask = real ? ~0u : 0u;
     const size_t w_expert_stride = (size_t)(d / 16) * KS * 512;
     // element (token t, column wave*32 + nt*16 + 4q) is at ybase + t * kDownStride + nt * 16
     float* ybase = Y + wave * 32 + 4 * q - (ptrdiff_t)t_base * kDownStride;
@@ -131,11 +141,11 @@ __device__ __forceinline__ void down_rmw_body(
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int row = row_first + (16 * h + c < rows ? 16 * h + c : 0);
-                const __bf16* hp = Hf + (size_t)row * row_neurons + 8 * q;  // (h_row_neurons)
+                const __bf16* hp = whole ? Hf + (size_t)row * RN + 8 * q : hbase + (size_t)((uint32_t)row & row_mask) * RN;
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
                     a[h][ks] = load8(wp + (h * KS + ks) * 512);
-                    b[h][ks] = KS > 1 || 8 * q < row_neurons ? load8(hp + ks * 32) : zero8();
+                    b[h][ks] = load8(hp + ks * 32);
                 }
                 tok[h] = alist[row];
             }

@@ -6,28 +6,28 @@ namespace dmoe {
 
 namespace {
 
-template <int KS>
+template <int KS, int RN>
 __global__ __launch_bounds__(kDownWaves * 64) void down_rmw_bf16_kernel(
     const __bf16* __restrict__ w2f, const __bf16* __restrict__ b_down, const int32_t* __restrict__ item_start,
     const int32_t* __restrict__ group_off, const int32_t* __restrict__ alist, const __bf16* __restrict__ Hf,
-    __bf16* __restrict__ y, int T, int d, int E, int NG, int rows_per_item, int row_neurons) {
+    __bf16* __restrict__ y, int T, int d, int E, int NG, int rows_per_item) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    down_rmw_body<KS>(w2f, b_down, item_start, group_off, alist, Hf, y, T, d, E, NG, rows_per_item, row_neurons, smem);
+    down_rmw_body<KS, RN>(w2f, b_down, item_start, group_off, alist, Hf, y, T, d, E, NG, rows_per_item, smem);
 }
 
-template <int KS>
+template <int KS, int RN>
 void launch_down_rmw_t(const dmoe_layer& L, const PackedLayout& P, int T, const int32_t* item_start,
                        const int32_t* group_off, const int32_t* alist, const void* H, void* y, hipStream_t s) {
     const int NG = div_up(T, kGroup), NC = div_up(T, kChunk), NS = L.d_model / kDownCols;
     static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
     std::call_once(attr_once, [&] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&down_rmw_bf16_kernel<KS>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&down_rmw_bf16_kernel<KS, RN>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDownLds);
     });
     const char* pk = static_cast<const char*>(L.packed);
-    launch_kernel(down_rmw_bf16_kernel<KS>, round_up(NC, 8) * NS, kDownWaves * 64, kDownLds, s, 
+    launch_kernel(down_rmw_bf16_kernel<KS, RN>, round_up(NC, 8) * NS, kDownWaves * 64, kDownLds, s, 
         (const __bf16*)(pk + P.w2f), (const __bf16*)L.b_down, item_start, group_off, alist,
-        (const __bf16*)H, (__bf16*)y, T, L.d_model, L.n_experts, NG, up_rows_bf16(L), h_row_neurons(L));
+        (const __bf16*)H, (__bf16*)y, T, L.d_model, L.n_experts, NG, up_rows_bf16(L));
 }
 
 }  // namespace
@@ -36,10 +36,15 @@ void launch_down_rmw_bf16(const dmoe_layer& L, int T, const int32_t* item_start,
                           const int32_t* group_off, const int32_t* alist, const void* H, void* y, hipStream_t s) {
     LaunchTimer tm(kSlotDownRmw, s);
     const PackedLayout P = packed_layout(L);
-    const int ks = m_pad_of(L.expert_size) / 32;
-    if (ks == 1) launch_down_rmw_t<1>(L, P, T, item_start, group_off, alist, H, y, s);
-    else if (ks == 2) launch_down_rmw_t<2>(L, P, T, item_start, group_off, alist, H, y, s);
-    else launch_down_rmw_t<4>(L, P, T, item_start, group_off, alist, H, y, s);
+#define DMOE_RMW(KS_, RN_) launch_down_rmw_t<KS_, RN_>(L, P, T, item_start, group_off, alist, H, y, s)
+    switch (h_row_neurons(L)) {
+    case 8: DMOE_RMW(1, 8); break;
+    case 16: DMOE_RMW(1, 16); break;
+    case 32: DMOE_RMW(1, 32); break;
+    case 64: DMOE_RMW(2, 64); break;
+    default: DMOE_RMW(4, 128); break;
+    }
+#undef DMOE_RMW
 }
 
 }  // namespace dmoe
