@@ -207,7 +207,7 @@ void launch_mask_topk(const float* scores, int T, int E, int k, uint64_t* mask,
 // Counts per (group, expert) and, if wanted, the per-expert token sets from mask bits.
 void launch_counts_from_mask(const uint64_t* mask, int T, int E, int32_t* group_off, uint64_t* colmask,
                              hipStream_t s);
-// scratch: E * 64 ceil(T / 64) bytes (16-byte aligned) for the way without atomics, where there are as many.
+// scratch: E * 64 ceil(T / 64) bytes (16-byte aligned) for the way without atomics, which is not taken with fewer.
 void launch_mask_from_lists(const int32_t* offsets, const int32_t* lists, int T, int E,
                             uint64_t* mask, int32_t* group_off, uint64_t* colmask, void* scratch,
                             size_t scratch_bytes, hipStream_t s);

@@ -32,6 +32,17 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
     return v;
 }
 
+// 64 x 64 bits over a wavefront: bit b of lane a becomes bit a of lane b.
+__device__ __forceinline__ uint64_t transpose64(uint64_t v, int lane) {
+    uint64_t out = 0;
+#pragma unroll 8
+    for (int b = 0; b < 64; ++b) {
+        const uint64_t bal = __ballot((v >> b) & 1ull);
+        if (lane == b) out = bal;
+    }
+    return out;
+}
+
 // Per-group expert counts from the mask words: one wavefront per (group of 64 tokens, mask word),
 // lane = token.  The ballot transpose gives, for every expert of the word, the 64-bit set of the
 // group's tokens that keep it: its population count goes to group_cnt[g][e], the set itself to
@@ -46,13 +57,8 @@ __global__ __launch_bounds__(256) void count_from_mask_kernel(const uint64_t* __
     const int g = wave / W, w = wave - g * W;
     if (g >= NG) return;  // uniform per wavefront
     const int t = g * kGroup + lane;
-    const uint64_t word = t < T ? mask[(size_t)t * W + w] : 0ull;
-    uint64_t col = 0;  // lane b: which tokens of the group keep expert 64w + b
-#pragma unroll 8
-    for (int b = 0; b < 64; ++b) {
-        const uint64_t bal = __ballot((word >> b) & 1ull);
-        if (lane == b) col = bal;
-    }
+    // lane b: which tokens of the group keep expert 64w + b
+    const uint64_t col = transpose64(t < T ? mask[(size_t)t * W + w] : 0ull, lane);
     const int e = 64 * w + lane;
     if (e < E) {
         group_cnt[(size_t)g * E + e] = __popcll(col);
@@ -213,42 +219,88 @@ __global__ __launch_bounds__(1024) void select_small_group_kernel(const SmallGro
     select_small_body(M.scores, mw, M.mask, nullptr, M.group_cnt, M.colmask, T, E, W, M.tau);
 }
 
-__global__ void zero_u64_kernel(uint64_t* p, size_t n) {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) p[i] = 0ull;
+// Caller-supplied lists -> mask words and group counts, in three launches (clear, scatter, finish) and in one of two
+// ways, which the number of positions on the device decides:
+//   by bytes: a byte per (expert, token), bytes[E][Tp]; an expert's positions go to one row of workgroups.  No atomics, but
+//   all E T bytes are written and read.
+//   by bits: an atomic OR per position into the mask words, lines that all XCDs write, and a count afterwards.
+// Entries outside [0, T) are dropped, duplicates meet in one byte or bit.  Bits / bytes, us: 605000 positions of 24
+// experts at 50432 tokens 19.0 / 12.5, 300000 of 2048 experts at 2000 tokens 25 / 13.6; 2048 experts, 50432 tokens, 0.05 / 0.3 /
+// 1 % of E T: 34 / 46 / 75 and 48 / 49 / 58; 256 experts, 66000 tokens, 0.3 / 1 / 3 %: 14 / 19 / 35 and 21 / 21 / 21.
+// CHOOSE: up to bits_max positions go by bits, and all where there are no bytes; otherwise all go by bytes.
+template <bool CHOOSE>
+__device__ __forceinline__ bool lists_by_bytes(const int32_t* offsets, int T, int E, const void* bytes, long long bits_max) {
+    if (!CHOOSE) return true;
+    return bytes && min((long long)offsets[E], (long long)T * E) - max((long long)offsets[0], 0ll) > bits_max;
 }
 
-// Caller-supplied lists -> a byte per (expert, token), bytes[E][Tp].  An expert's positions go to one row of
-// workgroups; entries outside [0, T) are dropped, duplicates meet in one byte.
-__global__ __launch_bounds__(256) void lists_to_bytes_kernel(const int32_t* __restrict__ offsets,
-                                                             const int32_t* __restrict__ lists, int T, int E,
-                                                             int Tp, uint8_t* __restrict__ bytes) {
-    const int e = blockIdx.y;
-    const long long cap = (long long)T * E;
-    const long long first = max((long long)max(offsets[0], 0), (long long)offsets[e]);
-    const long long last = min(min((long long)offsets[E], cap), (long long)offsets[e + 1]);
-    uint8_t* row = bytes + (size_t)e * Tp;
-    for (long long p = first + (long long)blockIdx.x * 256 + threadIdx.x; p < last; p += (long long)gridDim.x * 256) {
+template <bool CHOOSE>
+__global__ __launch_bounds__(256) void lists_clear_kernel(const int32_t* __restrict__ offsets, int T, int E,
+                                                          uint64_t* __restrict__ mask, size_t n_mask,
+                                                          uint64_t* __restrict__ bytes, size_t n_bytes, long long bits_max) {
+    const bool by_bytes = lists_by_bytes<CHOOSE>(offsets, T, E, bytes, bits_max);
+    uint64_t* p = by_bytes ? bytes : mask;
+    const size_t n = by_bytes ? n_bytes : n_mask, stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0ull;
+}
+
+// blockIdx.y = expert (by bytes)
+template <bool CHOOSE>
+__global__ __launch_bounds__(256) void lists_scatter_kernel(const int32_t* __restrict__ offsets,
+                                                            const int32_t* __restrict__ lists, int T, int E, int W,
+                                                            int Tp, uint8_t* __restrict__ bytes,
+                                                            unsigned long long* __restrict__ mask, long long bits_max) {
+    const long long cap = (long long)T * E, begin = max((long long)offsets[0], 0ll), end = min((long long)offsets[E], cap);
+    if (lists_by_bytes<CHOOSE>(offsets, T, E, bytes, bits_max)) {
+        const int e = blockIdx.y;
+        const long long first = max(begin, (long long)offsets[e]), last = min(end, (long long)offsets[e + 1]);
+        uint8_t* row = bytes + (size_t)e * Tp;
+        constexpr int kN = 8;  // positions in flight: one expert may have most of them
+        const long long stride = (long long)gridDim.x * 256;
+        for (long long p = first + (long long)blockIdx.x * 256 + threadIdx.x; p < last; p += kN * stride) {
+            int t[kN];
+#pragma unroll
+            for (int k = 0; k < kN; ++k) t[k] = lists[min(p + k * stride, last - 1)];
+#pragma unroll
+            for (int k = 0; k < kN; ++k)
+                if (p + k * stride < last && (unsigned)t[k] < (unsigned)T) row[t[k]] = 1;
+        }
+        return;
+    }
+    const long long stride = (long long)gridDim.x * gridDim.y * 256;
+    for (long long p = begin + (long long)(blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; p < end; p += stride) {
+        // expert of position p: the last e with offsets[e] <= p
+        int lo = 0, hi = E;  // answer in [lo, hi)
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if ((long long)offsets[mid] <= p) lo = mid; else hi = mid;
+        }
+        if (p >= (long long)offsets[lo + 1]) continue;  // non-monotone offsets: drop
         const int t = lists[p];
-        if ((unsigned)t < (unsigned)T) row[t] = 1;
+        if ((unsigned)t < (unsigned)T)
+            atomicOr(&mask[(size_t)t * W + (lo >> 6)], 1ull << (lo & 63));
     }
 }
 
-// ... -> mask words and group counts: one wavefront per (group of 64 tokens, mask word).  Lane b turns the group's 64
-// bytes of expert 64 w + b into its 64-bit token set, and the ballots over a token's bit of all the sets
-// are the mask words.  (With an atomic OR per position into the mask words, lines that all XCDs write, and a count
-// afterwards: 605000 positions of 24 experts at 50432 tokens 19.0 us, now 12.5, the whole call 403 -> 392; 300000 of
-// 2048 experts at 2000 tokens 25 us, now 13.6.)
-__global__ __launch_bounds__(256) void mask_from_bytes_kernel(const uint8_t* __restrict__ bytes, int T, int E, int W,
-                                                              int Tp, uint64_t* __restrict__ mask,
-                                                              int32_t* __restrict__ group_cnt) {
+// One wavefront per (group of 64 tokens, mask word).  By bytes: lane b turns the group's 64 bytes of expert 64 w + b
+// into its 64-bit token set, and the ballots over a token's bit of all the sets are the mask words.  By bits: the other
+// way round (count_from_mask_kernel).
+template <bool CHOOSE>
+__global__ __launch_bounds__(256) void lists_finish_kernel(const int32_t* __restrict__ offsets,
+                                                           const uint8_t* __restrict__ bytes, int T, int E, int W,
+                                                           int Tp, uint64_t* __restrict__ mask,
+                                                           int32_t* __restrict__ group_cnt, long long bits_max) {
     const int lane = lane_id();
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int NG = (T + kGroup - 1) / kGroup;
     const int g = wave / W, w = wave - g * W;
     if (g >= NG) return;  // uniform per wavefront
-    const int e = 64 * w + lane;
+    const int e = 64 * w + lane, t = g * kGroup + lane;
+    if (!lists_by_bytes<CHOOSE>(offsets, T, E, bytes, bits_max)) {
+        const uint64_t set = transpose64(t < T ? mask[(size_t)t * W + w] : 0ull, lane);
+        if (e < E) group_cnt[(size_t)g * E + e] = __popcll(set);
+        return;
+    }
     uint64_t set = 0;
     if (e < E) {
         const ulonglong2* src = reinterpret_cast<const ulonglong2*>(bytes + (size_t)e * Tp + g * kGroup);
@@ -262,39 +314,8 @@ __global__ __launch_bounds__(256) void mask_from_bytes_kernel(const uint8_t* __r
         }
         group_cnt[(size_t)g * E + e] = __popcll(set);
     }
-    uint64_t word = 0;  // lane t: token 64 g + t
-#pragma unroll 8
-    for (int t = 0; t < 64; ++t) {
-        const uint64_t bal = __ballot((set >> t) & 1ull);
-        if (lane == t) word = bal;
-    }
-    const int t = g * kGroup + lane;
+    const uint64_t word = transpose64(set, lane);
     if (t < T) mask[(size_t)t * W + w] = word;
-}
-
-// Caller-supplied lists -> mask bits.  One thread per list position; entries outside [0, T)
-// are dropped, duplicates collapse in the OR.
-__global__ void lists_to_mask_kernel(const int32_t* __restrict__ offsets,
-                                     const int32_t* __restrict__ lists, int T, int E, int W,
-                                     unsigned long long* __restrict__ mask) {
-    const long long cap = (long long)T * E;
-    long long first = offsets[0], last = offsets[E];
-    if (first < 0) first = 0;
-    if (last > cap) last = cap;
-    long long p = first + (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long stride = (long long)gridDim.x * blockDim.x;
-    for (; p < last; p += stride) {
-        // expert of position p: the last e with offsets[e] <= p
-        int lo = 0, hi = E;  // answer in [lo, hi)
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if ((long long)offsets[mid] <= p) lo = mid; else hi = mid;
-        }
-        if (p >= (long long)offsets[lo + 1]) continue;  // non-monotone offsets: drop
-        const int t = lists[p];
-        if ((unsigned)t < (unsigned)T)
-            atomicOr(&mask[(size_t)t * W + (lo >> 6)], 1ull << (lo & 63));
-    }
 }
 
 // One wavefront per expert: exclusive prefix sum of group_cnt[.][e] over the groups, in place;
@@ -700,24 +721,30 @@ void launch_mask_from_lists(const int32_t* offsets, const int32_t* lists, int T,
                             uint64_t* mask, int32_t* group_off, uint64_t* colmask, void* scratch,
                             size_t scratch_bytes, hipStream_t s) {
     const int W = div_up(E, 64), Tp = round_up(T, kGroup);
-    if (!colmask && group_off && (size_t)E * Tp <= scratch_bytes) {
-        LaunchTimer tm(kSlotListsToMask, s);
-        const size_t n = (size_t)E * Tp / 8;
-        launch_kernel(zero_u64_kernel, (int)std::min<size_t>(1024, (n + 255) / 256), 256, 0, s, (uint64_t*)scratch, n);
-        launch_kernel(lists_to_bytes_kernel, dim3(std::max(1, std::min(div_up(T, 256), 1024 / E)), E), 256, 0, s, offsets,
-                      lists, T, E, Tp, (uint8_t*)scratch);
-        launch_kernel(mask_from_bytes_kernel, div_up(div_up(T, kGroup) * W, 4), 256, 0, s, (const uint8_t*)scratch, T, E, W,
-                      Tp, mask, group_off);
-        return;
-    }
-    {
-        LaunchTimer tm(kSlotListsToMask, s);
-        const size_t n = (size_t)T * W;
-        launch_kernel(zero_u64_kernel, (int)std::min<size_t>(1024, (n + 255) / 256), 256, 0, s, mask, n);
-        launch_kernel(lists_to_mask_kernel, 1024, 256, 0, s, offsets, lists, T, E, W,
-                                                  reinterpret_cast<unsigned long long*>(mask));
-    }
-    launch_counts_from_mask(mask, T, E, group_off, colmask, s);
+    // by bytes where there is room for them and the counts are all that is wanted besides the mask words
+    uint8_t* bytes = !colmask && group_off && (size_t)E * Tp <= scratch_bytes ? (uint8_t*)scratch : nullptr;
+    // Up to 8 MB of bytes that way costs no more at any density, and looking at the number of positions in three
+    // launches costs 0.5 to 1 us (300 tokens x 256 experts of 64 77.3 us a call, 78.0 with the look).
+    const bool choose = !bytes || (size_t)E * Tp > ((size_t)8 << 20);
+    const long long bits_max = (long long)T * E / 192;
+    const size_t n_mask = (size_t)T * W, n_bytes = (size_t)E * Tp / 8, n = bytes ? n_bytes : n_mask;
+    const int clear_grid = (int)std::min<size_t>(1024, (n + 255) / 256), finish_grid = div_up(div_up(T, kGroup) * W, 4);
+    const dim3 scatter_grid(std::max(1, std::min(div_up(T, 256), 1024 / E)), E);
+    LaunchTimer tm(kSlotListsToMask, s);
+    auto go = [&](auto choose_c) {
+        constexpr bool kChoose = decltype(choose_c)::value;
+        launch_kernel(lists_clear_kernel<kChoose>, clear_grid, 256, 0, s, offsets, T, E, mask, n_mask, (uint64_t*)bytes, n_bytes,
+                      bits_max);
+        launch_kernel(lists_scatter_kernel<kChoose>, scatter_grid, 256, 0, s, offsets, lists, T, E, W, Tp, bytes,
+                      reinterpret_cast<unsigned long long*>(mask), bits_max);
+        if (bytes)
+            launch_kernel(lists_finish_kernel<kChoose>, finish_grid, 256, 0, s, offsets, bytes, T, E, W, Tp, mask, group_off,
+                          bits_max);
+        else
+            launch_counts_from_mask(mask, T, E, group_off, colmask, s);
+    };
+    if (choose) go(std::true_type{});
+    else go(std::false_type{});
 }
 
 void launch_mask_topk(const float* scores, int T, int E, int k, uint64_t* mask,

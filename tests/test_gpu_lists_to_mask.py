@@ -44,3 +44,34 @@ def test_lists_with_noise(oracle, T, E, p):
     idx = np.unique(np.concatenate([[0, 63, 64, T - 1], rng.integers(0, T, 20)]))
     ref = oracle_ffn(oracle, layer, x[idx], mask[idx])
     assert tokenwise_rel_err(B.from_device(y, cfg.dtype)[idx], ref) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("T,E,hot", [(4100, 2048, False), (4100, 2048, True), (70001, 130, False), (1000, 600, True), (2100, 4000, True)])
+def test_by_bits_and_by_bytes(oracle, T, E, hot):
+    """From 8 MB of bytes on (the first three sizes, the last), T E / 192 positions are the most that become mask words by
+    atomics; with a duplicate more the same selection goes by bytes.  hot: one expert has every token."""
+    import torch
+    from paper_2310_04361_amd import binding as B
+    n = T * E // 192
+    cfg = wl.Config("lists_rule", T, 256, E, 8, 64, False, "gelu_erf", "bf16", (0.5,), ffn_bias=True)
+    print(f"lists by bits and by bytes T={T} E={E} n={n} hot={hot}", flush=True)
+    layer, x = wl.make_layer(cfg, 3), wl.make_input(cfg, 3)
+    rng = np.random.default_rng(5)
+    mask = np.zeros(T * E, np.uint8)
+    if hot:
+        mask[np.arange(T) * E + E - 2] = 1
+    free = np.flatnonzero(mask == 0)
+    mask[rng.choice(free, n - int(mask.sum()), replace=False)] = 1
+    mask = mask.reshape(T, E)
+    offsets, lists = lists_from_mask(mask, shuffle_seed=2)
+    assert offsets[-1] == n
+    e = int(np.flatnonzero(mask.any(axis=0))[0])  # the duplicate: the first expert that has a token
+    more, moff = np.insert(lists, offsets[e], lists[offsets[e]]), offsets + (np.arange(E + 1) > e)
+    L, xd = B.Layer(layer, cfg.dtype), B.to_device(x, cfg.dtype)
+    dev = lambda a: torch.from_numpy(np.asarray(a, np.int32)).cuda()
+    y = B.dmoe_expert_ffn(L, xd, dev(offsets), dev(lists))
+    y2 = B.dmoe_expert_ffn(L, xd, dev(moff), dev(more))
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+    idx = np.unique(np.concatenate([np.arange(0, T, max(T // 300, 1)), [63, 64, T - 2, T - 1]]))
+    assert tokenwise_rel_err(B.from_device(y, cfg.dtype)[idx], oracle_ffn(oracle, layer, x[idx], mask[idx])) <= TOL["bf16"]
