@@ -143,9 +143,12 @@ int32_t dmoe_packed_bytes(const dmoe_layer *layer, size_t *out_bytes);
 /*
  * One-time re-layout of the weights for the MFMA kernels (bf16 layers): writes, into `packed`
  * (device, 256-byte aligned, dmoe_packed_bytes() large), the expert matrices (w_up, w_gate, w_down
- * -- the latter in two orders) and the router matrices (r_w1, r_w2) as 1 KiB blocks in the
- * register order of the matrix-core operands, the expert size rounded up to a multiple of 32
- * with zero neurons.  The layout is private to the library.  Reads the layer's weight pointers;
+ * -- the latter in two orders, or three where the kernel for sparse selections can be taken: experts of
+ * 33 to 128 neurons, and 625 and more of up to 8, but not fully 8-bit layers) and the router matrices
+ * (r_w1, r_w2) as 1 KiB blocks in the register order of the matrix-core operands, the expert size
+ * rounded up to a multiple of 32 (the third order: of 8 or 16) with zero neurons; 8-bit weights also as bytes
+ * for the small batches.  256 gated experts of 64, d = 2048, bf16: 337 MB for 201 MB of weights.
+ * The layout is private to the library.  Reads the layer's weight pointers;
  * asynchronous on `stream`.  Put the pointer into layer->packed afterwards and keep the buffer
  * (and the original weights) alive as long as the layer is used.  For fp32 layers this is a
  * no-op that accepts packed == NULL.

@@ -336,6 +336,7 @@ void launch_down_bf16(const dmoe_layer& L, int T, const int32_t* item_start,
                       hipStream_t s);
 bool down_bf16_wide(const dmoe_layer& L, int T);  // workgroups of 384 columns
 double down_walk_us(const dmoe_layer& L, int T);  // estimate of one workgroup's walk over the experts
+double down_walk_us(const dmoe_layer& L);         // ... where it is not divided
 void launch_pack_down_quad(const dmoe_layer& L, void* packed, hipStream_t s);
 long long down_quad_max_pairs(const dmoe_layer& L, int T);
 void launch_down_quad(const dmoe_layer& L, int T, const int32_t* item_start, const int32_t* group_off,

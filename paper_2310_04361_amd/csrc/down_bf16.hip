@@ -588,6 +588,7 @@ int down_parts(const dmoe_layer& L, int T) {
     return best;
 }
 
+double down_walk_us(const dmoe_layer& L) { return down_walk(L).us; }
 double down_walk_us(const dmoe_layer& L, int T) {
     const DownWalk dw = down_walk(L);
     return dw.us * down_part_trips(dw.trips, down_parts(L, T)) / dw.trips;

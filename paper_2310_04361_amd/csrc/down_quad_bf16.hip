@@ -386,9 +386,14 @@ double rmw_density(const dmoe_layer& L, int T) {
 
 }  // namespace
 
+// Walks of the dense kernel from which this one is worth a launch that may be for nothing (us, estimated): 256 gated experts
+// of 64 at 1200 tokens, a walk of 55, 7 % density: 59 against 70 us; 600 tokens, 30: 36 against 48.
+constexpr double kQuadMinWalk = 50.0;
+
 size_t down_quad_w_bytes(const dmoe_layer& L) {
     const int PG = quad_pieces(L.expert_size);
     if (L.dtype != DMOE_BF16 || down_x8_shape(L) || PG == 0) return 0;
+    if (PG == 1 && down_walk_us(L) < kQuadMinWalk) return 0;  // never launched (down_quad_max_pairs)
     const QuadShape q = quad_shape(PG);
     return (size_t)div_up(div_up(L.n_experts, 4), q.QS) * q.SPQ * (L.d_model / 32) * q.KS * 2048;
 }
@@ -408,16 +413,14 @@ void launch_pack_down_quad(const dmoe_layer& L, void* packed, hipStream_t s) {
 // experts of 128 at 50432 tokens 142 against 146 at 6.5 %, 148 against 147 at 8 %.
 long long down_quad_max_pairs(const dmoe_layer& L, int T) {
     const int PG = quad_pieces(L.expert_size);
-    if (PG == 0 || down_x8_shape(L)) return 0;
+    if (!down_quad_w_bytes(L)) return 0;
     double density = PG == 1 ? 0.14 : PG == 16 ? 0.075 : 0.11;
     const bool divided = down_parts(L, T) > 1;
     if (down_bf16_wide(L, T)) {
         // the dense kernel has a shape that fills the chip once, this one does not (16384 tokens x 512 experts
         // of 6, d = 768, 11 %: 88 us against 72)
         density = PG == 1 ? 0.0 : rmw_density(L, T);
-    } else if ((PG == 1 || divided) && down_walk_us(L, T) < 50.0) {
-        // short walks: too little to gain for a launch that may be for nothing (256 gated experts of 64 at 1200
-        // tokens, a walk of 55 us: 7 % density 59 against 70 us; 600 tokens, 30 us: 36 against 48)
+    } else if ((PG == 1 || divided) && down_walk_us(L, T) < kQuadMinWalk) {
         density = 0.0;
     }
     return (long long)(density * (double)T * (double)L.n_experts);

@@ -65,6 +65,28 @@ def test_workspace_sizes(lib):
     assert lib.dmoe_packed_bytes(ctypes.byref(L), ctypes.byref(n)) == B.DMOE_OK and n.value == 0
 
 
+@pytest.mark.parametrize("few,more,m,gated,order", [
+    (624, 625, 8, 1, 2 * 640 * 8 * 512),     # one piece of eight neurons: 40 stages of 16 experts
+    (624, 625, 3, 0, 2 * 640 * 8 * 512),
+    (624, 625, 16, 0, 0), (624, 625, 24, 0, 0),  # no such kernel for 9 to 32 neurons
+])
+def test_packed_third_order_of_the_down_matrices(lib, few, more, m, gated, order):
+    """Only layers for which the sparse down-projection can be launched carry its operands."""
+    d, n = 512, ctypes.c_size_t(0)
+
+    def packed(E):
+        L = _layer(dtype=B.DMOE_BF16, d_model=d, n_experts=E, expert_size=m, gated=gated, w_gate=0x1000 if gated else None)
+        assert lib.dmoe_packed_bytes(ctypes.byref(L), ctypes.byref(n)) == B.DMOE_OK
+        return n.value
+
+    def others(E):  # 32-neuron operands (down twice, one expert more in one of them), a one-tile one, the router
+        tiny = 2 * E * 16 * d if m <= (8 if gated else 16) else 0
+        return 2 * d * 32 * ((4 if gated else 3) * E + 1) + tiny + 2 * 32 * d + 2 * ((E + 15) // 16 * 16) * 32
+
+    assert packed(few) == others(few)
+    assert packed(more) == others(more) + order
+
+
 def test_workspace_never_shrinks_as_tokens_grow(lib):
     """A caller may size the workspace once for its largest batch: the requirement must be
     monotone in n_tokens, also across the token counts where the launch shapes change (small-token
