@@ -24,6 +24,24 @@ def selection(T, E, p, dense_every, seed):
     return mask.astype(np.uint8)
 
 
+def working_kernel(B, call):
+    """Both kernels are launched and the pair count on the device decides which one works: the one that takes the time
+    (the other ends at once, 4 us against 9 and more; medians of five calls)."""
+    us = {"expert_down": [], "expert_down_sparse": []}
+    for _ in range(5):
+        B.timing(True)
+        call()
+        read = B.timing_read()
+        B.timing(False)
+        for k in us:
+            assert read[k][0] == 1
+            us[k].append(read[k][1])
+    med = {k: float(np.median(v)) for k, v in us.items()}
+    first, second = sorted(med, key=med.get, reverse=True)
+    assert med[first] > 1.5 * med[second], med
+    return first
+
+
 @pytest.mark.parametrize("T,d,E,m,gated,p,dense_every", [
     # undivided walks (65 chunks x 2 slices of 256 columns), H rows of 64: one expert to three mask words
     (8300, 512, 1, 64, True, 0.09, 0), (8300, 512, 3, 57, True, 0.05, 40), (8300, 512, 5, 64, True, 0.05, 40),
@@ -46,15 +64,12 @@ def test_sparse_selections(oracle, T, d, E, m, gated, p, dense_every):
     print(f"T={T} d={d} E={E} m={m} gated={gated} p={p} dense_every={dense_every}", flush=True)
     layer, x = wl.make_layer(cfg, 11), wl.make_input(cfg, 11)
     mask = selection(T, E, p, dense_every, 12)
-    assert mask.mean() < 0.135 if m <= 8 else mask.mean() < 0.105  # the kernel's range
+    assert mask.mean() <= (0.14 if m <= 8 else 0.11 if m <= 64 else 0.075)  # the kernel's range
     offsets, lists = lists_from_mask(mask)
     L, xd = B.Layer(layer, cfg.dtype), B.to_device(x, cfg.dtype)
     off_d, list_d = torch.from_numpy(offsets).cuda(), torch.from_numpy(np.resize(lists, max(len(lists), 1))).cuda()
-    B.timing(True)
     y = B.dmoe_expert_ffn(L, xd, off_d, list_d)
-    launched = B.timing_read()["expert_down_sparse"][0]
-    B.timing(False)
-    assert launched == 1
+    assert working_kernel(B, lambda: B.dmoe_expert_ffn(L, xd, off_d, list_d)) == "expert_down_sparse"
     assert torch.equal(B.dmoe_expert_ffn(L, xd, off_d, list_d), y)  # run-to-run reproducible
     got = B.from_device(y, cfg.dtype)
     assert np.isfinite(got).all()
@@ -67,3 +82,38 @@ def test_sparse_selections(oracle, T, d, E, m, gated, p, dense_every):
     zero = np.abs(ref).max(axis=1) == 0
     assert (np.abs(got[idx][zero]) == 0).all()
     assert tokenwise_rel_err(got[idx][~zero], ref[~zero]) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("T,d,E,m,gated,limits", [
+    (8300, 512, 256, 64, True, (0.018, 0.11)), (8300, 512, 64, 48, True, (0.018, 0.11)),
+    (8300, 512, 96, 128, False, (0.008, 0.075)), (8300, 512, 1200, 8, True, (0.14,)),
+    (1200, 2048, 256, 64, True, (0.11,)),  # a divided walk
+    # 384-column workgroups of the dense kernel: pairs up to 3 %, the dense kernel above
+    (11000, 768, 24, 64, False, (0.03,)), (11000, 768, 24, 128, False, (0.03,)),
+])
+def test_limits_of_the_pair_count(oracle, T, d, E, m, gated, limits):
+    """The last number of pairs that a way of working takes and the first that it leaves to the next: pairs, then quads
+    (one kernel), then the dense kernel."""
+    import torch
+    from paper_2310_04361_amd import binding as B
+    cfg = wl.Config("limits", T, d, E, m, 64, gated, "gelu_tanh" if gated else "gelu_erf", "bf16", (0.5,), ffn_bias=not gated)
+    layer, x = wl.make_layer(cfg, 13), wl.make_input(cfg, 13)
+    L, xd = B.Layer(layer, cfg.dtype), B.to_device(x, cfg.dtype)
+    order = np.random.default_rng(14).permutation(T * E)
+    idx = np.unique(np.concatenate([[0, 63, 64, 127, 128, T - 1], np.random.default_rng(1).integers(0, T, 60)]))
+    for i, limit in enumerate(limits):
+        for more in (0, 1):
+            n = int(limit * float(T) * float(E)) + more
+            print(f"limits T={T} d={d} E={E} m={m} pairs={n}", flush=True)
+            mask = np.zeros(T * E, np.uint8)
+            mask[order[:n]] = 1
+            mask = mask.reshape(T, E)
+            offsets, lists = lists_from_mask(mask)
+            off_d, list_d = torch.from_numpy(offsets).cuda(), torch.from_numpy(lists).cuda()
+            y = B.dmoe_expert_ffn(L, xd, off_d, list_d)
+            dense = i == len(limits) - 1 and more
+            assert working_kernel(B, lambda: B.dmoe_expert_ffn(L, xd, off_d, list_d)) == ("expert_down" if dense else "expert_down_sparse")
+            got, ref = B.from_device(y, cfg.dtype)[idx], oracle_ffn(oracle, layer, x[idx], mask[idx])
+            some = np.abs(ref).max(axis=1) > 0
+            assert (got[~some] == 0).all()
+            assert tokenwise_rel_err(got[some], ref[some]) <= TOL["bf16"]
