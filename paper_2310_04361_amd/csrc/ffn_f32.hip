@@ -299,8 +299,12 @@ __global__ __launch_bounds__(kLayerThreads) void layer_f32_kernel(
 }
 
 // Where it is taken: rows of up to 1024 values (x, a share of y and a row of each matrix in registers), and
-// the wavefronts' shares with the scores in the 64 KB of LDS that need no attribute.  Wider layers keep
-// the kernels that hold x and y in LDS.
+// the wavefronts' shares with the scores in the 64 KB of LDS that need no attribute, which ends it somewhat earlier:
+// 16 d + 2 E + d_h <= 16384 with the gate inside, 16 d + E <= 16384 without.  Wider layers keep the kernels that hold
+// x and y in LDS.  Three launches / one, us: d = 960, 16 experts of 16, 1 / 128 / 2048 tokens 45 / 64 / 157 and 12 / 20 /
+// 115, 64 of 32 135 / 296 / 788 and 40 / 69 / 594; d = 512, 128 of 8 86 / 130 / 245 and 20 / 27 / 110; d = 768, 16 of 16, 2048
+// tokens 135 and 120, the closest of 45.  Experts alone (top-k, given lists), 512 tokens: d = 960, 128 of 8, 4 of them per
+// token 182 and 176, the closest of 45; 64 of 32, 30 % 319 and 200.
 constexpr int kF32FusedMaxD = 1024;
 
 size_t layer_f32_lds(const dmoe_layer& L, bool gate) {

@@ -92,14 +92,6 @@ __device__ __forceinline__ float e4m3_value(uint32_t b) {
     return (b & 0x80u) ? -mag : mag;
 }
 
-// Element `flat` of expert e's matrix `which` (0 up, 1 gate, 2 down) as a bf16 number: the stored
-// bf16 value, or scale * e4m3(byte) for 8-bit weights (exact: the scales are powers of two).
-__device__ __forceinline__ __bf16 expert_weight(const void* w, const float* scales, int fp8, int which,
-                                               int e, size_t flat) {
-    if (!fp8) return static_cast<const __bf16*>(w)[flat];
-    return (__bf16)(scales[3 * e + which] * e4m3_value(static_cast<const uint8_t*>(w)[flat]));
-}
-
 // Eight E4M3 bytes (one lane's share of a weight fragment) -> eight bf16 numbers, exactly, with
 // the hardware converter (two bytes per instruction) and a byte permute that keeps the upper
 // halves of the fp32 results.

@@ -16,8 +16,8 @@ typedef __bf16 bf16x8_any __attribute__((ext_vector_type(8), aligned(2)));
 typedef uint8_t u8x8 __attribute__((ext_vector_type(8)));
 typedef uint8_t u8x8_any __attribute__((ext_vector_type(8), aligned(1)));
 
-// Eight consecutive elements from `flat` on of expert e's matrix `which`: as bf16 numbers (8-bit weights scaled
-// out, as expert_weight does), or the raw bytes of 8-bit weights.
+// Eight consecutive elements from `flat` on of expert e's matrix `which` (0 up, 1 gate, 2 down): as bf16 numbers (8-bit
+// weights as scale * e4m3(byte), exact: the scales are powers of two), or the raw bytes of 8-bit weights.
 template <typename OUT>
 struct Packed8;
 template <>

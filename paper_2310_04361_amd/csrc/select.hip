@@ -583,10 +583,12 @@ __global__ __launch_bounds__(256) void fill_lists_kernel(
     // the experts), or, by_experts, over the items of the XCD's own share of the experts (each
     // XCD goes over all the tokens, but no two read the same weights).
     // Where the workgroups have three items and more each, three neighbouring items of an expert count as one of three
-    // times the size: they run side by side and share the weights.  4096 tokens x 256 gated experts of 64, d = 2048,
-    // 3.2 items per workgroup: 0.87 GB from beyond the L2 instead of 0.97, 8-bit whole call 253.9 -> 252.1 us, bf16 the
-    // same.  With 1.6 to 2.2 items the last ones run longer (pairs: 94 us instead of 90), and where all XCDs have all the
-    // experts (50432 tokens x 24 of 128) pairs were 1 % slower.
+    // times the size: they run side by side and share the weights.  Up-projection, one by one / in threes: 512 gated
+    // experts of 64, d = 1024, 4096 / 8192 tokens 189 / 182 and 228 / 219 us, 8-bit 125 / 119 and 147 / 139; 400 experts of 128,
+    // d = 2048, 4096 tokens 334 / 322; 256 gated experts of 64, d = 2048, 4096 tokens 196 / 194 (8-bit 111 / 111) with 1.00 GB
+    // from beyond the L2 instead of 1.05 (8-bit 0.48 instead of 0.56); 25 more sizes within 2 % either way.  The order itself
+    // takes 0.3 to 0.7 us longer to work out.  With 1.6 to 2.2 items the last ones run longer (pairs: 94 us instead
+    // of 90), and where all XCDs have all the experts (50432 tokens x 24 of 128) pairs were 1 % slower.
     if (worder) {
         const int N = s_item[E], run = by_experts && N >= 3 * 512 ? 3 : 1;
         auto expert_of = [&](int n) {  // the last e with s_item[e] <= n

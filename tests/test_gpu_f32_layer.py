@@ -1,6 +1,7 @@
 """The one-launch fp32 layer at the edges of its variants: rows that end inside, at and just beyond a
 register column, more experts than one mask word, neuron counts that leave part of a wavefront's rows
-empty, a single expert, and the first width that takes the kernels for wide layers instead."""
+empty, a single expert, and the last widths that fit (16 d + 2 E + d_h <= 16384, 16 d + E without the gate) with the
+first that take the kernels for wide layers instead, for the whole layer and for its experts alone."""
 import numpy as np
 import pytest
 
@@ -15,6 +16,7 @@ pytestmark = pytest.mark.gpu
     (17, 65, 65, 3, 64, False, 0.7), (9, 128, 64, 7, 65, True, 0.3), (9, 129, 63, 7, 130, False, 0.0),
     (4, 256, 130, 5, 16, True, 1.0), (4, 257, 20, 33, 32, False, 0.3), (3, 512, 9, 70, 40, True, 0.2),
     (3, 513, 300, 2, 24, False, 0.6), (2, 960, 12, 9, 48, False, 0.0), (2, 1025, 6, 11, 20, True, 0.4),
+    (2, 1020, 16, 9, 32, False, 0.4), (2, 1021, 16, 9, 32, True, 0.4), (2, 1023, 16, 5, 32, False, 0.4), (2, 1024, 1, 5, 32, False, 0.4),
 ])
 def test_fp32_layer_edges(oracle, T, d, E, m, d_h, gated, tau):
     import torch
