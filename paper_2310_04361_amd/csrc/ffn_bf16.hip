@@ -547,7 +547,7 @@ __global__ __launch_bounds__(256) void up_tiny_kernel(
 // The order of the items (select.hip) keeps the traffic beyond L2 down: 4096 tokens x 256 gated
 // experts of 64, d = 2048, 37 % density: 1.84 -> 0.82 GB from beyond L2 and, with the 32x32x16 MFMA (half
 // the instructions of the 16x16x32 one), 276 -> 240 us, both on one card in turn (224 to 253 over
-// cards and clocks), before the interleaving above, which lets the workgroups of an XCD drift apart: 1.00 GB since; 24 x 128 experts, half of them per token, at 50432 tokens: 210 -> 204 us.  Built and
+// cards and clocks), before the interleaving above, which lets the workgroups of an XCD drift apart: 0.97 to 1.00 GB since; 24 x 128 experts, half of them per token, at 50432 tokens: 210 -> 204 us.  Built and
 // slower: x rows by LDS-DMA and the weights straight to registers, with a 2 x 2 split over the
 // wavefronts (236 us against 220 on the card of that day: LDS instructions down to a sixth, but more bytes and more
 // drift between the workgroups, 0.96 GB).
