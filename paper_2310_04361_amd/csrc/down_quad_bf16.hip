@@ -96,16 +96,21 @@ __global__ __launch_bounds__(64 * kDqWaves, 2) void down_quad_kernel(
     static_assert((kDqTrip * KS / PS) % 2 == 0, "register sets of the codes");
     extern __shared__ __attribute__((aligned(16))) char img[];  // [kDqTrip][kBuf]
     if (offsets[E] > max_pairs) return;  // dense enough for down_bf16_kernel
-    if constexpr (PG > 4) {
-        if (offsets[E] <= max_rmw) {  // so sparse that work in proportion to the pairs is less
-            down_rmw_body<PG == 16 ? 4 : 2>(w2f, b_down, item_start, group_off, alist, H, y, T, d, E, NG, rows_per_item, img);
-            return;
-        }
-    }
     const int NS = d / kDqCols;
     const DownTile tile = down_tile(blockIdx.x, NS, (T + kDqTokens - 1) / kDqTokens, parts, xs);
     const int t_base = tile.chunk * kDqTokens;
     if (t_base >= T || tile.part >= parts) return;
+    if constexpr (PG > 4) {
+        if (offsets[E] <= max_rmw) {  // so sparse that work in proportion to the pairs is less
+            static_assert(kChunk == kDqTokens && kDownCols == kDqCols && kDownWaves == kDqWaves, "the same tiles");
+            constexpr int KS = PG == 16 ? 4 : 2, RN = 32 * KS;
+            const int chunk = tile.chunk, slice = tile.slice;
+            const __bf16* Hf = H;
+            char* smem = img;
+#include "down_rmw_walk.inc"
+            return;
+        }
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, c = lane & 31;

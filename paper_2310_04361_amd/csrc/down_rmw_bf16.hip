@@ -12,7 +12,13 @@ __global__ __launch_bounds__(kDownWaves * 64) void down_rmw_bf16_kernel(
     const int32_t* __restrict__ group_off, const int32_t* __restrict__ alist, const __bf16* __restrict__ Hf,
     __bf16* __restrict__ y, int T, int d, int E, int NG, int rows_per_item) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    down_rmw_body<KS, RN>(w2f, b_down, item_start, group_off, alist, Hf, y, T, d, E, NG, rows_per_item, smem);
+    // The slices of one chunk share its H rows and token lists: keep them on one XCD (workgroups
+    // are dealt round-robin to the 8 XCDs) and next to each other in launch order.
+    const int NS = d / kDownCols;
+    const int k_in_xcd = blockIdx.x >> 3;
+    const int chunk = (k_in_xcd / NS) * 8 + (blockIdx.x & 7), slice = k_in_xcd % NS;
+    if (chunk * kChunk >= T) return;  // the grid is rounded up to whole groups of 8 chunks
+#include "down_rmw_walk.inc"
 }
 
 template <int KS, int RN>
