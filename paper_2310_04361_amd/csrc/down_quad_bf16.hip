@@ -43,6 +43,8 @@ typedef __attribute__((address_space(3))) bf16x8 LdsBf16x8;
 
 constexpr int kDqTokens = 128, kDqTiles = 4;  // 4 tiles of 32 tokens = 2 select groups of 64
 constexpr int kDqWaves = 8, kDqCols = 32 * kDqWaves;
+// A tile of the pair walk in units of one of its rows (fits the walk's times over 24 to 699 experts, 0.4 to 4 %)
+constexpr int kTileCost64 = 9, kTileCost128 = 200;
 constexpr int kDqTrip = 4;                    // stages per loop trip = LDS buffers
 constexpr int kRawBuffer = 0x00020000;        // offsets from num_records on read as zero and move no data
 
@@ -79,6 +81,36 @@ struct QuadMap {
     }
 };
 
+// Whether the walk over the pairs of a chunk (down_rmw.h) is the shorter one (uniform).  It costs tile_cost for each tile of up to 32
+// rows of an expert and 1 for each row; limit: of four chunks, below 0: none.  If every pair were a tile of its own and that is still within
+// the limit, nothing is counted; else four chunks spread over the batch are, by every workgroup alike: where chunks decided for
+// themselves and some took the pairs, others the quads, both lost the weights that they share (50432 tokens x 100
+// experts of 128, d = 768, 0.8 %: all pairs 399 us, all quads 427, mixed 500).
+__device__ __forceinline__ bool pairs_are_less(int pairs, const int32_t* group_off, int T, int E, int NG, int tile_cost, int limit) {
+    __shared__ int s_cost[kDqWaves];
+    const int tid = threadIdx.x, n_chunks = (T + kChunk - 1) / kChunk;
+    if (limit < 0 || 4ll * pairs * (tile_cost + 1) <= (long long)limit * n_chunks) return true;
+    int cost = 0;
+    for (int e = tid; e < E; e += 64 * kDqWaves) {
+        int n[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int g = (n_chunks * (2 * i + 1) >> 3) * kChunkGroups;
+            n[i] = group_off[(size_t)min(g + kChunkGroups, NG) * E + e] - group_off[(size_t)g * E + e];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cost += ((n[i] + 31) >> 5) * tile_cost + n[i];
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) cost += __shfl_xor(cost, off, 64);
+    if ((tid & 63) == 0) s_cost[tid >> 6] = cost;
+    __syncthreads();
+    int all = 0;
+#pragma unroll
+    for (int w = 0; w < kDqWaves; ++w) all += s_cost[w];
+    return all <= limit;
+}
+
 // R: sets of weights (a k-step each) in flight.
 template <int PG, int R>
 __global__ __launch_bounds__(64 * kDqWaves, 2) void down_quad_kernel(
@@ -86,7 +118,7 @@ __global__ __launch_bounds__(64 * kDqWaves, 2) void down_quad_kernel(
     const int32_t* __restrict__ item_start, const int32_t* __restrict__ group_off, const int32_t* __restrict__ alist,
     const uint64_t* __restrict__ mask, const int32_t* __restrict__ offsets, const __bf16* __restrict__ H,
     __bf16* __restrict__ y, int T, int d, int E, int NG, int W, int rows_per_item, int row_shift, uint32_t w_bytes,
-    uint32_t h_bytes, long long max_pairs, long long max_rmw, int parts, int xs, float* __restrict__ partial) {
+    uint32_t h_bytes, long long max_pairs, long long max_rmw, int walk_limit, int parts, int xs, float* __restrict__ partial) {
     constexpr QuadShape Q = quad_shape(PG);
     constexpr int QS = Q.QS, PS = Q.PS, KS = Q.KS, SPQ = Q.SPQ;
     constexpr int TPB = kDqTrip * SPQ / QS;             // loop trips per batch of 64 experts
@@ -101,7 +133,8 @@ __global__ __launch_bounds__(64 * kDqWaves, 2) void down_quad_kernel(
     const int t_base = tile.chunk * kDqTokens;
     if (t_base >= T || tile.part >= parts) return;
     if constexpr (PG > 4) {
-        if (offsets[E] <= max_rmw) {  // so sparse that work in proportion to the pairs is less
+        const int pairs = offsets[E];
+        if (pairs <= max_rmw && pairs_are_less(pairs, group_off, T, E, NG, PG == 16 ? kTileCost128 : kTileCost64, walk_limit)) {
             static_assert(kChunk == kDqTokens && kDownCols == kDqCols && kDownWaves == kDqWaves, "the same tiles");
             constexpr int KS = PG == 16 ? 4 : 2, RN = 32 * KS;
             const int chunk = tile.chunk, slice = tile.slice;
@@ -355,7 +388,7 @@ __global__ __launch_bounds__(64 * kDqWaves, 2) void down_quad_kernel(
 template <int PG, int R>
 void launch_quad_t(const dmoe_layer& L, int T, const int32_t* item_start, const int32_t* group_off,
                    const int32_t* alist, const uint64_t* mask, const int32_t* offsets, const void* H, void* y,
-                   long long max_pairs, long long max_rmw, float* partial, hipStream_t s) {
+                   long long max_pairs, long long max_rmw, int walk_limit, float* partial, hipStream_t s) {
     constexpr QuadShape Q = quad_shape(PG);
     constexpr size_t lds = std::max((size_t)kDqTrip * (2 * Q.KS * kDqTiles * 1024 + Q.QS * 512), PG > 4 ? kDownLds : 0);
     static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
@@ -376,17 +409,31 @@ void launch_quad_t(const dmoe_layer& L, int T, const int32_t* item_start, const 
                   (const __bf16*)(pk + P.w2s), (const __bf16*)(pk + P.w2f), (const __bf16*)L.b_down, item_start, group_off,
                   alist, mask, offsets, (const __bf16*)H, (__bf16*)y, T, L.d_model, L.n_experts, div_up(T, kGroup),
                   div_up(L.n_experts, 64), up_rows_bf16(L), row_shift, (uint32_t)down_quad_w_bytes(L),
-                  (uint32_t)(h_fragments(L, T) * 16 * row_bytes), max_pairs, max_rmw, parts, xs, partial);
+                  (uint32_t)(h_fragments(L, T) * 16 * row_bytes), max_pairs, max_rmw, walk_limit, parts, xs, partial);
 }
 
-// Density up to which work in proportion to the pairs (down_rmw.h) is less, where the walk is not divided:
-// 4096 tokens x 256 gated experts of 64 at 1.2 / 1.9 / 2.6 %: 109 / 124 / 135 us against 122 / 123 / 125; 50432
-// tokens x 24 experts of 128 at 0.2 / 1 / 2 %: 83 / 147 / 172 against 129 / 130 / 133.
+// Density up to which the walk over the pairs (down_rmw.h) is a choice, where the walk over the experts is not divided.  Against
+// the dense kernel alone (384 columns) pairs decide: 3 %.  Against the quads the tiles that they make decide, on the device
+// (pair_walk_limit): how many there are depends on how evenly the pairs fall on the experts.  Experts of 64, uniform
+// selections of 1.8 and 2.4 %, pairs / quads: 4096 tokens x 256, d = 2048 142 / 121 and 152 / 123 us; a router's selection of
+// 2.7 %, 4254 tokens x 699, d = 1280: 215 / 354; of 1.3 %, 4137 tokens x 1030 experts of 96: 397 / 1100.
+constexpr double kPairDensity = 0.03;
 double rmw_density(const dmoe_layer& L, int T) {
+    if (quad_pieces(L.expert_size) == 1 || down_parts(L, T) > 1) return 0.0;
+    return kPairDensity;
+}
+
+// Cost of four chunks (pairs_are_less) up to which the pairs are taken, -1: whatever it is.  The quads take a time that is nearly proportional to
+// the experts, the longer for each the more their weights exceed the L2s.  Uniform selections, density of equal times: rows of 64
+// 9000 tokens x 500, d = 512 (33 MB of weights) 0.85 %, 4096 x 256, d = 2048 (67 MB) 1.2 %, 4254 x 699, d = 1280 (114 MB)
+// 1.8 %; rows of 128 50432 x 24, d = 768 (5 MB) 0.8 %, 4096 x 256, d = 2048 (134 MB) 1.3 %, 4254 x 699, d = 1280 (179 MB) 1.8 %.
+int pair_walk_limit(const dmoe_layer& L, int T) {
+    if (down_bf16_wide(L, T)) return -1;
     const int PG = quad_pieces(L.expert_size);
-    if (PG == 1 || down_parts(L, T) > 1) return 0.0;
-    if (down_bf16_wide(L, T)) return 0.03;  // against the dense kernel alone
-    return PG == 16 ? 0.008 : 0.018;
+    const double mb = 2e-6 * L.n_experts * m_pad_of(L.expert_size) * L.d_model;
+    const double per_expert = PG == 16 ? kTileCost128 * std::min(0.9, 0.62 + mb / 640.0)
+                                       : std::min(10.4, 7.2 + mb / 36.0) * (PG == 6 ? 0.7 : 1.0);  // (6 pieces: fewer products)
+    return (int)(4.0 * per_expert * L.n_experts);
 }
 
 }  // namespace
@@ -436,9 +483,10 @@ void launch_down_quad(const dmoe_layer& L, int T, const int32_t* item_start, con
                       float* partial, long long max_pairs, hipStream_t s) {
     LaunchTimer tm(kSlotDownRmw, s);
     const double rmw = rmw_density(L, T);
+    const int walk_limit = pair_walk_limit(L, T);
     const long long max_rmw = rmw > 0.0 ? (long long)(rmw * (double)T * (double)L.n_experts) : -1;
 #define DMOE_QUAD(PG_, R_) \
-    launch_quad_t<PG_, R_>(L, T, item_start, group_off, alist, mask, offsets, H, y, max_pairs, max_rmw, partial, s)
+    launch_quad_t<PG_, R_>(L, T, item_start, group_off, alist, mask, offsets, H, y, max_pairs, max_rmw, walk_limit, partial, s)
     switch (quad_pieces(L.expert_size)) {
     case 1: DMOE_QUAD(1, 8); break;
     case 6: DMOE_QUAD(6, 6); break;

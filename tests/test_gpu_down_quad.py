@@ -85,8 +85,8 @@ def test_sparse_selections(oracle, T, d, E, m, gated, p, dense_every):
 
 
 @pytest.mark.parametrize("T,d,E,m,gated,limits", [
-    (8300, 512, 256, 64, True, (0.018, 0.11)), (8300, 512, 64, 48, True, (0.018, 0.11)),
-    (8300, 512, 96, 128, False, (0.008, 0.075)), (8300, 512, 1200, 8, True, (0.14,)),
+    (8300, 512, 256, 64, True, (0.03, 0.11)), (8300, 512, 64, 48, True, (0.03, 0.11)),
+    (8300, 512, 96, 128, False, (0.03, 0.075)), (8300, 512, 1200, 8, True, (0.14,)),
     (1200, 2048, 256, 64, True, (0.11,)),  # a divided walk
     # 384-column workgroups of the dense kernel: pairs up to 3 %, the dense kernel above
     (11000, 768, 24, 64, False, (0.03,)), (11000, 768, 24, 128, False, (0.03,)),
@@ -117,3 +117,34 @@ def test_limits_of_the_pair_count(oracle, T, d, E, m, gated, limits):
             some = np.abs(ref).max(axis=1) > 0
             assert (got[~some] == 0).all()
             assert tokenwise_rel_err(got[some], ref[some]) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("T,d,E,m,gated", [
+    (8300, 512, 96, 64, True), (8300, 512, 300, 48, True), (8300, 512, 96, 128, False), (4300, 1280, 699, 64, True),
+    (50432, 768, 24, 100, False),
+])
+def test_even_and_uneven_selections_of_the_same_size(oracle, T, d, E, m, gated):
+    """Up to 3 % the tiles that the pairs make decide between pairs and quads: as many pairs spread evenly (a tile for
+    nearly every expert and chunk), on a few experts only, and in a part of the batch only."""
+    import torch
+    from paper_2310_04361_amd import binding as B
+    cfg = wl.Config("even", T, d, E, m, 64, gated, "gelu_tanh" if gated else "gelu_erf", "bf16", (0.5,), ffn_bias=not gated)
+    layer, x = wl.make_layer(cfg, 13), wl.make_input(cfg, 13)
+    L, xd = B.Layer(layer, cfg.dtype), B.to_device(x, cfg.dtype)
+    rng = np.random.default_rng(14)
+    idx = np.unique(np.concatenate([[0, 63, 64, 127, 128, T - 1], rng.integers(0, T, 60)]))
+    few, part = max(E // 20, 1), T // 8
+    for name, share in (("even", np.full((1, E), 0.028)), ("few", np.where(np.arange(E) % (E // few) == 1, 0.5, 0.001)[None]),
+                        ("part", np.where(np.arange(T) // part == 3, 0.2, 0.001)[:, None])):
+        mask = (rng.random((T, E)) < share).astype(np.uint8)
+        assert mask.mean() <= 0.03
+        print(f"{name} T={T} d={d} E={E} m={m} pairs={mask.sum()}", flush=True)
+        offsets, lists = lists_from_mask(mask)
+        off_d, list_d = torch.from_numpy(offsets).cuda(), torch.from_numpy(lists).cuda()
+        y = B.dmoe_expert_ffn(L, xd, off_d, list_d)
+        assert torch.equal(B.dmoe_expert_ffn(L, xd, off_d, list_d), y)
+        assert working_kernel(B, lambda: B.dmoe_expert_ffn(L, xd, off_d, list_d)) == "expert_down_sparse"
+        got, ref = B.from_device(y, cfg.dtype)[idx], oracle_ffn(oracle, layer, x[idx], mask[idx])
+        some = np.abs(ref).max(axis=1) > 0
+        assert (got[~some] == 0).all()
+        assert tokenwise_rel_err(got[some], ref[some]) <= TOL["bf16"]
