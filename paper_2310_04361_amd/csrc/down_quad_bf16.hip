@@ -412,14 +412,43 @@ void launch_quad_t(const dmoe_layer& L, int T, const int32_t* item_start, const 
                   (uint32_t)(h_fragments(L, T) * 16 * row_bytes), max_pairs, max_rmw, walk_limit, parts, xs, partial);
 }
 
+// Density up to which the quads are taken against the dense kernel: a - b / E, where b stands for what a workgroup does
+// before and after its walk.  The dense kernel has two workgroups per CU, which hide that behind each other's walks once there
+// is more than one workgroup per CU; here there is one of twice the wavefronts.  Quads / dense, us, at 3.5, 8 and 10.5 %: rows of
+// 64, 24298 tokens, d = 1280 (950 workgroups) 12 experts 60 / 44, 63 / 44, 66 / 43; 40 102 / 102, 114 / 105, 122 / 107; 80 174 / 189,
+// 194 / 199, 214 / 201; 256 483 / 588, 565 / 608, 626 / 629; 4096 tokens, d = 2048 (256) 12 experts 21 / 20, 23 / 21, 24 / 20; 40
+// 32 / 36, 37 / 36, 40 / 36; 256 131 / 158, 147 / 164, 161 / 168.  Of 48 neurons, 50432 tokens, d = 768, 80 experts 176 / 178, 196 / 184,
+// 220 / 187.  Rows of 128 at 3, 5, 7 %, 24298 tokens, d = 1280, 12 experts 73 / 66, 76 / 67, 80 / 68; 24 114 / 149, 120 / 124,
+// 124 / 122.  Of 8 neurons at 5, 10, 13.5 %: 9000 tokens, d = 1024, 650 experts 98 / 99, 111 / 101, 124 / 101, 2500 317 / 364,
+// 366 / 379, 414 / 413; 4096 tokens, d = 2048, 650 56 / 63, 63 / 65, 71 / 67.
+double quad_density(const dmoe_layer& L, int T) {
+    struct Line {
+        int pieces;
+        double most, a, b, a_more, b_more;  // up to one workgroup per CU, and more of them
+    };
+    constexpr Line lines[] = {{1, 0.14, 0.165, 33.0, 0.165, 75.0}, {6, 0.11, 0.105, 1.8, 0.1, 5.0},
+                              {8, 0.11, 0.125, 1.6, 0.125, 3.4}, {16, 0.075, 0.105, 0.45, 0.105, 1.1}};
+    const int PG = quad_pieces(L.expert_size), wgs = div_up(T, kDqTokens) * (L.d_model / kDqCols);
+    for (const Line& l : lines)
+        if (l.pieces == PG) return std::min(l.most, wgs > 256 ? l.a_more - l.b_more / L.n_experts : l.a - l.b / L.n_experts);
+    return 0.0;
+}
+
 // Density up to which the walk over the pairs (down_rmw.h) is a choice, where the walk over the experts is not divided.  Against
 // the dense kernel alone (384 columns) pairs decide: 3 %.  Against the quads the tiles that they make decide, on the device
 // (pair_walk_limit): how many there are depends on how evenly the pairs fall on the experts.  Experts of 64, uniform
 // selections of 1.8 and 2.4 %, pairs / quads: 4096 tokens x 256, d = 2048 142 / 121 and 152 / 123 us; a router's selection of
 // 2.7 %, 4254 tokens x 699, d = 1280: 215 / 354; of 1.3 %, 4137 tokens x 1030 experts of 96: 397 / 1100.
+// With few experts, for which the dense kernel is ahead of the quads, pairs are taken as far as they are ahead of it when even: 50432
+// tokens x 24, d = 768, rows of 64 at 0.4 / 0.8 % 69 / 83 us against 79, of 128 96 / 130 against 141.
 constexpr double kPairDensity = 0.03;
+bool pairs_alone(const dmoe_layer& L, int T) {
+    return down_bf16_wide(L, T) || (L.n_experts < 32 && quad_density(L, T) < kPairDensity);
+}
 double rmw_density(const dmoe_layer& L, int T) {
-    if (quad_pieces(L.expert_size) == 1 || down_parts(L, T) > 1) return 0.0;
+    const int PG = quad_pieces(L.expert_size);
+    if (PG == 1 || down_parts(L, T) > 1) return 0.0;
+    if (pairs_alone(L, T) && !down_bf16_wide(L, T)) return PG == 16 ? 0.01 : 0.007;
     return kPairDensity;
 }
 
@@ -428,7 +457,7 @@ double rmw_density(const dmoe_layer& L, int T) {
 // 9000 tokens x 500, d = 512 (33 MB of weights) 0.85 %, 4096 x 256, d = 2048 (67 MB) 1.2 %, 4254 x 699, d = 1280 (114 MB)
 // 1.8 %; rows of 128 50432 x 24, d = 768 (5 MB) 0.8 %, 4096 x 256, d = 2048 (134 MB) 1.3 %, 4254 x 699, d = 1280 (179 MB) 1.8 %.
 int pair_walk_limit(const dmoe_layer& L, int T) {
-    if (down_bf16_wide(L, T)) return -1;
+    if (pairs_alone(L, T)) return -1;
     const int PG = quad_pieces(L.expert_size);
     const double mb = 2e-6 * L.n_experts * m_pad_of(L.expert_size) * L.d_model;
     const double per_expert = PG == 16 ? kTileCost128 * std::min(0.9, 0.62 + mb / 640.0)
@@ -460,22 +489,18 @@ void launch_pack_down_quad(const dmoe_layer& L, void* packed, hipStream_t s) {
 }
 
 // Pairs up to which this kernel is taken; 0: not launched.  A launch that finds nothing to do costs 4 us.
-// Crossovers against the dense kernel: 2048 gated experts of 8 at 4096 tokens 185 against 198 us at 13 %, 210
-// against 207 at 18 %; 256 gated experts of 64 at 4096 tokens 157 against 164 at 9.9 %, 173 against 167 at 13 %; 24
-// experts of 128 at 50432 tokens 142 against 146 at 6.5 %, 148 against 147 at 8 %.
 long long down_quad_max_pairs(const dmoe_layer& L, int T) {
     const int PG = quad_pieces(L.expert_size);
     if (!down_quad_w_bytes(L)) return 0;
-    double density = PG == 1 ? 0.14 : PG == 16 ? 0.075 : 0.11;
-    const bool divided = down_parts(L, T) > 1;
+    double density = 0.0;
     if (down_bf16_wide(L, T)) {
         // the dense kernel has a shape that fills the chip once, this one does not (16384 tokens x 512 experts
         // of 6, d = 768, 11 %: 88 us against 72)
-        density = PG == 1 ? 0.0 : rmw_density(L, T);
-    } else if ((PG == 1 || divided) && down_walk_us(L, T) < kQuadMinWalk) {
-        density = 0.0;
+        density = rmw_density(L, T);
+    } else if ((PG != 1 && down_parts(L, T) <= 1) || down_walk_us(L, T) >= kQuadMinWalk) {
+        density = std::max(quad_density(L, T), rmw_density(L, T));
     }
-    return (long long)(density * (double)T * (double)L.n_experts);
+    return density > 0.0 ? (long long)(density * (double)T * (double)L.n_experts) : 0;
 }
 
 void launch_down_quad(const dmoe_layer& L, int T, const int32_t* item_start, const int32_t* group_off,
@@ -483,7 +508,7 @@ void launch_down_quad(const dmoe_layer& L, int T, const int32_t* item_start, con
                       float* partial, long long max_pairs, hipStream_t s) {
     LaunchTimer tm(kSlotDownRmw, s);
     const double rmw = rmw_density(L, T);
-    const int walk_limit = pair_walk_limit(L, T);
+    const int walk_limit = rmw > 0.0 ? pair_walk_limit(L, T) : -1;
     const long long max_rmw = rmw > 0.0 ? (long long)(rmw * (double)T * (double)L.n_experts) : -1;
 #define DMOE_QUAD(PG_, R_) \
     launch_quad_t<PG_, R_>(L, T, item_start, group_off, alist, mask, offsets, H, y, max_pairs, max_rmw, walk_limit, partial, s)

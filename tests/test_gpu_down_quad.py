@@ -42,12 +42,25 @@ def working_kernel(B, call):
     return first
 
 
+def densities(T, d, E, m):
+    """(most pairs, most quads) as shares of T E for up to 256 workgroups of 128 tokens x 256 columns and no walk or shape
+    in which the dense kernel is the only other one; above them the dense kernel."""
+    assert -(-T // 128) * (d // 256) <= 256
+    most, a, b = (0.14, 0.165, 33.0) if m <= 8 else (0.11, 0.105, 1.8) if m <= 48 else (0.11, 0.125, 1.6) if m <= 64 else (0.075, 0.105, 0.45)
+    quads = min(most, a - b / E)
+    pairs = 0.0 if m <= 8 else 0.03
+    if m > 8 and E < 32 and quads < 0.03:
+        pairs = 0.007 if m <= 64 else 0.01
+    return pairs, max(pairs, quads)
+
+
 @pytest.mark.parametrize("T,d,E,m,gated,p,dense_every", [
     # undivided walks (65 chunks x 2 slices of 256 columns), H rows of 64: one expert to three mask words
     (8300, 512, 1, 64, True, 0.09, 0), (8300, 512, 3, 57, True, 0.05, 40), (8300, 512, 5, 64, True, 0.05, 40),
     (8257, 512, 64, 63, True, 0.08, 0), (8300, 512, 66, 64, True, 0.05, 32), (8300, 512, 130, 60, False, 0.09, 0),
     # the other packings: six pieces (three k-steps a stage), sixteen
     (8300, 512, 18, 48, True, 0.05, 32), (8300, 512, 67, 41, False, 0.09, 0),
+    (8300, 512, 68, 41, False, 0.07, 0), (8300, 512, 27, 48, True, 0.03, 32), (8300, 512, 18, 64, True, 0.03, 0),
     (8300, 512, 24, 128, False, 0.03, 32), (8300, 512, 21, 100, False, 0.06, 0),
     # one piece: four quads per stage
     (8300, 512, 2048, 8, True, 0.05, 32), (8300, 512, 1990, 5, False, 0.1, 0), (8300, 512, 2011, 1, True, 0.12, 0),
@@ -64,12 +77,12 @@ def test_sparse_selections(oracle, T, d, E, m, gated, p, dense_every):
     print(f"T={T} d={d} E={E} m={m} gated={gated} p={p} dense_every={dense_every}", flush=True)
     layer, x = wl.make_layer(cfg, 11), wl.make_input(cfg, 11)
     mask = selection(T, E, p, dense_every, 12)
-    assert mask.mean() <= (0.14 if m <= 8 else 0.11 if m <= 64 else 0.075)  # the kernel's range
     offsets, lists = lists_from_mask(mask)
     L, xd = B.Layer(layer, cfg.dtype), B.to_device(x, cfg.dtype)
     off_d, list_d = torch.from_numpy(offsets).cuda(), torch.from_numpy(np.resize(lists, max(len(lists), 1))).cuda()
     y = B.dmoe_expert_ffn(L, xd, off_d, list_d)
-    assert working_kernel(B, lambda: B.dmoe_expert_ffn(L, xd, off_d, list_d)) == "expert_down_sparse"
+    sparse = mask.mean() <= densities(T, d, E, m)[1]
+    assert working_kernel(B, lambda: B.dmoe_expert_ffn(L, xd, off_d, list_d)) == ("expert_down_sparse" if sparse else "expert_down")
     assert torch.equal(B.dmoe_expert_ffn(L, xd, off_d, list_d), y)  # run-to-run reproducible
     got = B.from_device(y, cfg.dtype)
     assert np.isfinite(got).all()
@@ -85,9 +98,13 @@ def test_sparse_selections(oracle, T, d, E, m, gated, p, dense_every):
 
 
 @pytest.mark.parametrize("T,d,E,m,gated,limits", [
-    (8300, 512, 256, 64, True, (0.03, 0.11)), (8300, 512, 64, 48, True, (0.03, 0.11)),
-    (8300, 512, 96, 128, False, (0.03, 0.075)), (8300, 512, 1200, 8, True, (0.14,)),
+    (8300, 512, 256, 64, True, None), (8300, 512, 64, 48, True, None), (8300, 512, 20, 64, True, None), (8300, 512, 10, 64, True, None),
+    (8300, 512, 96, 128, False, None), (8300, 512, 5, 128, False, None), (8300, 512, 1200, 8, True, (0.1375,)),
     (1200, 2048, 256, 64, True, (0.11,)),  # a divided walk
+    # more than one workgroup per CU: 0.125 - 3.4 / E, 0.1 - 5 / E, 0.105 - 1.1 / E, 0.165 - 75 / E
+    (17000, 512, 60, 64, True, (0.03, 0.125 - 3.4 / 60)), (17000, 512, 130, 41, True, (0.03, 0.1 - 5.0 / 130)),
+    (17000, 512, 40, 64, True, (0.125 - 3.4 / 40,)),
+    (17000, 512, 20, 100, False, (0.03, 0.105 - 1.1 / 20)), (17000, 512, 900, 8, True, (0.165 - 75.0 / 900,)),
     # 384-column workgroups of the dense kernel: pairs up to 3 %, the dense kernel above
     (11000, 768, 24, 64, False, (0.03,)), (11000, 768, 24, 128, False, (0.03,)),
 ])
@@ -99,6 +116,8 @@ def test_limits_of_the_pair_count(oracle, T, d, E, m, gated, limits):
     cfg = wl.Config("limits", T, d, E, m, 64, gated, "gelu_tanh" if gated else "gelu_erf", "bf16", (0.5,), ffn_bias=not gated)
     layer, x = wl.make_layer(cfg, 13), wl.make_input(cfg, 13)
     L, xd = B.Layer(layer, cfg.dtype), B.to_device(x, cfg.dtype)
+    if limits is None:
+        limits = sorted(set(densities(T, d, E, m)))
     order = np.random.default_rng(14).permutation(T * E)
     idx = np.unique(np.concatenate([[0, 63, 64, 127, 128, T - 1], np.random.default_rng(1).integers(0, T, 60)]))
     for i, limit in enumerate(limits):
