@@ -796,7 +796,7 @@ void launch_down_tt(const dmoe_layer& L, const SmallGroup& G, int n_layers, int 
     // experts leave no registers for 16).  64 columns and 8 wavefronts read the hidden rows half as often, but
     // write twice the shares: 128 x 24, d = 768, 32 / 64 tokens 8.8 / 10.3 us against 6.5 / 7.7; 256 x 64, d = 2048,
     // 15.7 / 19.2 against 14.6 / 17.2, from HBM 18.9 / 22.8 against 18.0 / 21.8.  16 columns: 16.5 at 32 tokens.
-    // They stay for E4M3 weights that come from HBM, of which 32 columns are runs of 2 KB instead of 4: down weights of
+    // They stay for weights that come from HBM (below); E4M3, of which 32 columns are runs of 2 KB instead of 4: down weights of
     // 67 MB, 32 / 64 tokens, 20.2 / 26.7 us against 21.4 / 28.7, of 33 MB 12.4 / 16.1 against 12.8 / 16.5, and from the
     // last-level cache 17 MB 8.5 / 11.1 against 7.9 / 9.8.
     // Expert groups: one, or enough workgroups to fill the chip, and no more shares than the workspace
@@ -811,14 +811,19 @@ void launch_down_tt(const dmoe_layer& L, const SmallGroup& G, int n_layers, int 
     constexpr int U1 = KS <= 2 ? 4 : 2;  // (more would not fit the registers)
     constexpr int U2 = KS <= 2 ? 2 : 1, U4 = KS == 1 ? 2 : 1, NW4 = KS <= 2 ? 16 : 8;
     const int eg1 = div_up(E, 128);
-    const auto groups = [&](int ctw, int nw) { return std::min(div_up(256, d / (16 * ctw)), E / nw); };
-    if constexpr (W8) {
-        if (TT > 1 && (size_t)E * 32 * KS * d > ((size_t)24 << 20)) {
-            switch (TT) {
-            case 2: go(small_down_kernel<KS, 2, 4, 8, U2, W8>, 4, 8, groups(4, 8)); return;
-            case 3: go(small_down_kernel<KS, 3, 4, 8, U2, W8>, 4, 8, groups(4, 8)); return;
-            default: go(small_down_kernel<KS, 4, 4, 8, U2, W8>, 4, 8, groups(4, 8)); return;
-            }
+    // As many groups as leave at most one workgroup per CU (of 16 wavefronts there is room for one, and a few in a second round cost as
+    // much as the first).  Rounded up / down, us: d = 1280 (280 / 240 workgroups), 1000 x 24, 20 / 40 / 60 tokens 22.3 / 26.2 / 28.8 and 17.4
+    // / 19.1 / 20.6; d = 768 (264 / 240), 1000 x 48, 20 tokens 29.2 and 22.1; d = 3072 (288 / 192), 500 x 24 23.9 / 28.0 / 30.4
+    // and 19.2 / 20.8 / 22.7.
+    const auto groups = [&](int ctw, int nw) { return std::min(std::max(1, 256 / (d / (16 * ctw))), E / nw); };
+    // Weights from HBM: runs of 64 columns.  bf16 beyond the last-level cache or near it, 32 / 64 columns, 60 tokens: 1000 x 24, d = 3072
+    // (196 MB) 59.4 / 41.3; 1600 x 24, d = 2048 (209 MB) 53.1 / 44.9, 1000 (131 MB) 27.4 / 28.6; d = 1536 1000 x 48 (196 MB) 50.4 / 48.0;
+    // narrower layers not: d = 768, 1000 x 128 (196 MB) 59.2 / 75.2.
+    if (TT > 1 && (W8 ? (size_t)E * 32 * KS * d > ((size_t)24 << 20) : d >= 1536 && (size_t)E * 64 * KS * d > ((size_t)150 << 20))) {
+        switch (TT) {
+        case 2: go(small_down_kernel<KS, 2, 4, 8, U2, W8>, 4, 8, groups(4, 8)); return;
+        case 3: go(small_down_kernel<KS, 3, 4, 8, U2, W8>, 4, 8, groups(4, 8)); return;
+        default: go(small_down_kernel<KS, 4, 4, 8, U2, W8>, 4, 8, groups(4, 8)); return;
         }
     }
     switch (TT) {

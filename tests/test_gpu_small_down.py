@@ -1,6 +1,6 @@
 """Down-projection of small batches: the column and wavefront splits at the edges of their ranges (few experts for
-many wavefronts, one expert group or several, narrow and wide experts, E4M3 weights below and above the
-size from which they take 64 columns)."""
+many wavefronts, one expert group or several, narrow and wide experts, weights below and above the sizes
+from which they take 64 columns)."""
 import numpy as np
 import pytest
 
@@ -23,7 +23,10 @@ def B():
 CASES = [(256, 15, 24, False, "native", (17, 64)), (256, 16, 64, True, "native", (33, 49)),
          (768, 47, 128, False, "native", (32, 48, 50, 64)), (1024, 300, 32, False, "native", (18, 47, 64)),
          (256, 31, 128, False, "e4m3", (20, 40, 64)), (2048, 64, 24, True, "e4m3", (31, 63)),
-         (2048, 192, 64, True, "e4m3", (17, 33, 64)), (2048, 193, 64, True, "e4m3", (17, 33, 64))]
+         (2048, 192, 64, True, "e4m3", (17, 33, 64)), (2048, 193, 64, True, "e4m3", (17, 33, 64)),
+         # column counts that do not divide the workgroups of a chip; bf16 weights above the size for 64 columns
+         (1280, 140, 48, False, "native", (20, 40, 60)), (3072, 50, 24, True, "native", (17, 33, 49)),
+         (2048, 1220, 24, False, "native", (18, 47, 64))]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(str(v) for v in c[:5]))
