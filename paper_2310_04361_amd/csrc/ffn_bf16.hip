@@ -143,7 +143,8 @@ struct XRows {
 // branch.  K advances in blocks of 64: the wavefront loads the next block of its x rows
 // (lane = (row % 8, 16-byte piece of the 128-byte row segment)) and of the weight fragments
 // while the MFMAs run on the current block out of LDS / registers.
-template <int MT, bool GATED, int TT, int NBUF, bool NEAR>
+// PTR: the weights by address and all lanes, with as many registers as one wavefront per SIMD may have.
+template <int MT, bool GATED, int TT, int NBUF, bool NEAR, bool PTR = false>
 __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf,
     const __bf16* __restrict__ wgatef, const __bf16* __restrict__ b_up,
@@ -205,11 +206,17 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
         // arithmetic and the spills: 50432 tokens x 128 experts of 24, d = 768, 117 -> 110 us, 2000 tokens 13.7 -> 12.4;
         // neither does it alone.)
         __amdgpu_buffer_rsrc_t wf[BR];
+        const __bf16* wp[BR];
         uint32_t wlane[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
             wlane[mt] = neuron_of_slot(mt, c) < m ? (uint32_t)(mt * NK32 * 1024 + lane * 16) : 0x80000000u;
         auto weights_of = [&](int ee) {
+            if constexpr (PTR) {
+                wp[0] = wupf + (size_t)ee * MT * NK32 * 512 + lane * 8;
+                if (GATED) wp[BR - 1] = wgatef + (size_t)ee * MT * NK32 * 512 + lane * 8;
+                return;
+            }
             const size_t at = (size_t)__builtin_amdgcn_readfirstlane(ee) * MT * NK32 * 512;
             wf[0] = __builtin_amdgcn_make_buffer_rsrc((void*)(wupf + at), 0, MT * NK32 * 1024, kRawBuffer);
             if (GATED) wf[BR - 1] = __builtin_amdgcn_make_buffer_rsrc((void*)(wgatef + at), 0, MT * NK32 * 1024, kRawBuffer);
@@ -236,7 +243,8 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
                 for (int br = 0; br < BR; ++br)
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt)
-                        a[ks][br][mt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wf[br], wlane[mt], (2 * kb + ks) * 1024, 0));
+                        a[ks][br][mt] = PTR ? load8(wp[br] + ((size_t)mt * NK32 + 2 * kb + ks) * 512)
+                                            : __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wf[br], wlane[mt], (2 * kb + ks) * 1024, 0));
         };
         auto store_x = [&](int buf) {
             char* dst = xs + (buf % NBUF) * (UR * kUpRowBytes) + ld_row * kUpRowBytes + ld_piece * 16;
@@ -791,19 +799,22 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
 }
 
 // ---- launchers ---------------------------------------------------------------------------------------
-template <int MT, bool GATED, int TT, int NBUF, bool NEAR>
+size_t up_lds(const dmoe_layer& L, int TT, int NBUF) {  // the item table of a window and the staged rows
+    return ((2 * (size_t)L.n_experts + 1) * 4 + 15) / 16 * 16 + 4 * NBUF * (size_t)TT * 16 * kUpRowBytes;
+}
+
+template <int MT, bool GATED, int TT, int NBUF, bool NEAR, bool PTR = false>
 void launch_up_t(const dmoe_layer& L, const void* x, const PackedLayout& P, const int32_t* witem,
                  const int32_t* wfirst, int NW, const int32_t* alist, void* H, int grid,
                  hipStream_t s) {
-    const size_t lds = ((2 * (size_t)L.n_experts + 1) * 4 + 15) / 16 * 16 +
-                       4 * NBUF * (size_t)TT * 16 * kUpRowBytes;
+    const size_t lds = up_lds(L, TT, NBUF);
     static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
     std::call_once(attr_once, [&] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_bf16_kernel<MT, GATED, TT, NBUF, NEAR>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_bf16_kernel<MT, GATED, TT, NBUF, NEAR, PTR>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
     const char* pk = static_cast<const char*>(L.packed);
-    launch_kernel(up_bf16_kernel<MT, GATED, TT, NBUF, NEAR>, grid, 256, lds, s, 
+    launch_kernel(up_bf16_kernel<MT, GATED, TT, NBUF, NEAR, PTR>, grid, 256, lds, s, 
         (const __bf16*)x, (const __bf16*)(pk + P.wupf), (const __bf16*)(pk + P.wgatef),
         (const __bf16*)L.b_up, witem, wfirst, NW, alist, (__bf16*)H, L.d_model, L.n_experts,
         L.expert_size, L.act);
@@ -972,7 +983,12 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
     auto go = [&](auto near_c) {
         constexpr bool kNear = decltype(near_c)::value;
         if (L.gated) {
-            launch_up_t<2, true, 4, 2, kNear>(L, x, P, witem, wfirst, NW, alist, H, grid, s);
+            // One workgroup per CU, for want of LDS beside the item table (more than 820 experts) or of items: then what counts is a
+            // wavefront alone, and the registers that keep a second workgroup away are free.  992 tokens x 1627 experts of 32, d = 2048, all
+            // selected 1073 / 1002 us; 141 x 40 of 16, d = 3072 44.2 / 42.2.  Elsewhere two share a CU: 4096 tokens x 256 of 32,
+            // d = 2048, 30 % 122 / 164; 300 tokens 34 / 57.
+            if (up_lds(L, 4, 2) > 80 * 1024 || worst <= 256) launch_up_t<2, true, 4, 2, false, true>(L, x, P, witem, wfirst, NW, alist, H, grid, s);
+            else launch_up_t<2, true, 4, 2, kNear>(L, x, P, witem, wfirst, NW, alist, H, grid, s);
         } else if (mt == 2) {
             // 32-neuron rows: one staging buffer, three workgroups per CU
             const int grid3 = round_up((int)std::min<long long>(worst, 256 * 3), 8);
