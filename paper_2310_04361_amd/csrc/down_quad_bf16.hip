@@ -455,13 +455,13 @@ double rmw_density(const dmoe_layer& L, int T) {
 // Cost of four chunks (pairs_are_less) up to which the pairs are taken, -1: whatever it is.  The quads take a time that is nearly proportional to
 // the experts, the longer for each the more their weights exceed the L2s.  Uniform selections, density of equal times: rows of 64
 // 9000 tokens x 500, d = 512 (33 MB of weights) 0.85 %, 4096 x 256, d = 2048 (67 MB) 1.2 %, 4254 x 699, d = 1280 (114 MB)
-// 1.8 %; rows of 128 50432 x 24, d = 768 (5 MB) 0.8 %, 4096 x 256, d = 2048 (134 MB) 1.3 %, 4254 x 699, d = 1280 (179 MB) 1.8 %.
+// 1.8 %, of 48 neurons 0.72 % at 256 workgroups, 0.8 to 0.95 % at 516 to 1032; rows of 128 50432 x 24, d = 768 (5 MB) 0.8 %, 4096 x 256, d = 2048 (134 MB) 1.3 %, 4254 x 699, d = 1280 (179 MB) 1.8 %.
 int pair_walk_limit(const dmoe_layer& L, int T) {
     if (pairs_alone(L, T)) return -1;
     const int PG = quad_pieces(L.expert_size);
     const double mb = 2e-6 * L.n_experts * m_pad_of(L.expert_size) * L.d_model;
     const double per_expert = PG == 16 ? kTileCost128 * std::min(0.9, 0.62 + mb / 640.0)
-                                       : std::min(10.4, 7.2 + mb / 36.0) * (PG == 6 ? 0.7 : 1.0);  // (6 pieces: fewer products)
+                                       : std::min(10.4, 7.2 + mb / 36.0) * (PG == 6 ? 0.82 : 1.0);  // (6 pieces: fewer products)
     return (int)(4.0 * per_expert * L.n_experts);
 }
 
