@@ -983,11 +983,11 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
     auto go = [&](auto near_c) {
         constexpr bool kNear = decltype(near_c)::value;
         if (L.gated) {
-            // One workgroup per CU, for want of LDS beside the item table (more than 820 experts) or of items: then what counts is a
-            // wavefront alone, and the registers that keep a second workgroup away are free.  992 tokens x 1627 experts of 32, d = 2048, all
-            // selected 1073 / 1002 us; 141 x 40 of 16, d = 3072 44.2 / 42.2.  Elsewhere two share a CU: 4096 tokens x 256 of 32,
-            // d = 2048, 30 % 122 / 164; 300 tokens 34 / 57.
-            if (up_lds(L, 4, 2) > 80 * 1024 || worst <= 256) launch_up_t<2, true, 4, 2, false, true>(L, x, P, witem, wfirst, NW, alist, H, grid, s);
+            // One workgroup per CU, for want of LDS beside the item table (more than 820 experts): then the registers that keep a second
+            // one away are free.  992 tokens x 1627 experts of 32, d = 2048, all selected 1073 / 1002 us.  But by address padding rows
+            // move as well: 737 x 1436 of 16, d = 1024, 60 % 183 / 238; 49 x 114 of 16, d = 3072 37.7 / 42.1.  Elsewhere two
+            // share a CU: 4096 tokens x 256 of 32, d = 2048, 30 % 122 / 164; 300 tokens 34 / 57.
+            if (up_lds(L, 4, 2) > 80 * 1024 && L.expert_size > 24) launch_up_t<2, true, 4, 2, false, true>(L, x, P, witem, wfirst, NW, alist, H, grid, s);
             else launch_up_t<2, true, 4, 2, kNear>(L, x, P, witem, wfirst, NW, alist, H, grid, s);
         } else if (mt == 2) {
             // 32-neuron rows: one staging buffer, three workgroups per CU

@@ -4,7 +4,7 @@ experts, plain and gated)."""
 import numpy as np
 import pytest
 
-from helpers import TOL, oracle_ffn, tokenwise_rel_err
+from helpers import TOL, lists_from_mask, oracle_ffn, tokenwise_rel_err
 from paper_2310_04361_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -37,3 +37,20 @@ def test_far_rows(oracle, m, gated, T):
     keep = np.abs(ref).max(axis=1) > 0
     assert (got[~keep] == 0).all()
     assert tokenwise_rel_err(got[keep], ref[keep]) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("T,E,m", [(131, 840, 32), (70, 840, 27), (131, 840, 24), (131, 780, 32)])
+def test_narrow_gated_experts_with_a_large_item_table(oracle, T, E, m):
+    """More than about 820 gated experts of 25 to 32 leave LDS for one workgroup per CU and take the weights by address;
+    fewer and narrower ones by a buffer that skips padding rows."""
+    import torch
+    from paper_2310_04361_amd import binding as B
+    cfg = wl.Config("items", T, 256, E, m, 64, True, "gelu_tanh", "bf16", (0.5,))
+    print(f"item table T={T} E={E} m={m}", flush=True)
+    layer, x = wl.make_layer(cfg, 3), wl.make_input(cfg, 3)
+    mask = wl.bernoulli_mask(T, E, 0.3, seed=5)
+    mask[:, 7] = 0
+    mask[:, E - 1] = 1
+    offsets, lists = lists_from_mask(mask)
+    y = B.dmoe_expert_ffn(B.Layer(layer, cfg.dtype), B.to_device(x, cfg.dtype), torch.from_numpy(offsets).cuda(), torch.from_numpy(lists).cuda())
+    assert tokenwise_rel_err(B.from_device(y, cfg.dtype), oracle_ffn(oracle, layer, x, mask)) <= TOL["bf16"]
