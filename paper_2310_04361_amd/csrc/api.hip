@@ -294,7 +294,24 @@ bool counts_in_sub(const dmoe_layer& L, int T, int split) {
     return L.dtype == DMOE_BF16 && !use_small_path(L, T) && (split > 1 || fold_scan(T, L.n_experts, 1));
 }
 
-// Experts from mask bits whose group counts are already in the workspace (counts_in_sub).
+// Small batches without lists (token_sets.h), unless the caller wants them: the gate's rows in sub_cnt are then
+// token sets.  As long as x fits an XCD's L2: no order of the items by their tokens is missed then.  Forward, us, lists / sets:
+// 128 x 24, d = 768, 400 tokens 42.3 / 36.5, 1600 52.6 / 48.2, 2500 59.9 / 56.1, 3152 (4.8 MB) 64.9 / 73.0; 512 x 6 (kernel of one weight
+// tile) 400 tokens 57.1 / 46.6, 1200 66.8 / 58.3, 2000 73.2 / 73.0, 3000 85.0 / 96.5; 2048 gated of 8, d = 2048, 300 tokens 122 / 103, 1000
+// 199 / 185; 256 gated of 64, 333 tokens 121 / 103, 1024 tokens (37 %) 183 / 183, 8-bit 133 / 124, 1500 tokens, 8-bit, 155 / 169; 64 gated of
+// 64, d = 512, 2000 tokens 58 / 52, 3500 71 / 74; 256 x 48, d = 768, 1000 tokens 90 / 77, 2000 116 / 118.
+// Not where the sparse down-projection may run, which decides by the number of pairs, nor where another kernel
+// goes over all the rows of H.
+bool use_sets(const dmoe_layer& L, int T, bool want_lists) {
+    if (L.dtype != DMOE_BF16 || want_lists || use_small_path(L, T) || T <= kSmallTokens) return false;
+    if (T > kSetTokens || (size_t)T * L.d_model * 2 > ((size_t)4 << 20)) return false;
+    const long long most = up_tiny_supported(L) ? 2048ll * L.n_experts : (up_rows_bf16(L) == 256 ? 262144 : 400000);
+    if ((long long)T * L.n_experts > most) return false;
+    if (!down_bf16_addressable(L, T)) return false;
+    return hidden_fp8(L) ? down_x8_shape(L) && down_x8_addressable(L, T) && up_x8_supported(L) : down_quad_max_pairs(L, T) <= 0;
+}
+
+// Experts from mask bits whose group counts (or token sets) are already in the workspace (counts_in_sub, use_sets).
 // gate_mod: the small-token path takes router and gate into its up-projection (scores and mask are
 // then outputs of that kernel, described by gate_mod).
 int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const LayerWs& w,
@@ -331,17 +348,20 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
         G.m[0] = gate_mod ? *gate_mod : small_mod(L, ws, w, nullptr, nullptr, y, 0.0f);
         launch_small_bf16(L, G, 1, x_router, x, T, gate_mod != nullptr, s);
         if (offsets_out) {  // after the experts: with the gate folded in, they write the mask
-            launch_counts_from_mask(mask, T, L.n_experts, group_off, nullptr, s);
+            launch_counts_from_mask(mask, T, L.n_experts, group_off, nullptr, false, s);
             launch_scan_and_fill(mask, T, L.n_experts, group_off, counts, offsets, nullptr, 64,
                                  lists_out, nullptr, 1, nullptr, nullptr, s);
         }
     } else {
         int32_t* witem = reinterpret_cast<int32_t*>(ws + w.witem);
         int32_t* wfirst = reinterpret_cast<int32_t*>(ws + w.wfirst);
-        launch_scan_and_fill(mask, T, L.n_experts, group_off, counts, offsets, item_start,
-                             up_rows_bf16(L), lists_out, alist, up_window_groups(L, T), witem,
-                             wfirst, s, sub_cnt, split, up_rows_bf16(L) == 256 ? ws + w.worder : nullptr,
-                             up_items_by_experts(L));
+        const bool sets = use_sets(L, T, offsets_out != nullptr);
+        const TokenSets S{sets ? reinterpret_cast<const int32_t*>(ws + w.sub_cnt) : nullptr, group_off, item_start, T, false};
+        if (!sets)
+            launch_scan_and_fill(mask, T, L.n_experts, group_off, counts, offsets, item_start,
+                                 up_rows_bf16(L), lists_out, alist, up_window_groups(L, T), witem,
+                                 wfirst, s, sub_cnt, split, up_rows_bf16(L) == 256 ? ws + w.worder : nullptr,
+                                 up_items_by_experts(L));
         void* H = ws + w.H;
         float* partial = reinterpret_cast<float*>(ws + w.partial);
         // 8-bit hidden activations on the 8-bit matrix cores: the rows as codes + scale bytes
@@ -352,10 +372,10 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
         // up-projection a kernel of its own quantises the bf16 rows)
         const bool up_writes_codes = down8 && up_x8_supported(L);
         if (up_x8_supported(L))
-            launch_up_x8(L, x8, xscale, T, witem, ws + w.worder, alist, H, up_writes_codes ? H8 : nullptr,
+            launch_up_x8(L, x8, xscale, T, witem, ws + w.worder, alist, S, H, up_writes_codes ? H8 : nullptr,
                          up_writes_codes ? hs8 : nullptr, s);
         else
-            launch_up_bf16(L, x, T, witem, wfirst, ws + w.worder, alist, H, s);
+            launch_up_bf16(L, x, T, witem, wfirst, ws + w.worder, alist, S, H, s);
         if (down8) {
             if (!up_writes_codes) launch_h_rows_to_e4m3(L, item_start, H, H8, hs8, s);
             launch_down_x8(L, T, item_start, group_off, mask, H8, hs8, y, partial, s);
@@ -469,7 +489,7 @@ int32_t dmoe_router(const dmoe_layer* layer, const void* x, int32_t n_tokens, fl
     if (layer->dtype == DMOE_F32) launch_router_f32(*layer, (const float*)x, n_tokens, scores, s);
     else if (router_fused_scores_supported(*layer))
         launch_router_fused(*layer, x, n_tokens, router_fused_split(*layer, n_tokens), scores, 0.0f,
-                            nullptr, nullptr, s);
+                            nullptr, nullptr, false, s);
     else launch_router_bf16(*layer, x, n_tokens, scores, s);
     return check_launch("router");
 }
@@ -507,9 +527,9 @@ int select_impl(const float* scores, int32_t n_tokens, int32_t n_experts, Gate g
     uint64_t* mask = mask_bits ? mask_bits : reinterpret_cast<uint64_t*>(ws + w.mask);
     if (n_tokens > 0) {
         if (gate.top_k < 0)
-            launch_mask_from_scores(scores, n_tokens, n_experts, gate.tau, mask, k_per_token, cnt, nullptr, s);
+            launch_mask_from_scores(scores, n_tokens, n_experts, gate.tau, mask, k_per_token, cnt, nullptr, false, s);
         else
-            launch_mask_topk(scores, n_tokens, n_experts, gate.top_k, mask, k_per_token, cnt, nullptr, s);
+            launch_mask_topk(scores, n_tokens, n_experts, gate.top_k, mask, k_per_token, cnt, nullptr, false, s);
     }
     launch_scan_and_fill(mask, n_tokens, n_experts, group_off, counts, offsets, nullptr, 64,
                          n_tokens > 0 ? token_lists : nullptr, nullptr, 1, nullptr, nullptr, s, sub_cnt);
@@ -549,9 +569,10 @@ int32_t dmoe_expert_ffn(const dmoe_layer* layer, const void* x, int32_t n_tokens
     hipStream_t s = (hipStream_t)stream;
     uint64_t* mask = reinterpret_cast<uint64_t*>(ws + w.mask);
     uint64_t* colmask = use_small_path(*layer, n_tokens) ? reinterpret_cast<uint64_t*>(ws + w.colmask) : nullptr;
+    const bool sets = use_sets(*layer, n_tokens, false);
     launch_mask_from_lists(offsets, token_lists, n_tokens, layer->n_experts, mask,
-                           reinterpret_cast<int32_t*>(ws + (counts_in_sub(*layer, n_tokens, 1) ? w.sub_cnt : w.group_off)),
-                           colmask, ws + w.H, w.H_bytes, s);  // (the H rows come later)
+                           reinterpret_cast<int32_t*>(ws + (sets || counts_in_sub(*layer, n_tokens, 1) ? w.sub_cnt : w.group_off)),
+                           colmask, sets, ws + w.H, w.H_bytes, s);  // (the H rows come later)
     return run_experts(*layer, x, n_tokens, ws, w, mask, nullptr, nullptr, y, s);
 }
 
@@ -577,14 +598,15 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
     float* scores = scores_out ? scores_out : reinterpret_cast<float*>(ws + w.scores);
     uint64_t* mask = mask_out ? mask_out : reinterpret_cast<uint64_t*>(ws + w.mask);
     uint64_t* colmask = use_small_path(*layer, n_tokens) ? reinterpret_cast<uint64_t*>(ws + w.colmask) : nullptr;
-    auto counts_of = [&](int parts) {  // where the gate's counts go
-        return reinterpret_cast<int32_t*>(ws + (counts_in_sub(*layer, n_tokens, parts) ? w.sub_cnt : w.group_off));
+    const bool sets = use_sets(*layer, n_tokens, offsets_out != nullptr);
+    auto counts_of = [&](int parts) {  // where the gate's counts (or token sets) go
+        return reinterpret_cast<int32_t*>(ws + (sets || counts_in_sub(*layer, n_tokens, parts) ? w.sub_cnt : w.group_off));
     };
     if (gate.top_k < 0 && layer_f32_fused(*layer)) {  // fp32, small enough: the whole layer in one launch
         launch_layer_f32(*layer, (const float*)x, n_tokens, tau, mask_out || offsets_out ? mask : nullptr, scores_out,
                          (float*)y, s);
         if (offsets_out) {
-            launch_counts_from_mask(mask, n_tokens, layer->n_experts, counts_of(1), nullptr, s);
+            launch_counts_from_mask(mask, n_tokens, layer->n_experts, counts_of(1), nullptr, false, s);
             launch_scan_and_fill(mask, n_tokens, layer->n_experts, counts_of(1),
                                  reinterpret_cast<int32_t*>(ws + w.counts), offsets_out, nullptr, 64,
                                  token_lists_out, nullptr, 1, nullptr, nullptr, s);
@@ -609,9 +631,9 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
         // asked for them)
         // (the hidden rows of a router in two launches lie where the experts' will, if there is room)
         if (router_two_launches(*layer, n_tokens) && 2 * (size_t)n_tokens * layer->router_hidden <= w.H_bytes)
-            launch_router_two(*layer, x, n_tokens, split, ws + w.H, scores_out, tau, mask, counts_of(split), s);
+            launch_router_two(*layer, x, n_tokens, split, ws + w.H, scores_out, tau, mask, counts_of(split), sets, s);
         else
-            launch_router_fused(*layer, x, n_tokens, split, scores_out, tau, mask, counts_of(split), s);
+            launch_router_fused(*layer, x, n_tokens, split, scores_out, tau, mask, counts_of(split), sets, s);
     } else {
         if (fused_router && n_tokens <= kSmallTokens) {
             SmallGroup G{};
@@ -622,7 +644,7 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
             launch_router_sliced(*layer, x, n_tokens, ws + w.hid, scores, s);
         else if (fused_router)
             launch_router_fused(*layer, x, n_tokens, router_fused_split(*layer, n_tokens), scores,
-                                0.0f, nullptr, nullptr, s);
+                                0.0f, nullptr, nullptr, false, s);
         else if (layer->dtype == DMOE_F32)
             launch_router_f32(*layer, (const float*)x, n_tokens, scores, s);
         else
@@ -631,12 +653,12 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
         int32_t* cnt = layer->dtype == DMOE_F32 && !offsets_out && n_tokens > 16 ? nullptr : counts_of(1);
         if (gate.top_k < 0 && fused_router && !colmask && gate_counts_supported(n_tokens, layer->n_experts)) {
             split = 4;
-            launch_gate_counts(scores, n_tokens, layer->n_experts, tau, mask, counts_of(split), s);
+            launch_gate_counts(scores, n_tokens, layer->n_experts, tau, mask, counts_of(split), sets, s);
         }
         else if (gate.top_k < 0)
-            launch_mask_from_scores(scores, n_tokens, layer->n_experts, tau, mask, nullptr, cnt, colmask, s);
+            launch_mask_from_scores(scores, n_tokens, layer->n_experts, tau, mask, nullptr, cnt, colmask, sets, s);
         else
-            launch_mask_topk(scores, n_tokens, layer->n_experts, gate.top_k, mask, nullptr, cnt, colmask, s);
+            launch_mask_topk(scores, n_tokens, layer->n_experts, gate.top_k, mask, nullptr, cnt, colmask, sets, s);
     }
     return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s, split);
 }

@@ -198,18 +198,19 @@ inline void launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_
 // number of tokens < 64*g that selected expert e, and row NG holds the per-expert totals.
 // (For more than 16 tokens group_off may be null, if colmask is: then nothing is counted.)
 // colmask (nullable) is [NG][E] u64: bit j of colmask[g][e] = token 64g + j keeps expert e.
+// sets, in these launchers: the rows are token sets (token_sets.h), of 16 tokens each, instead of counts.
 void launch_mask_from_scores(const float* scores, int T, int E, float tau, uint64_t* mask,
-                             int32_t* k_per_token, int32_t* group_off, uint64_t* colmask,
+                             int32_t* k_per_token, int32_t* group_off, uint64_t* colmask, bool sets,
                              hipStream_t s);
 // Top-k gate: exactly k experts per token, ties at the k-th score to the lower expert index.
 void launch_mask_topk(const float* scores, int T, int E, int k, uint64_t* mask,
-                      int32_t* k_per_token, int32_t* group_off, uint64_t* colmask, hipStream_t s);
+                      int32_t* k_per_token, int32_t* group_off, uint64_t* colmask, bool sets, hipStream_t s);
 // Counts per (group, expert) and, if wanted, the per-expert token sets from mask bits.
-void launch_counts_from_mask(const uint64_t* mask, int T, int E, int32_t* group_off, uint64_t* colmask,
+void launch_counts_from_mask(const uint64_t* mask, int T, int E, int32_t* group_off, uint64_t* colmask, bool sets,
                              hipStream_t s);
 // scratch: E * 64 ceil(T / 64) bytes (16-byte aligned) for the way without atomics, which is not taken with fewer.
 void launch_mask_from_lists(const int32_t* offsets, const int32_t* lists, int T, int E,
-                            uint64_t* mask, int32_t* group_off, uint64_t* colmask, void* scratch,
+                            uint64_t* mask, int32_t* group_off, uint64_t* colmask, bool sets, void* scratch,
                             size_t scratch_bytes, hipStream_t s);
 // sub_cnt (nullable): the counts come as `split` rows per group (ceil(T * split / 64) rows) that
 // are added up into group_off on the way; with few such rows (fold_scan) the list fill does that
@@ -218,7 +219,17 @@ constexpr int kFoldRows = 32;
 bool fold_scan(int T, int E, int split);
 // Dynamic-k gate on stored scores and the counts of its decisions, four rows per group, in one launch.
 bool gate_counts_supported(int T, int E);
-void launch_gate_counts(const float* scores, int T, int E, float tau, uint64_t* mask, int32_t* cnt, hipStream_t s);
+void launch_gate_counts(const float* scores, int T, int E, float tau, uint64_t* mask, int32_t* cnt, bool sets, hipStream_t s);
+// What the up-projections of a small batch read instead of lists, and what they write for the
+// down-projections (token_sets.h); sets == nullptr: there are lists.
+constexpr int kSetTokens = 3072;  // (a lane of a wavefront holds up to four rows)
+struct TokenSets {
+    const int32_t* sets;   // [ceil(T / 16)][E]: bit j of row r: token 16 r + j keeps the expert
+    int32_t* group_off;    // [ceil(T / 64) + 1][E]
+    int32_t* item_start;   // [E + 1]
+    int T;
+    bool in_order;         // (sets_grid)
+};
 void launch_scan_and_fill(const uint64_t* mask, int T, int E, int32_t* group_off, int32_t* counts,
                           int32_t* offsets, int32_t* item_start, int rows_per_item,
                           int32_t* token_lists, int32_t* aligned_lists, int window_groups,
@@ -255,13 +266,14 @@ int router_fused_split(const dmoe_layer& L, int T);
 bool router_sliced(const dmoe_layer& L);
 void launch_router_sliced(const dmoe_layer& L, const void* x, int T, void* hid, float* scores,
                           hipStream_t s);
+// (sets, here and below: the gate leaves the token sets of token_sets.h in the rows of counts)
 // Small and medium batches of a router whose first matrix takes 512 KB or more: the hidden rows (a [T][d_h] bf16 buffer) in one launch, the
 // scores and the gate in another; the bits of launch_router_fused with the gate.
 bool router_two_launches(const dmoe_layer& L, int T);
 void launch_router_two(const dmoe_layer& L, const void* x, int T, int split, void* hid, float* scores, float tau,
-                       uint64_t* mask, int32_t* group_cnt, hipStream_t s);
+                       uint64_t* mask, int32_t* group_cnt, bool sets, hipStream_t s);
 void launch_router_fused(const dmoe_layer& L, const void* x, int T, int split, float* scores,
-                         float tau, uint64_t* mask, int32_t* group_cnt, hipStream_t s);
+                         float tau, uint64_t* mask, int32_t* group_cnt, bool sets, hipStream_t s);
 
 // ---- small-token path (use_small_path in api.hip): up to kGroupMax layers of one shape per launch ------
 // The attention projections Q, K and V are three converted layers with the same input (Sec. 3.5),
@@ -320,7 +332,7 @@ void launch_pack_bf16(const dmoe_layer& L, void* packed, hipStream_t s);
 // H holds one row of m_pad hidden activations per list row (layout: see ffn_bf16.hip).
 // alist is the work-item-aligned token list (see select.hip); its index is the row index of H.
 void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* witem,
-                    const int32_t* wfirst, const void* worder, const int32_t* alist, void* H, hipStream_t s);
+                    const int32_t* wfirst, const void* worder, const int32_t* alist, const TokenSets& S, void* H, hipStream_t s);
 // Down-projection and merge (down_bf16.hip): mask is the token-major selection bitmask that the
 // lists were built from; group_off[g][e] = rows of expert e that belong to tokens before group g.
 bool down_bf16_supported(const dmoe_layer& L);
@@ -406,7 +418,7 @@ void launch_pack_x8(const dmoe_layer& L, void* packed, hipStream_t s);
 // H8 / hs8 non-null: the rows go out quantised for the 8-bit
 // down-projection instead of as bf16 rows in H.
 void launch_up_x8(const dmoe_layer& L, const uint8_t* x8, const float* xscale, int T,
-                  const int32_t* witem, const void* worder, const int32_t* alist, void* H,
+                  const int32_t* witem, const void* worder, const int32_t* alist, const TokenSets& S, void* H,
                   uint8_t* H8, uint8_t* hs8, hipStream_t s);
 
 bool experts_bf16_supported(const dmoe_layer& L);

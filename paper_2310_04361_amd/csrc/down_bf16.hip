@@ -125,7 +125,8 @@ __global__ __launch_bounds__(256, WPS) void down_bf16_kernel(
     long long max_pairs, int parts, float* __restrict__ partial) {
     static_assert((kDnTrip * KSP) % R == 0 && 32 % (kDnTrip * G) == 0, "loop trip");
     static_assert(UPE == 1 || (UPE == 2 && G == 1), "two units per expert: one unit per stage");
-    if (offsets[E] <= max_pairs) return;  // sparse enough for the other kernel (down_quad_bf16.hip)
+    // sparse enough for the other kernel (down_quad_bf16.hip); -1: there is no other, and offsets need not exist
+    if (max_pairs >= 0 && offsets[E] <= max_pairs) return;
     constexpr int PG = 2 * KSP / G;                  // pieces per expert
     constexpr int kImage = kDnTiles * KSP * 1024;    // the B tiles of one stage
     constexpr int PH = kDnTrip * KSP;                // phases per loop trip

@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "pack.h"
+#include "token_sets.h"
 
 namespace dmoe {
 
@@ -144,22 +145,25 @@ struct XRows {
 // (lane = (row % 8, 16-byte piece of the 128-byte row segment)) and of the weight fragments
 // while the MFMAs run on the current block out of LDS / registers.
 // PTR: the weights by address and all lanes, with as many registers as one wavefront per SIMD may have.
-template <int MT, bool GATED, int TT, int NBUF, bool NEAR, bool PTR = false>
-__global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
+// SETS: a small batch, whose items come from the token sets (token_sets.h) instead of the lists.
+template <int MT, bool GATED, int TT, int NBUF, bool NEAR, bool PTR = false, bool SETS = false>
+__global__ __launch_bounds__(256, NBUF == 1 ? 3 : (SETS ? 2 : 1)) void up_bf16_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf,
     const __bf16* __restrict__ wgatef, const __bf16* __restrict__ b_up,
     const int32_t* __restrict__ witem, const int32_t* __restrict__ wfirst, int NW,
-    const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act) {
+    const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act, const TokenSets S) {
     constexpr int BR = GATED ? 2 : 1;
     constexpr int KS = MT / 2;
     constexpr int UR = TT * 16;
     constexpr int NL = TT * 2;  // x load instructions per K block: 8 rows x 128 bytes each
+    static_assert(!SETS || UR == 64, "a wavefront's list of rows");
     extern __shared__ char smem[];
     int32_t* s_wit = reinterpret_cast<int32_t*>(smem);  // witem[w][0..E], then wfirst[w][0..E-1]
     int32_t* s_wf = s_wit + (E + 1);
-    const int items_bytes = ((2 * E + 1) * 4 + 15) & ~15;
+    const int items_bytes = SETS ? 4 * 64 * 4 : ((2 * E + 1) * 4 + 15) & ~15;
     const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
     const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int32_t* s_list = s_wit + 64 * wave_in_block;  // SETS: the rows of this wavefront's item
     char* xs = smem + items_bytes + wave_in_block * (NBUF * UR * kUpRowBytes);
     const int NK32 = d / 32, NKB = d / 64;
     const int ld_row = lane >> 3, ld_piece = lane & 7;
@@ -171,12 +175,15 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
     // Of fewer than eight windows each belongs to several XCDs, which share its items: neighbouring
     // experts on one XCD.
     const int xcd = blockIdx.x & 7, shares = NW < 8 ? 8 / NW : 1, share = xcd % shares;
-    for (int wdx = xcd / shares; wdx < NW; wdx += 8) {
-    __syncthreads();  // the previous window's table is no longer read
-    for (int i = threadIdx.x; i <= 2 * E; i += blockDim.x)
-        s_wit[i] = i <= E ? witem[(size_t)wdx * (E + 1) + i] : wfirst[(size_t)wdx * E + (i - E - 1)];
-    __syncthreads();
-    const long long all = s_wit[E];
+    const int sets_items = SETS ? (S.T + UR - 1) / UR : 0;  // an expert's most
+    for (int wdx = SETS ? 0 : xcd / shares; wdx < (SETS ? 1 : NW); wdx += 8) {
+    if (!SETS) {
+        __syncthreads();  // the previous window's table is no longer read
+        for (int i = threadIdx.x; i <= 2 * E; i += blockDim.x)
+            s_wit[i] = i <= E ? witem[(size_t)wdx * (E + 1) + i] : wfirst[(size_t)wdx * E + (i - E - 1)];
+        __syncthreads();
+    }
+    const long long all = SETS ? 0 : s_wit[E];
     const int first = (int)(all * share / shares), total = (int)(all * (share + 1) / shares);
     const int n_waves = (int)(gridDim.x >> 3) * 4, wave = wave_of(total - first, wave_in_block, n_waves);
     // item jj: its expert is the last e with s_wit[e] <= jj
@@ -190,9 +197,22 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
         item = s_wf[lo] + (jj - s_wit[lo]);
     };
     int j = first + wave;
-    if (j < total) {
+    SetItems si;
+    if (SETS ? si.start(S, E, wave_in_block, UR) : j < total) {
         int e, item;
-        locate(j, e, item);
+        if (SETS) {
+            e = si.e;
+            item = e * sets_items + si.item;
+        } else {
+            locate(j, e, item);
+        }
+        // the item's rows that this lane gathers
+        auto tokens_of = [&](int it, int (&tok)[NL]) {
+            if (SETS) si.tok.list<64, 64>(S.T, UR * si.item, s_list, [](int r) { return r; });
+            const int32_t* tl = (SETS ? s_list : alist + (size_t)it * UR) + ld_row;
+#pragma unroll
+            for (int i = 0; i < NL; ++i) tok[i] = tl[8 * i];
+        };
         // Rows of the aligned list past the expert's last token hold -1.
         const XRows<NEAR> xrows(x, d);
         uint32_t xoff[NL];
@@ -222,10 +242,8 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
             if (GATED) wf[BR - 1] = __builtin_amdgcn_make_buffer_rsrc((void*)(wgatef + at), 0, MT * NK32 * 1024, kRawBuffer);
         };
         {
-            const int32_t* tl = alist + (size_t)item * UR + ld_row;
             int tok[NL];
-#pragma unroll
-            for (int i = 0; i < NL; ++i) tok[i] = tl[8 * i];
+            tokens_of(item, tok);
             rows_from(tok);
         }
         weights_of(e);
@@ -311,15 +329,18 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
             load_x(NKB - 1);
             load_a(NKB - 1, a1);
             const int jn = j + n_waves;
-            const bool more = jn < total;
+            const bool more = SETS ? si.next(S, E, UR) : jn < total;
             int en = e, itemn = item;
-            if (more) locate(jn, en, itemn);
-            int tokn[NL];
-            {
-                const int32_t* tl = alist + (size_t)itemn * UR + ld_row;
-#pragma unroll
-                for (int i = 0; i < NL; ++i) tokn[i] = tl[8 * i];
+            if (more) {
+                if (SETS) {
+                    en = si.e;
+                    itemn = en * sets_items + si.item;
+                } else {
+                    locate(jn, en, itemn);
+                }
             }
+            int tokn[NL];
+            tokens_of(itemn, tokn);
             compute(0, a0);
             store_x(1);
             rows_from(tokn);
@@ -375,19 +396,21 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : 1) void up_bf16_kernel(
 // and issues a quarter / half of the MFMAs, and what remains is the gather of the x rows.  Same
 // work items and x staging as up_bf16_kernel<2, GATED, TT>; the H rows hold only the expert's pieces
 // (h_row_neurons).
-template <int TT, bool GATED, bool NEAR>
+template <int TT, bool GATED, bool NEAR, bool SETS>
 __global__ __launch_bounds__(256) void up_tiny_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wtf, const __bf16* __restrict__ b_up,
     const int32_t* __restrict__ witem, const int32_t* __restrict__ wfirst, int NW,
-    const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act, int row_neurons) {
+    const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act, int row_neurons, const TokenSets S) {
     constexpr int UR = TT * 16;
     constexpr int NL = TT * 2;
     extern __shared__ char smem[];
     int32_t* s_wit = reinterpret_cast<int32_t*>(smem);  // witem[w][0..E-1], then wfirst[w][0..E-1]
     int32_t* s_wf = s_wit + E;
-    const int items_bytes = (2 * E * 4 + 15) & ~15;
+    const int items_bytes = SETS ? 4 * 64 * 4 : (2 * E * 4 + 15) & ~15;
     const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
-    const int wave_in_block = threadIdx.x >> 6;
+    const int wave_in_block = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int32_t* s_list = s_wit + 64 * wave_in_block;  // SETS: the rows of this wavefront's item
+    static_assert(!SETS || UR == 64, "a wavefront's list of rows");
     // one staging buffer per wavefront (its LDS accesses keep their order, so a second one buys
     // nothing): with thousands of experts the work-item table already takes 16 KiB or more, and
     // the LDS left decides how many wavefronts a CU holds
@@ -397,23 +420,35 @@ __global__ __launch_bounds__(256) void up_tiny_kernel(
 
     // (who works on what: see up_bf16_kernel)
     const int xcd = blockIdx.x & 7, shares = NW < 8 ? 8 / NW : 1, share = xcd % shares;
-    for (int wdx = xcd / shares; wdx < NW; wdx += 8) {
-    __syncthreads();  // the previous window's table is no longer read
-    for (int i = threadIdx.x; i < 2 * E; i += blockDim.x)
-        s_wit[i] = i < E ? witem[(size_t)wdx * (E + 1) + i] : wfirst[(size_t)wdx * E + (i - E)];
-    const long long all = witem[(size_t)wdx * (E + 1) + E];
+    const int sets_items = SETS ? (S.T + UR - 1) / UR : 0;  // an expert's most
+    for (int wdx = SETS ? 0 : xcd / shares; wdx < (SETS ? 1 : NW); wdx += 8) {
+    if (!SETS) {
+        __syncthreads();  // the previous window's table is no longer read
+        for (int i = threadIdx.x; i < 2 * E; i += blockDim.x)
+            s_wit[i] = i < E ? witem[(size_t)wdx * (E + 1) + i] : wfirst[(size_t)wdx * E + (i - E)];
+    }
+    const long long all = SETS ? 0 : witem[(size_t)wdx * (E + 1) + E];
     const int first = (int)(all * share / shares), total = (int)(all * (share + 1) / shares);
     const int n_waves = (int)(gridDim.x >> 3) * 4, wave = wave_of(total - first, wave_in_block, n_waves);
-    __syncthreads();
-    for (int j = first + wave; j < total; j += n_waves) {
-        int lo = 0, hi = E;  // last e with s_wit[e] <= j
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (s_wit[mid] <= j) lo = mid; else hi = mid;
+    if (!SETS) __syncthreads();
+    SetItems si;
+    bool work = SETS ? si.start(S, E, wave_in_block, UR) : first + wave < total;
+    for (int j = first + wave; work; j += n_waves, work = SETS ? si.next(S, E, UR) : j < total) {
+        int e, item;
+        if (SETS) {
+            e = si.e;
+            item = e * sets_items + si.item;
+            si.tok.list<64, 64>(S.T, UR * si.item, s_list, [](int r) { return r; });
+        } else {
+            int lo = 0, hi = E;  // last e with s_wit[e] <= j
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (s_wit[mid] <= j) lo = mid; else hi = mid;
+            }
+            e = lo;
+            item = s_wf[e] + (j - s_wit[e]);
         }
-        const int e = lo;
-        const int item = s_wf[e] + (j - s_wit[e]);
-        const int32_t* tl = alist + (size_t)item * UR + ld_row;
+        const int32_t* tl = (SETS ? s_list : alist + (size_t)item * UR) + ld_row;
         // Valid rows are a prefix of the item and padding rows hold -1.  With thousands of experts
         // most items are part-filled (4096 tokens, 2048 experts, 7 % density: 36 of 64 rows), and
         // what the kernel spends is load instructions: a load whose eight rows are all padding is
@@ -798,26 +833,227 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     }
 }
 
-// ---- launchers ---------------------------------------------------------------------------------------
-size_t up_lds(const dmoe_layer& L, int TT, int NBUF) {  // the item table of a window and the staged rows
-    return ((2 * (size_t)L.n_experts + 1) * 4 + 15) / 16 * 16 + 4 * NBUF * (size_t)TT * 16 * kUpRowBytes;
+// The same for a small batch (token_sets.h): a workgroup of eight wavefronts has one item, of 128 TJ rows.  There are few items
+// -- one or two an expert -- so that a CU has one workgroup, and what bounds the kernel is how much of the weights is on
+// its way from HBM (D K blocks, in registers) and, for an expert of more than 128 rows, the LDS traffic of its rows.
+// Wavefront w has the 32-row tiles w & 3 and 4 + (w & 3) of the item, so that a part-filled item keeps all of them busy, and
+// half of the neurons; it works on as many tiles as there are.  256 gated experts of 64, d = 2048, against the kernel above: 120
+// tokens 35.1 -> 31.1 us (134 MB of weights: half of the workgroups end after 27), 333 tokens (125 rows an expert, up to
+// 250) 50.5 -> 43.4 (half end after 29, the fullest after 40), 512 tokens 50.3 -> 49.8; 24 plain ones of 128, 788 tokens 21.4 -> 12.5.
+// Slower: four wavefronts with all the neurons (47.5 at 333 tokens); spilled registers (57: a reload waits for all that is on its way).
+template <int MT, bool GATED, int TJ>
+__global__ __launch_bounds__(512, 2) void up_wide_sets_kernel(
+    const __bf16* __restrict__ x, const __bf16* __restrict__ wupf, const __bf16* __restrict__ wgatef,
+    const __bf16* __restrict__ b_up, __bf16* __restrict__ Hf, int d, int E, int m, int act, const TokenSets S) {
+    constexpr int BR = GATED ? 2 : 1;
+    constexpr int KS = MT / 2;
+    constexpr int NT = BR * MT;         // neuron tiles (of 16) per K step
+    constexpr int NJ = NT / 4;          // ... of 32, per wavefront
+    constexpr int WR = 32 * TJ;         // rows per pair of wavefronts
+    constexpr int UR = 4 * WR;          // rows per work item
+    constexpr int NWF = 2 * NT;         // weight fragments (1 KiB each) per K block
+    constexpr int NWL = NWF / 8;        // ... of which each wavefront copies every eighth
+    constexpr int D = 4;                // blocks on their way
+    static_assert(NJ == 2 && NWL == 2, "eight neuron tiles");
+    extern __shared__ char smem[];  // three K blocks
+    constexpr int kBuf = NWF * 1024 + 4 * WR * kUpRowBytes;  // a K block: its weights, then the rows of x
+    const int lane = threadIdx.x & 63, h = lane >> 5, c32 = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wt = w & 3, wn = w >> 2;
+    float* sbias = reinterpret_cast<float*>(smem + 3 * kBuf);  // [MT * 16]
+    int32_t* s_list = reinterpret_cast<int32_t*>(sbias + MT * 16) + WR * w;
+    const int NK32 = d / 32, NKB = d / 64;   // NKB: a multiple of D
+    const int ld_row = lane >> 3, ld_piece = lane & 7;
+    const int e = blockIdx.x % E, slot = blockIdx.x / E;
+    ExpertTokens tok;
+    tok.load(S, E, e, 256, w == 0 && slot == 0);
+    const int rows = tok.total - UR * slot;
+    if (rows <= 0) return;
+    // row 128 tj + 32 wt + c of the item is row 32 tj + c of the pair of wavefronts
+    tok.list<WR, UR>(S.T, UR * slot, s_list, [&](int r) { return ((r >> 5) & 3) == wt ? 32 * (r >> 7) + (r & 31) : -1; });
+    // Weight fragment f = (br * MT + mt) * 2 + ks of a K block; this wavefront copies the
+    // fragments f = 8 i + w: ks = w & 1, mt = (4 i) % MT + (w >> 1), br = (4 i) / MT.
+    const size_t we = (size_t)e * MT * NK32 * 512 + (size_t)(((w >> 1) * NK32 + (w & 1)) * 512 + lane * 8);
+    bf16x8 wr[D][NWL];
+    auto issue_w = [&](int i, int kb, bf16x8& r) {
+        const __bf16* base = (GATED && (4 * i) / MT == BR - 1) ? wgatef : wupf;
+        r = load8(base + we + (size_t)kb * 1024 + (size_t)((4 * i) % MT) * NK32 * 512);
+    };
+    auto park_w = [&](int i, char* buf, const bf16x8& r) {
+        *reinterpret_cast<bf16x8*>(buf + (8 * i + w) * 1024 + lane * 16) = r;
+    };
+    if (!GATED && (int)threadIdx.x < MT * 16)  // plain experts: the biases, by neuron
+        sbias[threadIdx.x] = b_up ? (float)b_up[(size_t)e * m + min((int)threadIdx.x, m - 1)] : 0.0f;
+    const size_t row0 = (size_t)e * ((S.T + 255) / 256) * 256 + (size_t)slot * UR;
+    // this wavefront's neuron tiles: an up tile and the gate tile of the same neurons, or two neighbouring ones
+    auto tile_of = [&](int nj) { return GATED ? 2 * nj + wn : 2 * wn + nj; };
+
+    // all of the item for a wavefront of NTJ tiles
+    auto work = [&](auto ntj_c) {
+        constexpr int NTJ = decltype(ntj_c)::value, NA = NTJ ? NTJ : 1;
+        constexpr int NL = 2 * NTJ, NLA = NL ? NL : 1;  // x load instructions per K block: 8 rows x 128 bytes each
+        uint32_t xoff[NLA];  // (none: token 0, rows that nobody merges)
+#pragma unroll
+        for (int i = 0; i < NL; ++i) xoff[i] = (uint32_t)max(s_list[ld_row + 16 * i + 8 * wn], 0);
+        bf16x8 xr[D][NLA];
+        auto issue_x = [&](int i, int kb, bf16x8& r) {
+            r = load8(x + ((size_t)xoff[i] * (uint32_t)d + (uint32_t)(8 * ld_piece + 64 * kb)));
+        };
+        auto park_x = [&](int i, char* buf, const bf16x8& r) {
+            *reinterpret_cast<bf16x8*>(buf + NWF * 1024 + (wt * WR + ld_row + 16 * i + 8 * wn) * kUpRowBytes + ld_piece * 16) = r;
+        };
+#pragma unroll
+        for (int b = 0; b < D; ++b) {
+#pragma unroll
+            for (int i = 0; i < NWL; ++i) issue_w(i, b, wr[b][i]);
+#pragma unroll
+            for (int i = 0; i < NL; ++i) issue_x(i, b, xr[b][i]);
+        }
+        // operands of k-step s (16 wide)
+        struct Step {
+            bf16x8 a[NJ], b[NA];
+        };
+        auto read = [&](const char* buf, int s, Step& o) {
+#pragma unroll
+            for (int nj = 0; nj < NJ; ++nj)
+                o.a[nj] = *reinterpret_cast<const bf16x8*>(buf + (2 * tile_of(nj) + (c32 >> 4)) * 2048 + (s >> 1) * 1024 + (s & 1) * 512 +
+                                                           (h * 16 + (c32 & 15)) * 16);
+#pragma unroll
+            for (int tj = 0; tj < NTJ; ++tj)
+                o.b[tj] = *reinterpret_cast<const bf16x8*>(buf + NWF * 1024 + (wt * WR + 32 * tj + c32) * kUpRowBytes + h * 16 + s * 32);
+        };
+        f32x16 acc[NJ][NA];
+#pragma unroll
+        for (int nj = 0; nj < NJ; ++nj)
+#pragma unroll
+            for (int tj = 0; tj < NA; ++tj)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[nj][tj][r] = 0.f;
+        auto multiply = [&](const Step& o) {
+#pragma unroll
+            for (int nj = 0; nj < NJ; ++nj)
+#pragma unroll
+                for (int tj = 0; tj < NTJ; ++tj) acc[nj][tj] = mfma32(o.a[nj], o.b[tj], acc[nj][tj]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        char *cur = smem, *nxt = smem + kBuf, *then = smem + 2 * kBuf;
+#pragma unroll
+        for (int i = 0; i < NWL; ++i) {
+            park_w(i, cur, wr[0][i]);
+            issue_w(i, min(D, NKB - 1), wr[0][i]);
+        }
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            park_x(i, cur, xr[0][i]);
+            issue_x(i, min(D, NKB - 1), xr[0][i]);
+        }
+        lds_barrier();
+        Step o[2];
+        read(cur, 0, o[0]);
+        // A block: the next one is parked (register set R, into which block kb is then requested; kb < 0: none) while its
+        // first half is multiplied; the barrier; operands are read a k-step ahead.  (A wavefront that has passed the
+        // barrier may still be reading this block and a faster one parking the block after the next: three buffers.)
+        auto block = [&](auto i_c, auto park_c, int kb) {
+            constexpr int I = decltype(i_c)::value, R = (I + 1) % D;
+            constexpr bool PARK = decltype(park_c)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            read(cur, 1, o[1]);
+            if (PARK) {
+#pragma unroll
+                for (int i = 0; i < NWL; ++i) {
+                    park_w(i, nxt, wr[R][i]);
+                    if (kb >= 0) issue_w(i, kb, wr[R][i]);
+                }
+            }
+            multiply(o[0]);
+            read(cur, 2, o[0]);
+            if (PARK) {
+#pragma unroll
+                for (int i = 0; i < NL; ++i) {
+                    park_x(i, nxt, xr[R][i]);
+                    if (kb >= 0) issue_x(i, kb, xr[R][i]);
+                }
+            }
+            multiply(o[1]);
+            if (PARK) lds_barrier();
+            read(cur, 3, o[1]);
+            multiply(o[0]);
+            if (PARK) read(nxt, 0, o[0]);
+            multiply(o[1]);
+            char* const t = cur;
+            cur = nxt;
+            nxt = then;
+            then = t;
+        };
+        const std::true_type yes;
+        const std::integral_constant<int, 0> i0;
+        const std::integral_constant<int, 1> i1;
+        const std::integral_constant<int, 2> i2;
+        const std::integral_constant<int, 3> i3;
+        int kb0 = 0;
+        for (; kb0 + D < NKB; kb0 += D) {
+            block(i0, yes, kb0 + 5);
+            block(i1, yes, kb0 + 6);
+            block(i2, yes, kb0 + 7);
+            block(i3, yes, min(kb0 + 8, NKB - 1));  // (past the end: the last block again, never used)
+        }
+        block(i0, yes, -1);
+        block(i1, yes, -1);
+        block(i2, yes, -1);
+        block(i3, std::false_type{}, -1);
+        if constexpr (NTJ > 0) with_activation(act, [&](auto act_c) {
+            constexpr int ACT = decltype(act_c)::value;
+            // (which register is which neuron: see up_wide_bf16_kernel)
+#pragma unroll
+            for (int tj = 0; tj < NTJ; ++tj) {
+                __bf16* dst = Hf + (row0 + 128 * tj + 32 * wt + c32) * (KS * 32);
+#pragma unroll
+                for (int nj = 0; nj < (GATED ? 1 : 2); ++nj) {
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) {
+                        const int n0 = 8 * (4 * tile_of(nj) + 2 * half + h);
+                        bf16x8 hv;
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) {
+                            const int i = 4 * half + (r & 3) + 8 * (r >> 2);
+                            float v;
+                            if (GATED) v = activate_fast(ACT, acc[1][tj][i]) * acc[0][tj][i];
+                            else v = activate_fast(ACT, acc[nj][tj][i] + sbias[n0 + r]);
+                            if (n0 + r >= m) v = 0.0f;
+                            hv[r] = (__bf16)v;
+                        }
+                        *reinterpret_cast<bf16x8*>(dst + n0) = hv;
+                    }
+                }
+            }
+        });
+    };
+    // (every path has the same barriers)
+    if (TJ == 2 && rows > 128 + 32 * wt) work(std::integral_constant<int, TJ>{});
+    else if (rows > 32 * wt) work(std::integral_constant<int, 1>{});
+    else work(std::integral_constant<int, 0>{});
 }
 
-template <int MT, bool GATED, int TT, int NBUF, bool NEAR, bool PTR = false>
+// ---- launchers ---------------------------------------------------------------------------------------
+size_t up_lds(const dmoe_layer& L, int TT, int NBUF, bool sets) {  // the item table of a window (or four lists) and the staged rows
+    return (sets ? 4 * 64 * 4 : ((2 * (size_t)L.n_experts + 1) * 4 + 15) / 16 * 16) + 4 * NBUF * (size_t)TT * 16 * kUpRowBytes;
+}
+
+template <int MT, bool GATED, int TT, int NBUF, bool NEAR, bool PTR = false, bool SETS = false>
 void launch_up_t(const dmoe_layer& L, const void* x, const PackedLayout& P, const int32_t* witem,
-                 const int32_t* wfirst, int NW, const int32_t* alist, void* H, int grid,
+                 const int32_t* wfirst, int NW, const int32_t* alist, TokenSets S, void* H, int grid,
                  hipStream_t s) {
-    const size_t lds = up_lds(L, TT, NBUF);
+    if (SETS) grid = sets_grid(S, L.n_experts, 16 * TT, 256 * (NBUF == 1 ? 3 : 2));
+    const size_t lds = up_lds(L, TT, NBUF, SETS);
     static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
     std::call_once(attr_once, [&] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_bf16_kernel<MT, GATED, TT, NBUF, NEAR, PTR>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_bf16_kernel<MT, GATED, TT, NBUF, NEAR, PTR, SETS>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
     const char* pk = static_cast<const char*>(L.packed);
-    launch_kernel(up_bf16_kernel<MT, GATED, TT, NBUF, NEAR, PTR>, grid, 256, lds, s, 
+    launch_kernel(up_bf16_kernel<MT, GATED, TT, NBUF, NEAR, PTR, SETS>, grid, 256, lds, s, 
         (const __bf16*)x, (const __bf16*)(pk + P.wupf), (const __bf16*)(pk + P.wgatef),
         (const __bf16*)L.b_up, witem, wfirst, NW, alist, (__bf16*)H, L.d_model, L.n_experts,
-        L.expert_size, L.act);
+        L.expert_size, L.act, S);
 }
 
 template <int MT, bool GATED, int TT>
@@ -836,6 +1072,30 @@ void launch_up_wide_t(const dmoe_layer& L, const void* x, const PackedLayout& P,
         (const __bf16*)x, (const __bf16*)(pk + P.wupf), (const __bf16*)(pk + P.wgatef),
         (const __bf16*)L.b_up, witem, (const int2*)worder, alist, (__bf16*)H, L.d_model, L.n_experts,
         L.expert_size, L.act);
+}
+
+template <int MT, bool GATED, int TJ>
+void launch_up_wide_sets_t(const dmoe_layer& L, const void* x, const PackedLayout& P, const TokenSets& S, void* H, hipStream_t s) {
+    constexpr int NWF = 2 * (GATED ? 2 : 1) * MT;
+    const size_t lds = 3 * (NWF * 1024 + 4 * (size_t)TJ * 32 * kUpRowBytes) + MT * 16 * sizeof(float) + 8 * 32 * TJ * sizeof(int32_t);
+    static_assert(3 * (NWF * 1024 + 4 * TJ * 32 * kUpRowBytes) + MT * 16 * 4 + 8 * 32 * TJ * 4 <= 160 * 1024, "LDS");
+    static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
+    std::call_once(attr_once, [&] {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_wide_sets_kernel<MT, GATED, TJ>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    });
+    const char* pk = static_cast<const char*>(L.packed);
+    launch_kernel(up_wide_sets_kernel<MT, GATED, TJ>, L.n_experts * div_up(S.T, 128 * TJ), 512, lds, s, (const __bf16*)x,
+                  (const __bf16*)(pk + P.wupf), (const __bf16*)(pk + P.wgatef), (const __bf16*)L.b_up, (__bf16*)H, L.d_model,
+                  L.n_experts, L.expert_size, L.act, S);
+}
+
+template <int MT, bool GATED>
+void launch_up_wide_sets(const dmoe_layer& L, const void* x, const PackedLayout& P, const TokenSets& S, void* H, hipStream_t s) {
+    // With few experts items of 128 rows, as long as every one has a CU: 24 x 128 experts, 788 tokens, a quarter of them per token, 12.5 us
+    // against 17.7.  Otherwise the experts of more than 128 rows would wait for a second round: 256 x 64, 200 tokens 41.6 against 36.6.
+    if (L.n_experts * div_up(S.T, 128) <= 256) launch_up_wide_sets_t<MT, GATED, 1>(L, x, P, S, H, s);
+    else launch_up_wide_sets_t<MT, GATED, 2>(L, x, P, S, H, s);
 }
 
 }  // namespace
@@ -933,7 +1193,7 @@ int up_window_groups(const dmoe_layer& L, int T) {
 }
 
 void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* witem,
-                    const int32_t* wfirst, const void* worder, const int32_t* alist, void* H,
+                    const int32_t* wfirst, const void* worder, const int32_t* alist, const TokenSets& S, void* H,
                     hipStream_t s) {
     LaunchTimer tm(kSlotUp, s);
     const PackedLayout P = packed_layout(L);
@@ -946,19 +1206,23 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
     if (up_rows_bf16(L) == 256) {  // wide experts: weights shared through LDS
         const int wgrid = round_up(
             (int)std::min<long long>((long long)T * L.n_experts / 256 + L.n_experts, 512), 8);
-        if (L.gated) launch_up_wide_t<4, true, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
+        if (S.sets && L.gated) launch_up_wide_sets<4, true>(L, x, P, S, H, s);
+        else if (S.sets) launch_up_wide_sets<8, false>(L, x, P, S, H, s);
+        else if (L.gated) launch_up_wide_t<4, true, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
         else launch_up_wide_t<8, false, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
         return;
     }
     const bool near = (size_t)T * L.d_model * 2 < ((size_t)1 << 31);  // (XRows)
     if (up_tiny_supported(L)) {
         constexpr int TT = 4;
-        const size_t lds = (2 * (size_t)L.n_experts * 4 + 15) / 16 * 16 +
+        const size_t lds = (S.sets ? 4 * 64 * 4 : (2 * (size_t)L.n_experts * 4 + 15) / 16 * 16) +
                            4 * (size_t)TT * 16 * kUpRowBytes;
         // as many workgroups per CU as LDS allows, at most the three that the registers allow
         // (squeezed into a fourth wavefront per SIMD's share of registers the kernel got slower)
         const int per_cu = std::max(1, std::min(3, (int)(160 * 1024 / lds)));
-        const int grid = round_up((int)std::min<long long>(worst, 256 * per_cu), 8);
+        TokenSets Sg = S;
+        const int grid = S.sets ? sets_grid(Sg, L.n_experts, 64, 256 * per_cu)
+                                : round_up((int)std::min<long long>(worst, 256 * per_cu), 8);
         const char* pk = static_cast<const char*>(L.packed);
         auto go = [&](auto kernel, std::once_flag& attr_once) {
             std::call_once(attr_once, [&] {  // kernel attributes: once per process, thread-safe
@@ -967,38 +1231,42 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
             });
             launch_kernel(kernel, grid, 256, lds, s, (const __bf16*)x, (const __bf16*)(pk + P.wtinyf),
                           L.gated ? nullptr : (const __bf16*)L.b_up, witem, wfirst, NW, alist, (__bf16*)H, L.d_model,
-                          L.n_experts, L.expert_size, L.act, h_row_neurons(L));
+                          L.n_experts, L.expert_size, L.act, h_row_neurons(L), Sg);
         };
-        static std::once_flag once[4];
-        if (L.gated) {
-            if (near) go(up_tiny_kernel<TT, true, true>, once[0]);
-            else go(up_tiny_kernel<TT, true, false>, once[1]);
+        static std::once_flag once[6];
+        if (S.sets) {  // (so few tokens that x is always near)
+            if (L.gated) go(up_tiny_kernel<TT, true, true, true>, once[4]);
+            else go(up_tiny_kernel<TT, false, true, true>, once[5]);
+        } else if (L.gated) {
+            if (near) go(up_tiny_kernel<TT, true, true, false>, once[0]);
+            else go(up_tiny_kernel<TT, true, false, false>, once[1]);
         } else {
-            if (near) go(up_tiny_kernel<TT, false, true>, once[2]);
-            else go(up_tiny_kernel<TT, false, false>, once[3]);
+            if (near) go(up_tiny_kernel<TT, false, true, false>, once[2]);
+            else go(up_tiny_kernel<TT, false, false, false>, once[3]);
         }
         return;
     }
     // (gated experts of 64 and plain ones of 128 are wide)
-    auto go = [&](auto near_c) {
-        constexpr bool kNear = decltype(near_c)::value;
+    auto go = [&](auto near_c, auto sets_c) {
+        constexpr bool kNear = decltype(near_c)::value, kSets = decltype(sets_c)::value;
         if (L.gated) {
             // One workgroup per CU, for want of LDS beside the item table (more than 820 experts): then the registers that keep a second
             // one away are free.  992 tokens x 1627 experts of 32, d = 2048, all selected 1073 / 1002 us.  But by address padding rows
             // move as well: 737 x 1436 of 16, d = 1024, 60 % 183 / 238; 49 x 114 of 16, d = 3072 37.7 / 42.1.  Elsewhere two
             // share a CU: 4096 tokens x 256 of 32, d = 2048, 30 % 122 / 164; 300 tokens 34 / 57.
-            if (up_lds(L, 4, 2) > 80 * 1024 && L.expert_size > 24) launch_up_t<2, true, 4, 2, false, true>(L, x, P, witem, wfirst, NW, alist, H, grid, s);
-            else launch_up_t<2, true, 4, 2, kNear>(L, x, P, witem, wfirst, NW, alist, H, grid, s);
+            if (up_lds(L, 4, 2, kSets) > 80 * 1024 && L.expert_size > 24) launch_up_t<2, true, 4, 2, false, true>(L, x, P, witem, wfirst, NW, alist, S, H, grid, s);
+            else launch_up_t<2, true, 4, 2, kNear, false, kSets>(L, x, P, witem, wfirst, NW, alist, S, H, grid, s);
         } else if (mt == 2) {
             // 32-neuron rows: one staging buffer, three workgroups per CU
             const int grid3 = round_up((int)std::min<long long>(worst, 256 * 3), 8);
-            launch_up_t<2, false, 4, 1, kNear>(L, x, P, witem, wfirst, NW, alist, H, grid3, s);
+            launch_up_t<2, false, 4, 1, kNear, false, kSets>(L, x, P, witem, wfirst, NW, alist, S, H, grid3, s);
         } else {
-            launch_up_t<4, false, 4, 2, kNear>(L, x, P, witem, wfirst, NW, alist, H, grid, s);
+            launch_up_t<4, false, 4, 2, kNear, false, kSets>(L, x, P, witem, wfirst, NW, alist, S, H, grid, s);
         }
     };
-    if (near) go(std::true_type{});
-    else go(std::false_type{});
+    if (S.sets) go(std::true_type{}, std::true_type{});  // (so few tokens that x is always near)
+    else if (near) go(std::true_type{}, std::false_type{});
+    else go(std::false_type{}, std::false_type{});
 }
 
 }  // namespace dmoe

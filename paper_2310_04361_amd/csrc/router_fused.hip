@@ -42,7 +42,7 @@ template <int NH, int ETW, int KBC, int TT, int MODE = kWhole>
 __global__ __launch_bounds__(256) void router_fused_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ r1f, const __bf16* __restrict__ r_b1,
     const __bf16* __restrict__ r2f, const __bf16* __restrict__ r_b2, float* __restrict__ scores,
-    int T, int d, int E, float tau, int do_select, uint64_t* __restrict__ mask,
+    int T, int d, int E, float tau, int do_select /* 2: token sets */, uint64_t* __restrict__ mask,
     int32_t* __restrict__ group_cnt, __bf16* __restrict__ hid_g, int dh_g, int tiles_y) {
     constexpr int dh = NH * 16, HT = NH / 4, TOK = 16 * TT;
     constexpr int NR = (TOK + 31) / 32;  // staging passes of 32 rows
@@ -336,13 +336,14 @@ __global__ __launch_bounds__(256) void router_fused_kernel(
             if (lane == b) col = bal;
         }
         const int e = 64 * wi + lane;
-        if ((lane >> 4) == w && e < E) group_cnt[(size_t)g * E + e] = __popcll(col);
+        // (two: token sets instead of their sizes, of 16 tokens a workgroup)
+        if ((lane >> 4) == w && e < E) group_cnt[(size_t)g * E + e] = TT == 1 && do_select == 2 ? (int32_t)col : __popcll(col);
     }
 }
 
 template <int NH, int ETW, int KBC, int TT>
 void launch_t3(const dmoe_layer& L, const void* x, int T, float* scores, float tau, uint64_t* mask,
-               int32_t* group_cnt, hipStream_t s) {
+               int32_t* group_cnt, bool sets, hipStream_t s) {
     const PackedLayout P = packed_layout(L);
     const int E = L.n_experts, W = div_up(E, 64);
     constexpr int TOK = 16 * TT;
@@ -357,23 +358,23 @@ void launch_t3(const dmoe_layer& L, const void* x, int T, float* scores, float t
     launch_kernel(router_fused_kernel<NH, ETW, KBC, TT>, div_up(T, TOK), 256, lds, s, 
         (const __bf16*)x, (const __bf16*)(pk + P.r1f), (const __bf16*)L.r_b1,
         (const __bf16*)(pk + P.r2f), (const __bf16*)L.r_b2, scores, T, L.d_model, E, tau,
-        mask != nullptr, mask, group_cnt, nullptr, 0, 0);
+        mask ? (sets ? 2 : 1) : 0, mask, group_cnt, nullptr, 0, 0);
 }
 
 template <int NH, int ETW>
 void launch_t2(const dmoe_layer& L, const void* x, int T, int split, float* scores, float tau,
-               uint64_t* mask, int32_t* group_cnt, hipStream_t s) {
+               uint64_t* mask, int32_t* group_cnt, bool sets, hipStream_t s) {
     constexpr int kBig = NH <= 8 ? 12 : (NH == 16 ? 8 : 4);
     // parts of a group per workgroup: only where workgroups are few (one per CU, nothing hides
     // the latency of an x chunk), and the fewer rows leave LDS for chunks of 1024 columns
     if (split == 4)
-        launch_t3<NH, ETW, 16, 1>(L, x, T, scores, tau, mask, group_cnt, s);
+        launch_t3<NH, ETW, 16, 1>(L, x, T, scores, tau, mask, group_cnt, sets, s);
     else if (split == 2)
-        launch_t3<NH, ETW, 16, 2>(L, x, T, scores, tau, mask, group_cnt, s);
+        launch_t3<NH, ETW, 16, 2>(L, x, T, scores, tau, mask, group_cnt, sets, s);
     else if (kBig > 4 && div_up(T, 64) <= 512)
-        launch_t3<NH, ETW, kBig, 4>(L, x, T, scores, tau, mask, group_cnt, s);
+        launch_t3<NH, ETW, kBig, 4>(L, x, T, scores, tau, mask, group_cnt, sets, s);
     else
-        launch_t3<NH, ETW, 4, 4>(L, x, T, scores, tau, mask, group_cnt, s);
+        launch_t3<NH, ETW, 4, 4>(L, x, T, scores, tau, mask, group_cnt, sets, s);
 }
 
 // ---- hidden rows of a large router, tile by tile ------------------------------------------------------
@@ -569,13 +570,13 @@ __global__ __launch_bounds__(256) void router_small_scores_kernel(const SmallGro
 
 template <int NH>
 void launch_t(const dmoe_layer& L, const void* x, int T, int split, float* scores, float tau,
-              uint64_t* mask, int32_t* group_cnt, hipStream_t s) {
+              uint64_t* mask, int32_t* group_cnt, bool sets, hipStream_t s) {
     if (L.n_experts <= 128 || !mask)  // the router alone keeps no scores in registers
-        launch_t2<NH, 2>(L, x, T, split, scores, tau, mask, group_cnt, s);
+        launch_t2<NH, 2>(L, x, T, split, scores, tau, mask, group_cnt, sets, s);
     else if (L.n_experts <= 256)
-        launch_t2<NH, 4>(L, x, T, split, scores, tau, mask, group_cnt, s);
+        launch_t2<NH, 4>(L, x, T, split, scores, tau, mask, group_cnt, sets, s);
     else
-        launch_t2<NH, 8>(L, x, T, split, scores, tau, mask, group_cnt, s);
+        launch_t2<NH, 8>(L, x, T, split, scores, tau, mask, group_cnt, sets, s);
 }
 
 }  // namespace
@@ -690,7 +691,7 @@ bool router_two_launches(const dmoe_layer& L, int T) {
 
 template <int NH, int ETW, int TT>
 static void launch_gate_rows(const dmoe_layer& L, int T, const __bf16* hid, float* scores, float tau, uint64_t* mask,
-                             int32_t* group_cnt, hipStream_t s) {
+                             int32_t* group_cnt, bool sets, hipStream_t s) {
     const PackedLayout P = packed_layout(L);
     const int E = L.n_experts, W = div_up(E, 64);
     constexpr int TOK = 16 * TT;
@@ -702,31 +703,31 @@ static void launch_gate_rows(const dmoe_layer& L, int T, const __bf16* hid, floa
     });
     launch_kernel(router_fused_kernel<NH, ETW, 4, TT, kScoresSlice>, div_up(T, TOK), 256, lds, s, nullptr, nullptr, nullptr,
                   (const __bf16*)(static_cast<const char*>(L.packed) + P.r2f), (const __bf16*)L.r_b2, scores, T, L.d_model, E,
-                  tau, 1, mask, group_cnt, const_cast<__bf16*>(hid), L.router_hidden, div_up(E, 16));
+                  tau, sets ? 2 : 1, mask, group_cnt, const_cast<__bf16*>(hid), L.router_hidden, div_up(E, 16));
 }
 template <int NH, int ETW>
 static void launch_gate_split(const dmoe_layer& L, int T, int split, const __bf16* hid, float* scores, float tau,
-                              uint64_t* mask, int32_t* group_cnt, hipStream_t s) {
-    if (split == 4) launch_gate_rows<NH, ETW, 1>(L, T, hid, scores, tau, mask, group_cnt, s);
-    else if (split == 2) launch_gate_rows<NH, ETW, 2>(L, T, hid, scores, tau, mask, group_cnt, s);
-    else launch_gate_rows<NH, ETW, 4>(L, T, hid, scores, tau, mask, group_cnt, s);
+                              uint64_t* mask, int32_t* group_cnt, bool sets, hipStream_t s) {
+    if (split == 4) launch_gate_rows<NH, ETW, 1>(L, T, hid, scores, tau, mask, group_cnt, sets, s);
+    else if (split == 2) launch_gate_rows<NH, ETW, 2>(L, T, hid, scores, tau, mask, group_cnt, sets, s);
+    else launch_gate_rows<NH, ETW, 4>(L, T, hid, scores, tau, mask, group_cnt, sets, s);
 }
 template <int NH>
 static void launch_gate(const dmoe_layer& L, int T, int split, const __bf16* hid, float* scores, float tau, uint64_t* mask,
-                        int32_t* group_cnt, hipStream_t s) {
-    if (L.n_experts <= 128) launch_gate_split<NH, 2>(L, T, split, hid, scores, tau, mask, group_cnt, s);
-    else if (L.n_experts <= 256) launch_gate_split<NH, 4>(L, T, split, hid, scores, tau, mask, group_cnt, s);
-    else launch_gate_split<NH, 8>(L, T, split, hid, scores, tau, mask, group_cnt, s);
+                        int32_t* group_cnt, bool sets, hipStream_t s) {
+    if (L.n_experts <= 128) launch_gate_split<NH, 2>(L, T, split, hid, scores, tau, mask, group_cnt, sets, s);
+    else if (L.n_experts <= 256) launch_gate_split<NH, 4>(L, T, split, hid, scores, tau, mask, group_cnt, sets, s);
+    else launch_gate_split<NH, 8>(L, T, split, hid, scores, tau, mask, group_cnt, sets, s);
 }
 
 void launch_router_two(const dmoe_layer& L, const void* x, int T, int split, void* hid, float* scores, float tau,
-                       uint64_t* mask, int32_t* group_cnt, hipStream_t s) {
+                       uint64_t* mask, int32_t* group_cnt, bool sets, hipStream_t s) {
     LaunchTimer tm(kSlotRouter, s);
     launch_router_hidden(L, x, T, hid, s);
     const __bf16* h = (const __bf16*)hid;
-    if (L.router_hidden == 128) launch_gate<8>(L, T, split, h, scores, tau, mask, group_cnt, s);
-    else if (L.router_hidden == 256) launch_gate<16>(L, T, split, h, scores, tau, mask, group_cnt, s);
-    else launch_gate<32>(L, T, split, h, scores, tau, mask, group_cnt, s);
+    if (L.router_hidden == 128) launch_gate<8>(L, T, split, h, scores, tau, mask, group_cnt, sets, s);
+    else if (L.router_hidden == 256) launch_gate<16>(L, T, split, h, scores, tau, mask, group_cnt, sets, s);
+    else launch_gate<32>(L, T, split, h, scores, tau, mask, group_cnt, sets, s);
 }
 
 void launch_router_sliced(const dmoe_layer& L, const void* x, int T, void* hid, float* scores,
@@ -748,13 +749,13 @@ int router_fused_split(const dmoe_layer&, int T) {
 }
 
 void launch_router_fused(const dmoe_layer& L, const void* x, int T, int split, float* scores,
-                         float tau, uint64_t* mask, int32_t* group_cnt, hipStream_t s) {
+                         float tau, uint64_t* mask, int32_t* group_cnt, bool sets, hipStream_t s) {
     LaunchTimer tm(kSlotRouter, s);
     switch (L.router_hidden) {
-    case 64: launch_t<4>(L, x, T, split, scores, tau, mask, group_cnt, s); break;
-    case 128: launch_t<8>(L, x, T, split, scores, tau, mask, group_cnt, s); break;
-    case 256: launch_t<16>(L, x, T, split, scores, tau, mask, group_cnt, s); break;
-    case 512: launch_t<32>(L, x, T, split, scores, tau, mask, group_cnt, s); break;
+    case 64: launch_t<4>(L, x, T, split, scores, tau, mask, group_cnt, sets, s); break;
+    case 128: launch_t<8>(L, x, T, split, scores, tau, mask, group_cnt, sets, s); break;
+    case 256: launch_t<16>(L, x, T, split, scores, tau, mask, group_cnt, sets, s); break;
+    case 512: launch_t<32>(L, x, T, split, scores, tau, mask, group_cnt, sets, s); break;
     default: break;  // refused by router_fused_supported
     }
 }

@@ -43,6 +43,18 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t v, int lane) {
     return out;
 }
 
+// The group's tokens that keep expert e: their number to row g of the table, or (sets, see token_sets.h) they
+// themselves, 16 tokens a row, to the rows 4 g .. 4 g + 3 of it.
+__device__ __forceinline__ void store_group(int32_t* __restrict__ cnt, int g, int T, int E, int e, uint64_t col, bool sets) {
+    if (!sets) {
+        cnt[(size_t)g * E + e] = __popcll(col);
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (16 * (4 * g + i) < T) cnt[(size_t)(4 * g + i) * E + e] = (int32_t)((col >> (16 * i)) & 0xffffu);
+}
+
 // Per-group expert counts from the mask words: one wavefront per (group of 64 tokens, mask word),
 // lane = token.  The ballot transpose gives, for every expert of the word, the 64-bit set of the
 // group's tokens that keep it: its population count goes to group_cnt[g][e], the set itself to
@@ -50,7 +62,7 @@ __device__ __forceinline__ uint64_t transpose64(uint64_t v, int lane) {
 __global__ __launch_bounds__(256) void count_from_mask_kernel(const uint64_t* __restrict__ mask,
                                                               int32_t* __restrict__ group_cnt,
                                                               uint64_t* __restrict__ colmask,
-                                                              int T, int E, int W) {
+                                                              int T, int E, int W, bool sets) {
     const int lane = lane_id();
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int NG = (T + kGroup - 1) / kGroup;
@@ -61,7 +73,7 @@ __global__ __launch_bounds__(256) void count_from_mask_kernel(const uint64_t* __
     const uint64_t col = transpose64(t < T ? mask[(size_t)t * W + w] : 0ull, lane);
     const int e = 64 * w + lane;
     if (e < E) {
-        group_cnt[(size_t)g * E + e] = __popcll(col);
+        store_group(group_cnt, g, T, E, e, col, sets);
         if (colmask) colmask[(size_t)g * E + e] = col;
     }
 }
@@ -108,7 +120,7 @@ __global__ __launch_bounds__(256) void tau_mask_kernel(const float* __restrict__
 // it is reading the scores.
 template <int CH>
 __global__ __launch_bounds__(1024) void gate_counts_kernel(const float* __restrict__ scores, uint64_t* __restrict__ mask,
-                                                           int32_t* __restrict__ cnt, int T, int E, int W, float tau) {
+                                                           int32_t* __restrict__ cnt, int T, int E, int W, float tau, bool sets) {
     extern __shared__ uint64_t words[];  // [16][W]
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = blockIdx.x * 16 + w;
@@ -139,10 +151,10 @@ __global__ __launch_bounds__(1024) void gate_counts_kernel(const float* __restri
     __syncthreads();
     for (int c = w; c < W; c += 16) {
         const int e = 64 * c + lane;
-        int n = 0;
+        int set = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) n += (int)(words[i * W + c] >> lane) & 1;
-        if (e < E) cnt[(size_t)blockIdx.x * E + e] = n;
+        for (int i = 0; i < 16; ++i) set |= ((int)(words[i * W + c] >> lane) & 1) << i;
+        if (e < E) cnt[(size_t)blockIdx.x * E + e] = sets ? set : __popc(set);
     }
 }
 
@@ -289,7 +301,7 @@ template <bool CHOOSE>
 __global__ __launch_bounds__(256) void lists_finish_kernel(const int32_t* __restrict__ offsets,
                                                            const uint8_t* __restrict__ bytes, int T, int E, int W,
                                                            int Tp, uint64_t* __restrict__ mask,
-                                                           int32_t* __restrict__ group_cnt, long long bits_max) {
+                                                           int32_t* __restrict__ group_cnt, bool sets, long long bits_max) {
     const int lane = lane_id();
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const int NG = (T + kGroup - 1) / kGroup;
@@ -298,7 +310,7 @@ __global__ __launch_bounds__(256) void lists_finish_kernel(const int32_t* __rest
     const int e = 64 * w + lane, t = g * kGroup + lane;
     if (!lists_by_bytes<CHOOSE>(offsets, T, E, bytes, bits_max)) {
         const uint64_t set = transpose64(t < T ? mask[(size_t)t * W + w] : 0ull, lane);
-        if (e < E) group_cnt[(size_t)g * E + e] = __popcll(set);
+        if (e < E) store_group(group_cnt, g, T, E, e, set, sets);
         return;
     }
     uint64_t set = 0;
@@ -312,7 +324,7 @@ __global__ __launch_bounds__(256) void lists_finish_kernel(const int32_t* __rest
             set |= ((v[i].x * 0x0102040810204080ull) >> 56) << (16 * i);
             set |= ((v[i].y * 0x0102040810204080ull) >> 56) << (16 * i + 8);
         }
-        group_cnt[(size_t)g * E + e] = __popcll(set);
+        store_group(group_cnt, g, T, E, e, set, sets);
     }
     const uint64_t word = transpose64(set, lane);
     if (t < T) mask[(size_t)t * W + w] = word;
@@ -665,7 +677,7 @@ __global__ __launch_bounds__(256) void fill_lists_kernel(
 }  // namespace
 
 void launch_mask_from_scores(const float* scores, int T, int E, float tau, uint64_t* mask,
-                             int32_t* k_per_token, int32_t* group_off, uint64_t* colmask,
+                             int32_t* k_per_token, int32_t* group_off, uint64_t* colmask, bool sets,
                              hipStream_t s) {
     const int W = div_up(E, 64), NG = div_up(T, kGroup);
     LaunchTimer tm(kSlotMask, s);
@@ -683,7 +695,7 @@ void launch_mask_from_scores(const float* scores, int T, int E, float tau, uint6
     else if (W <= 32) launch_kernel(tau_mask_kernel<32>, grid, 256, 0, s, scores, mask, k_per_token, T, E, W, tau);
     else launch_kernel(tau_mask_kernel<64>, grid, 256, 0, s, scores, mask, k_per_token, T, E, W, tau);
     if (!group_off && !colmask) return;  // nobody reads the counts
-    launch_kernel(count_from_mask_kernel, div_up(NG * W, 4), 256, 0, s, mask, group_off, colmask, T, E, W);
+    launch_kernel(count_from_mask_kernel, div_up(NG * W, 4), 256, 0, s, mask, group_off, colmask, T, E, W, sets);
 }
 
 // 16 tokens per workgroup, four rows of counts per group: where the scan over the groups is a launch of its own anyway
@@ -694,11 +706,11 @@ bool gate_counts_supported(int T, int E) {
     return !fold_scan(T, E, 1) && div_up(T, kGroup) < 192;
 }
 
-void launch_gate_counts(const float* scores, int T, int E, float tau, uint64_t* mask, int32_t* cnt, hipStream_t s) {
+void launch_gate_counts(const float* scores, int T, int E, float tau, uint64_t* mask, int32_t* cnt, bool sets, hipStream_t s) {
     const int W = div_up(E, 64);
     LaunchTimer tm(kSlotMask, s);
     auto go = [&](auto kernel) {
-        launch_kernel(kernel, div_up(T, 16), 1024, sizeof(uint64_t) * 16 * W, s, scores, mask, cnt, T, E, W, tau);
+        launch_kernel(kernel, div_up(T, 16), 1024, sizeof(uint64_t) * 16 * W, s, scores, mask, cnt, T, E, W, tau, sets);
     };
     if (W <= 16) go(gate_counts_kernel<16>);
     else if (W <= 32) go(gate_counts_kernel<32>);
@@ -712,15 +724,15 @@ void launch_select_small_group(const dmoe_layer& L, const SmallGroup& G, int n_l
     launch_kernel(select_small_group_kernel, dim3(1, 1, n_layers), 1024, sizeof(uint64_t) * 16 * W, s, G, T, E, W);
 }
 
-void launch_counts_from_mask(const uint64_t* mask, int T, int E, int32_t* group_off, uint64_t* colmask,
+void launch_counts_from_mask(const uint64_t* mask, int T, int E, int32_t* group_off, uint64_t* colmask, bool sets,
                              hipStream_t s) {
     const int W = div_up(E, 64), NG = div_up(T, kGroup);
     LaunchTimer tm(kSlotMask, s);
-    launch_kernel(count_from_mask_kernel, div_up(NG * W, 4), 256, 0, s, mask, group_off, colmask, T, E, W);
+    launch_kernel(count_from_mask_kernel, div_up(NG * W, 4), 256, 0, s, mask, group_off, colmask, T, E, W, sets);
 }
 
 void launch_mask_from_lists(const int32_t* offsets, const int32_t* lists, int T, int E,
-                            uint64_t* mask, int32_t* group_off, uint64_t* colmask, void* scratch,
+                            uint64_t* mask, int32_t* group_off, uint64_t* colmask, bool sets, void* scratch,
                             size_t scratch_bytes, hipStream_t s) {
     const int W = div_up(E, 64), Tp = round_up(T, kGroup);
     // by bytes where there is room for them and the counts are all that is wanted besides the mask words
@@ -741,16 +753,16 @@ void launch_mask_from_lists(const int32_t* offsets, const int32_t* lists, int T,
                       reinterpret_cast<unsigned long long*>(mask), bits_max);
         if (bytes)
             launch_kernel(lists_finish_kernel<kChoose>, finish_grid, 256, 0, s, offsets, bytes, T, E, W, Tp, mask, group_off,
-                          bits_max);
+                          sets, bits_max);
         else
-            launch_counts_from_mask(mask, T, E, group_off, colmask, s);
+            launch_counts_from_mask(mask, T, E, group_off, colmask, sets, s);
     };
     if (choose) go(std::true_type{});
     else go(std::false_type{});
 }
 
 void launch_mask_topk(const float* scores, int T, int E, int k, uint64_t* mask,
-                      int32_t* k_per_token, int32_t* group_off, uint64_t* colmask, hipStream_t s) {
+                      int32_t* k_per_token, int32_t* group_off, uint64_t* colmask, bool sets, hipStream_t s) {
     const int W = div_up(E, 64), NG = div_up(T, kGroup);
     LaunchTimer tm(kSlotMask, s);
     const int grid = div_up(T, 4);
@@ -763,7 +775,7 @@ void launch_mask_topk(const float* scores, int T, int E, int k, uint64_t* mask,
     else launch_kernel(topk_mask_kernel<64>, grid, 256, 0, s, scores, mask, k_per_token, T, E, W, k);
     if (!group_off && !colmask) return;  // nobody reads the counts
     // counts per (group, expert) and, if wanted, the per-expert token sets
-    launch_kernel(count_from_mask_kernel, div_up(NG * W, 4), 256, 0, s, mask, group_off, colmask, T, E, W);
+    launch_kernel(count_from_mask_kernel, div_up(NG * W, 4), 256, 0, s, mask, group_off, colmask, T, E, W, sets);
 }
 
 bool fold_scan(int T, int E, int split) {
