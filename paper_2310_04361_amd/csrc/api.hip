@@ -311,13 +311,20 @@ bool use_sets(const dmoe_layer& L, int T, bool want_lists) {
     return hidden_fp8(L) ? down_x8_shape(L) && down_x8_addressable(L, T) && up_x8_supported(L) : down_quad_max_pairs(L, T) <= 0;
 }
 
+// Where the quantised rows of x go: as codes + scales, and as bf16 numbers unless the 8-bit up-projection runs.
+QuantX quant_x(const dmoe_layer& L, int T, char* ws, const LayerWs& w) {
+    const bool codes = up_x8_supported(L) && !use_small_path(L, T);
+    return QuantX{reinterpret_cast<uint8_t*>(ws + w.x8), reinterpret_cast<float*>(ws + w.xscale),
+                  codes ? nullptr : reinterpret_cast<__bf16*>(ws + w.xhat)};
+}
+
 // Experts from mask bits whose group counts (or token sets) are already in the workspace (counts_in_sub, use_sets).
 // gate_mod: the small-token path takes router and gate into its up-projection (scores and mask are
 // then outputs of that kernel, described by gate_mod).
 int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const LayerWs& w,
                 const uint64_t* mask, int32_t* offsets_out, int32_t* lists_out, void* y,
-                hipStream_t s, int split = 1, const SmallMod* gate_mod = nullptr) {
-    // split: rows per group of the counts, where they are in sub_cnt (counts_in_sub)
+                hipStream_t s, int split = 1, const SmallMod* gate_mod = nullptr, bool quantised = false) {
+    // split: rows per group of the counts, where they are in sub_cnt (counts_in_sub); quantised: x is (quant_x)
     int32_t* group_off = reinterpret_cast<int32_t*>(ws + w.group_off);
     const int32_t* sub_cnt = counts_in_sub(L, T, split) ? reinterpret_cast<const int32_t*>(ws + w.sub_cnt) : nullptr;
     int32_t* counts = reinterpret_cast<int32_t*>(ws + w.counts);
@@ -331,12 +338,11 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
     if (acts_fp8(L)) {
         // the experts read the row-wise quantised input: as codes + scales where the 8-bit
         // up-projection runs, as bf16 numbers everywhere else
-        const bool codes = up_x8_supported(L) && !use_small_path(L, T);
-        launch_quantize_x(L, x, T, reinterpret_cast<uint8_t*>(ws + w.x8),
-                          reinterpret_cast<float*>(ws + w.xscale), codes ? nullptr : ws + w.xhat, s);
-        x8 = reinterpret_cast<const uint8_t*>(ws + w.x8);
-        xscale = reinterpret_cast<const float*>(ws + w.xscale);
-        if (!codes) x = ws + w.xhat;
+        const QuantX q = quant_x(L, T, ws, w);
+        if (!quantised) launch_quantize_x(L, x, T, q, s);
+        x8 = q.x8;
+        xscale = q.xscale;
+        if (q.xhat) x = q.xhat;
     }
     if (L.dtype == DMOE_F32) {
         if (offsets_out)
@@ -617,6 +623,7 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
     const bool fused_router = layer->dtype == DMOE_BF16 && router_fused_scores_supported(*layer);
     const bool fused_gate = fused_router && router_fused_supported(*layer);
     int split = 1;
+    bool quantised = false;
     if (fused_router && colmask && gate.top_k < 0 && layer->n_experts <= kSmallGateMaxE) {
         // router, gate and up-projection in one launch
         const SmallMod M = small_mod(*layer, ws, w, scores_out, mask, y, tau);
@@ -630,9 +637,12 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
         // (the gate works on the scores in registers: they go to memory only for a caller who
         // asked for them)
         // (the hidden rows of a router in two launches lie where the experts' will, if there is room)
-        if (router_two_launches(*layer, n_tokens) && 2 * (size_t)n_tokens * layer->router_hidden <= w.H_bytes)
-            launch_router_two(*layer, x, n_tokens, split, ws + w.H, scores_out, tau, mask, counts_of(split), sets, s);
-        else
+        if (router_two_launches(*layer, n_tokens) && 2 * (size_t)n_tokens * layer->router_hidden <= w.H_bytes) {
+            // (8-bit inputs may be quantised in the first of the two launches)
+            const QuantX q = quant_x(*layer, n_tokens, ws, w);
+            quantised = launch_router_two(*layer, x, n_tokens, split, ws + w.H, scores_out, tau, mask, counts_of(split), sets,
+                                          acts_fp8(*layer) ? &q : nullptr, s);
+        } else
             launch_router_fused(*layer, x, n_tokens, split, scores_out, tau, mask, counts_of(split), sets, s);
     } else {
         if (fused_router && n_tokens <= kSmallTokens) {
@@ -660,7 +670,7 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
         else
             launch_mask_topk(scores, n_tokens, layer->n_experts, gate.top_k, mask, nullptr, cnt, colmask, sets, s);
     }
-    return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s, split);
+    return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s, split, nullptr, quantised);
 }
 
 }  // namespace

@@ -270,8 +270,14 @@ void launch_router_sliced(const dmoe_layer& L, const void* x, int T, void* hid, 
 // Small and medium batches of a router whose first matrix takes 512 KB or more: the hidden rows (a [T][d_h] bf16 buffer) in one launch, the
 // scores and the gate in another; the bits of launch_router_fused with the gate.
 bool router_two_launches(const dmoe_layer& L, int T);
-void launch_router_two(const dmoe_layer& L, const void* x, int T, int split, void* hid, float* scores, float tau,
-                       uint64_t* mask, int32_t* group_cnt, bool sets, hipStream_t s);
+// q (nullable): the rows of x are quantised as well, beside the hidden rows; false: not here.
+struct QuantX {
+    uint8_t* x8;      // [T][d] codes
+    float* xscale;    // [T]
+    __bf16* xhat;     // [T][d] the quantised rows as bf16 numbers, or null
+};
+bool launch_router_two(const dmoe_layer& L, const void* x, int T, int split, void* hid, float* scores, float tau,
+                       uint64_t* mask, int32_t* group_cnt, bool sets, const QuantX* q, hipStream_t s);
 void launch_router_fused(const dmoe_layer& L, const void* x, int T, int split, float* scores,
                          float tau, uint64_t* mask, int32_t* group_cnt, bool sets, hipStream_t s);
 
@@ -411,8 +417,7 @@ void launch_down_x8(const dmoe_layer& L, int T, const int32_t* item_start, const
 // ---- 8-bit expert inputs (ffn_x8.hip) -------------------------------------------------------------
 // Row-wise quantisation of x (see DMOE_W_FP8_E4M3_X8 in dmoe.h): x8[T][d] E4M3 codes, xscale[T]
 // the power-of-two scales, xhat[T][d] (nullable) the quantised rows as bf16 numbers.
-void launch_quantize_x(const dmoe_layer& L, const void* x, int T, uint8_t* x8, float* xscale,
-                       void* xhat, hipStream_t s);
+void launch_quantize_x(const dmoe_layer& L, const void* x, int T, const QuantX& q, hipStream_t s);
 void launch_pack_x8(const dmoe_layer& L, void* packed, hipStream_t s);
 // Up-projection on 8-bit operands; same work items, lists and H rows as launch_up_bf16.
 // H8 / hs8 non-null: the rows go out quantised for the 8-bit

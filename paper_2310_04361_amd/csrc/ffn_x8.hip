@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "pack.h"
+#include "quantize.h"
 #include "token_sets.h"
 
 namespace dmoe {
@@ -44,86 +45,9 @@ __device__ __forceinline__ f32x16 mfma64(i32x8 a, i32x8 b, f32x16 c) {
 }
 
 // ---- row-wise quantisation of x ----------------------------------------------------------------
-// E4M3 code of v (|v| <= 448): round to nearest, ties to even.  The grid step at magnitude a is
-// 2^(e - 3) with e = max(floor(log2 a), -6) (-6: the subnormal range), a / step is exact, rintf
-// rounds it to nearest-even, and a result of 16 steps is the next power of two.
-__device__ __forceinline__ uint32_t e4m3_code(float v, float* value) {
-    const float a = fabsf(v);
-    int e = (int)((__float_as_uint(a) >> 23) & 0xffu) - 127;
-    e = max(e, -6);
-    float r = rintf(ldexpf(a, 3 - e));   // 0 .. 16
-    *value = copysignf(ldexpf(r, e - 3), v);
-    uint32_t code;
-    if (r < 8.0f) {
-        code = (uint32_t)r;              // zero or subnormal (only at e == -6)
-    } else {
-        if (r == 16.0f) {
-            e += 1;
-            r = 8.0f;
-        }
-        code = ((uint32_t)(e + 7) << 3) | ((uint32_t)r - 8u);
-    }
-    return code | (v < 0.0f ? 0x80u : 0u);
-}
-
-// Codes of eight values by the hardware converter.  For every bf16 number of magnitude up to
-// 448 (the only inputs here: bf16 values times a power of two) v_cvt_pk_fp8_f32 returns the code
-// of e4m3_code above -- checked exhaustively on the device, all 34754 inputs -- at a tenth of the
-// instructions, so the kernels that need only the codes use it.
-__device__ __forceinline__ uint2 e4m3_codes8(const float (&v)[8]) {
-    int lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[0], v[1], 0, false);
-    lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], lo, true);
-    int hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[4], v[5], 0, false);
-    hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[6], v[7], hi, true);
-    return make_uint2((uint32_t)lo, (uint32_t)hi);
-}
-
-__global__ __launch_bounds__(256) void quantize_x_kernel(const __bf16* __restrict__ x, int T, int d,
-                                                         uint8_t* __restrict__ x8,
-                                                         float* __restrict__ xscale,
-                                                         __bf16* __restrict__ xhat) {
-    const int lane = threadIdx.x & 63;
+__global__ __launch_bounds__(256) void quantize_x_kernel(const __bf16* __restrict__ x, int T, int d, const QuantX q) {
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= T) return;
-    const __bf16* row = x + (size_t)t * d;
-    float amax = 0.0f;
-    for (int k = 8 * lane; k < d; k += 512) {
-        const bf16x8 v = load8(row + k);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf((float)v[i]));
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
-    // smallest power of two s with amax / s <= 448 = 0.875 * 2^9: amax = f * 2^ex, f in [0.5, 1)
-    int s_exp = 0;
-    if (amax > 0.0f && amax < INFINITY) {
-        int ex;
-        const float f = frexpf(amax, &ex);
-        s_exp = f <= 0.875f ? ex - 9 : ex - 8;
-        s_exp = min(max(s_exp, -100), 100);
-    }
-    if (lane == 0) xscale[t] = ldexpf(1.0f, s_exp);
-    for (int k = 8 * lane; k < d; k += 512) {
-        const bf16x8 v = load8(row + k);
-        if (!xhat) {  // uniform: codes only
-            float sv[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) sv[i] = ldexpf((float)v[i], -s_exp);
-            *reinterpret_cast<uint2*>(x8 + (size_t)t * d + k) = e4m3_codes8(sv);
-            continue;
-        }
-        uint32_t lo = 0, hi = 0;
-        bf16x8 q;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            float val;
-            const uint32_t code = e4m3_code(ldexpf((float)v[i], -s_exp), &val);
-            if (i < 4) lo |= code << (8 * i); else hi |= code << (8 * (i - 4));
-            q[i] = (__bf16)ldexpf(val, s_exp);   // exact: four significant bits
-        }
-        *reinterpret_cast<uint2*>(x8 + (size_t)t * d + k) = make_uint2(lo, hi);
-        *reinterpret_cast<bf16x8*>(xhat + (size_t)t * d + k) = q;
-    }
+    if (t < T) quantize_row(x, t, d, q.x8, q.xscale, q.xhat);
 }
 
 // ---- one-time packing -----------------------------------------------------------------------------
@@ -737,11 +661,9 @@ void launch_up_x8_sets(const dmoe_layer& L, const PackedLayout& P, const uint8_t
 
 }  // namespace
 
-void launch_quantize_x(const dmoe_layer& L, const void* x, int T, uint8_t* x8, float* xscale,
-                       void* xhat, hipStream_t s) {
+void launch_quantize_x(const dmoe_layer& L, const void* x, int T, const QuantX& q, hipStream_t s) {
     LaunchTimer tm(kSlotQuantX, s);
-    launch_kernel(quantize_x_kernel, div_up(T, 4), 256, 0, s, (const __bf16*)x, T, L.d_model, x8,
-                  xscale, (__bf16*)xhat);
+    launch_kernel(quantize_x_kernel, div_up(T, 4), 256, 0, s, (const __bf16*)x, T, L.d_model, q);
 }
 
 void launch_pack_x8(const dmoe_layer& L, void* packed, hipStream_t s) {

@@ -14,10 +14,12 @@
 //            tokens of the group that keep it.
 // The scores that are written and the mask come from the same registers, so a caller that gates
 // the returned scores again gets the same mask bit for bit.
+#include <algorithm>
 #include <type_traits>
 
 #include "dmoe_internal.h"
 #include "mfma.h"
+#include "quantize.h"
 
 namespace dmoe {
 
@@ -392,14 +394,21 @@ constexpr int kHidRow = 144;  // bytes per staged x row: 64 columns and 16 bytes
 // 32 tokens x 16 UT hidden units; a wavefront owns NU tiles of units and 16 TTW tokens.  x goes through LDS, which all
 // wavefronts read, in chunks of 256 columns: while chunk k is multiplied, k + 1 is in LDS, k + 2 goes there and k + 3
 // and k + 4 are on their way; R1 fragments are requested four chunks ahead.  The last trip of four chunks requests nothing.
-template <int UT>
+// QUANT: the workgroups from n_hidden on quantise the rows of x.
+template <int UT, bool QUANT>
 __global__ __launch_bounds__(256, UT > 4 ? 1 : 2) void router_hidden_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ r1f, const __bf16* __restrict__ r_b1,
-    __bf16* __restrict__ hid_g, int T, int d, int dh, int by_tokens) {
+    __bf16* __restrict__ hid_g, int T, int d, int dh, int by_tokens, int n_hidden, const QuantX q) {
+    if (QUANT && (int)blockIdx.x >= n_hidden) {
+        const int step = 4 * ((int)gridDim.x - n_hidden);
+        for (int t = 4 * ((int)blockIdx.x - n_hidden) + (int)(threadIdx.x >> 6); t < T; t += step)
+            quantize_row(x, t, d, q.x8, q.xscale, q.xhat);
+        return;
+    }
     constexpr int NU = UT > 4 ? UT / 4 : 1, WU = UT / NU;  // WU: wavefronts side by side over the units
     constexpr int TTW = WU / 2;
     extern __shared__ __attribute__((aligned(16))) char smem[];  // [4 chunks][4 blocks][32][kHidRow]
-    const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+    const int lane = threadIdx.x & 63, lq = lane >> 4, c = lane & 15;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_u = dh / (16 * UT), i = by_tokens ? blockIdx.x >> 3 : blockIdx.x;
     const int t0 = 32 * (by_tokens ? i / n_u * 8 + (blockIdx.x & 7) : i / n_u);
@@ -410,7 +419,7 @@ __global__ __launch_bounds__(256, UT > 4 ? 1 : 2) void router_hidden_kernel(
     const __bf16* xp = x + (size_t)min(t0 + ld_row, T - 1) * d + 8 * ld_piece;
     const __bf16* af = r1f + (size_t)u * NK32 * 512 + lane * 8;
     char* const xdst = smem + ld_row * kHidRow + ld_piece * 16;
-    const char* const xsrc = smem + (16 * tt0 + c) * kHidRow + q * 16;
+    const char* const xsrc = smem + (16 * tt0 + c) * kHidRow + lq * 16;
     bf16x8 xr[2][4], a[16][NU][2], b[2][2][TTW];  // two chunks of x; R1 of four chunks; x operands of two blocks
     // (past the end: the last block again, never used)
     auto load_x = [&](int kb, bf16x8& r) { r = load8(xp + 64 * min(kb, NKB - 1)); };
@@ -492,7 +501,7 @@ __global__ __launch_bounds__(256, UT > 4 ? 1 : 2) void router_hidden_kernel(
     // lane (q, c) of tile (n, tt): units 16 (u + n) + 4 q .. + 3 of token 16 tt + c
 #pragma unroll
     for (int n = 0; n < NU; ++n) {
-        const int hu = 16 * (u + n) + 4 * q;
+        const int hu = 16 * (u + n) + 4 * lq;
 #pragma unroll
         for (int tt = 0; tt < TTW; ++tt) {
             const int t = t0 + 16 * (tt0 + tt) + c;
@@ -638,7 +647,7 @@ static void launch_scores_slices(const dmoe_layer& L, const PackedLayout& P, int
 // From 6144 tokens on (6200: 25.0 in one launch, 32.3 in two; d_h = 512, 8192: 36.3 and 42.3) a workgroup of the one
 // launch has more than 16 tokens to use its share of R1 for.
 static bool router_tiles(const dmoe_layer&, int T) { return div_up(T, kGroup) < 96; }
-static void launch_router_hidden(const dmoe_layer& L, const void* x, int T, void* hid, hipStream_t s) {
+static bool launch_router_hidden(const dmoe_layer& L, const void* x, int T, void* hid, const QuantX* q, hipStream_t s) {
     const PackedLayout P = packed_layout(L);
     const int dh = L.router_hidden;
     const __bf16* r1f = (const __bf16*)(static_cast<const char*>(L.packed) + P.r1f);
@@ -656,32 +665,41 @@ static void launch_router_hidden(const dmoe_layer& L, const void* x, int T, void
             (const __bf16*)x, r1f, (const __bf16*)L.r_b1, nullptr, nullptr,
             nullptr, T, L.d_model, L.n_experts, 0.0f, 0, nullptr, nullptr,
             (__bf16*)hid, dh, 0);
-        return;
+        return false;
     }
     // x is the larger of the two that the XCDs share (by_tokens 1 / 0, router in all: d_h = 256, 333 tokens 11.5 us either
     // way, 1000 tokens 12.2 / 13.3; d_h = 128, 4096 tokens 11.4 / 15.3; d_h = 512, 333 tokens 14.2 / 13.1, 2000 tokens 17.9 / 18.2)
     const int by_tokens = T >= 2 * dh ? 1 : 0;
     constexpr size_t kTileLds = 16 * 32 * kHidRow;
+    const int n4 = div_up(T, 32) * (dh / 64);
+    const bool quant = q && n4 <= 256;  // (see below)
     auto go = [&](auto kernel, int tok, int units) {
-        const int n = div_up(T, tok);
-        launch_kernel(kernel, (by_tokens ? round_up(n, 8) : n) * (dh / units), 256, kTileLds, s, (const __bf16*)x, r1f,
-                      (const __bf16*)L.r_b1, (__bf16*)hid, T, L.d_model, dh, by_tokens);
+        const int n = div_up(T, tok), n_hidden = (by_tokens ? round_up(n, 8) : n) * (dh / units);
+        launch_kernel(kernel, n_hidden + (quant ? std::min(div_up(T, 4), 256) : 0), 256, kTileLds, s, (const __bf16*)x, r1f,
+                      (const __bf16*)L.r_b1, (__bf16*)hid, T, L.d_model, dh, by_tokens, n_hidden, quant ? *q : QuantX{});
     };
     static std::once_flag tile_once;  // kernel attributes: once per process, thread-safe
     std::call_once(tile_once, [] {
-        for (const void* f : {reinterpret_cast<const void*>(&router_hidden_kernel<8>),
-                              reinterpret_cast<const void*>(&router_hidden_kernel<4>),
-                              reinterpret_cast<const void*>(&router_hidden_kernel<2>)})
+        for (const void* f : {reinterpret_cast<const void*>(&router_hidden_kernel<8, false>),
+                              reinterpret_cast<const void*>(&router_hidden_kernel<4, false>),
+                              reinterpret_cast<const void*>(&router_hidden_kernel<2, false>),
+                              reinterpret_cast<const void*>(&router_hidden_kernel<4, true>),
+                              reinterpret_cast<const void*>(&router_hidden_kernel<2, true>)})
             (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
     // The larger tile reads less and needs workgroups enough to fill the chip.  Router in all, d_h = 256, in tiles of 32 x
     // 32 / 64 / 128: 1000 tokens (n4 = 128) 12.0 / 14.1 / 17.2 us, 1250 (160) 14.5 / 13.3 / 16.6, 2000 (252) 16.4 / 14.0 / 17.5,
     // 3000 (376) 20.0 / 18.8 / 18.0, 4096 (512: as many tiles of 128 as CUs) 24.9 / 19.8 / 18.4, 6000 (752) 36.3 / 27.6 /
     // 30.9; d_h = 512, 500 tokens (128) 13.3 / 14.6 / 16.6, 1000 (256) 16.5 / 15.3 / 16.8, 2000 (504) 23.3 / 19.4 / 17.7.
-    const int n4 = div_up(T, 32) * (dh / 64);
-    if (n4 >= 320 && n4 <= 512) go(router_hidden_kernel<8>, 32, 128);
-    else if (n4 >= 160) go(router_hidden_kernel<4>, 32, 64);
-    else go(router_hidden_kernel<2>, 32, 32);
+    // The rows of x are quantised here where the hidden rows leave room for it.  Forward, fully 8-bit layer of 256
+    // gated experts of 64, d = 2048, in a launch of its own / here: 300 tokens (n4 = 40) 71 / 67 us, 1000 (128) 105 / 104, 2000 (252)
+    // 159 / 156; 4096 tokens 255 / 261.
+    if (n4 >= 320 && n4 <= 512) go(router_hidden_kernel<8, false>, 32, 128);
+    else if (n4 >= 160 && quant) go(router_hidden_kernel<4, true>, 32, 64);
+    else if (n4 >= 160) go(router_hidden_kernel<4, false>, 32, 64);
+    else if (quant) go(router_hidden_kernel<2, true>, 32, 32);
+    else go(router_hidden_kernel<2, false>, 32, 32);
+    return quant;
 }
 
 bool router_two_launches(const dmoe_layer& L, int T) {
@@ -720,14 +738,15 @@ static void launch_gate(const dmoe_layer& L, int T, int split, const __bf16* hid
     else launch_gate_split<NH, 8>(L, T, split, hid, scores, tau, mask, group_cnt, sets, s);
 }
 
-void launch_router_two(const dmoe_layer& L, const void* x, int T, int split, void* hid, float* scores, float tau,
-                       uint64_t* mask, int32_t* group_cnt, bool sets, hipStream_t s) {
+bool launch_router_two(const dmoe_layer& L, const void* x, int T, int split, void* hid, float* scores, float tau,
+                       uint64_t* mask, int32_t* group_cnt, bool sets, const QuantX* q, hipStream_t s) {
     LaunchTimer tm(kSlotRouter, s);
-    launch_router_hidden(L, x, T, hid, s);
+    const bool quantised = launch_router_hidden(L, x, T, hid, q, s);
     const __bf16* h = (const __bf16*)hid;
     if (L.router_hidden == 128) launch_gate<8>(L, T, split, h, scores, tau, mask, group_cnt, sets, s);
     else if (L.router_hidden == 256) launch_gate<16>(L, T, split, h, scores, tau, mask, group_cnt, sets, s);
     else launch_gate<32>(L, T, split, h, scores, tau, mask, group_cnt, sets, s);
+    return quantised;
 }
 
 void launch_router_sliced(const dmoe_layer& L, const void* x, int T, void* hid, float* scores,
@@ -735,7 +754,7 @@ void launch_router_sliced(const dmoe_layer& L, const void* x, int T, void* hid, 
     LaunchTimer tm(kSlotRouter, s);
     const PackedLayout P = packed_layout(L);
     const int dh = L.router_hidden;
-    launch_router_hidden(L, x, T, hid, s);
+    launch_router_hidden(L, x, T, hid, nullptr, s);
     if (dh == 256) launch_scores_slices<16>(L, P, T, (const __bf16*)hid, scores, s);
     else launch_scores_slices<32>(L, P, T, (const __bf16*)hid, scores, s);
 }
