@@ -330,6 +330,61 @@ __global__ __launch_bounds__(256) void lists_finish_kernel(const int32_t* __rest
     if (t < T) mask[(size_t)t * W + w] = word;
 }
 
+// The same in one launch, for so few positions that every workgroup may look at all those of its experts: workgroup = 256 tokens
+// and one mask word (64 experts), whose bits it collects in LDS.
+constexpr int kListsTokens = 256;
+__global__ __launch_bounds__(1024) void lists_small_kernel(const int32_t* __restrict__ offsets, const int32_t* __restrict__ lists,
+                                                           int T, int E, int W, uint64_t* __restrict__ mask,
+                                                           int32_t* __restrict__ group_cnt, uint64_t* __restrict__ colmask, bool sets) {
+    __shared__ uint32_t bits[64][kListsTokens / 32 + 1];  // [expert][32 tokens]
+    __shared__ int s_off[128];  // from ne on: the end
+    __shared__ int s_ordered;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int w = blockIdx.y, e0 = 64 * w, ne = min(64, E - e0), t0 = blockIdx.x * kListsTokens;
+    if (tid == 0) s_ordered = 1;
+    for (int i = tid; i < 64 * (kListsTokens / 32 + 1); i += 1024) (&bits[0][0])[i] = 0u;
+    const long long cap = (long long)T * E, begin = max((long long)offsets[0], 0ll), end = min((long long)offsets[E], cap);
+    if (tid < 128) s_off[tid] = (int)min(max((long long)offsets[e0 + min(tid, ne)], begin), max(begin, end));
+    __syncthreads();
+    if (tid < ne && s_off[tid] > s_off[tid + 1]) s_ordered = 0;
+    __syncthreads();
+    constexpr int kN = 8;  // positions in flight
+    auto mark = [&](int e, int t) {
+        if ((unsigned)t < (unsigned)T && (unsigned)(t - t0) < (unsigned)kListsTokens)
+            atomicOr(&bits[e][(t - t0) >> 5], 1u << ((t - t0) & 31));
+    };
+    if (s_ordered) {  // the positions of all the experts as one range
+        const int last = s_off[ne];
+        for (int p = s_off[0] + tid; p < last; p += kN * 1024) {
+            int t[kN];
+#pragma unroll
+            for (int k = 0; k < kN; ++k) t[k] = lists[min(p + k * 1024, last - 1)];
+            int e[kN] = {};  // their experts: the last with s_off[e] <= position, all searches side by side
+#pragma unroll
+            for (int step = 32; step > 0; step >>= 1)
+#pragma unroll
+                for (int k = 0; k < kN; ++k) e[k] += s_off[e[k] + step] <= p + k * 1024 ? step : 0;
+#pragma unroll
+            for (int k = 0; k < kN; ++k)
+                if (p + k * 1024 < last) mark(e[k], t[k]);
+        }
+    } else {  // offsets that fall: expert by expert
+        for (int e = wave; e < ne; e += 16)
+            for (int p = s_off[e] + lane; p < s_off[e + 1]; p += 64) mark(e, lists[p]);
+    }
+    __syncthreads();
+    if (wave >= kListsTokens / kGroup) return;
+    const int g = t0 / kGroup + wave, t = g * kGroup + lane;  // wavefront = group of 64 tokens
+    if (g * kGroup >= T) return;  // uniform
+    const uint64_t set = bits[lane][2 * wave] | (uint64_t)bits[lane][2 * wave + 1] << 32;  // lane = expert
+    if (lane < ne) {
+        store_group(group_cnt, g, T, E, e0 + lane, set, sets);
+        if (colmask) colmask[(size_t)g * E + e0 + lane] = set;
+    }
+    const uint64_t word = transpose64(set, lane);
+    if (t < T) mask[(size_t)t * W + w] = word;
+}
+
 // One wavefront per expert: exclusive prefix sum of group_cnt[.][e] over the groups, in place;
 // row NG receives the total.  With sub != nullptr the counts of group g are read as the sum of
 // the rows split * g .. split * g + split - 1 of sub (n_sub rows in all).
@@ -735,6 +790,14 @@ void launch_mask_from_lists(const int32_t* offsets, const int32_t* lists, int T,
                             uint64_t* mask, int32_t* group_off, uint64_t* colmask, bool sets, void* scratch,
                             size_t scratch_bytes, hipStream_t s) {
     const int W = div_up(E, 64), Tp = round_up(T, kGroup);
+    // In one launch, forward us against three: 24 experts of 128, 40 tokens 23.7 / 21.3, 197 tokens (5 and 50 % per expert) 34.7 / 31.7
+    // and 36.9 / 35.5, 788 tokens 39.0 / 36.8 and 41.6 / 41.3; beyond, what every workgroup reads of the lists decides: 3152
+    // tokens 69.8 / 66.9 and 75.1 / 78.9.
+    if (group_off && (long long)T * std::min(E, 64) <= 20000) {
+        LaunchTimer tm(kSlotListsToMask, s);
+        launch_kernel(lists_small_kernel, dim3(div_up(T, kListsTokens), W), 1024, 0, s, offsets, lists, T, E, W, mask, group_off, colmask, sets);
+        return;
+    }
     // by bytes where there is room for them and the counts are all that is wanted besides the mask words
     uint8_t* bytes = !colmask && group_off && (size_t)E * Tp <= scratch_bytes ? (uint8_t*)scratch : nullptr;
     // Up to 8 MB of bytes that way costs no more at any density, and looking at the number of positions in three

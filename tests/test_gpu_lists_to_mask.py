@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T,E,p", [(65, 1, 0.5), (127, 63, 0.3), (128, 64, 0.0), (129, 65, 0.4), (200, 130, 0.1),
-                                   (4097, 24, 0.5), (1000, 600, 0.02)])
+                                   (4097, 24, 0.5), (1000, 600, 0.02),
+                                   # one launch: the small-batch kernels, a mask word more, 256 tokens, up to its last size
+                                   (16, 24, 0.3), (40, 65, 0.3), (255, 65, 0.2), (256, 64, 0.5), (257, 24, 0.5), (312, 64, 0.3), (313, 64, 0.3)])
 def test_lists_with_noise(oracle, T, E, p):
     import torch
     from paper_2310_04361_amd import binding as B
@@ -41,9 +43,31 @@ def test_lists_with_noise(oracle, T, E, p):
     y2 = B.dmoe_expert_ffn(L, xd, dev(noff), dev(noisy))
     torch.cuda.synchronize()
     assert torch.equal(y, y2)
-    idx = np.unique(np.concatenate([[0, 63, 64, T - 1], rng.integers(0, T, 20)]))
+    idx = np.unique(np.minimum(np.concatenate([[0, 63, 64, T - 1], rng.integers(0, T, 20)]), T - 1))
     ref = oracle_ffn(oracle, layer, x[idx], mask[idx])
     assert tokenwise_rel_err(B.from_device(y, cfg.dtype)[idx], ref) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("T", [100, 2000])
+def test_falling_offsets(oracle, T):
+    """Offsets that fall: an expert has the positions from its own offset to the next one, if that is not the smaller."""
+    import torch
+    from paper_2310_04361_amd import binding as B
+    cfg = wl.Config("falling", T, 256, 24, 24, 64, False, "gelu_erf", "bf16", (0.5,), ffn_bias=True)
+    print(f"falling offsets T={T}", flush=True)
+    layer, x = wl.make_layer(cfg, 3), wl.make_input(cfg, 3)
+    rng = np.random.default_rng(6)
+    lists = rng.integers(0, T, 40 * 24).astype(np.int32)
+    offsets = np.sort(rng.integers(0, len(lists), 25)).astype(np.int32)
+    offsets[0], offsets[-1] = 0, len(lists)
+    offsets[7], offsets[8] = offsets[8], offsets[7] - 3
+    mask = np.zeros((T, 24), np.uint8)
+    for e in range(24):
+        mask[lists[offsets[e]:max(offsets[e], offsets[e + 1])], e] = 1
+    L = B.Layer(layer, cfg.dtype)
+    y = B.dmoe_expert_ffn(L, B.to_device(x, cfg.dtype), torch.from_numpy(offsets).cuda(), torch.from_numpy(lists).cuda())
+    torch.cuda.synchronize()
+    assert tokenwise_rel_err(B.from_device(y, cfg.dtype), oracle_ffn(oracle, layer, x, mask)) <= TOL["bf16"]
 
 
 @pytest.mark.parametrize("T,E,hot", [(4100, 2048, False), (4100, 2048, True), (70001, 130, False), (1000, 600, True), (2100, 4000, True)])
