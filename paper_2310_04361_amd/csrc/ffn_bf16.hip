@@ -120,6 +120,11 @@ __device__ __forceinline__ int wave_of(int n_items, int wave_in_block, int n_wav
 // into a buffer and a padding row (-1) an offset beyond it, which moves no data.  Otherwise 16-byte units from
 // x, and padding rows read token 0.  Either way they produce H rows that nobody merges.
 constexpr int kRawBuffer = 0x00020000;  // offsets from num_records on read as zero and move no data
+typedef __attribute__((address_space(3))) void* LdsPtr;
+// 16 bytes a lane straight to 1 KB of LDS
+__device__ __forceinline__ void buffer_to_lds(__amdgpu_buffer_rsrc_t buf, uint32_t lane_off, uint32_t off, char* lds) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (LdsPtr)lds, 16, lane_off, off, 0, 0);
+}
 template <bool NEAR>
 struct XRows {
     __amdgpu_buffer_rsrc_t buf;
@@ -132,6 +137,11 @@ struct XRows {
     __device__ __forceinline__ uint32_t row(int tok, int piece) const {
         if (NEAR) return tok < 0 ? 0x80000000u : (uint32_t)tok * (uint32_t)(2 * d) + 16u * (uint32_t)piece;
         return (uint32_t)(((size_t)max(tok, 0) * d) >> 3) + (uint32_t)piece;
+    }
+    // K block kb of 64 columns, 16 bytes a lane, to 1 KB of LDS
+    __device__ __forceinline__ void to_lds(uint32_t row, int kb, char* lds) const {
+        if (NEAR) buffer_to_lds(buf, row, 128 * kb, lds);
+        else __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(x + (((size_t)row + 8 * kb) << 3)), (LdsPtr)lds, 16, 0, 0);
     }
     __device__ __forceinline__ bf16x8 load(uint32_t row, int kb) const {  // K block kb of 64 columns
         if (NEAR) return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(buf, row, 128 * kb, 0));
@@ -570,7 +580,7 @@ __global__ __launch_bounds__(256) void up_tiny_kernel(
     }  // windows
 }
 
-// Up-projection for wide experts (8 or more neuron tiles per item, e.g. gated m = 64): there the
+// Up-projection for wide gated experts (8 neuron tiles per K step, e.g. m = 64): there the
 // weights of an expert are as large as its x rows, so streaming them once per wavefront made the
 // kernel a weight stream.  Here a workgroup of four wavefronts owns 4 x 16*TT consecutive list
 // rows of one expert and shares each K block of the weight fragments through LDS (double
@@ -584,23 +594,25 @@ __global__ __launch_bounds__(256) void up_tiny_kernel(
 // as soon as its LDS write is issued, between two MFMAs: requests are in flight all the time, and
 // neither the writes nor the issue of the loads wait for the end of the block.  (As three phases in
 // sequence -- multiply; write; barrier, then request -- 4096 tokens x 256 gated experts of 64, d = 2048, 37 % density
-// took 222 us against 197, 24 x 128 experts, half of them per token, at 50432 tokens 172 against 158, 333 tokens of the former
-// 53 against 45.)
+// took 222 us against 197, 333 tokens 53 against 45.)
 //
 // The order of the items (select.hip) keeps the traffic beyond L2 down: 4096 tokens x 256 gated
 // experts of 64, d = 2048, 37 % density: 1.84 -> 0.82 GB from beyond L2 and, with the 32x32x16 MFMA (half
 // the instructions of the 16x16x32 one), 276 -> 240 us, both on one card in turn (224 to 253 over
-// cards and clocks), before the interleaving above, which lets the workgroups of an XCD drift apart: 0.97 to 1.00 GB since; 24 x 128 experts, half of them per token, at 50432 tokens: 210 -> 204 us.  Built and
+// cards and clocks), before the interleaving above, which lets the workgroups of an XCD drift apart: 0.97 to 1.00 GB since.  Built and
 // slower: x rows by LDS-DMA and the weights straight to registers, with a 2 x 2 split over the
 // wavefronts (236 us against 220 on the card of that day: LDS instructions down to a sixth, but more bytes and more
-// drift between the workgroups, 0.96 GB).
-template <int MT, bool GATED, int TT>
+// drift between the workgroups, 0.96 GB); rows and weights straight to LDS, one block ahead (up_wide_plain_kernel, below): 420 -> 414 us
+// for a whole forward, but 450 -> 473 for the first one on new weights, whose way from HBM is longer than a block; one workgroup
+// of 512 rows per CU that way, four blocks of weights ahead, which halves what comes from beyond L2: 412, but 1400 tokens
+// 166 -> 186, as nothing works beside a workgroup's epilogue and tail.
+template <int MT, int TT>
 __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf,
-    const __bf16* __restrict__ wgatef, const __bf16* __restrict__ b_up,
+    const __bf16* __restrict__ wgatef,
     const int32_t* __restrict__ witem, const int2* __restrict__ worder,
     const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act) {
-    constexpr int BR = GATED ? 2 : 1;
+    constexpr int BR = 2;
     constexpr int KS = MT / 2;
     constexpr int NT = BR * MT;         // neuron tiles per K step
     constexpr int NJ = NT / 2, TJ = TT / 2;  // tiles of the 32x32x16 MFMA: neurons, list rows
@@ -614,7 +626,6 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     char* wbuf = smem;                                   // [2][NWF][1024]
     const int lane = threadIdx.x & 63, h = lane >> 5, c32 = lane & 31, w = threadIdx.x >> 6;
     char* xs = smem + 2 * NWF * 1024 + w * (WR * kUpRowBytes);   // [WR][kUpRowBytes], private
-    float* sbias = reinterpret_cast<float*>(smem + 2 * NWF * 1024 + 4 * (WR * kUpRowBytes));  // [2][MT * 16]
     const int NK32 = d / 32, NKB = d / 64;   // NKB >= 2
     const int ld_row = lane >> 3, ld_piece = lane & 7;
     // this XCD's share of the items (workgroups are dealt round-robin to the 8 XCDs; the grid is a
@@ -645,7 +656,7 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     const uint32_t woff = (uint32_t)(((w >> 1) * NK32 + (w & 1)) * 512 + lane * 8);
     bf16x8 xr[NL], wr[NWL];
     auto issue_w = [&](int i, int e, int kb) {
-        const __bf16* base = (GATED && (2 * i) / MT == BR - 1) ? wgatef : wupf;
+        const __bf16* base = (2 * i) / MT == 1 ? wgatef : wupf;
         wr[i] = load8(base + (size_t)e * MT * NK32 * 512 + (size_t)kb * 1024 + woff + (size_t)((2 * i) % MT) * NK32 * 512);
     };
     auto issue_x = [&](int i, const uint32_t (&xoff)[NL], int kb) {
@@ -657,12 +668,6 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     auto park_x = [&](int i) {
         *reinterpret_cast<bf16x8*>(xs + (ld_row + 8 * i) * kUpRowBytes + ld_piece * 16) = xr[i];
     };
-    auto park_bias = [&](int e, int par) {  // plain experts: the item's biases, by neuron
-        if (!GATED && (int)threadIdx.x < MT * 16)
-            sbias[par * MT * 16 + threadIdx.x] =
-                b_up ? (float)b_up[(size_t)e * m + min((int)threadIdx.x, m - 1)] : 0.0f;
-    };
-
     int e, item;
     uint32_t xoff[NL];
     bool active;
@@ -682,9 +687,8 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
         park_x(i);
         issue_x(i, xoff, 1);
     }
-    park_bias(e, 0);
     lds_barrier();
-    int buf = 0, par = 0;
+    int buf = 0;
     for (;;) {
         // the item after this one (the last item names itself: its first blocks are read again
         // and never used)
@@ -786,9 +790,222 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
         lds_barrier();
         buf ^= 1;
         block(en, xoffn, 1, activen, activen);  // block NKB - 1; the next item's block 0 is parked
-        park_bias(en, par ^ 1);
         lds_barrier();
         buf ^= 1;
+
+        if (active) with_activation(act, [&](auto act_c) {
+            constexpr int ACT = decltype(act_c)::value;
+            // lane (h, c) of tile (nj, tj): list row 32 tj + c; registers 0..3 and 8..11 are the eight
+            // neurons of piece 4 nj + h of the H row, 4..7 and 12..15 those of piece 4 nj + 2 + h
+            // (neuron_of_slot over a pair of 16-row tiles)
+#pragma unroll
+            for (int tj = 0; tj < TJ; ++tj) {
+                __bf16* dst = Hf + ((size_t)item * UR + w * WR + 32 * tj + c32) * (KS * 32);
+#pragma unroll
+                for (int nj = 0; nj < KS; ++nj) {
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) {
+                        const int n0 = 8 * (4 * nj + 2 * half + h);
+                        bf16x8 hv;
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) {
+                            const int i = 4 * half + (r & 3) + 8 * (r >> 2);
+                            float v;
+                            v = activate_fast(ACT, acc[NJ / 2 + nj][tj][i]) * acc[nj][tj][i];
+                            if (n0 + r >= m) v = 0.0f;
+                            hv[r] = (__bf16)v;
+                        }
+                        *reinterpret_cast<bf16x8*>(dst + n0) = hv;
+                        // eight values at a time: interleaving more of them costs registers the
+                        // requests in flight are using
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+        });
+        if (!more) break;
+        j = jn;
+        e = en;
+        item = itemn;
+        active = activen;
+#pragma unroll
+        for (int i = 0; i < NL; ++i) xoff[i] = xoffn[i];
+    }
+}
+
+// The same for plain experts of 65 to 128 neurons.  The K blocks of all the items of a workgroup form one stream: while block k is
+// multiplied, the loads of block k+1 go straight to LDS -- also across the end of an item, so that the first block of the
+// next item arrives during the activation epilogue of the current one.  A wavefront has the x rows of its block in registers
+// before it requests the next ones into their place; the weights, which all four wait for, are requested first.  What
+// bounds it: the requests that go beyond the L2s (without any of them 100 us instead of 170), and the vector path.  A ds_write_b128 of staging
+// registers takes 35 clocks of a CU per KB beside the 17 of its load, a load to LDS the 17 alone.  24 x 128 experts, d = 768, whole call,
+// through registers with two blocks in flight / straight to LDS with one: 50432 tokens at 50 % 377 / 367 us (the first call on new
+// buffers 412 / 398), 30000 at 30 % 192 / 187, 12608 at 20 % 94 / 93.  Built and slower: rows before weights (374), everything at the
+// block's start (376), one workgroup of 512 rows per CU (388).
+template <int MT, int TT, bool NEAR>
+__global__ __launch_bounds__(256, 2) void up_wide_plain_kernel(
+    const __bf16* __restrict__ x, const __bf16* __restrict__ wupf, const __bf16* __restrict__ b_up,
+    const int32_t* __restrict__ witem, const int2* __restrict__ worder,
+    const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act) {
+    constexpr int KS = MT / 2;
+    constexpr int NJ = MT / 2, TJ = TT / 2;  // tiles of the 32x32x16 MFMA: neurons, list rows
+    constexpr int WR = TT * 16;         // rows per wavefront
+    constexpr int UR = 4 * WR;          // rows per work item
+    constexpr int NL = TT * 2;          // x load instructions per K block
+    constexpr int NWF = 2 * MT;         // weight fragments (1 KiB each) per K block
+    constexpr int NWL = NWF / 4;        // ... of which each wavefront requests every fourth
+    static_assert(NWF % 4 == 0 && MT % 2 == 0, "weight fragments are copied four at a time");
+    // (arrays of their own: the compiler then sees that reads of one do not wait for loads to another)
+    __shared__ __attribute__((aligned(128))) char wbuf0[NWF * 1024];
+    __shared__ __attribute__((aligned(128))) char wbuf1[NWF * 1024];
+    __shared__ __attribute__((aligned(128))) char xbuf[4 * WR * 128];
+    __shared__ float sbias[2 * MT * 16];
+    const int lane = threadIdx.x & 63, h = lane >> 5, c32 = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    char* const xs = xbuf + w * (WR * 128);  // [WR][128], private to the wavefront
+    const int NK32 = d / 32, NKB = d / 64;   // NKB is even
+    const int ld_row = lane >> 3, ld_piece = lane & 7;
+    // this XCD's share of the items (workgroups are dealt round-robin to the 8 XCDs; the grid is a
+    // multiple of 8), in the order laid out by the list fill
+    const int xcd = blockIdx.x & 7, step = gridDim.x >> 3;
+    const int total = xcd_first(witem[E], xcd + 1);
+    const int first = xcd_first(witem[E], xcd);
+    int j = first + (int)(blockIdx.x >> 3);
+    if (j >= total) return;
+    // (from the end: an expert's last item, often nearly empty, comes before its full ones, so that the
+    // workgroups do not end with items of a wavefront or two)
+    auto locate = [&](int jj, int& e, int& item) {
+        const int2 v = worder[total - 1 - (jj - first)];
+        e = v.x;
+        item = v.y;
+    };
+    // tokens of the x rows this lane fetches; padding rows (-1) read token 0 and produce H rows
+    // that nobody merges
+    const XRows<NEAR> xrows(x, d);
+    auto rows_of = [&](int item, uint32_t (&xoff)[NL], bool& active) {
+        const int32_t* tl = alist + (size_t)item * UR + w * WR;
+        active = __builtin_amdgcn_readfirstlane(tl[0]) >= 0;  // valid rows are a prefix
+#pragma unroll
+        for (int i = 0; i < NL; ++i)  // piece p of row c lies at p ^ (c / 2): 16 rows' pieces use all the banks
+            xoff[i] = xrows.row(max(tl[ld_row + 8 * i], 0), ld_piece ^ (4 * (i & 1) + (ld_row >> 1)));
+    };
+    // Weight fragment f = mt * 2 + ks of a K block; this wavefront requests the fragments f = 4 i + w: ks = w & 1, mt = 2 i + (w >> 1).
+    __amdgpu_buffer_rsrc_t wf;
+    auto weights_of = [&](int e) {
+        const size_t at = (size_t)__builtin_amdgcn_readfirstlane(e) * MT * NK32 * 512;
+        wf = __builtin_amdgcn_make_buffer_rsrc((void*)(wupf + at), 0, MT * NK32 * 1024, kRawBuffer);
+    };
+    auto request_w = [&](int i, int kb, char* to) {
+        buffer_to_lds(wf, lane * 16, ((2 * i + (w >> 1)) * NK32 + 2 * kb + (w & 1)) * 1024, to + (4 * i + w) * 1024);
+    };
+    auto request_x = [&](int i, const uint32_t (&xoff)[NL], int kb) { xrows.to_lds(xoff[i], kb, xs + 1024 * i); };
+    auto park_bias = [&](int e, int par) {  // the item's biases, by neuron
+        if ((int)threadIdx.x < MT * 16)
+            sbias[par * MT * 16 + threadIdx.x] =
+                b_up ? (float)b_up[(size_t)e * m + min((int)threadIdx.x, m - 1)] : 0.0f;
+    };
+
+    int e, item;
+    uint32_t xoff[NL];
+    bool active;
+    locate(j, e, item);
+    rows_of(item, xoff, active);
+    weights_of(e);
+#pragma unroll
+    for (int i = 0; i < NWL; ++i) request_w(i, 0, wbuf0);
+    if (active) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) request_x(i, xoff, 0);
+    }
+    park_bias(e, 0);
+    wait_vmem();
+    lds_barrier();
+    int par = 0;
+    for (;;) {
+        // the item after this one (the last item names itself: its first block is read again
+        // and never used)
+        const int jn = j + step;
+        const bool more = jn < total;
+        int en = e, itemn = item;
+        if (more) locate(jn, en, itemn);
+
+        f32x16 acc[NJ][TJ];
+#pragma unroll
+        for (int nj = 0; nj < NJ; ++nj)
+#pragma unroll
+            for (int tj = 0; tj < TJ; ++tj)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[nj][tj][r] = 0.f;
+        // One K block: its rows of x to registers, then the requests of the next block (kb; of this item or the next: rows
+        // xo, xi whether they are wanted) between the products of this one.  The wait for them and the barrier
+        // stand at the end.
+        auto block = [&](const char* wb, char* wn, const uint32_t (&xo)[NL], int kb, bool xi) {
+            if (active) {
+                // operands of k-step s (16 wide): neuron tile nj from the fragments of its two
+                // 16-row tiles, token tile tj from the staged rows; the next neuron tile's (and the
+                // next k-step's) operands are read while the current tile's MFMAs run
+                const char* wsrc_l = wb + (c32 >> 4) * 2048 + (h * 16 + (c32 & 15)) * 16;
+                auto read_a = [&](int s, int nj) {
+                    return *reinterpret_cast<const bf16x8*>(wsrc_l + nj * 4096 + (s >> 1) * 1024 + (s & 1) * 512);
+                };
+                constexpr int kAhead = 3;  // weight tiles
+                bf16x8 b[4][TJ], a[kAhead + 1];
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int tj = 0; tj < TJ; ++tj)
+                        b[s][tj] = *reinterpret_cast<const bf16x8*>(xs + (32 * tj + c32) * 128 + (((2 * s + h) ^ ((c32 >> 1) & 7)) << 4));
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) a[q] = read_a(q / NJ, q % NJ);
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the rows are out of the LDS that the requests below fill
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+#pragma unroll
+                    for (int nj = 0; nj < NJ; ++nj) {
+                        const int q = s * NJ + nj;
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (q + kAhead < 4 * NJ) a[(q + kAhead) % (kAhead + 1)] = read_a((q + kAhead) / NJ, (q + kAhead) % NJ);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int tj = 0; tj < TJ; ++tj) {
+                            acc[nj][tj] = mfma32(a[q % (kAhead + 1)], b[s][tj], acc[nj][tj]);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (q < NWL) {
+                            request_w(q, kb, wn);
+                        } else if (q < NWL + NL / 2) {
+                            if (xi) {
+                                request_x(2 * (q - NWL), xo, kb);
+                                request_x(2 * (q - NWL) + 1, xo, kb);
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            } else {
+                if (xi) {
+#pragma unroll
+                    for (int i = 0; i < NL; ++i) request_x(i, xo, kb);
+                }
+#pragma unroll
+                for (int i = 0; i < NWL; ++i) request_w(i, kb, wn);
+            }
+            wait_vmem();
+            lds_barrier();
+        };
+        for (int kb = 0; kb < NKB - 2; kb += 2) {
+            block(wbuf0, wbuf1, xoff, kb + 1, active);
+            block(wbuf1, wbuf0, xoff, kb + 2, active);
+        }
+        uint32_t xoffn[NL];
+        bool activen;
+        rows_of(itemn, xoffn, activen);
+        block(wbuf0, wbuf1, xoff, NKB - 1, active);
+        park_bias(en, par ^ 1);
+        weights_of(en);
+        block(wbuf1, wbuf0, xoffn, 0, activen);  // the next item's block 0 is requested
 
         if (active) with_activation(act, [&](auto act_c) {
             constexpr int ACT = decltype(act_c)::value;
@@ -808,9 +1025,7 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
 #pragma unroll
                         for (int r = 0; r < 8; ++r) {
                             const int i = 4 * half + (r & 3) + 8 * (r >> 2);
-                            float v;
-                            if (GATED) v = activate_fast(ACT, acc[NJ / 2 + nj][tj][i]) * acc[nj][tj][i];
-                            else v = activate_fast(ACT, acc[nj][tj][i] + sb[n0 + r]);
+                            float v = activate_fast(ACT, acc[nj][tj][i] + sb[n0 + r]);
                             if (n0 + r >= m) v = 0.0f;
                             hv[r] = (__bf16)v;
                         }
@@ -1056,22 +1271,29 @@ void launch_up_t(const dmoe_layer& L, const void* x, const PackedLayout& P, cons
         L.expert_size, L.act, S);
 }
 
-template <int MT, bool GATED, int TT>
+template <int MT, int TT>
 void launch_up_wide_t(const dmoe_layer& L, const void* x, const PackedLayout& P,
                       const int32_t* witem, const void* worder, const int32_t* alist,
                       void* H, int grid, hipStream_t s) {
-    constexpr int NWF = 2 * (GATED ? 2 : 1) * MT;
-    const size_t lds = 2 * NWF * 1024 + 4 * (size_t)TT * 16 * kUpRowBytes + 2 * MT * 16 * sizeof(float);
+    const size_t lds = 2 * 4 * MT * 1024 + 4 * (size_t)TT * 16 * kUpRowBytes;
     static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
     std::call_once(attr_once, [&] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_wide_bf16_kernel<MT, GATED, TT>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_wide_bf16_kernel<MT, TT>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
     const char* pk = static_cast<const char*>(L.packed);
-    launch_kernel(up_wide_bf16_kernel<MT, GATED, TT>, grid, 256, lds, s, 
-        (const __bf16*)x, (const __bf16*)(pk + P.wupf), (const __bf16*)(pk + P.wgatef),
-        (const __bf16*)L.b_up, witem, (const int2*)worder, alist, (__bf16*)H, L.d_model, L.n_experts,
-        L.expert_size, L.act);
+    launch_kernel(up_wide_bf16_kernel<MT, TT>, grid, 256, lds, s,
+        (const __bf16*)x, (const __bf16*)(pk + P.wupf), (const __bf16*)(pk + P.wgatef), witem, (const int2*)worder,
+        alist, (__bf16*)H, L.d_model, L.n_experts, L.expert_size, L.act);
+}
+
+template <int MT, int TT, bool NEAR>
+void launch_up_wide_plain_t(const dmoe_layer& L, const void* x, const PackedLayout& P,
+                            const int32_t* witem, const void* worder, const int32_t* alist,
+                            void* H, int grid, hipStream_t s) {
+    launch_kernel(up_wide_plain_kernel<MT, TT, NEAR>, grid, 256, 0, s, (const __bf16*)x,
+        (const __bf16*)(static_cast<const char*>(L.packed) + P.wupf), (const __bf16*)L.b_up, witem, (const int2*)worder,
+        alist, (__bf16*)H, L.d_model, L.n_experts, L.expert_size, L.act);
 }
 
 template <int MT, bool GATED, int TJ>
@@ -1203,16 +1425,17 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
     const long long worst = (long long)T * L.n_experts / up_rows_bf16(L) + L.n_experts;
     const int grid = round_up((int)std::min<long long>(worst, 256 * 2), 8);
     const int mt = m_pad_of(L.expert_size) / 16;
+    const bool near = (size_t)T * L.d_model * 2 < ((size_t)1 << 31);  // (XRows)
     if (up_rows_bf16(L) == 256) {  // wide experts: weights shared through LDS
         const int wgrid = round_up(
             (int)std::min<long long>((long long)T * L.n_experts / 256 + L.n_experts, 512), 8);
         if (S.sets && L.gated) launch_up_wide_sets<4, true>(L, x, P, S, H, s);
         else if (S.sets) launch_up_wide_sets<8, false>(L, x, P, S, H, s);
-        else if (L.gated) launch_up_wide_t<4, true, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
-        else launch_up_wide_t<8, false, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
+        else if (L.gated) launch_up_wide_t<4, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
+        else if (near) launch_up_wide_plain_t<8, 4, true>(L, x, P, witem, worder, alist, H, wgrid, s);
+        else launch_up_wide_plain_t<8, 4, false>(L, x, P, witem, worder, alist, H, wgrid, s);
         return;
     }
-    const bool near = (size_t)T * L.d_model * 2 < ((size_t)1 << 31);  // (XRows)
     if (up_tiny_supported(L)) {
         constexpr int TT = 4;
         const size_t lds = (S.sets ? 4 * 64 * 4 : (2 * (size_t)L.n_experts * 4 + 15) / 16 * 16) +

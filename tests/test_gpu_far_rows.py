@@ -1,6 +1,6 @@
 """Gathers of x beyond 2 GiB: the narrow up-projections switch from 32-bit row offsets to 64-bit addresses.  Tokens on
-both sides of the 2 GiB mark and a batch just below it, for both kernels (tiles of 32 neurons, one-tile
-experts, plain and gated)."""
+both sides of the 2 GiB mark and a batch just below it, for the kernels of tiles of 32 neurons, of one-tile
+experts and of wide ones, plain and gated."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("m,gated,T", [(24, False, 524288 + 70), (8, True, 524288 + 70), (6, False, 524288 + 70),
-                                       (20, True, 524288 + 70), (24, False, 524287)])
+                                       (20, True, 524288 + 70), (24, False, 524287), (60, True, 524288 + 70),
+                                       (128, False, 524288 + 70), (64, True, 524287)])
 def test_far_rows(oracle, m, gated, T):
     import torch
     from paper_2310_04361_amd import binding as B
