@@ -644,6 +644,10 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
                                           acts_fp8(*layer) ? &q : nullptr, s);
         } else
             launch_router_fused(*layer, x, n_tokens, split, scores_out, tau, mask, counts_of(split), sets, s);
+    } else if (fused_router && !colmask && gate.top_k < 0 && scores_gate_supported(*layer, n_tokens)) {
+        // more experts than that kernel's gate takes: hidden rows, then scores, gate and counts
+        split = 4;
+        launch_router_gate_sliced(*layer, x, n_tokens, ws + w.hid, scores_out, tau, mask, counts_of(split), sets, s);
     } else {
         if (fused_router && n_tokens <= kSmallTokens) {
             SmallGroup G{};

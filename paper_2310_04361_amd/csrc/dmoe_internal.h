@@ -266,6 +266,10 @@ int router_fused_split(const dmoe_layer& L, int T);
 bool router_sliced(const dmoe_layer& L);
 void launch_router_sliced(const dmoe_layer& L, const void* x, int T, void* hid, float* scores,
                           hipStream_t s);
+// ... and with the dynamic-k gate and the counts of its decisions, four rows per group or token sets (513 to 2048 experts).
+bool scores_gate_supported(const dmoe_layer& L, int T);
+void launch_router_gate_sliced(const dmoe_layer& L, const void* x, int T, void* hid, float* scores, float tau, uint64_t* mask,
+                               int32_t* cnt, bool sets, hipStream_t s);
 // (sets, here and below: the gate leaves the token sets of token_sets.h in the rows of counts)
 // Small and medium batches of a router whose first matrix takes 512 KB or more: the hidden rows (a [T][d_h] bf16 buffer) in one launch, the
 // scores and the gate in another; the bits of launch_router_fused with the gate.

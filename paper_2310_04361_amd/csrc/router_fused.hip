@@ -391,6 +391,101 @@ void launch_t2(const dmoe_layer& L, const void* x, int T, int split, float* scor
 // tokens.
 constexpr int kHidRow = 144;  // bytes per staged x row: 64 columns and 16 bytes of bank skew
 
+// Second product, gate and counts of a router of more than 512 experts: a workgroup has 16 tokens and all the experts, its
+// eight wavefronts NTW tiles of 16 experts each, whose scores stay in registers until the token's maximum is known.  Sums,
+// decisions and rows of counts are those of router_fused_kernel and gate_counts_kernel.  What bounds it: every workgroup
+// reads all of R2 out of its XCD's L2 (2 MB for 2048 experts and d_h = 512: 15 us at 60 B per clock and CU); as two launches the
+// scores went to memory and back (4096 tokens: 33 MB each way).
+template <int KS2, int NTW>
+__global__ __launch_bounds__(512, 2) void scores_gate_kernel(
+    const __bf16* __restrict__ hid, const __bf16* __restrict__ r2f, const __bf16* __restrict__ r_b2,
+    float* __restrict__ scores, int T, int E, float tau, uint64_t* __restrict__ mask, int32_t* __restrict__ cnt, int sets) {
+    __shared__ float pmax[8][16];
+    const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = (int)blockIdx.x * 16 + c, W = (E + 63) >> 6, NE = (E + 15) >> 4, et0 = w * NTW;
+    const bool real = t < T;
+    // R2 fragments one after the other through a ring, two tiles' worth in flight
+    constexpr int kFrags = NTW * KS2, kAhead = 16;
+    bf16x8 ring[kAhead];
+    const __bf16* const rp = r2f + lane * 8;
+    auto request = [&](int f) {  // (past the last tile of the router that tile again)
+        const int et = min(et0 + f / KS2, NE - 1);
+        ring[f % kAhead] = load8(rp + ((size_t)et * KS2 + f % KS2) * 512);
+    };
+    bf16x8 b[KS2];
+    const __bf16* const hrow = hid + (size_t)min(t, T - 1) * (KS2 * 32) + 8 * q;
+#pragma unroll
+    for (int ks = 0; ks < KS2; ++ks) b[ks] = load8(hrow + 32 * ks);
+#pragma unroll
+    for (int f = 0; f < kAhead; ++f) request(f);
+    float sc[NTW][4], m = 0.f;
+#pragma unroll
+    for (int j = 0; j < NTW; ++j) {
+        f32x4 a2 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS2; ++ks) {
+            const int f = j * KS2 + ks;
+            a2 = mfma16(ring[f % kAhead], b[ks], a2);
+            if (f + kAhead < kFrags) request(f + kAhead);
+        }
+        const int e0 = 16 * (et0 + j) + 4 * q;  // this lane: experts e0 .. e0+3 of token c
+        f32x4 b2 = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (r_b2) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float bv = (float)r_b2[min(e0 + r, E - 1)];
+                b2[r] = e0 + r < E ? bv : 0.0f;
+            }
+        }
+        // padding experts (from E on) score 0
+        const float4 out = e0 < E ? router_scores4(a2 + b2, nullptr, e0, E) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if (scores && real && e0 < E) store_scores4(scores + (size_t)t * E, e0, E, out);
+        sc[j][0] = out.x; sc[j][1] = out.y; sc[j][2] = out.z; sc[j][3] = out.w;
+        m = fmaxf(m, fmaxf(fmaxf(out.x, out.y), fmaxf(out.z, out.w)));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    m = fmaxf(m, __shfl_xor(m, 16, 64));
+    m = fmaxf(m, __shfl_xor(m, 32, 64));
+    if (q == 0) pmax[w][c] = m;
+    lds_barrier();
+    m = pmax[0][c];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) m = fmaxf(m, pmax[i][c]);
+    const double thr = (double)tau * (double)m;  // exact: at most 48 significant bits
+    const uint32_t keep_all = tau == 0.0f ? 1u : 0u, row = real ? 1u : 0u;
+#pragma unroll
+    for (int i = 0; i < NTW / 4; ++i) {
+        const int wi = et0 / 4 + i;
+        if (wi >= W) break;  // uniform
+        uint64_t word = 0ull;  // of token c
+        int set = 0;           // of expert 64 wi + lane: which of the tokens keep it
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int e0 = 64 * wi + 16 * k + 4 * q;
+            uint32_t bits = 0;
+            uint64_t kept[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t ge = (double)sc[4 * i + k][r] >= thr ? 1u : 0u;
+                const uint32_t keep = (keep_all | ge) & row & (e0 + r < E ? 1u : 0u);
+                bits |= keep << (4 * q + r);
+                kept[r] = __ballot(keep != 0u);  // bit 16 q + c
+            }
+            bits |= __shfl_xor(bits, 16, 64);
+            bits |= __shfl_xor(bits, 32, 64);
+            word |= (uint64_t)bits << (16 * k);
+            // lane 16 k + 4 q' + r' takes expert 16 k + 4 q' + r' of the word
+            const uint64_t mine = (c & 2) ? ((c & 1) ? kept[3] : kept[2]) : ((c & 1) ? kept[1] : kept[0]);
+            const int field = (int)(mine >> (16 * (c >> 2))) & 0xffff;
+            set = q == k ? field : set;
+        }
+        if (q == 0 && real) mask[(size_t)t * W + wi] = word;
+        const int e = 64 * wi + lane;
+        if (e < E) cnt[(size_t)blockIdx.x * E + e] = sets ? set : __popc(set);
+    }
+}
+
 // 32 tokens x 16 UT hidden units; a wavefront owns NU tiles of units and 16 TTW tokens.  x goes through LDS, which all
 // wavefronts read, in chunks of 256 columns: while chunk k is multiplied, k + 1 is in LDS, k + 2 goes there and k + 3
 // and k + 4 are on their way; R1 fragments are requested four chunks ahead.  The last trip of four chunks requests nothing.
@@ -747,6 +842,34 @@ bool launch_router_two(const dmoe_layer& L, const void* x, int T, int split, voi
     else if (L.router_hidden == 256) launch_gate<16>(L, T, split, h, scores, tau, mask, group_cnt, sets, s);
     else launch_gate<32>(L, T, split, h, scores, tau, mask, group_cnt, sets, s);
     return quantised;
+}
+
+// E above 512: the gate of fewer experts is router_fused_kernel's; a wavefront has 16 tiles at most.  Rows of counts as
+// gate_counts_kernel leaves them, so the same limit on the tokens.  Below some 1450 tokens the launch takes as long as for 4096, and the
+// scores are few: whole forward, 2048 gated experts of 8, d = 2048, as two launches / one, 900 tokens 149 / 154 us, 1300 169.0 / 170.5, 1500
+// 179 / 173, 2500 269 / 259, 4096 416 / 400, 4200 510 / 492, 9000 854 / 812; d_h = 256, 1400 tokens 164 / 157, 3000 267 / 254; 1024
+// experts, d = 1280, 1400 tokens 97 / 98, 3000 145 / 138.
+bool scores_gate_supported(const dmoe_layer& L, int T) {
+    return router_sliced(L) && L.n_experts > 512 && L.n_experts <= 2048 && T >= 1500 && gate_counts_supported(T, L.n_experts);
+}
+
+template <int KS2>
+static void launch_scores_gate_t(const dmoe_layer& L, int T, const __bf16* hid, float* scores, float tau, uint64_t* mask, int32_t* cnt,
+                                 bool sets, hipStream_t s) {
+    const __bf16* r2f = (const __bf16*)(static_cast<const char*>(L.packed) + packed_layout(L).r2f);
+    auto go = [&](auto kernel) {
+        launch_kernel(kernel, div_up(T, 16), 512, 0, s, hid, r2f, (const __bf16*)L.r_b2, scores, T, L.n_experts, tau, mask, cnt, sets ? 1 : 0);
+    };
+    if (L.n_experts <= 1024) go(scores_gate_kernel<KS2, 8>);
+    else go(scores_gate_kernel<KS2, 16>);
+}
+
+void launch_router_gate_sliced(const dmoe_layer& L, const void* x, int T, void* hid, float* scores, float tau, uint64_t* mask,
+                               int32_t* cnt, bool sets, hipStream_t s) {
+    LaunchTimer tm(kSlotRouter, s);
+    launch_router_hidden(L, x, T, hid, nullptr, s);
+    if (L.router_hidden == 256) launch_scores_gate_t<8>(L, T, (const __bf16*)hid, scores, tau, mask, cnt, sets, s);
+    else launch_scores_gate_t<16>(L, T, (const __bf16*)hid, scores, tau, mask, cnt, sets, s);
 }
 
 void launch_router_sliced(const dmoe_layer& L, const void* x, int T, void* hid, float* scores,
