@@ -27,6 +27,11 @@ namespace {
 
 constexpr int kMaxTilesPerWave = 8;   // expert tiles per wavefront: E <= 4 * 8 * 16 = 512
 
+// Eight rows x 128 bytes, 16 bytes a lane, straight to 1 KB of LDS
+__device__ __forceinline__ void row_set_to_lds(const __bf16* p, char* lds) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+
 // NH = d_h / 16; ETW = expert tiles per wavefront (E <= 64 * ETW); KBC = K blocks (64 wide) of x
 // that sit in LDS at a time: 12 (all of d = 768) when there is at most about one workgroup per
 // CU and its own latency is what counts, 4 when several workgroups share a CU and hide it.
@@ -40,19 +45,22 @@ constexpr int kMaxTilesPerWave = 8;   // expert tiles per wavefront: E <= 4 * 8 
 // hidden units from blockIdx.y * NH * 16 on and stores them to hid_g[T][dh_g]; kScoresSlice (NH * 16 =
 // d_h) reads the stored hidden rows and computes the expert tiles blockIdx.y * tiles_y .. + tiles_y - 1.
 enum { kWhole = 0, kHiddenSlice = 1, kScoresSlice = 2 };
+// Registers for four workgroups per CU, whose LDS they leave room for.
+constexpr bool four_per_cu(int nh, int etw, int kbc, int mode) { return mode == kWhole && kbc == 4 && nh <= 8 && etw <= 2; }
 template <int NH, int ETW, int KBC, int TT, int MODE = kWhole>
-__global__ __launch_bounds__(256) void router_fused_kernel(
+__global__ __launch_bounds__(256, (four_per_cu(NH, ETW, KBC, MODE) ? 4 : 1)) void router_fused_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ r1f, const __bf16* __restrict__ r_b1,
     const __bf16* __restrict__ r2f, const __bf16* __restrict__ r_b2, float* __restrict__ scores,
     int T, int d, int E, float tau, int do_select /* 2: token sets */, uint64_t* __restrict__ mask,
     int32_t* __restrict__ group_cnt, __bf16* __restrict__ hid_g, int dh_g, int tiles_y) {
     constexpr int dh = NH * 16, HT = NH / 4, TOK = 16 * TT;
-    constexpr int NR = (TOK + 31) / 32;  // staging passes of 32 rows
+    constexpr int kBlock = TOK * 128;    // bytes of a staged K block: rows of 128
     constexpr int kHRow = dh * 2 + 16;  // bytes per hidden row in LDS
-    constexpr int kXRowC = KBC * 128 + 16;  // bytes per staged x row: KBC blocks + bank skew
-    extern __shared__ char smem[];
-    char* xs = smem;                                            // [TOK][kXRowC]
-    char* hid = MODE == kScoresSlice ? smem : smem + TOK * kXRowC;  // [TOK][kHRow]
+    extern __shared__ __attribute__((aligned(128))) char smem[];
+    char* xs = smem;                                            // [KBC][TOK][128]
+    // [TOK][kHRow]: afterwards, in the place of x, where several workgroups shall fit a CU
+    constexpr bool kInPlace = KBC == 4;
+    char* hid = MODE == kScoresSlice || kInPlace ? smem : smem + KBC * kBlock;
     float* pmax = reinterpret_cast<float*>(hid + TOK * kHRow);  // [4][64]
     uint64_t* pw = reinterpret_cast<uint64_t*>(pmax + 256);     // [4][64][W]
     const int W = (E + 63) >> 6;
@@ -67,11 +75,18 @@ __global__ __launch_bounds__(256) void router_fused_kernel(
     // once per chunk, not once per K block (loads complete in issue order, so a prefetch of x
     // inside the K loop would hold up the R1 fragments behind it).  The K loop itself has no
     // barrier and only L2-resident loads.
-    const int ld_row = tid >> 3, ld_piece = tid & 7;
-    const bool ld_ok = ld_row < TOK;  // 16 tokens: half of the threads stage nothing
-    const __bf16* xp0 = x + (size_t)min(t0 + ld_row, T - 1) * d + 8 * ld_piece;
-    const __bf16* xp1 = x + (size_t)min(t0 + ld_row + 32, T - 1) * d + 8 * ld_piece;
-    char* xst = xs + ld_row * kXRowC + ld_piece * 16;
+    // Straight to LDS, eight rows a load (staged through registers, a ds_write_b128 took 35 clocks of the CU per KB): 16-byte
+    // piece p of row r of a block lies at p ^ (r / 2), so that the 16 lanes that read a piece of 16 rows use all the banks.
+    // Forward, through registers / so: 512 experts of 6, d = 768, 1300 tokens 56.9 / 54.2 us, 3000 80.0 / 77.5; 128 experts of 24,
+    // 50432 tokens, with the hidden rows in the place of x besides (two -> four workgroups per CU), 317 / 312; 16384 tokens 122.7 / 122.3.
+    constexpr int kRowSets = TOK / 8;                        // loads per K block, dealt to the wavefronts in turn
+    constexpr int kOwn = kRowSets >= 4 ? kRowSets / 4 : 1;   // row sets of a wavefront
+    const __bf16* xp[kOwn];
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+        const int rs = kRowSets >= 4 ? w + 4 * i : w % kRowSets, r = lane >> 3;
+        xp[i] = x + (size_t)min(t0 + 8 * rs + r, T - 1) * d + 8 * ((lane & 7) ^ (4 * (rs & 1) + (r >> 1)));
+    }
     // (a hidden slice starts at hidden tile blockIdx.y * NH)
     const __bf16* af = r1f + (((size_t)(MODE == kHiddenSlice ? blockIdx.y * NH : 0) + w * HT) * NK32 * 64 + lane) * 8;
 
@@ -92,13 +107,13 @@ __global__ __launch_bounds__(256) void router_fused_kernel(
             for (int h = 0; h < HT; ++h) a[ks][h] = load8(af + ((size_t)h * NK32 + 2 * kb + ks) * 512);
     };
     auto compute = [&](int kbl, const bf16x8 (&a)[2][HT]) {
-        const char* src = xs + c * kXRowC + kbl * 128 + q * 16;
+        const char* src = xs + kbl * kBlock + c * 128;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             bf16x8 b[TT];
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
-                b[tt] = *reinterpret_cast<const bf16x8*>(src + tt * 16 * kXRowC + ks * 64);
+                b[tt] = *reinterpret_cast<const bf16x8*>(src + tt * 16 * 128 + (((4 * ks + q) ^ (c >> 1)) << 4));
 #pragma unroll
             for (int h = 0; h < HT; ++h)
 #pragma unroll
@@ -109,27 +124,29 @@ __global__ __launch_bounds__(256) void router_fused_kernel(
     if constexpr (MODE != kScoresSlice) {
     for (int kb0 = 0; kb0 < NKB; kb0 += KBC) {
         const int nkb = min(KBC, NKB - kb0);  // a multiple of 4: d is a multiple of 256
-        {
-            bf16x8 xr[NR * KBC];
-#pragma unroll
-            for (int i = 0; i < KBC; ++i)
-                if (i < nkb && ld_ok) {
-                    xr[NR * i] = load8(xp0 + 64 * (kb0 + i));
-                    if (NR == 2) xr[NR * i + NR - 1] = load8(xp1 + 64 * (kb0 + i));
-                }
-            if (kb0 > 0) lds_barrier();  // the previous chunk has been consumed
-#pragma unroll
-            for (int i = 0; i < KBC; ++i)
-                if (i < nkb && ld_ok) {
-                    *reinterpret_cast<bf16x8*>(xst + i * 128) = xr[NR * i];
-                    if (NR == 2)
-                        *reinterpret_cast<bf16x8*>(xst + 32 * kXRowC + i * 128) = xr[NR * i + NR - 1];
-                }
-        }
         if (kb0 == 0) {
 #pragma unroll
             for (int i = 0; i < 3; ++i) load_a(i, ar[i]);
+        } else {
+            lds_barrier();  // the previous chunk has been consumed
         }
+        if (kRowSets >= 4) {
+#pragma unroll
+            for (int k = 0; k < KBC; ++k)
+                if (k < nkb) {
+#pragma unroll
+                    for (int i = 0; i < kOwn; ++i) row_set_to_lds(xp[i] + 64 * (kb0 + k), xs + k * kBlock + (w + 4 * i) * 1024);
+                }
+        } else {
+            constexpr int kAtOnce = kRowSets >= 4 ? 1 : 4 / kRowSets;  // K blocks that the wavefronts share at a time
+#pragma unroll
+            for (int k0 = 0; k0 < KBC; k0 += kAtOnce)
+                if (k0 < nkb) {
+                    const int k = k0 + w / kRowSets;
+                    row_set_to_lds(xp[0] + 64 * (kb0 + k), xs + k * kBlock + (w % kRowSets) * 1024);
+                }
+        }
+        wait_vmem();
         lds_barrier();
         for (int kbl = 0; kbl < nkb; kbl += 4) {  // nkb is a multiple of 4
 #pragma unroll
@@ -158,6 +175,7 @@ __global__ __launch_bounds__(256) void router_fused_kernel(
     if constexpr (MODE == kScoresSlice) load_r2(blockIdx.y * tiles_y + w, r2a[0]);
     else if constexpr (MODE == kWhole) load_r2(w, r2a[0]);
 
+    if constexpr (MODE == kWhole && kInPlace) lds_barrier();  // every wavefront is done with x
     // lane (q, c) of tile (h, tt): hidden units 16*(w*HT + h) + 4q + r of token 16tt + c
 #pragma unroll
     for (int h = 0; h < HT && MODE != kScoresSlice; ++h) {
@@ -349,8 +367,8 @@ void launch_t3(const dmoe_layer& L, const void* x, int T, float* scores, float t
     const PackedLayout P = packed_layout(L);
     const int E = L.n_experts, W = div_up(E, 64);
     constexpr int TOK = 16 * TT;
-    const size_t lds = TOK * (KBC * 128 + 16) + TOK * (NH * 32 + 16) + 256 * 4 +
-                       (mask ? (size_t)5 * 64 * W * 8 : 0);  // the gate's words only when it runs
+    const size_t hid = TOK * (NH * 32 + 16) + 256 * 4 + (mask ? (size_t)5 * 64 * W * 8 : 0);  // the gate's words only when it runs
+    const size_t lds = KBC == 4 ? std::max<size_t>(TOK * KBC * 128, hid) : TOK * KBC * 128 + hid;
     static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
     std::call_once(attr_once, [&] {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&router_fused_kernel<NH, ETW, KBC, TT>),
@@ -373,7 +391,10 @@ void launch_t2(const dmoe_layer& L, const void* x, int T, int split, float* scor
         launch_t3<NH, ETW, 16, 1>(L, x, T, scores, tau, mask, group_cnt, sets, s);
     else if (split == 2)
         launch_t3<NH, ETW, 16, 2>(L, x, T, scores, tau, mask, group_cnt, sets, s);
-    else if (kBig > 4 && div_up(T, 64) <= 512)
+    // (chunks of four blocks and the hidden rows in their place: four workgroups of d_h <= 128 and up to 128 experts share a CU
+    // and hide each other's latency, which pays as soon as a CU has more than one.  Forward, 128 experts of 24, d = 768, large chunks / these:
+    // 17000 tokens 130.5 / 126.3 us, 20000 121.5 / 117.6, 30000 179 / 174)
+    else if (kBig > 4 && div_up(T, 64) <= (four_per_cu(NH, ETW, 4, kWhole) ? 256 : 512))
         launch_t3<NH, ETW, kBig, 4>(L, x, T, scores, tau, mask, group_cnt, sets, s);
     else
         launch_t3<NH, ETW, 4, 4>(L, x, T, scores, tau, mask, group_cnt, sets, s);
@@ -749,7 +770,7 @@ static bool launch_router_hidden(const dmoe_layer& L, const void* x, int T, void
     const int NG = div_up(T, kGroup);
     if (NG * (dh / 128) >= 256) {  // tiles of 64 x 128 fill the chip: 4096 tokens, d_h = 512, 2048 experts 39.5 against 43.8 us
         constexpr int NH = 8, KBC = 12;
-        const size_t lds = 64 * (KBC * 128 + 16) + 64 * (NH * 32 + 16) + 256 * 4;
+        const size_t lds = 64 * KBC * 128;
         static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
         std::call_once(attr_once, [&] {
             (void)hipFuncSetAttribute(
