@@ -842,7 +842,8 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
 // through registers with two blocks in flight / straight to LDS with one: 50432 tokens at 50 % 377 / 367 us (the first call on new
 // buffers 412 / 398), 30000 at 30 % 192 / 187, 12608 at 20 % 94 / 93.  Built and slower: rows before weights (374), everything at the
 // block's start (376), one workgroup of 512 rows per CU (388).
-template <int MT, int TT, bool NEAR>
+// ALIGNED: x at a 16-byte address, as loads to LDS want it; at any other its rows go through registers.
+template <int MT, int TT, bool NEAR, bool ALIGNED>
 __global__ __launch_bounds__(256, 2) void up_wide_plain_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf, const __bf16* __restrict__ b_up,
     const int32_t* __restrict__ witem, const int2* __restrict__ worder,
@@ -898,7 +899,10 @@ __global__ __launch_bounds__(256, 2) void up_wide_plain_kernel(
     auto request_w = [&](int i, int kb, char* to) {
         buffer_to_lds(wf, lane * 16, ((2 * i + (w >> 1)) * NK32 + 2 * kb + (w & 1)) * 1024, to + (4 * i + w) * 1024);
     };
-    auto request_x = [&](int i, const uint32_t (&xoff)[NL], int kb) { xrows.to_lds(xoff[i], kb, xs + 1024 * i); };
+    auto request_x = [&](int i, const uint32_t (&xoff)[NL], int kb) {
+        if constexpr (ALIGNED) xrows.to_lds(xoff[i], kb, xs + 1024 * i);
+        else *reinterpret_cast<bf16x8*>(xs + 1024 * i + lane * 16) = xrows.load(xoff[i], kb);
+    };
     auto park_bias = [&](int e, int par) {  // the item's biases, by neuron
         if ((int)threadIdx.x < MT * 16)
             sbias[par * MT * 16 + threadIdx.x] =
@@ -1287,11 +1291,11 @@ void launch_up_wide_t(const dmoe_layer& L, const void* x, const PackedLayout& P,
         alist, (__bf16*)H, L.d_model, L.n_experts, L.expert_size, L.act);
 }
 
-template <int MT, int TT, bool NEAR>
+template <int MT, int TT, bool NEAR, bool ALIGNED = true>
 void launch_up_wide_plain_t(const dmoe_layer& L, const void* x, const PackedLayout& P,
                             const int32_t* witem, const void* worder, const int32_t* alist,
                             void* H, int grid, hipStream_t s) {
-    launch_kernel(up_wide_plain_kernel<MT, TT, NEAR>, grid, 256, 0, s, (const __bf16*)x,
+    launch_kernel(up_wide_plain_kernel<MT, TT, NEAR, ALIGNED>, grid, 256, 0, s, (const __bf16*)x,
         (const __bf16*)(static_cast<const char*>(L.packed) + P.wupf), (const __bf16*)L.b_up, witem, (const int2*)worder,
         alist, (__bf16*)H, L.d_model, L.n_experts, L.expert_size, L.act);
 }
@@ -1432,6 +1436,7 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
         if (S.sets && L.gated) launch_up_wide_sets<4, true>(L, x, P, S, H, s);
         else if (S.sets) launch_up_wide_sets<8, false>(L, x, P, S, H, s);
         else if (L.gated) launch_up_wide_t<4, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
+        else if (reinterpret_cast<uintptr_t>(x) & 15) launch_up_wide_plain_t<8, 4, false, false>(L, x, P, witem, worder, alist, H, wgrid, s);
         else if (near) launch_up_wide_plain_t<8, 4, true>(L, x, P, witem, worder, alist, H, wgrid, s);
         else launch_up_wide_plain_t<8, 4, false>(L, x, P, witem, worder, alist, H, wgrid, s);
         return;

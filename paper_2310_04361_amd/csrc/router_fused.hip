@@ -81,6 +81,7 @@ __global__ __launch_bounds__(256, (four_per_cu(NH, ETW, KBC, MODE) ? 4 : 1)) voi
     // 50432 tokens, with the hidden rows in the place of x besides (two -> four workgroups per CU), 317 / 312; 16384 tokens 122.7 / 122.3.
     constexpr int kRowSets = TOK / 8;                        // loads per K block, dealt to the wavefronts in turn
     constexpr int kOwn = kRowSets >= 4 ? kRowSets / 4 : 1;   // row sets of a wavefront
+    const bool x_aligned = (reinterpret_cast<uintptr_t>(x) & 15) == 0;
     const __bf16* xp[kOwn];
 #pragma unroll
     for (int i = 0; i < kOwn; ++i) {
@@ -130,22 +131,19 @@ __global__ __launch_bounds__(256, (four_per_cu(NH, ETW, KBC, MODE) ? 4 : 1)) voi
         } else {
             lds_barrier();  // the previous chunk has been consumed
         }
-        if (kRowSets >= 4) {
-#pragma unroll
-            for (int k = 0; k < KBC; ++k)
-                if (k < nkb) {
-#pragma unroll
-                    for (int i = 0; i < kOwn; ++i) row_set_to_lds(xp[i] + 64 * (kb0 + k), xs + k * kBlock + (w + 4 * i) * 1024);
-                }
-        } else {
-            constexpr int kAtOnce = kRowSets >= 4 ? 1 : 4 / kRowSets;  // K blocks that the wavefronts share at a time
+        constexpr int kAtOnce = kRowSets >= 4 ? 1 : 4 / kRowSets;  // K blocks that the wavefronts share at a time
+        auto stage = [&](auto&& set) {
 #pragma unroll
             for (int k0 = 0; k0 < KBC; k0 += kAtOnce)
                 if (k0 < nkb) {
-                    const int k = k0 + w / kRowSets;
-                    row_set_to_lds(xp[0] + 64 * (kb0 + k), xs + k * kBlock + (w % kRowSets) * 1024);
+                    const int k = kRowSets >= 4 ? k0 : k0 + w / kRowSets, rs = kRowSets >= 4 ? w : w % kRowSets;
+#pragma unroll
+                    for (int i = 0; i < kOwn; ++i) set(xp[i] + 64 * (kb0 + k), xs + k * kBlock + (rs + 4 * i) * 1024);
                 }
-        }
+        };
+        // (a load to LDS wants 16-byte addresses; x at any other one goes through registers)
+        if (x_aligned) stage([](const __bf16* p, char* to) { row_set_to_lds(p, to); });
+        else stage([&](const __bf16* p, char* to) { *reinterpret_cast<bf16x8*>(to + lane * 16) = load8(p); });
         wait_vmem();
         lds_barrier();
         for (int kbl = 0; kbl < nkb; kbl += 4) {  // nkb is a multiple of 4
