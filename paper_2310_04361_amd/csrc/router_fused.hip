@@ -132,18 +132,32 @@ __global__ __launch_bounds__(256, (four_per_cu(NH, ETW, KBC, MODE) ? 4 : 1)) voi
             lds_barrier();  // the previous chunk has been consumed
         }
         constexpr int kAtOnce = kRowSets >= 4 ? 1 : 4 / kRowSets;  // K blocks that the wavefronts share at a time
-        auto stage = [&](auto&& set) {
+        auto place = [&](int k0, int i, int& k) {
+            k = kRowSets >= 4 ? k0 : k0 + w / kRowSets;
+            return xs + k * kBlock + ((kRowSets >= 4 ? w : w % kRowSets) + 4 * i) * 1024;
+        };
+        if (x_aligned) {
 #pragma unroll
             for (int k0 = 0; k0 < KBC; k0 += kAtOnce)
                 if (k0 < nkb) {
-                    const int k = kRowSets >= 4 ? k0 : k0 + w / kRowSets, rs = kRowSets >= 4 ? w : w % kRowSets;
 #pragma unroll
-                    for (int i = 0; i < kOwn; ++i) set(xp[i] + 64 * (kb0 + k), xs + k * kBlock + (rs + 4 * i) * 1024);
+                    for (int i = 0; i < kOwn; ++i) {
+                        int k;
+                        char* const to = place(k0, i, k);
+                        row_set_to_lds(xp[i] + 64 * (kb0 + k), to);
+                    }
                 }
-        };
-        // (a load to LDS wants 16-byte addresses; x at any other one goes through registers)
-        if (x_aligned) stage([](const __bf16* p, char* to) { row_set_to_lds(p, to); });
-        else stage([&](const __bf16* p, char* to) { *reinterpret_cast<bf16x8*>(to + lane * 16) = load8(p); });
+        } else {  // a load to LDS wants 16-byte addresses; x at any other one goes through registers
+#pragma nounroll
+            for (int k0 = 0; k0 < nkb; k0 += kAtOnce) {
+#pragma unroll
+                for (int i = 0; i < kOwn; ++i) {
+                    int k;
+                    char* const to = place(k0, i, k);
+                    *reinterpret_cast<bf16x8*>(to + lane * 16) = load8(xp[i] + 64 * (kb0 + k));
+                }
+            }
+        }
         wait_vmem();
         lds_barrier();
         for (int kbl = 0; kbl < nkb; kbl += 4) {  // nkb is a multiple of 4
