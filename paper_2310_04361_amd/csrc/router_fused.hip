@@ -47,7 +47,8 @@ __device__ __forceinline__ void row_set_to_lds(const __bf16* p, char* lds) {
 enum { kWhole = 0, kHiddenSlice = 1, kScoresSlice = 2 };
 // Registers for four workgroups per CU, whose LDS they leave room for.
 constexpr bool four_per_cu(int nh, int etw, int kbc, int mode) { return mode == kWhole && kbc == 4 && nh <= 8 && etw <= 2; }
-template <int NH, int ETW, int KBC, int TT, int MODE = kWhole>
+// ALIGNED: x at a 16-byte address, as loads to LDS want it; at any other its rows go through registers.
+template <int NH, int ETW, int KBC, int TT, int MODE = kWhole, bool ALIGNED = true>
 __global__ __launch_bounds__(256, (four_per_cu(NH, ETW, KBC, MODE) ? 4 : 1)) void router_fused_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ r1f, const __bf16* __restrict__ r_b1,
     const __bf16* __restrict__ r2f, const __bf16* __restrict__ r_b2, float* __restrict__ scores,
@@ -81,7 +82,6 @@ __global__ __launch_bounds__(256, (four_per_cu(NH, ETW, KBC, MODE) ? 4 : 1)) voi
     // 50432 tokens, with the hidden rows in the place of x besides (two -> four workgroups per CU), 317 / 312; 16384 tokens 122.7 / 122.3.
     constexpr int kRowSets = TOK / 8;                        // loads per K block, dealt to the wavefronts in turn
     constexpr int kOwn = kRowSets >= 4 ? kRowSets / 4 : 1;   // row sets of a wavefront
-    const bool x_aligned = (reinterpret_cast<uintptr_t>(x) & 15) == 0;
     const __bf16* xp[kOwn];
 #pragma unroll
     for (int i = 0; i < kOwn; ++i) {
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256, (four_per_cu(NH, ETW, KBC, MODE) ? 4 : 1)) voi
             k = kRowSets >= 4 ? k0 : k0 + w / kRowSets;
             return xs + k * kBlock + ((kRowSets >= 4 ? w : w % kRowSets) + 4 * i) * 1024;
         };
-        if (x_aligned) {
+        if constexpr (ALIGNED) {
 #pragma unroll
             for (int k0 = 0; k0 < KBC; k0 += kAtOnce)
                 if (k0 < nkb) {
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256, (four_per_cu(NH, ETW, KBC, MODE) ? 4 : 1)) voi
                         row_set_to_lds(xp[i] + 64 * (kb0 + k), to);
                     }
                 }
-        } else {  // a load to LDS wants 16-byte addresses; x at any other one goes through registers
+        } else {
 #pragma nounroll
             for (int k0 = 0; k0 < nkb; k0 += kAtOnce) {
 #pragma unroll
@@ -381,16 +381,19 @@ void launch_t3(const dmoe_layer& L, const void* x, int T, float* scores, float t
     constexpr int TOK = 16 * TT;
     const size_t hid = TOK * (NH * 32 + 16) + 256 * 4 + (mask ? (size_t)5 * 64 * W * 8 : 0);  // the gate's words only when it runs
     const size_t lds = KBC == 4 ? std::max<size_t>(TOK * KBC * 128, hid) : TOK * KBC * 128 + hid;
-    static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
-    std::call_once(attr_once, [&] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&router_fused_kernel<NH, ETW, KBC, TT>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    });
     const char* pk = static_cast<const char*>(L.packed);
-    launch_kernel(router_fused_kernel<NH, ETW, KBC, TT>, div_up(T, TOK), 256, lds, s, 
-        (const __bf16*)x, (const __bf16*)(pk + P.r1f), (const __bf16*)L.r_b1,
-        (const __bf16*)(pk + P.r2f), (const __bf16*)L.r_b2, scores, T, L.d_model, E, tau,
-        mask ? (sets ? 2 : 1) : 0, mask, group_cnt, nullptr, 0, 0);
+    auto go = [&](auto kernel, std::once_flag& attr_once) {
+        std::call_once(attr_once, [&] {  // kernel attributes: once per process, thread-safe
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        });
+        launch_kernel(kernel, div_up(T, TOK), 256, lds, s,
+            (const __bf16*)x, (const __bf16*)(pk + P.r1f), (const __bf16*)L.r_b1,
+            (const __bf16*)(pk + P.r2f), (const __bf16*)L.r_b2, scores, T, L.d_model, E, tau,
+            mask ? (sets ? 2 : 1) : 0, mask, group_cnt, nullptr, 0, 0);
+    };
+    static std::once_flag once[2];
+    if (reinterpret_cast<uintptr_t>(x) & 15) go(router_fused_kernel<NH, ETW, KBC, TT, kWhole, false>, once[1]);
+    else go(router_fused_kernel<NH, ETW, KBC, TT>, once[0]);
 }
 
 template <int NH, int ETW>
@@ -783,16 +786,18 @@ static bool launch_router_hidden(const dmoe_layer& L, const void* x, int T, void
     if (NG * (dh / 128) >= 256) {  // tiles of 64 x 128 fill the chip: 4096 tokens, d_h = 512, 2048 experts 39.5 against 43.8 us
         constexpr int NH = 8, KBC = 12;
         const size_t lds = 64 * KBC * 128;
-        static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
-        std::call_once(attr_once, [&] {
-            (void)hipFuncSetAttribute(
-                reinterpret_cast<const void*>(&router_fused_kernel<NH, 2, KBC, 4, kHiddenSlice>),
-                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        });
-        launch_kernel(router_fused_kernel<NH, 2, KBC, 4, kHiddenSlice>, dim3(NG, dh / 128), 256, lds, s,
-            (const __bf16*)x, r1f, (const __bf16*)L.r_b1, nullptr, nullptr,
-            nullptr, T, L.d_model, L.n_experts, 0.0f, 0, nullptr, nullptr,
-            (__bf16*)hid, dh, 0);
+        auto go = [&](auto kernel, std::once_flag& attr_once) {
+            std::call_once(attr_once, [&] {
+                (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            });
+            launch_kernel(kernel, dim3(NG, dh / 128), 256, lds, s,
+                (const __bf16*)x, r1f, (const __bf16*)L.r_b1, nullptr, nullptr,
+                nullptr, T, L.d_model, L.n_experts, 0.0f, 0, nullptr, nullptr,
+                (__bf16*)hid, dh, 0);
+        };
+        static std::once_flag once[2];
+        if (reinterpret_cast<uintptr_t>(x) & 15) go(router_fused_kernel<NH, 2, KBC, 4, kHiddenSlice, false>, once[1]);
+        else go(router_fused_kernel<NH, 2, KBC, 4, kHiddenSlice>, once[0]);
         return false;
     }
     // x is the larger of the two that the XCDs share (by_tokens 1 / 0, router in all: d_h = 256, 333 tokens 11.5 us either
