@@ -9,9 +9,11 @@ from paper_2310_04361_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("skip", [2, 4])  # elements: 4 and 8 bytes
+@pytest.mark.parametrize("skip", [1, 2, 4])  # elements: 2, 4 and 8 bytes
 @pytest.mark.parametrize("d,E,m,d_h,T", [(768, 24, 128, 128, 3200), (768, 128, 24, 128, 1000), (512, 40, 100, 128, 16500), (256, 70, 90, 64, 130),
-                                         (2048, 600, 2, 512, 1600)])
+                                         (2048, 600, 2, 512, 1600),
+                                         # 32 and 64 tokens a workgroup, a last chunk of four K blocks; hidden rows in slices of 128
+                                         (1280, 100, 8, 128, 7000), (1024, 60, 8, 128, 12300), (2048, 600, 2, 512, 4100)])
 def test_unaligned_x(d, E, m, d_h, T, skip):
     import torch
     from paper_2310_04361_amd import binding as B
