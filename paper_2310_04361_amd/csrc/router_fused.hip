@@ -399,7 +399,12 @@ void launch_t3(const dmoe_layer& L, const void* x, int T, float* scores, float t
             mask ? (sets ? 2 : 1) : 0, mask, group_cnt, nullptr, 0, 0);
     };
     static std::once_flag once[2];
-    if (reinterpret_cast<uintptr_t>(x) & 15) go(router_fused_kernel<NH, ETW, KBC, TT, kWhole, false>, once[1]);
+    // Through registers also where two workgroups of 32 tokens share a CU and there are more of them than CUs: on an x
+    // that comes from memory a workgroup whose loads go to LDS, which can only wait for all of them, then takes longer.  d = 768, 128 experts of
+    // 24, forward, straight to LDS / so: 9000 tokens 85.2 / 83.8 us, 10000 91.5 / 90.4, 12000 104.2 / 102.7; 512 experts, router alone, 12000 tokens 18.1 /
+    // 16.7.  With at most one per CU 7000 tokens 75.2 / 75.5; with LDS for one only (512 experts with the gate, 12000 tokens) 177.1 / 177.2.
+    const bool share = TT == 2 && div_up(T, TOK) > 256 && lds <= 80 * 1024;
+    if (share || (reinterpret_cast<uintptr_t>(x) & 15)) go(router_fused_kernel<NH, ETW, KBC, TT, kWhole, false>, once[1]);
     else go(router_fused_kernel<NH, ETW, KBC, TT>, once[0]);
 }
 
