@@ -362,7 +362,7 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
         int32_t* witem = reinterpret_cast<int32_t*>(ws + w.witem);
         int32_t* wfirst = reinterpret_cast<int32_t*>(ws + w.wfirst);
         const bool sets = use_sets(L, T, offsets_out != nullptr);
-        const TokenSets S{sets ? reinterpret_cast<const int32_t*>(ws + w.sub_cnt) : nullptr, group_off, item_start, T, false};
+        const TokenSets S{sets ? reinterpret_cast<const int32_t*>(ws + w.sub_cnt) : nullptr, group_off, item_start, T, 0, 0};
         if (!sets)
             launch_scan_and_fill(mask, T, L.n_experts, group_off, counts, offsets, item_start,
                                  up_rows_bf16(L), lists_out, alist, up_window_groups(L, T), witem,

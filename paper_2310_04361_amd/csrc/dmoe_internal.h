@@ -228,7 +228,7 @@ struct TokenSets {
     int32_t* group_off;    // [ceil(T / 64) + 1][E]
     int32_t* item_start;   // [E + 1]
     int T;
-    bool in_order;         // (sets_grid)
+    int wave_step, block_step;  // (sets_grid)
 };
 void launch_scan_and_fill(const uint64_t* mask, int T, int E, int32_t* group_off, int32_t* counts,
                           int32_t* offsets, int32_t* item_start, int rows_per_item,

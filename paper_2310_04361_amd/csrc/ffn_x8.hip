@@ -428,10 +428,11 @@ __device__ __forceinline__ void hidden_row_x8(const f32x16 (&up)[MT / 2], const 
     if (h == 0) hs8[row] = (uint8_t)(127 + s_exp);
 }
 
-// The same for a small batch: one item of 128 TJ rows per workgroup, D K blocks in flight, the item's tiles
+// The same for a small batch: one item of 256 rows per workgroup, D K blocks in flight, the item's tiles
 // dealt to the wavefronts (see up_wide_sets_kernel in ffn_bf16.hip).
-template <int MT, bool GATED, bool H8OUT, int TJ, int D>
-__global__ __launch_bounds__(256, TJ == 1 ? 2 : 1) void up_wide_sets_x8_kernel(
+constexpr int kSetsTiles = 2;  // tiles of 32 rows a wavefront
+template <int MT, bool GATED, bool H8OUT, int D>
+__global__ __launch_bounds__(256, 1) void up_wide_sets_x8_kernel(
     const uint8_t* __restrict__ x8, const float* __restrict__ xscale, const uint8_t* __restrict__ wupx,
     const uint8_t* __restrict__ wgatex, const float* __restrict__ w_scales, const __bf16* __restrict__ b_up,
     __bf16* __restrict__ Hf, uint8_t* __restrict__ H8, uint8_t* __restrict__ hs8, int d, int E, int m, int act, const TokenSets S) {
@@ -439,6 +440,7 @@ __global__ __launch_bounds__(256, TJ == 1 ? 2 : 1) void up_wide_sets_x8_kernel(
     constexpr int KS = MT / 2;
     constexpr int NT = BR * MT;         // neuron tiles (2 KiB of weights each) per K block
     constexpr int NJ = NT / 2;          // ... of 32 rows
+    constexpr int TJ = kSetsTiles;
     constexpr int WR = 32 * TJ;         // rows per wavefront
     constexpr int UR = 4 * WR;          // rows per work item
     constexpr int NWL = NT / 2;         // weight load instructions per thread and K block
@@ -458,7 +460,7 @@ __global__ __launch_bounds__(256, TJ == 1 ? 2 : 1) void up_wide_sets_x8_kernel(
     const int rows = tok.total - UR * slot;
     if (rows <= 0) return;
     // row 128 tj + 32 w + c of the item is row 32 tj + c of wavefront w
-    tok.list<WR, UR>(S.T, UR * slot, s_list, [&](int r) { return ((r >> 5) & 3) == w ? 32 * (r >> 7) + (r & 31) : -1; });
+    tok.list<WR, UR>(UR * slot, s_list, [&](int r) { return ((r >> 5) & 3) == w ? 32 * (r >> 7) + (r & 31) : -1; });
     // (the copies of the weights: see up_wide_x8_kernel)
     const size_t we = (size_t)e * MT * NKB * 2048 + (threadIdx.x >> 7) * (size_t)NKB * 2048 + (threadIdx.x & 127) * 16;
     const size_t wstride = (size_t)2 * NKB * 2048;
@@ -612,7 +614,7 @@ __global__ __launch_bounds__(256, TJ == 1 ? 2 : 1) void up_wide_sets_x8_kernel(
         });
     };
     // (every path has the same barriers)
-    if (TJ == 2 && rows > 128 + 32 * w) work(std::integral_constant<int, TJ>{});
+    if (rows > 128 + 32 * w) work(std::integral_constant<int, TJ>{});
     else if (rows > 32 * w) work(std::integral_constant<int, 1>{});
     else work(std::integral_constant<int, 0>{});
 }
@@ -636,18 +638,18 @@ void launch_up_x8_t(const dmoe_layer& L, const PackedLayout& P, const uint8_t* x
                   (__bf16*)H, H8, hs8, L.d_model, L.n_experts, L.expert_size, L.act);
 }
 
-template <int MT, bool GATED, bool H8OUT, int TJ, int D>
+template <int MT, bool GATED, bool H8OUT, int D>
 void launch_up_x8_sets_t(const dmoe_layer& L, const PackedLayout& P, const uint8_t* x8, const float* xscale, const TokenSets& S,
                          void* H, uint8_t* H8, uint8_t* hs8, hipStream_t s) {
-    constexpr int NT = (GATED ? 2 : 1) * MT;
+    constexpr int NT = (GATED ? 2 : 1) * MT, TJ = kSetsTiles;
     const size_t lds = 2 * NT * 2048 + 4 * (size_t)TJ * 32 * kX8RowBytes + MT * 16 * sizeof(float) + 4 * 32 * TJ * sizeof(int32_t);
     static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
     std::call_once(attr_once, [&] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_wide_sets_x8_kernel<MT, GATED, H8OUT, TJ, D>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_wide_sets_x8_kernel<MT, GATED, H8OUT, D>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
     const char* pk = static_cast<const char*>(L.packed);
-    launch_kernel(up_wide_sets_x8_kernel<MT, GATED, H8OUT, TJ, D>, L.n_experts * div_up(S.T, 128 * TJ), 256, lds, s, x8, xscale,
+    launch_kernel(up_wide_sets_x8_kernel<MT, GATED, H8OUT, D>, L.n_experts * div_up(S.T, 128 * TJ), 256, lds, s, x8, xscale,
                   (const uint8_t*)(pk + P.wupx8), (const uint8_t*)(pk + P.wgatex8), (const float*)(pk + P.scales),
                   (const __bf16*)L.b_up, (__bf16*)H, H8, hs8, L.d_model, L.n_experts, L.expert_size, L.act, S);
 }
@@ -655,8 +657,8 @@ void launch_up_x8_sets_t(const dmoe_layer& L, const PackedLayout& P, const uint8
 template <int MT, bool GATED, bool H8OUT>
 void launch_up_x8_sets(const dmoe_layer& L, const PackedLayout& P, const uint8_t* x8, const float* xscale, const TokenSets& S,
                        void* H, uint8_t* H8, uint8_t* hs8, hipStream_t s) {
-    if (L.d_model % 512) launch_up_x8_sets_t<MT, GATED, H8OUT, 2, 2>(L, P, x8, xscale, S, H, H8, hs8, s);  // (whole trips)
-    else launch_up_x8_sets_t<MT, GATED, H8OUT, 2, 4>(L, P, x8, xscale, S, H, H8, hs8, s);
+    if (L.d_model % 512) launch_up_x8_sets_t<MT, GATED, H8OUT, 2>(L, P, x8, xscale, S, H, H8, hs8, s);  // (whole trips)
+    else launch_up_x8_sets_t<MT, GATED, H8OUT, 4>(L, P, x8, xscale, S, H, H8, hs8, s);
 }
 
 }  // namespace

@@ -27,15 +27,15 @@ __device__ __forceinline__ int wave_prefix(int v) {
 // One expert's tokens, over the lanes of a wavefront: lane l has the 16 C tokens from 16 C l on, C = 1, 2 or 4.
 struct ExpertTokens {
     uint32_t set[4];  // which of them, 16 in each
+    int C;            // (uniform)
     int first;        // how many come before them
     int total;        // all of the expert's (uniform)
 
-    static __device__ __forceinline__ int rows_of_lane(int T) { return T <= 1024 ? 1 : (T <= 2048 ? 2 : 4); }
-
     // leave: this wavefront writes the expert's group_off and item_start (rows_per_item rows an item).
     __device__ __forceinline__ void load(const TokenSets& S, int E, int e, int rows_per_item, bool leave) {
-        const int lane = threadIdx.x & 63, rows = (S.T + 15) >> 4, C = rows_of_lane(S.T);
+        const int lane = threadIdx.x & 63, rows = (S.T + 15) >> 4;
         int n = 0;
+        C = S.T <= 1024 ? 1 : (S.T <= 2048 ? 2 : 4);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             set[c] = 0u;
@@ -60,8 +60,8 @@ struct ExpertTokens {
     }
     // The tokens of ranks lo + r, 0 <= r < RANKS, to list[at(r)] (LDS of this wavefront) where 0 <= at(r) < N; -1 where there is none.
     template <int N, int RANKS, class At>
-    __device__ __forceinline__ void list(int T, int lo, int32_t* list, At&& at) const {
-        const int lane = threadIdx.x & 63, C = rows_of_lane(T);
+    __device__ __forceinline__ void list(int lo, int32_t* list, At&& at) const {
+        const int lane = threadIdx.x & 63;
         if (lane < N) list[lane] = -1;
         int rank = first - lo;
 #pragma unroll
@@ -83,43 +83,28 @@ struct ExpertTokens {
     }
 };
 
-// The work items (of rows_per_item rows) of a wavefront, four to a workgroup.  Wavefront i has expert i % E, and of its items every
-// (n / E)th from i / E on, or, of more experts than wavefronts, every nth expert.  So the first items of all experts, which
-// there always are, come first.  There is a wavefront for every item that an expert can have, so that none has two while others
-// have none.  Where the chip holds them all (at most `resident` workgroups) the first items go over all the CUs before a CU
-// gets a second one, otherwise (S.in_order) they go to the workgroups that start first.
+// The work item (of rows_per_item rows) of a wavefront, four to a workgroup: wavefront i has item i / E of expert i % E, so
+// that the first items of all experts, which there always are, come first.  There is a wavefront for every item that an
+// expert can have.  Where the chip holds them all (at most `resident` workgroups) the first items go over all the CUs before
+// a CU gets a second one, otherwise they go to the workgroups that start first.
 inline int sets_grid(TokenSets& S, int E, int rows_per_item, int resident) {
     const int grid = (int)(((long long)E * div_up(S.T, rows_per_item) + 3) / 4);
-    S.in_order = grid > resident;
+    S.wave_step = grid > resident ? 1 : grid;
+    S.block_step = grid > resident ? 4 : 1;
     return grid;
 }
-struct SetItems {
-    int e, item, slot, per, e_step;
+struct SetItem {
+    int e, item;  // the expert and which of its items
+    int index;    // the item's place among all that there can be
     ExpertTokens tok;
-    // false: no work.  The first wavefront of an expert leaves its group_off and item_start.
+    // false: no such item.  The first wavefront of an expert leaves its group_off and item_start.
     __device__ __forceinline__ bool start(const TokenSets& S, int E, int wave, int rows_per_item) {
-        const int n = 4 * (int)gridDim.x, i = S.in_order ? 4 * (int)blockIdx.x + wave : wave * (int)gridDim.x + (int)blockIdx.x;
-        per = n >= E ? n / E : 1;
-        e_step = n >= E ? E : n;
-        e = n >= E ? i % E : i;
-        slot = n >= E ? i / E : 0;
-        if (slot >= per) return false;
-        item = slot;
-        tok.load(S, E, e, rows_per_item, slot == 0);
-        return seek(S, E, rows_per_item);
-    }
-    __device__ __forceinline__ bool next(const TokenSets& S, int E, int rows_per_item) {
-        item += per;
-        return seek(S, E, rows_per_item);
-    }
-    __device__ __forceinline__ bool seek(const TokenSets& S, int E, int rows_per_item) {
-        while (item * rows_per_item >= tok.total) {
-            if (e + e_step >= E) return false;
-            e += e_step;
-            item = slot;
-            tok.load(S, E, e, rows_per_item, slot == 0);
-        }
-        return true;
+        const int i = S.wave_step * wave + S.block_step * (int)blockIdx.x;
+        e = i % E;
+        item = i / E;
+        index = e * ((S.T + rows_per_item - 1) / rows_per_item) + item;
+        tok.load(S, E, e, rows_per_item, item == 0);
+        return item * rows_per_item < tok.total;
     }
 };
 
