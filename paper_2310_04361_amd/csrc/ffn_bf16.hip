@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : (SETS ? 2 : 1)) void up_bf16_k
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf,
     const __bf16* __restrict__ wgatef, const __bf16* __restrict__ b_up,
     const int32_t* __restrict__ witem, const int32_t* __restrict__ wfirst, int NW,
-    const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act, const TokenSets S) {
+    const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act, const SetsArg<SETS> S) {
     constexpr int BR = GATED ? 2 : 1;
     constexpr int KS = MT / 2;
     constexpr int UR = TT * 16;
@@ -207,7 +207,9 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : (SETS ? 2 : 1)) void up_bf16_k
     };
     int j = first + wave;
     SetItem si;  // SETS: the only one
-    if (SETS ? si.start(S, E, wave_in_block, UR) : j < total) {
+    bool work = j < total;
+    if constexpr (SETS) work = si.start(S, E, wave_in_block, UR);
+    if (work) {
         int e, item;
         if (SETS) {
             e = si.e;
@@ -405,7 +407,7 @@ template <int TT, bool GATED, bool NEAR, bool SETS>
 __global__ __launch_bounds__(256) void up_tiny_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wtf, const __bf16* __restrict__ b_up,
     const int32_t* __restrict__ witem, const int32_t* __restrict__ wfirst, int NW,
-    const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act, int row_neurons, const TokenSets S) {
+    const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act, int row_neurons, const SetsArg<SETS> S) {
     constexpr int UR = TT * 16;
     constexpr int NL = TT * 2;
     extern __shared__ char smem[];
@@ -436,7 +438,8 @@ __global__ __launch_bounds__(256) void up_tiny_kernel(
     const int n_waves = (int)(gridDim.x >> 3) * 4, wave = wave_of(total - first, wave_in_block, n_waves);
     if (!SETS) __syncthreads();
     SetItem si;  // SETS: the only one
-    bool work = SETS ? si.start(S, E, wave_in_block, UR) : first + wave < total;
+    bool work = first + wave < total;
+    if constexpr (SETS) work = si.start(S, E, wave_in_block, UR);
     for (int j = first + wave; work; j += n_waves, work = !SETS && j < total) {
         int e, item;
         if (SETS) {

@@ -9,6 +9,8 @@
 // (group_off) and the expert's first item (item_start).
 #pragma once
 
+#include <type_traits>
+
 #include "dmoe_internal.h"
 
 namespace dmoe {
@@ -107,5 +109,13 @@ struct SetItem {
         return item * rows_per_item < tok.total;
     }
 };
+
+// The sets as an argument of a kernel that has an instance for lists, which has no such argument: 32 bytes more of them cost the
+// up-projection of every batch with lists 0.3 to 0.6 us (forward, 16384 tokens x 128 experts of 24, d = 768, with them 122.5, without 121.9).
+struct NoSets {
+    NoSets(const TokenSets&) {}
+};
+template <bool SETS>
+using SetsArg = std::conditional_t<SETS, TokenSets, NoSets>;
 
 }  // namespace dmoe
