@@ -579,7 +579,8 @@ __global__ __launch_bounds__(256) void up_tiny_kernel(
     }  // windows
 }
 
-// Up-projection for wide gated experts (8 neuron tiles per K step, e.g. m = 64): there the
+// Up-projection for wide experts (8 neuron tiles per K step: gated m = 64; plain m = 128 where x does not allow for
+// up_wide_plain_kernel): there the
 // weights of an expert are as large as its x rows, so streaming them once per wavefront made the
 // kernel a weight stream.  Here a workgroup of four wavefronts owns 4 x 16*TT consecutive list
 // rows of one expert and shares each K block of the weight fragments through LDS (double
@@ -605,13 +606,13 @@ __global__ __launch_bounds__(256) void up_tiny_kernel(
 // for a whole forward, but 450 -> 473 for the first one on new weights, whose way from HBM is longer than a block; one workgroup
 // of 512 rows per CU that way, four blocks of weights ahead, which halves what comes from beyond L2: 412, but 1400 tokens
 // 166 -> 186, as nothing works beside a workgroup's epilogue and tail.
-template <int MT, int TT>
+template <int MT, bool GATED, int TT>
 __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf,
-    const __bf16* __restrict__ wgatef,
+    const __bf16* __restrict__ wgatef, const __bf16* __restrict__ b_up,
     const int32_t* __restrict__ witem, const int2* __restrict__ worder,
     const int32_t* __restrict__ alist, __bf16* __restrict__ Hf, int d, int E, int m, int act) {
-    constexpr int BR = 2;
+    constexpr int BR = GATED ? 2 : 1;
     constexpr int KS = MT / 2;
     constexpr int NT = BR * MT;         // neuron tiles per K step
     constexpr int NJ = NT / 2, TJ = TT / 2;  // tiles of the 32x32x16 MFMA: neurons, list rows
@@ -625,6 +626,7 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     char* wbuf = smem;                                   // [2][NWF][1024]
     const int lane = threadIdx.x & 63, h = lane >> 5, c32 = lane & 31, w = threadIdx.x >> 6;
     char* xs = smem + 2 * NWF * 1024 + w * (WR * kUpRowBytes);   // [WR][kUpRowBytes], private
+    float* sbias = reinterpret_cast<float*>(smem + 2 * NWF * 1024 + 4 * (WR * kUpRowBytes));  // [2][MT * 16]
     const int NK32 = d / 32, NKB = d / 64;   // NKB >= 2
     const int ld_row = lane >> 3, ld_piece = lane & 7;
     // this XCD's share of the items (workgroups are dealt round-robin to the 8 XCDs; the grid is a
@@ -655,7 +657,7 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     const uint32_t woff = (uint32_t)(((w >> 1) * NK32 + (w & 1)) * 512 + lane * 8);
     bf16x8 xr[NL], wr[NWL];
     auto issue_w = [&](int i, int e, int kb) {
-        const __bf16* base = (2 * i) / MT == 1 ? wgatef : wupf;
+        const __bf16* base = (GATED && (2 * i) / MT == BR - 1) ? wgatef : wupf;
         wr[i] = load8(base + (size_t)e * MT * NK32 * 512 + (size_t)kb * 1024 + woff + (size_t)((2 * i) % MT) * NK32 * 512);
     };
     auto issue_x = [&](int i, const uint32_t (&xoff)[NL], int kb) {
@@ -667,6 +669,12 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
     auto park_x = [&](int i) {
         *reinterpret_cast<bf16x8*>(xs + (ld_row + 8 * i) * kUpRowBytes + ld_piece * 16) = xr[i];
     };
+    auto park_bias = [&](int e, int par) {  // plain experts: the item's biases, by neuron
+        if (!GATED && (int)threadIdx.x < MT * 16)
+            sbias[par * MT * 16 + threadIdx.x] =
+                b_up ? (float)b_up[(size_t)e * m + min((int)threadIdx.x, m - 1)] : 0.0f;
+    };
+
     int e, item;
     uint32_t xoff[NL];
     bool active;
@@ -686,8 +694,9 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
         park_x(i);
         issue_x(i, xoff, 1);
     }
+    park_bias(e, 0);
     lds_barrier();
-    int buf = 0;
+    int buf = 0, par = 0;
     for (;;) {
         // the item after this one (the last item names itself: its first blocks are read again
         // and never used)
@@ -789,11 +798,13 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
         lds_barrier();
         buf ^= 1;
         block(en, xoffn, 1, activen, activen);  // block NKB - 1; the next item's block 0 is parked
+        park_bias(en, par ^ 1);
         lds_barrier();
         buf ^= 1;
 
         if (active) with_activation(act, [&](auto act_c) {
             constexpr int ACT = decltype(act_c)::value;
+            const float* sb = sbias + par * MT * 16;
             // lane (h, c) of tile (nj, tj): list row 32 tj + c; registers 0..3 and 8..11 are the eight
             // neurons of piece 4 nj + h of the H row, 4..7 and 12..15 those of piece 4 nj + 2 + h
             // (neuron_of_slot over a pair of 16-row tiles)
@@ -810,7 +821,8 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
                         for (int r = 0; r < 8; ++r) {
                             const int i = 4 * half + (r & 3) + 8 * (r >> 2);
                             float v;
-                            v = activate_fast(ACT, acc[NJ / 2 + nj][tj][i]) * acc[nj][tj][i];
+                            if (GATED) v = activate_fast(ACT, acc[NJ / 2 + nj][tj][i]) * acc[nj][tj][i];
+                            else v = activate_fast(ACT, acc[nj][tj][i] + sb[n0 + r]);
                             if (n0 + r >= m) v = 0.0f;
                             hv[r] = (__bf16)v;
                         }
@@ -827,6 +839,7 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
         e = en;
         item = itemn;
         active = activen;
+        par ^= 1;
 #pragma unroll
         for (int i = 0; i < NL; ++i) xoff[i] = xoffn[i];
     }
@@ -841,8 +854,9 @@ __global__ __launch_bounds__(256, 2) void up_wide_bf16_kernel(
 // through registers with two blocks in flight / straight to LDS with one: 50432 tokens at 50 % 377 / 367 us (the first call on new
 // buffers 412 / 398), 30000 at 30 % 192 / 187, 12608 at 20 % 94 / 93.  Built and slower: rows before weights (374), everything at the
 // block's start (376), one workgroup of 512 rows per CU (388).
-// ALIGNED: x at a 16-byte address, as loads to LDS want it; at any other its rows go through registers.
-template <int MT, int TT, bool NEAR, bool ALIGNED>
+// Only for x at a 16-byte address, as loads to LDS want it: at any other the kernel above takes them.  (With rows through registers
+// here, x at 8 bytes from such an address, 50432 tokens at 50 % 466 us, loaded at a block's start and written at its end 416, above 387.)
+template <int MT, int TT, bool NEAR>
 __global__ __launch_bounds__(256, 2) void up_wide_plain_kernel(
     const __bf16* __restrict__ x, const __bf16* __restrict__ wupf, const __bf16* __restrict__ b_up,
     const int32_t* __restrict__ witem, const int2* __restrict__ worder,
@@ -899,8 +913,7 @@ __global__ __launch_bounds__(256, 2) void up_wide_plain_kernel(
         buffer_to_lds(wf, lane * 16, ((2 * i + (w >> 1)) * NK32 + 2 * kb + (w & 1)) * 1024, to + (4 * i + w) * 1024);
     };
     auto request_x = [&](int i, const uint32_t (&xoff)[NL], int kb) {
-        if constexpr (ALIGNED) xrows.to_lds(xoff[i], kb, xs + 1024 * i);
-        else *reinterpret_cast<bf16x8*>(xs + 1024 * i + lane * 16) = xrows.load(xoff[i], kb);
+        xrows.to_lds(xoff[i], kb, xs + 1024 * i);
     };
     auto park_bias = [&](int e, int par) {  // the item's biases, by neuron
         if ((int)threadIdx.x < MT * 16)
@@ -1274,27 +1287,29 @@ void launch_up_t(const dmoe_layer& L, const void* x, const PackedLayout& P, cons
         L.expert_size, L.act, S);
 }
 
-template <int MT, int TT>
+template <int MT, bool GATED, int TT>
 void launch_up_wide_t(const dmoe_layer& L, const void* x, const PackedLayout& P,
                       const int32_t* witem, const void* worder, const int32_t* alist,
                       void* H, int grid, hipStream_t s) {
-    const size_t lds = 2 * 4 * MT * 1024 + 4 * (size_t)TT * 16 * kUpRowBytes;
+    constexpr int NWF = 2 * (GATED ? 2 : 1) * MT;
+    const size_t lds = 2 * NWF * 1024 + 4 * (size_t)TT * 16 * kUpRowBytes + 2 * MT * 16 * sizeof(float);
     static std::once_flag attr_once;  // kernel attributes: once per process, thread-safe
     std::call_once(attr_once, [&] {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_wide_bf16_kernel<MT, TT>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_wide_bf16_kernel<MT, GATED, TT>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
     const char* pk = static_cast<const char*>(L.packed);
-    launch_kernel(up_wide_bf16_kernel<MT, TT>, grid, 256, lds, s,
-        (const __bf16*)x, (const __bf16*)(pk + P.wupf), (const __bf16*)(pk + P.wgatef), witem, (const int2*)worder,
-        alist, (__bf16*)H, L.d_model, L.n_experts, L.expert_size, L.act);
+    launch_kernel(up_wide_bf16_kernel<MT, GATED, TT>, grid, 256, lds, s,
+        (const __bf16*)x, (const __bf16*)(pk + P.wupf), (const __bf16*)(pk + P.wgatef),
+        (const __bf16*)L.b_up, witem, (const int2*)worder, alist, (__bf16*)H, L.d_model, L.n_experts,
+        L.expert_size, L.act);
 }
 
-template <int MT, int TT, bool NEAR, bool ALIGNED = true>
+template <int MT, int TT, bool NEAR>
 void launch_up_wide_plain_t(const dmoe_layer& L, const void* x, const PackedLayout& P,
                             const int32_t* witem, const void* worder, const int32_t* alist,
                             void* H, int grid, hipStream_t s) {
-    launch_kernel(up_wide_plain_kernel<MT, TT, NEAR, ALIGNED>, grid, 256, 0, s, (const __bf16*)x,
+    launch_kernel(up_wide_plain_kernel<MT, TT, NEAR>, grid, 256, 0, s, (const __bf16*)x,
         (const __bf16*)(static_cast<const char*>(L.packed) + P.wupf), (const __bf16*)L.b_up, witem, (const int2*)worder,
         alist, (__bf16*)H, L.d_model, L.n_experts, L.expert_size, L.act);
 }
@@ -1434,8 +1449,8 @@ void launch_up_bf16(const dmoe_layer& L, const void* x, int T, const int32_t* wi
             (int)std::min<long long>((long long)T * L.n_experts / 256 + L.n_experts, 512), 8);
         if (S.sets && L.gated) launch_up_wide_sets<4, true>(L, x, P, S, H, s);
         else if (S.sets) launch_up_wide_sets<8, false>(L, x, P, S, H, s);
-        else if (L.gated) launch_up_wide_t<4, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
-        else if (reinterpret_cast<uintptr_t>(x) & 15) launch_up_wide_plain_t<8, 4, false, false>(L, x, P, witem, worder, alist, H, wgrid, s);
+        else if (L.gated) launch_up_wide_t<4, true, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
+        else if (reinterpret_cast<uintptr_t>(x) & 15) launch_up_wide_t<8, false, 4>(L, x, P, witem, worder, alist, H, wgrid, s);
         else if (near) launch_up_wide_plain_t<8, 4, true>(L, x, P, witem, worder, alist, H, wgrid, s);
         else launch_up_wide_plain_t<8, 4, false>(L, x, P, witem, worder, alist, H, wgrid, s);
         return;
