@@ -401,10 +401,15 @@ void launch_t3(const dmoe_layer& L, const void* x, int T, float* scores, float t
     static std::once_flag once[2];
     // Through registers also where two workgroups of 32 tokens share a CU and there are more of them than CUs: on an x
     // that comes from memory a workgroup whose loads go to LDS, which can only wait for all of them, then takes longer.  d = 768, 128 experts of
-    // 24, forward, straight to LDS / so: 9000 tokens 85.2 / 83.8 us, 10000 91.5 / 90.4, 12000 104.2 / 102.7; 512 experts, router alone, 12000 tokens 18.1 /
-    // 16.7.  With at most one per CU 7000 tokens 75.2 / 75.5; with LDS for one only (512 experts with the gate, 12000 tokens) 177.1 / 177.2.
+    // 24, forward, straight to LDS / so: 9000 tokens 85.2 / 83.8 us, 10000 91.5 / 90.4, 12000 104.2 / 102.7.
+    // With at most one per CU 7000 tokens 75.2 / 75.5; with LDS for one only (512 experts with the gate, 12000 tokens) 177.1 / 177.2.
     const bool share = TT == 2 && div_up(T, TOK) > 256 && lds <= 80 * 1024;
-    if (share || (reinterpret_cast<uintptr_t>(x) & 15)) go(router_fused_kernel<NH, ETW, KBC, TT, kWhole, false>, once[1]);
+    // And where the router runs alone, which writes all the scores: d = 768, d_h = 128, straight to LDS / so: 512 experts, 5000 tokens 13.2 / 12.4 us,
+    // 20000 31.0 / 28.3, 50432 68.3 / 51.1; 128 experts, 50432 39.6 / 33.0; d = 2048, d_h = 256, 20000 tokens 53.1 / 50.3.  Not at d_h = 512
+    // (d = 2048, 12500 tokens 44.8 / 55.7, 20000 87 / 109), nor for the chunks of four blocks at d_h = 64 (64 experts, 65536 tokens 25.3 / 27.9;
+    // 256 experts, 40000 25.4 / 28.3).
+    const bool alone = !mask && NH <= 16 && !(NH == 4 && KBC == 4);
+    if (share || alone || (reinterpret_cast<uintptr_t>(x) & 15)) go(router_fused_kernel<NH, ETW, KBC, TT, kWhole, false>, once[1]);
     else go(router_fused_kernel<NH, ETW, KBC, TT>, once[0]);
 }
 
@@ -421,7 +426,7 @@ void launch_t2(const dmoe_layer& L, const void* x, int T, int split, float* scor
     // (chunks of four blocks and the hidden rows in their place: four workgroups of d_h <= 128 and up to 128 experts share a CU
     // and hide each other's latency, which pays as soon as a CU has more than one.  Forward, 128 experts of 24, d = 768, large chunks / these:
     // 17000 tokens 130.5 / 126.3 us, 20000 121.5 / 117.6, 30000 179 / 174)
-    else if (kBig > 4 && div_up(T, 64) <= (four_per_cu(NH, ETW, 4, kWhole) ? 256 : 512))
+    else if (kBig > 4 && div_up(T, 64) <= (mask && four_per_cu(NH, ETW, 4, kWhole) ? 256 : 512))
         launch_t3<NH, ETW, kBig, 4>(L, x, T, scores, tau, mask, group_cnt, sets, s);
     else
         launch_t3<NH, ETW, 4, 4>(L, x, T, scores, tau, mask, group_cnt, sets, s);

@@ -1,6 +1,6 @@
 """Staging of x in the router: rows of 64, 32 and 16 tokens per workgroup, one chunk, whole chunks and a shorter last one,
-and both sides of the rules between large chunks and four workgroups per CU (256 groups of 64 tokens) and between loads to LDS
-and to registers (256 workgroups of 32 tokens)."""
+and both sides of the rules between large chunks and four workgroups per CU (256 groups of 64 tokens, 512 of the router alone) and
+between loads to LDS and to registers (256 workgroups of 32 tokens; the router alone)."""
 import numpy as np
 import pytest
 
@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("d,E,d_h,T", [(256, 128, 128, 33), (768, 128, 128, 1000), (1280, 100, 64, 9000), (768, 512, 128, 1300), (2304, 40, 128, 3000),
                                        (768, 128, 128, 16384), (768, 128, 128, 16385), (256, 128, 64, 16449), (768, 300, 128, 16500),
                                        (512, 200, 256, 17000), (256, 130, 512, 7000),
-                                       (768, 128, 128, 8192), (768, 128, 128, 8193), (1280, 100, 64, 11001)])
+                                       (768, 128, 128, 8192), (768, 128, 128, 8193), (1280, 100, 64, 11001),
+                                       # the router alone: chunks of four blocks of d_h = 64 and 128, 257 workgroups of 64 tokens at d_h = 256
+                                       (256, 70, 64, 32801), (256, 70, 128, 32801), (512, 40, 256, 16400)])
 def test_scores_and_decisions(oracle, d, E, d_h, T):
     import torch
     from paper_2310_04361_amd import binding as B
