@@ -900,12 +900,16 @@ bool launch_router_two(const dmoe_layer& L, const void* x, int T, int split, voi
 }
 
 // E above 512: the gate of fewer experts is router_fused_kernel's; a wavefront has 16 tiles at most.  Rows of counts as
-// gate_counts_kernel leaves them, so the same limit on the tokens.  Below some 1450 tokens the launch takes as long as for 4096, and the
-// scores are few: whole forward, 2048 gated experts of 8, d = 2048, as two launches / one, 900 tokens 149 / 154 us, 1300 169.0 / 170.5, 1500
-// 179 / 173, 2500 269 / 259, 4096 416 / 400, 4200 510 / 492, 9000 854 / 812; d_h = 256, 1400 tokens 164 / 157, 3000 267 / 254; 1024
-// experts, d = 1280, 1400 tokens 97 / 98, 3000 145 / 138.
+// gate_counts_kernel leaves them, so below its limit on the tokens (its other condition, more rows of counts than the list fill adds up
+// itself, always holds here).  The launch reads all of R2 once per 16 tokens, and takes as long for few tokens as for 4096 and for few experts as for
+// the 1024 or 2048 that its wavefronts hold.  Whole forward of gated experts of 8, us, as two launches / one, d_h = 512: 2048 experts, d = 2048,
+// 1300 tokens 169.0 / 170.5, 1500 222 / 217, 2500 329 / 326, 4096 440 / 420, 9000 1043 / 1010; 1900 experts 1500 tokens 200 / 206, 1700 220 / 214,
+// 2500 306 / 307; 1300 experts 1700 tokens 177 / 183, 2300 226 / 232, 2600 253 / 249; 1025 experts, d = 1280, 1500 tokens 115 / 122, 2500 165 / 167,
+// 2700 173 / 170; 1024 experts 1500 tokens 108 / 109, 2000 133 / 134, 2300 158 / 152, 4096 202 / 195; 640 experts, d = 2048, 2000 tokens 132 / 134,
+// 4096 188 / 186.  d_h = 256: 2048 experts, d = 2304, 1500 tokens 231 / 228, 4096 533 / 514.
 bool scores_gate_supported(const dmoe_layer& L, int T) {
-    return router_sliced(L) && L.n_experts > 512 && L.n_experts <= 2048 && T >= 1500 && gate_counts_supported(T, L.n_experts);
+    const int E = L.n_experts;
+    return router_sliced(L) && E > 512 && E <= 2048 && T >= (E <= 1024 ? 2300 : E <= 1792 ? 2600 : 1500) && gate_counts_supported(T, E);
 }
 
 template <int KS2>
