@@ -80,8 +80,9 @@ __global__ __launch_bounds__(256, (DIRECT && four_per_cu(NH, ETW, KBC, MODE) ? 4
     // barrier and only L2-resident loads.
     // Straight to LDS, eight rows a load (staged through registers, a ds_write_b128 took 35 clocks of the CU per KB): 16-byte
     // piece p of row r of a block lies at p ^ (r / 2), so that the 16 lanes that read a piece of 16 rows use all the banks.
-    // Forward, through registers / so: 512 experts of 6, d = 768, 1300 tokens 56.9 / 54.2 us, 3000 80.0 / 77.5; 128 experts of 24,
-    // 50432 tokens, with the hidden rows in the place of x besides (two -> four workgroups per CU), 317 / 312; 16384 tokens 122.7 / 122.3.
+    // Forward, through registers / so: 128 experts of 24, d = 768, 300 tokens 35.6 / 35.4 us, 3000 62.9 / 62.5, 16384 126.3 / 126.3, 50432 (with
+    // the hidden rows in the place of x, two -> four workgroups per CU) 358.7 / 354.5; 512 experts of 6, 1300 tokens 57.2 / 57.0, 5000 105.7 / 106.6;
+    // 256 experts of 8, d = 1024, d_h = 512, 20000 tokens 259 / 248.
     constexpr int kRowSets = TOK / 8;                        // loads per K block, dealt to the wavefronts in turn
     constexpr int kOwn = kRowSets >= 4 ? kRowSets / 4 : 1;   // row sets of a wavefront
     const __bf16* xp[kOwn];
@@ -424,8 +425,8 @@ void launch_t2(const dmoe_layer& L, const void* x, int T, int split, float* scor
     else if (split == 2)
         launch_t3<NH, ETW, 16, 2>(L, x, T, scores, tau, mask, group_cnt, sets, s);
     // (chunks of four blocks and the hidden rows in their place: four workgroups of d_h <= 128 and up to 128 experts share a CU
-    // and hide each other's latency, which pays as soon as a CU has more than one.  Forward, 128 experts of 24, d = 768, large chunks / these:
-    // 17000 tokens 130.5 / 126.3 us, 20000 121.5 / 117.6, 30000 179 / 174)
+    // and hide each other's latency, which pays as soon as a CU has more than one.  Forward, 128 experts of 24, d = 768, large chunks up to
+    // 512 groups / up to 256: 17000 tokens 145.5 / 141.0 us, 20000 157.4 / 152.2, 32768 234.6 / 229.1.  The router alone: up to 512)
     else if (kBig > 4 && div_up(T, 64) <= (mask && four_per_cu(NH, ETW, 4, kWhole) ? 256 : 512))
         launch_t3<NH, ETW, kBig, 4>(L, x, T, scores, tau, mask, group_cnt, sets, s);
     else
