@@ -300,6 +300,11 @@ bool counts_in_sub(const dmoe_layer& L, int T, int split) {
 // tile) 400 tokens 57.1 / 46.6, 1200 66.8 / 58.3, 2000 73.2 / 73.0, 3000 85.0 / 96.5; 2048 gated of 8, d = 2048, 300 tokens 122 / 103, 1000
 // 199 / 185; 256 gated of 64, 333 tokens 121 / 103, 1024 tokens (37 %) 183 / 183, 8-bit 133 / 124, 1500 tokens, 8-bit, 155 / 169; 64 gated of
 // 64, d = 512, 2000 tokens 58 / 52, 3500 71 / 74; 256 x 48, d = 768, 1000 tokens 90 / 77, 2000 116 / 118.
+// The host does not know how many experts a token will keep, and the lines are those of sparse gates; near them a dense one is slower:
+// given lists, 256 gated of 64, d = 2048, 1023 tokens 10 % 113 / 103, 37 % 145 / 147, 60 % 183 / 191, 90 % 226 / 241, 512 tokens 91 / 78,
+// 102 / 92, 121 / 121, 136 / 136; 64 of 64, d = 512, 2600 tokens 58 / 51, 62 / 55, 71 / 67, 82 / 85; 200 gated of 30, d = 1024, 1400 tokens
+// 70 / 65, 77 / 73, 93 / 93, 102 / 112; forward, 1024 gated of 8, d = 1280, 1000 tokens, tau = 0.6 94 / 83, 0.4 115 / 104, 1600 tokens 109 / 110,
+// 133 / 144; 2048 of 8, d = 1024, 1000 tokens 108 / 99, 131 / 126, 2000 tokens 157 / 149, 205 / 225.
 // Not where the sparse down-projection may run, which decides by the number of pairs, nor where another kernel
 // goes over all the rows of H.
 bool use_sets(const dmoe_layer& L, int T, bool want_lists) {
