@@ -190,3 +190,35 @@ def test_static_workspace_and_graph_replay_with_8bit_inputs(B):
         B.dmoe_forward(L, xs[i], tau, y=y_eager)
         torch.cuda.synchronize()
         assert torch.equal(y_graph, y_eager), f"replay {i}"
+
+
+@pytest.mark.parametrize("fmt", ["x8", "a8"])
+@pytest.mark.parametrize("d_h,T,beside", [(256, 1248, True), (256, 1249, True), (256, 2047, True), (256, 2049, False), (512, 609, True),
+                                          (512, 1024, True), (512, 1025, False)])
+@pytest.mark.parametrize("m", [64, 24])  # codes alone; the quantised rows as bf16 numbers too
+def test_rows_quantised_beside_the_routers_hidden_rows(B, m, d_h, T, beside, fmt):
+    """In tiles of 32 and of 64 hidden units (1249 tokens on, d_h = 256; 609, d_h = 512), up to 256 workgroups of the latter: the same bits
+    as where the rows are quantised in a launch of their own, as with given lists."""
+    import torch
+    print(f"quantised beside hidden rows {fmt} m={m} d_h={d_h} T={T}", flush=True)
+    cfg = wl.Config("beside", T, 2048, 20, m, d_h, True, "gelu_tanh", "bf16", (0.4,))
+    layer, x = _x8_layer(cfg, T), wl.make_input(cfg, T)
+    layer[fmt] = True
+    L, xd = B.Layer(layer, cfg.dtype), B.to_device(x, cfg.dtype)
+
+    def launches_of(call):
+        L.workspace(T).fill_(0xff)
+        B.timing(True)
+        y = call()
+        launches = B.timing_read()
+        B.timing(False)
+        return y, launches["quantize_x"][0]
+
+    tau = float(np.float32(0.4))
+    (y, ex), own = launches_of(lambda: B.dmoe_forward(L, xd, tau, want_mask=True))
+    assert own == (0 if beside else 1)
+    offs, lst = lists_from_mask(B.mask_bits_to_bool(ex["mask_bits"], cfg.E))
+    off_d, list_d = torch.from_numpy(offs).cuda(), torch.from_numpy(lst).cuda()
+    want, own = launches_of(lambda: B.dmoe_expert_ffn(L, xd, off_d, list_d))
+    assert own == 1
+    assert torch.equal(y.view(torch.int16), want.view(torch.int16))
