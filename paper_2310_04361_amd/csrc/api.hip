@@ -300,18 +300,27 @@ bool counts_in_sub(const dmoe_layer& L, int T, int split) {
 // tile) 400 tokens 57.1 / 46.6, 1200 66.8 / 58.3, 2000 73.2 / 73.0, 3000 85.0 / 96.5; 2048 gated of 8, d = 2048, 300 tokens 122 / 103, 1000
 // 199 / 185; 256 gated of 64, 333 tokens 121 / 103, 1024 tokens (37 %) 183 / 183, 8-bit 133 / 124, 1500 tokens, 8-bit, 155 / 169; 64 gated of
 // 64, d = 512, 2000 tokens 58 / 52, 3500 71 / 74; 256 x 48, d = 768, 1000 tokens 90 / 77, 2000 116 / 118.
-// The host does not know how many experts a token will keep, and the lines are those of sparse gates; near them a dense one is slower:
-// given lists, 256 gated of 64, d = 2048, 1023 tokens 10 % 113 / 103, 37 % 145 / 147, 60 % 183 / 191, 90 % 226 / 241, 512 tokens 91 / 78,
-// 102 / 92, 121 / 121, 136 / 136; 64 of 64, d = 512, 2600 tokens 58 / 51, 62 / 55, 71 / 67, 82 / 85; 200 gated of 30, d = 1024, 1400 tokens
-// 70 / 65, 77 / 73, 93 / 93, 102 / 112; forward, 1024 gated of 8, d = 1280, 1000 tokens, tau = 0.6 94 / 83, 0.4 115 / 104, 1600 tokens 109 / 110,
-// 133 / 144; 2048 of 8, d = 1024, 1000 tokens 108 / 99, 131 / 126, 2000 tokens 157 / 149, 205 / 225.
+// The host does not know how many experts a token will keep, and these lines are those of sparse gates.  Near them a dense gate is slower without
+// lists -- items of 256 rows one to a CU come in rounds, and the many rows of a thousand one-tile experts take an x of 2 MB and more out of one
+// L2 -- so that what a call says of its density stops it earlier.  Forward, tau = 0 | 0.3 | 0.4 | 0.5: 256 gated of 64, d = 2048, 640 tokens
+// 180 / 184 | 131 / 132 | 124 / 122 | 120 / 112, 781 212 / 226 | 138 / 150 | 131 / 132 | 126 / 122, 898 228 / 241 | 146 / 165 | 137 / 139 | 132 / 129; 64 of 64, d = 512, 2048
+// tokens 76 / 67 | 57 / 56 | 55 / 55 | 55 / 49, 2812 85 / 87 | 66 / 70 | 60 / 62 | 57 / 61; but 512 of 64, d = 1024, 512 tokens 155 / 165 | 116 / 112 | 110 / 97 | 107 / 92.
+// 2048 gated of 8, d = 1024, 1024 tokens 298 / 290 | 160 / 163 | 133 / 132 | 124 / 111, 2048 566 / 553 | 264 / 307 | 205 / 240 | 170 / 186; d = 512, 1536 tokens
+// 269 / 254 | 152 / 152 | 131 / 127 | 118 / 109, 2048 342 / 337 | 174 / 186 | 144 / 151 | 127 / 125; d = 2048, 768 tokens 428 / 400 | 217 / 219 | 179 / 175 | 149 / 146,
+// 1024 550 / 519 | 261 / 275 | 207 / 210 | 183 / 164; 1024 of 8, d = 1024, 1280 tokens 196 / 188 | 126 / 122 | 110 / 104 | 96 / 95, 2048 300 / 288 | 158 / 170 | 128 / 138 |
+// 117 / 118; but 600 of 8, d = 1536, 1194 tokens 191 / 181 | 121 / 118 | 102 / 102 | 96 / 90.  Of given lists nothing is known: 256 gated of 64, 1023
+// tokens, 10 % 113 / 103, 37 % 145 / 147, 60 % 183 / 191, 90 % 226 / 241; 200 gated of 30, d = 1024, 1400 tokens 70 / 65, 77 / 73, 93 / 93, 102 / 112.
 // Not where the sparse down-projection may run, which decides by the number of pairs, nor where another kernel
 // goes over all the rows of H.
-bool use_sets(const dmoe_layer& L, int T, bool want_lists) {
+enum Density { kUnknown, kMany, kAll };  // of the selection, as far as the call says (density_of)
+bool use_sets(const dmoe_layer& L, int T, bool want_lists, Density density) {
     if (L.dtype != DMOE_BF16 || want_lists || use_small_path(L, T) || T <= kSmallTokens) return false;
     if (T > kSetTokens || (size_t)T * L.d_model * 2 > ((size_t)4 << 20)) return false;
     const long long most = up_tiny_supported(L) ? 2048ll * L.n_experts : (up_rows_bf16(L) == 256 ? 262144 : 400000);
     if ((long long)T * L.n_experts > most) return false;
+    const long long pairs = (long long)T * L.n_experts;
+    if (density == kMany && L.gated && up_tiny_supported(L) && pairs > 1500000 && (size_t)T * L.d_model * 2 > ((size_t)7 << 18)) return false;
+    if (density != kUnknown && L.gated && up_rows_bf16(L) == 256 && !acts_fp8(L) && T > 640 && pairs > 131072) return false;
     if (!down_bf16_addressable(L, T)) return false;
     return hidden_fp8(L) ? down_x8_shape(L) && down_x8_addressable(L, T) && up_x8_supported(L) : down_quad_max_pairs(L, T) <= 0;
 }
@@ -328,8 +337,8 @@ QuantX quant_x(const dmoe_layer& L, int T, char* ws, const LayerWs& w) {
 // then outputs of that kernel, described by gate_mod).
 int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const LayerWs& w,
                 const uint64_t* mask, int32_t* offsets_out, int32_t* lists_out, void* y,
-                hipStream_t s, int split = 1, const SmallMod* gate_mod = nullptr, bool quantised = false) {
-    // split: rows per group of the counts, where they are in sub_cnt (counts_in_sub); quantised: x is (quant_x)
+                hipStream_t s, bool sets, int split = 1, const SmallMod* gate_mod = nullptr, bool quantised = false) {
+    // sets: use_sets; split: rows per group of the counts, where they are in sub_cnt (counts_in_sub); quantised: x is (quant_x)
     int32_t* group_off = reinterpret_cast<int32_t*>(ws + w.group_off);
     const int32_t* sub_cnt = counts_in_sub(L, T, split) ? reinterpret_cast<const int32_t*>(ws + w.sub_cnt) : nullptr;
     int32_t* counts = reinterpret_cast<int32_t*>(ws + w.counts);
@@ -366,7 +375,6 @@ int run_experts(const dmoe_layer& L, const void* x, int T, char* ws, const Layer
     } else {
         int32_t* witem = reinterpret_cast<int32_t*>(ws + w.witem);
         int32_t* wfirst = reinterpret_cast<int32_t*>(ws + w.wfirst);
-        const bool sets = use_sets(L, T, offsets_out != nullptr);
         const TokenSets S{sets ? reinterpret_cast<const int32_t*>(ws + w.sub_cnt) : nullptr, group_off, item_start, T, 0, 0};
         if (!sets)
             launch_scan_and_fill(mask, T, L.n_experts, group_off, counts, offsets, item_start,
@@ -514,6 +522,11 @@ struct Gate {
     float tau;
     int top_k;
 };
+// kMany: a fifth of the experts a token and more; a threshold says no more than this: of half-normal scores 0.45 keeps 18 % of 256, 25 % of 64.
+Density density_of(const Gate& g, int E) {
+    if (g.top_k < 0 ? g.tau == 0.0f : g.top_k == E) return kAll;
+    return (g.top_k < 0 ? g.tau < 0.45f : 5 * g.top_k > E) ? kMany : kUnknown;
+}
 int check_gate(const Gate& g, int E) {
     if (g.top_k < 0) return check_tau(g.tau);
     if (g.top_k > E) return fail(DMOE_ERR_SHAPE, "k = %d exceeds the %d experts", g.top_k, E);
@@ -580,11 +593,11 @@ int32_t dmoe_expert_ffn(const dmoe_layer* layer, const void* x, int32_t n_tokens
     hipStream_t s = (hipStream_t)stream;
     uint64_t* mask = reinterpret_cast<uint64_t*>(ws + w.mask);
     uint64_t* colmask = use_small_path(*layer, n_tokens) ? reinterpret_cast<uint64_t*>(ws + w.colmask) : nullptr;
-    const bool sets = use_sets(*layer, n_tokens, false);
+    const bool sets = use_sets(*layer, n_tokens, false, kUnknown);
     launch_mask_from_lists(offsets, token_lists, n_tokens, layer->n_experts, mask,
                            reinterpret_cast<int32_t*>(ws + (sets || counts_in_sub(*layer, n_tokens, 1) ? w.sub_cnt : w.group_off)),
                            colmask, sets, ws + w.H, w.H_bytes, s);  // (the H rows come later)
-    return run_experts(*layer, x, n_tokens, ws, w, mask, nullptr, nullptr, y, s);
+    return run_experts(*layer, x, n_tokens, ws, w, mask, nullptr, nullptr, y, s, sets);
 }
 
 }  // extern "C"
@@ -609,7 +622,7 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
     float* scores = scores_out ? scores_out : reinterpret_cast<float*>(ws + w.scores);
     uint64_t* mask = mask_out ? mask_out : reinterpret_cast<uint64_t*>(ws + w.mask);
     uint64_t* colmask = use_small_path(*layer, n_tokens) ? reinterpret_cast<uint64_t*>(ws + w.colmask) : nullptr;
-    const bool sets = use_sets(*layer, n_tokens, offsets_out != nullptr);
+    const bool sets = use_sets(*layer, n_tokens, offsets_out != nullptr, density_of(gate, layer->n_experts));
     auto counts_of = [&](int parts) {  // where the gate's counts (or token sets) go
         return reinterpret_cast<int32_t*>(ws + (sets || counts_in_sub(*layer, n_tokens, parts) ? w.sub_cnt : w.group_off));
     };
@@ -632,7 +645,7 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
     if (fused_router && colmask && gate.top_k < 0 && layer->n_experts <= kSmallGateMaxE) {
         // router, gate and up-projection in one launch
         const SmallMod M = small_mod(*layer, ws, w, scores_out, mask, y, tau);
-        return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s, 1, &M);
+        return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s, sets, 1, &M);
     }
     if (fused_gate && n_tokens > kSmallTokens && gate.top_k < 0) {
         // router, dynamic-k gate and group counts in one kernel (with few token groups: several
@@ -679,7 +692,7 @@ int forward_impl(const dmoe_layer* layer, const void* x, int32_t n_tokens, Gate 
         else
             launch_mask_topk(scores, n_tokens, layer->n_experts, gate.top_k, mask, nullptr, cnt, colmask, sets, s);
     }
-    return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s, split, nullptr, quantised);
+    return run_experts(*layer, x, n_tokens, ws, w, mask, offsets_out, token_lists_out, y, s, sets, split, nullptr, quantised);
 }
 
 }  // namespace

@@ -26,17 +26,20 @@ SHAPES = {
     "rows32": dict(d=512, E=33, m=24, gated=False), "rows32_gated": dict(d=256, E=17, m=30, gated=True),
     "rows64": dict(d=256, E=60, m=40, gated=False), "wide_gated": dict(d=512, E=40, m=60, gated=True),
     "wide": dict(d=512, E=24, m=128, gated=False), "wide_24": dict(d=768, E=24, m=128, gated=False), "wide_130": dict(d=256, E=130, m=100, gated=False),
+    "wide_gated_210": dict(d=256, E=210, m=60, gated=True), "tile_gated_2048": dict(d=512, E=2048, m=2, gated=True),
 }
 TOKENS = [63, 64, 65, 127, 129, 255, 257, 1023, 1024, 1025, 1039, 2047, 2049, 3072]
 # items of 256 rows: 24 experts from 1281 tokens on, 130 from 129 on, 40 from 769 on
-TOKENS_OF = {"wide_24": [1280, 1281, 1379, 2561], "wide_130": [128, 129, 200, 257, 300, 1025]}
+TOKENS_OF = {"wide_24": [1280, 1281, 1379, 2561], "wide_130": [128, 129, 200, 257, 300, 1025], "wide_gated_210": [640, 641, 700], "tile_gated_2048": [1792, 1793]}
 # up to here: no lists (2048 tokens of one weight tile; where only small batches of plain wide experts do without the merge by pairs of experts)
-LAST = {"tile": 2048, "tile_gated": 2048, "wide_130": 2016}
-SMALL = {"tile": 16, "tile_gated": 16, "rows64": 16}  # up to here, otherwise up to 64, the kernels for a few tokens
+LAST = {"tile": 2048, "tile_gated": 2048, "tile_gated_2048": 2048, "wide_130": 2016}
+# the same of gates that keep many (a threshold below 0.45, more than a fifth of the experts) or all
+LAST_MANY, LAST_ALL = {"tile_gated_2048": 1792, "wide_gated_210": 640}, {"wide_gated_210": 640}
+SMALL = {"tile": 16, "tile_gated": 16, "tile_gated_2048": 16, "rows64": 16}  # up to here, otherwise up to 64, the kernels for a few tokens
 
 
-def has_sets(name, T, fmt="native"):
-    return (16 if fmt == "a8" else SMALL.get(name, 64)) < T <= LAST.get(name, 3072)
+def has_sets(name, T, fmt="native", last={}):
+    return (16 if fmt == "a8" else SMALL.get(name, 64)) < T <= min(LAST.get(name, 3072), last.get(name, 3072))
 
 
 def layer_of(B, name, T, fmt="native"):
@@ -61,7 +64,7 @@ def forward_without_lists(B, L, xd, tau, **kw):
     return y, launches["expert_up"][0] == 1 and launches["fill_lists"][0] == 0 and launches["scan_groups"][0] == 0
 
 
-CASES = [(name, "native", T) for name in sorted(SHAPES) for T in [17] * (name in SMALL) + TOKENS_OF.get(name, TOKENS)]
+CASES = [(name, "native", T) for name in sorted(SHAPES) for T in [17] * (name in SMALL and name not in TOKENS_OF) + TOKENS_OF.get(name, TOKENS)]
 CASES += [(name, fmt, T) for name in ("wide", "wide_gated") for fmt in ("x8", "a8") for T in [17] * (fmt == "a8") + [128, 129, 257, 1024, 1040]]
 
 
@@ -71,16 +74,17 @@ def test_sets_and_lists(B, name, fmt, T):
     print(f"token sets {name} {fmt} T={T}", flush=True)
     cfg, layer, x = layer_of(B, name, T, fmt)
     L, xd = B.Layer(layer, cfg.dtype), B.to_device(x, cfg.dtype)
-    for tau in (0.0, 0.4, 1.0):  # every expert, some, one or two
+    for tau in (0.0, 0.4, 0.45, 1.0):  # every expert, some, on the other side of the line, one or two
         tau = float(np.float32(tau))
         want, _ = B.dmoe_forward(L, xd, tau, want_lists=True)
         got, sets = forward_without_lists(B, L, xd, tau)
-        assert sets == has_sets(name, T, fmt)
+        assert sets == has_sets(name, T, fmt, LAST_ALL if tau == 0 else LAST_MANY if tau < float(np.float32(0.45)) else {})
         assert torch.equal(got.view(torch.int16), want.view(torch.int16)), tau
-    want, _ = B.dmoe_forward(L, xd, 0.0, top_k=3, want_lists=True)
-    got, sets = forward_without_lists(B, L, xd, 0.0, top_k=3)
-    assert sets == has_sets(name, T, fmt)
-    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    for k, last in ((cfg.E // 5, {}), (cfg.E // 5 + 1, LAST_MANY), (cfg.E, LAST_ALL)):
+        want, _ = B.dmoe_forward(L, xd, 0.0, top_k=k, want_lists=True)
+        got, sets = forward_without_lists(B, L, xd, 0.0, top_k=k)
+        assert sets == has_sets(name, T, fmt, last)
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
 
 
 GIVEN = [(name, T) for name in ("tile", "tile_gated", "rows32", "rows64", "wide_gated", "wide") for T in (65, 130, 1030)]
