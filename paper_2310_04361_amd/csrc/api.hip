@@ -303,7 +303,7 @@ bool counts_in_sub(const dmoe_layer& L, int T, int split) {
 // The host does not know how many experts a token will keep, and these lines are those of sparse gates.  Near them a dense gate is slower without
 // lists -- items of 256 rows one to a CU come in rounds, and the many rows of a thousand one-tile experts take an x of 2 MB and more out of one
 // L2 -- so that what a call says of its density stops it earlier.  Forward, tau = 0 | 0.3 | 0.4 | 0.5: 256 gated of 64, d = 2048, 640 tokens
-// 180 / 184 | 131 / 132 | 124 / 122 | 120 / 112, 781 212 / 226 | 138 / 150 | 131 / 132 | 126 / 122, 898 228 / 241 | 146 / 165 | 137 / 139 | 132 / 129; 64 of 64, d = 512, 2048
+// 180 / 184 | 131 / 132 | 124 / 122 | 120 / 112 (0.44, 700 tokens 125 / 123), 781 212 / 226 | 138 / 150 | 131 / 132 | 126 / 122, 898 228 / 241 | 146 / 165 | 137 / 139 | 132 / 129; 64 of 64, d = 512, 2048
 // tokens 76 / 67 | 57 / 56 | 55 / 55 | 55 / 49, 2812 85 / 87 | 66 / 70 | 60 / 62 | 57 / 61; but 512 of 64, d = 1024, 512 tokens 155 / 165 | 116 / 112 | 110 / 97 | 107 / 92.
 // 2048 gated of 8, d = 1024, 1024 tokens 298 / 290 | 160 / 163 | 133 / 132 | 124 / 111, 2048 566 / 553 | 264 / 307 | 205 / 240 | 170 / 186; d = 512, 1536 tokens
 // 269 / 254 | 152 / 152 | 131 / 127 | 118 / 109, 2048 342 / 337 | 174 / 186 | 144 / 151 | 127 / 125; d = 2048, 768 tokens 428 / 400 | 217 / 219 | 179 / 175 | 149 / 146,
@@ -320,7 +320,7 @@ bool use_sets(const dmoe_layer& L, int T, bool want_lists, Density density) {
     if ((long long)T * L.n_experts > most) return false;
     const long long pairs = (long long)T * L.n_experts;
     if (density == kMany && L.gated && up_tiny_supported(L) && pairs > 1500000 && (size_t)T * L.d_model * 2 > ((size_t)7 << 18)) return false;
-    if (density != kUnknown && L.gated && up_rows_bf16(L) == 256 && !acts_fp8(L) && T > 640 && pairs > 131072) return false;
+    if (density != kUnknown && L.gated && up_rows_bf16(L) == 256 && !acts_fp8(L) && T > 704 && pairs > 131072) return false;
     if (!down_bf16_addressable(L, T)) return false;
     return hidden_fp8(L) ? down_x8_shape(L) && down_x8_addressable(L, T) && up_x8_supported(L) : down_quad_max_pairs(L, T) <= 0;
 }

@@ -30,11 +30,11 @@ SHAPES = {
 }
 TOKENS = [63, 64, 65, 127, 129, 255, 257, 1023, 1024, 1025, 1039, 2047, 2049, 3072]
 # items of 256 rows: 24 experts from 1281 tokens on, 130 from 129 on, 40 from 769 on
-TOKENS_OF = {"wide_24": [1280, 1281, 1379, 2561], "wide_130": [128, 129, 200, 257, 300, 1025], "wide_gated_210": [640, 641, 700], "tile_gated_2048": [1792, 1793]}
+TOKENS_OF = {"wide_24": [1280, 1281, 1379, 2561], "wide_130": [128, 129, 200, 257, 300, 1025], "wide_gated_210": [704, 705, 720], "tile_gated_2048": [1792, 1793]}
 # up to here: no lists (2048 tokens of one weight tile; where only small batches of plain wide experts do without the merge by pairs of experts)
 LAST = {"tile": 2048, "tile_gated": 2048, "tile_gated_2048": 2048, "wide_130": 2016}
 # the same of gates that keep many (a threshold below 0.45, more than a fifth of the experts) or all
-LAST_MANY, LAST_ALL = {"tile_gated_2048": 1792, "wide_gated_210": 640}, {"wide_gated_210": 640}
+LAST_MANY, LAST_ALL = {"tile_gated_2048": 1792, "wide_gated_210": 704}, {"wide_gated_210": 704}
 SMALL = {"tile": 16, "tile_gated": 16, "tile_gated_2048": 16, "rows64": 16}  # up to here, otherwise up to 64, the kernels for a few tokens
 
 
